@@ -196,6 +196,57 @@ int dgnn_mproduct(const void *z, void *y, int64_t T, int64_t n, int32_t f, int32
                   const float *m_band, dgnn_dtype dt, void *stream);
 
 /*
+ * ---- Several timesteps per call.  The differences, features and weights of a block are usually all at hand, and on small
+ * and middle-sized snapshots a launch per kernel and timestep costs more than the work it starts.  These calls take the
+ * steps of a block together; tables of pointers are HOST arrays, read before the call returns, and hold device pointers.
+ */
+
+/* The most steps dgnn_delta_rebuild_series takes per launch; longer series are cut into launches of that many. */
+#define DGNN_SERIES_STEPS 32
+
+/* One step of a series: its difference lists (as in dgnn_delta_rebuild) and the arrays its snapshot goes to (dinv may be NULL). */
+typedef struct {
+    const int32_t *add_row, *add_col, *del_row, *del_col;
+    int64_t n_add, n_del;
+    int32_t *rowptr, *colidx;
+    float *dinv;
+} dgnn_series_step;
+
+/*
+ * A_2 .. A_{steps+1} from A_1 and the difference lists of the steps (Section "Graph-difference Based Input Transfer"): what
+ * `steps` calls of dgnn_delta_rebuild give, bit for bit, in two launches per DGNN_SERIES_STEPS steps.  Every snapshot needs
+ * rowptr and colidx arrays of its own (each colidx of `cap` entries, at least the stored entries of the densest snapshot),
+ * different from A_1's; lists and preconditions as in dgnn_delta_rebuild, without its validation.  No workspace.
+ */
+int dgnn_delta_rebuild_series(int64_t n, const int32_t *rowptr_first, const int32_t *colidx_first, int64_t nnz_first,
+                              int32_t steps, const dgnn_series_step *step, int64_t cap, void *stream);
+
+/* One product of dgnn_feature_transform_batch: h = diag(row_scale) x w (row_scale may be NULL). */
+typedef struct {
+    const void *x, *w;
+    const float *row_scale;
+    void *h;
+} dgnn_transform_item;
+
+/* dgnn_feature_transform for `count` products of the same shape and storage type.  flags: 0 or DGNN_RELU (the ReLU of the result). */
+int dgnn_feature_transform_batch(int32_t count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int32_t f_out,
+                                 uint32_t flags, dgnn_dtype dt, void *stream);
+
+/* One aggregation of dgnn_spmm_batch; val NULL in all items (dgnn_spmm) or in none (dgnn_spmm_weighted); dinv in all or in none. */
+typedef struct {
+    const int32_t *rowptr, *colidx;
+    const float *dinv, *val;
+    const void *h;
+    void *z;
+    int64_t nnz;
+} dgnn_spmm_item;
+
+/* dgnn_spmm (dgnn_spmm_weighted) for `count` snapshots of n vertices, same results bit for bit.  nnz: the largest of the items'. */
+int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, size_t *bytes);
+int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *items, int32_t f, dgnn_dtype dt, uint32_t flags,
+                    void *ws, size_t ws_bytes, void *stream);
+
+/*
  * ---- Snapshots that carry a value per stored entry (Section "Graph-difference Based Input Transfer" ships the
  * values of the new snapshot along with the two index lists; the smoothed graphs of Section "Smoothening the
  * Input Graphs" are where values other than 0/1 come from).  val[e] belongs to the stored entry colidx[e].

@@ -1,0 +1,115 @@
+"""Tables for the library calls that take several timesteps at once (dgnn_delta_rebuild_series,
+dgnn_feature_transform_batch, dgnn_spmm_batch).  A table is a numpy array of 64-bit words laid out like the C structs of
+include/dgnn.h: device pointers and counts; the drivers fill it once and refresh, per pass, the columns a caller may have
+replaced (features, weights, difference lists)."""
+from __future__ import annotations
+
+import ctypes
+from typing import List, Optional, Sequence
+
+import numpy as np
+import torch
+
+from . import binding as B
+
+# Timesteps whose GCN operation is enqueued together: as many as keep the rows of H that the aggregations gather within this
+# many bytes (a quarter of the Infinity Cache).  Snapshots with larger frames fill the chip one at a time, and their H is
+# still in the cache when it is gathered.
+BATCH_BYTES = 64 << 20
+
+# Stored entries up to which a block's snapshots are rebuilt as a series.  A workgroup of the series kernel walks its stretch
+# through all steps, 2.3 us a step, where one rebuild after the other pays two launches, 13 us a step; with more entries
+# the step-by-step merge, whose wavefronts stream, is the faster one (per step, series / step by step: 11 thousand entries
+# 4.5 / 12.7 us, 1.7 M 8.0 / 14.7 us, 17 M 65 / 53 us).
+SERIES_ENTRIES = 1 << 22
+
+
+def steps_together(frame_bytes: int, T: int) -> int:
+    return max(1, min(T, BATCH_BYTES // max(frame_bytes, 1)))
+
+
+def pointers(tensors: Sequence[Optional[torch.Tensor]]) -> List[int]:
+    return [0 if t is None else t.data_ptr() for t in tensors]
+
+
+class Seen:
+    """Whether a list of tensors (or tuples of them) holds the objects it held before; the checks of shape, type and layout
+    that a call makes are only repeated when it does not."""
+
+    def __init__(self):
+        self.ids = None
+
+    def same(self, objects) -> bool:
+        ids = [id(o) for o in objects]
+        if ids == self.ids:
+            return True
+        self.ids = ids
+        return False
+
+
+class Table:
+    """`rows` structs of `words` 64-bit words each; addresses of the stretch [a, b) for a call."""
+
+    def __init__(self, rows: int, words: int):
+        self.words = np.zeros((max(rows, 1), words), dtype=np.int64)
+        self.base, self.stride = self.words.ctypes.data, words * 8
+
+    def at(self, row: int = 0) -> int:
+        return self.base + row * self.stride
+
+    def column(self, k: int, values, rows: slice = slice(None)) -> None:
+        self.words[rows, k] = values
+
+
+class SeriesTable(Table):
+    """dgnn_series_step: add_row, add_col, del_row, del_col, n_add, n_del, rowptr, colidx, dinv."""
+
+    def __init__(self, rowptr, colidx, dinv):
+        super().__init__(len(rowptr), 9)
+        self.column(6, pointers(rowptr)) if rowptr else None
+        self.column(7, pointers(colidx)) if colidx else None
+        self.column(8, pointers(dinv)) if dinv else None
+        self.seen, self.kept = Seen(), None
+
+    def lists(self, deltas) -> None:
+        """The difference lists of the steps, (add_row, add_col, del_row, del_col) each."""
+        if self.seen.same(deltas):
+            return
+        self.kept = list(deltas)                     # the objects compared by identity must stay alive
+        for k, d in enumerate(deltas):
+            for t in d:
+                B._need(t, torch.int32, "difference list")
+                assert t.is_contiguous()
+            self.words[k, :6] = [t.data_ptr() if t.numel() else 0 for t in d] + [d[0].numel(), d[2].numel()]
+
+
+class TransformTable(Table):
+    """dgnn_transform_item: x, w, row_scale, h."""
+    X, W, SCALE, H = range(4)
+
+    def __init__(self, rows: int):
+        super().__init__(rows, 4)
+
+
+class SpmmTable(Table):
+    """dgnn_spmm_item: rowptr, colidx, dinv, val, h, z, nnz."""
+    ROWPTR, COLIDX, DINV, VAL, H, Z, NNZ = range(7)
+
+    def __init__(self, rows: int):
+        super().__init__(rows, 7)
+
+
+class Frames:
+    """Checks of a list of per-timestep tensors, made when the list's objects change, and their addresses."""
+
+    def __init__(self, shape, dtype, name: str):
+        self.shape, self.dtype, self.name = tuple(shape), dtype, name
+        self.seen, self.kept = Seen(), None
+
+    def addresses(self, tensors) -> List[int]:
+        if not self.seen.same(tensors):
+            self.kept = list(tensors)
+            for t in tensors:
+                if tuple(t.shape) != self.shape or t.dtype != self.dtype or not t.is_contiguous():
+                    raise ValueError(f"{self.name}: expected contiguous {self.dtype} tensors of shape {self.shape}")
+        return [t.data_ptr() for t in tensors]

@@ -28,6 +28,7 @@ EXPORTS = (
     "dgnn_spmm_static", "dgnn_mproduct",
     "dgnn_delta_rebuild_weighted", "dgnn_spmm_weighted", "dgnn_csr_combine_workspace", "dgnn_csr_combine", "dgnn_csr_weighted_dinv_workspace", "dgnn_csr_weighted_dinv", "dgnn_concat_relu", "dgnn_transform_concat_relu", "dgnn_lstm_cell", "dgnn_lstm_step", "dgnn_lstm_cell_backward", "dgnn_lstm_step_backward", "dgnn_concat_relu_backward", "dgnn_bias_grad_workspace", "dgnn_bias_grad", "dgnn_add",
     "dgnn_csr_transpose_workspace", "dgnn_csr_transpose", "dgnn_coo_transpose_workspace", "dgnn_coo_transpose",
+    "dgnn_delta_rebuild_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch",
     "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
 )
 
@@ -101,6 +102,10 @@ def load_library():
     lib.dgnn_spmm.argtypes = [_i64, _i64, _vp, _vp, _vp, _vp, _i32, _vp, ctypes.c_int, _u32, _vp, _sz, _vp]
     lib.dgnn_spmm_static_limit.argtypes = [ctypes.POINTER(_sz)]
     lib.dgnn_spmm_static.argtypes = [_i64, _i64, _vp, _vp, _vp, _vp, _i32, _vp, ctypes.c_int, _u32, _vp]
+    lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp]
+    lib.dgnn_feature_transform_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _u32, ctypes.c_int, _vp]
+    lib.dgnn_spmm_batch_workspace.argtypes = [_i32, _i64, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_spmm_batch.argtypes = [_i64, _i32, _vp, _i32, ctypes.c_int, _u32, _vp, _sz, _vp]
     lib.dgnn_mproduct.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, ctypes.c_int, _vp]
     lib.dgnn_mproduct_backward.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, ctypes.c_int, _vp]
     lib.dgnn_delta_rebuild_weighted.argtypes = [_i64, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _i64, _vp, _vp, _i64,
@@ -281,6 +286,27 @@ def mproduct(z: torch.Tensor, y: torch.Tensor, w: int, m_band: Optional[torch.Te
         if m_band.numel() != T * w:
             raise ValueError("m_band must be [T, w]")
     _check(load_library().dgnn_mproduct(_ptr(z), _ptr(y), T, n, f, w, _ptr(m_band), dt, _stream(z)), "dgnn_mproduct")
+
+
+# ---- several timesteps per call: tables of structs (batch.py) instead of tensors, checked by their owner -------------------
+def delta_rebuild_series(n: int, rowptr_first: torch.Tensor, colidx_first: torch.Tensor, nnz_first: int, steps: int, table: int, cap: int,
+                         stream) -> None:
+    _check(load_library().dgnn_delta_rebuild_series(n, _ptr(rowptr_first), _ptr(colidx_first), nnz_first, steps, table, cap, stream),
+           "dgnn_delta_rebuild_series")
+
+
+def feature_transform_batch(count: int, table: int, n: int, f_in: int, f_out: int, flags: int, dt: int, stream) -> None:
+    _check(load_library().dgnn_feature_transform_batch(count, table, n, f_in, f_out, flags, dt, stream), "dgnn_feature_transform_batch")
+
+
+def spmm_batch_workspace(count: int, nnz: int, f: int) -> int:
+    out = _sz(0)
+    _check(load_library().dgnn_spmm_batch_workspace(count, nnz, f, ctypes.byref(out)), "dgnn_spmm_batch_workspace")
+    return int(out.value)
+
+
+def spmm_batch(n: int, count: int, table: int, f: int, dt: int, flags: int, ws: torch.Tensor, stream) -> None:
+    _check(load_library().dgnn_spmm_batch(n, count, table, f, dt, flags, _ptr(ws), ws.numel() * ws.element_size(), stream), "dgnn_spmm_batch")
 
 
 def delta_rebuild_weighted(rowptr_prev, colidx_prev, val_prev, nnz_prev: int, add, dele, upd,

@@ -44,6 +44,9 @@ class CdgcnLayer(BlockRunner):
         self.h_all = torch.empty((blk.T, n, hidden), dtype=dt, device=dev)      # h_t for every timestep
         self.h0 = torch.zeros((n, hidden), dtype=dt, device=dev)
 
+    def _series_pays(self) -> bool:
+        return False
+
     def step(self, t: int) -> None:
         blk = self.blk
         slot = self.slot_of(t)

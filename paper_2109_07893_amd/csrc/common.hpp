@@ -50,6 +50,20 @@ inline int64_t resident_workgroups(K kernel, int threads, int64_t fallback) {
     return value;
 }
 
+// A pointer that came to a kernel inside a struct, known to point to global memory (the compiler sees that by itself for
+// pointers that are arguments of their own; without it every access becomes a flat one).
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
+
+// The `count` 32-bit words at p (the same in all lanes) behind a buffer descriptor: a load beyond them gives 0, a store
+// beyond them is dropped, so that no access needs a branch and the compiler can count the accesses in flight exactly.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int count) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, count * 4, 0x00027000);
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // First index in [lo, hi) whose element is >= key (array ascending).
 __device__ __forceinline__ int lower_bound(const int32_t *__restrict__ a, int lo, int hi, int32_t key) {
     while (lo < hi) {
@@ -90,21 +104,20 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Inclusive wavefront scans over 64 lanes.
-__device__ __forceinline__ int wave_scan_add(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int o = __shfl_up(v, d, kWave);
-        if (lane >= d) v += o;
-    }
-    return v;
-}
-__device__ __forceinline__ int wave_scan_max(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int o = __shfl_up(v, d, kWave);
-        if (lane >= d) v = max(v, o);
-    }
+// Workgroup barrier for data in LDS.  __syncthreads() also waits until the wavefront's global loads and stores have
+// completed, which puts a trip to memory into every phase of a kernel that keeps loads and stores in flight across them.
+__device__ __forceinline__ void block_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Inclusive wavefront scan over 64 lanes, every lane active: shifts inside the rows of 16 lanes and broadcasts of a row's
+// last lane, all of them operand modifiers of an addition (six dependent vector instructions; through the LDS permute
+// network the same scan waits six times for it).
+__device__ __forceinline__ int wave_scan_add(int v, int) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);    // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);    // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);    // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
     return v;
 }
 

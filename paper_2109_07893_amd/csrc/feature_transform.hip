@@ -36,13 +36,21 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// One product of a launch; blockIdx.y says which (a launch may take the products of several timesteps).
+struct Item {
+    const void *x, *w;
+    const float *row_scale;
+    void *h;
+};
+constexpr int kMaxBatch = 32;
+struct Batch { Item item[kMaxBatch]; };
+
 constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 
 template <int FIN, int FOUT>
-__global__ __launch_bounds__(kThreads) void xw_f32_kernel(const float *__restrict__ x, const float *__restrict__ w,
-                                                          const float *__restrict__ row_scale, float *__restrict__ h,
-                                                          int64_t n, int64_t n_tiles, int wt) {
+__device__ __forceinline__ void xw_f32(const float *__restrict__ x, const float *__restrict__ w,
+        const float *__restrict__ row_scale, float *__restrict__ h, int64_t n, int64_t n_tiles, int wt, int relu) {
     constexpr int NT = (FOUT + 31) / 32;   // 32-wide column tiles (FOUT = 16 is zero-padded)
     constexpr int LD = NT * 32;
     constexpr int KH = FIN / 2;            // k values owned by one lane
@@ -106,10 +114,17 @@ __global__ __launch_bounds__(kThreads) void xw_f32_kernel(const float *__restric
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int64_t r = tile * 32 + 8 * (v / 4) + 4 * hh + (v % 4);
-                if (r < n && col < FOUT) h[r * FOUT + col] = acc[jt][v] * sc[v];
+                const float out = acc[jt][v] * sc[v];
+                if (r < n && col < FOUT) h[r * FOUT + col] = relu ? fmaxf(out, 0.0f) : out;
             }
         }
     }
+}
+template <int FIN, int FOUT>
+__global__ __launch_bounds__(kThreads) void xw_f32_kernel(Batch batch, int64_t n, int64_t n_tiles, int wt, int relu) {
+    const Item &it = batch.item[blockIdx.y];
+    xw_f32<FIN, FOUT>(as_global(static_cast<const float *>(it.x)), as_global(static_cast<const float *>(it.w)), as_global(it.row_scale),
+        as_global(static_cast<float *>(it.h)), n, n_tiles, wt, relu);
 }
 
 // The same product with both tiles staged through LDS, for widths whose tiles fit: the 32 rows of X arrive as
@@ -120,9 +135,8 @@ __global__ __launch_bounds__(kThreads) void xw_f32_kernel(const float *__restric
 // CONCAT: the output row is relu([x | x W]), FIN + FOUT wide (the skip connection of the CD-GCN layer, Section
 // "CD-GCN"): the result tile is laid down behind the input tile, which is still in LDS, and both leave together.
 template <int FIN, int FOUT, bool CONCAT>
-__global__ __launch_bounds__(kThreads) void xw_f32_staged_kernel(const float *__restrict__ x, const float *__restrict__ w,
-                                                                 const float *__restrict__ row_scale, float *__restrict__ h,
-                                                                 int64_t n, int64_t n_tiles, int wt) {
+__device__ __forceinline__ void xw_f32_staged(const float *__restrict__ x, const float *__restrict__ w,
+        const float *__restrict__ row_scale, float *__restrict__ h, int64_t n, int64_t n_tiles, int wt, int relu) {
     constexpr int NT = FOUT / 32;
     constexpr int KH = FIN / 2;
     constexpr int FMAX = FIN > FOUT ? FIN : FOUT;
@@ -201,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void xw_f32_staged_kernel(const float *__
                 const int64_t piece = tile * (32 * OUTW / 4) + q * kWave + lane;
                 if (piece * 4 < n * OUTW) {
                     floatx4 v = *reinterpret_cast<const floatx4 *>(&tile_lds[(e / OUTW) * LDT + e % OUTW]);
-                    if (CONCAT) v = floatx4{fmaxf(v[0], 0.0f), fmaxf(v[1], 0.0f), fmaxf(v[2], 0.0f), fmaxf(v[3], 0.0f)};
+                    if (CONCAT || relu) v = floatx4{fmaxf(v[0], 0.0f), fmaxf(v[1], 0.0f), fmaxf(v[2], 0.0f), fmaxf(v[3], 0.0f)};
                     __builtin_nontemporal_store(v, reinterpret_cast<floatx4 *>(h) + piece);   // whole lines, read by a later kernel: 4 % faster than plain stores
                 }
             }
@@ -209,11 +223,16 @@ __global__ __launch_bounds__(kThreads) void xw_f32_staged_kernel(const float *__
         wave_lds_sync();                                                      // the tile buffer is reused
     }
 }
+template <int FIN, int FOUT, bool CONCAT>
+__global__ __launch_bounds__(kThreads) void xw_f32_staged_kernel(Batch batch, int64_t n, int64_t n_tiles, int wt, int relu) {
+    const Item &it = batch.item[blockIdx.y];
+    xw_f32_staged<FIN, FOUT, CONCAT>(as_global(static_cast<const float *>(it.x)), as_global(static_cast<const float *>(it.w)), as_global(it.row_scale),
+        as_global(static_cast<float *>(it.h)), n, n_tiles, wt, relu);
+}
 
 template <int FIN, int FOUT>
-__global__ __launch_bounds__(kThreads) void xw_bf16_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
-                                                           const float *__restrict__ row_scale, uint16_t *__restrict__ h,
-                                                           int64_t n, int64_t n_tiles, int wt) {
+__device__ __forceinline__ void xw_bf16(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
+        const float *__restrict__ row_scale, uint16_t *__restrict__ h, int64_t n, int64_t n_tiles, int wt, int relu) {
     constexpr int NT = (FOUT + 31) / 32;
     constexpr int JG = NT > 2 ? 2 : NT;    // column tiles accumulated at a time (bounds the live accumulators)
     constexpr int KH = FIN / 2;            // bf16 values owned by one lane
@@ -279,9 +298,14 @@ __global__ __launch_bounds__(kThreads) void xw_bf16_kernel(const uint16_t *__res
                     for (int g = 0; g < 4; ++g) {
                         const int col = (j0 + jj) * 32 + 8 * g + 4 * hh;
                         if (col < FOUT) {
-                            const uint32_t lo = f32_to_bf16(acc[jj][4 * g] * scale) | (f32_to_bf16(acc[jj][4 * g + 1] * scale) << 16);
-                            const uint32_t hi = f32_to_bf16(acc[jj][4 * g + 2] * scale) | (f32_to_bf16(acc[jj][4 * g + 3] * scale) << 16);
-                            *reinterpret_cast<uint2 *>(h + row * FOUT + col) = make_uint2(lo, hi);
+                            float v[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                v[q] = acc[jj][4 * g + q] * scale;
+                                if (relu) v[q] = fmaxf(v[q], 0.0f);
+                            }
+                            *reinterpret_cast<uint2 *>(h + row * FOUT + col) =
+                                make_uint2(f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16), f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16));
                         }
                     }
             }
@@ -289,13 +313,18 @@ __global__ __launch_bounds__(kThreads) void xw_bf16_kernel(const uint16_t *__res
         }
     }
 }
+template <int FIN, int FOUT>
+__global__ __launch_bounds__(kThreads) void xw_bf16_kernel(Batch batch, int64_t n, int64_t n_tiles, int wt, int relu) {
+    const Item &it = batch.item[blockIdx.y];
+    xw_bf16<FIN, FOUT>(as_global(static_cast<const uint16_t *>(it.x)), as_global(static_cast<const uint16_t *>(it.w)), as_global(it.row_scale),
+        as_global(static_cast<uint16_t *>(it.h)), n, n_tiles, wt, relu);
+}
 
 // bf16 with both widths at least 32: as the staged fp32 kernel, tiles pass through LDS so that every global
 // access is a run of whole lines, and the transposed product leaves four consecutive columns per lane.
 template <int FIN, int FOUT, bool CONCAT>
-__global__ __launch_bounds__(kThreads) void xw_bf16_staged_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
-                                                                  const float *__restrict__ row_scale, uint16_t *__restrict__ h,
-                                                                  int64_t n, int64_t n_tiles, int wt) {
+__device__ __forceinline__ void xw_bf16_staged(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
+        const float *__restrict__ row_scale, uint16_t *__restrict__ h, int64_t n, int64_t n_tiles, int wt, int relu) {
     constexpr int NT = FOUT / 32;
     constexpr int JG = NT > 2 ? 2 : NT;              // column tiles accumulated at a time
     constexpr int KH = FIN / 2;
@@ -381,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void xw_bf16_staged_kernel(const uint16_t
                 const int64_t piece = tile * (32 * OUTW / 8) + q * kWave + lane;
                 if (piece * 8 < n * OUTW) {
                     uintx4 v = *reinterpret_cast<const uintx4 *>(&tile_lds[(e / OUTW) * LDT + e % OUTW]);
-                    if (CONCAT) {      // a bf16 with its sign bit set becomes zero (a negative zero too)
+                    if (CONCAT || relu) {      // a bf16 with its sign bit set becomes zero (a negative zero too)
 #pragma unroll
                         for (int c = 0; c < 4; ++c) v[c] = ((v[c] & 0x8000u) ? 0u : (v[c] & 0xffffu)) | ((v[c] & 0x80000000u) ? 0u : (v[c] & 0xffff0000u));
                     }
@@ -392,6 +421,12 @@ __global__ __launch_bounds__(kThreads) void xw_bf16_staged_kernel(const uint16_t
         wave_lds_sync();                                                      // the tile buffer is reused
     }
 }
+template <int FIN, int FOUT, bool CONCAT>
+__global__ __launch_bounds__(kThreads) void xw_bf16_staged_kernel(Batch batch, int64_t n, int64_t n_tiles, int wt, int relu) {
+    const Item &it = batch.item[blockIdx.y];
+    xw_bf16_staged<FIN, FOUT, CONCAT>(as_global(static_cast<const uint16_t *>(it.x)), as_global(static_cast<const uint16_t *>(it.w)), as_global(it.row_scale),
+        as_global(static_cast<uint16_t *>(it.h)), n, n_tiles, wt, relu);
+}
 
 // Grid.  A large W wants a persistent launch: as many workgroups as the device holds at once, so that W is staged
 // once per resident workgroup and every wavefront walks many row tiles.  A small W (up to 8 KB) is cheap to stage
@@ -399,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void xw_bf16_staged_kernel(const uint16_t
 // rows 0.83 -> 0.75 ms with one tile per wavefront): a wavefront then takes just enough tiles to move about 8 KB
 // and to keep the staging of W a small share of its traffic.
 template <int FIN, int FOUT>
-int launch(const void *x, const void *w, int wt, const float *row_scale, void *h, int64_t n, dgnn_dtype dt, hipStream_t s) {
+int launch(int count, const Batch &b, int wt, int relu, int64_t n, dgnn_dtype dt, hipStream_t s) {
     const int64_t n_tiles = (n + 31) / 32;
     const int64_t needed = (n_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const int64_t elem = dt == DGNN_F32 ? 4 : 2;
@@ -408,24 +443,19 @@ int launch(const void *x, const void *w, int wt, const float *row_scale, void *h
     auto grid = [&](auto kernel) {
         const int64_t resident = resident_workgroups(kernel, kThreads, 1024);
         const int64_t many = tiles_per_wave > 0 ? (needed + tiles_per_wave - 1) / tiles_per_wave : 0;
-        return dim3((unsigned)(many >= 4 * resident ? many : std::min(needed, resident)));
+        const int64_t share = std::max<int64_t>(1, resident / count);
+        return dim3((unsigned)(many >= 4 * share ? many : std::min(needed, share)), (unsigned)count);
     };
     if (dt == DGNN_F32) {
         if constexpr (FIN <= 64 && FOUT <= 64 && FOUT % 32 == 0)   // both tiles and W fit in LDS
-            hipLaunchKernelGGL((xw_f32_staged_kernel<FIN, FOUT, false>), grid(xw_f32_staged_kernel<FIN, FOUT, false>), dim3(kThreads), 0, s,
-                               static_cast<const float *>(x), static_cast<const float *>(w), row_scale, static_cast<float *>(h), n, n_tiles, wt);
+            hipLaunchKernelGGL((xw_f32_staged_kernel<FIN, FOUT, false>), grid(xw_f32_staged_kernel<FIN, FOUT, false>), dim3(kThreads), 0, s, b, n, n_tiles, wt, relu);
         else
-            hipLaunchKernelGGL((xw_f32_kernel<FIN, FOUT>), grid(xw_f32_kernel<FIN, FOUT>), dim3(kThreads), 0, s,
-                               static_cast<const float *>(x), static_cast<const float *>(w), row_scale, static_cast<float *>(h), n, n_tiles, wt);
+            hipLaunchKernelGGL((xw_f32_kernel<FIN, FOUT>), grid(xw_f32_kernel<FIN, FOUT>), dim3(kThreads), 0, s, b, n, n_tiles, wt, relu);
     } else {
         if constexpr (FIN % 32 == 0 && FOUT % 32 == 0)
-            hipLaunchKernelGGL((xw_bf16_staged_kernel<FIN, FOUT, false>), grid(xw_bf16_staged_kernel<FIN, FOUT, false>), dim3(kThreads), 0, s,
-                               static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(w), row_scale,
-                               static_cast<uint16_t *>(h), n, n_tiles, wt);
+            hipLaunchKernelGGL((xw_bf16_staged_kernel<FIN, FOUT, false>), grid(xw_bf16_staged_kernel<FIN, FOUT, false>), dim3(kThreads), 0, s, b, n, n_tiles, wt, relu);
         else
-            hipLaunchKernelGGL((xw_bf16_kernel<FIN, FOUT>), grid(xw_bf16_kernel<FIN, FOUT>), dim3(kThreads), 0, s,
-                               static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(w), row_scale,
-                               static_cast<uint16_t *>(h), n, n_tiles, wt);
+            hipLaunchKernelGGL((xw_bf16_kernel<FIN, FOUT>), grid(xw_bf16_kernel<FIN, FOUT>), dim3(kThreads), 0, s, b, n, n_tiles, wt, relu);
     }
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
@@ -434,6 +464,8 @@ int launch(const void *x, const void *w, int wt, const float *row_scale, void *h
 // out = relu([x | x W]) where both tiles of a wavefront and W fit in LDS together; other width pairs are refused.
 template <int FIN, int FOUT>
 int launch_concat(const void *x, const void *w, void *out, int64_t n, dgnn_dtype dt, hipStream_t s) {
+    Batch b;
+    b.item[0] = Item{x, w, nullptr, out};
     const int64_t n_tiles = (n + 31) / 32;
     const int64_t needed = (n_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const int64_t elem = dt == DGNN_F32 ? 4 : 2;
@@ -446,15 +478,12 @@ int launch_concat(const void *x, const void *w, void *out, int64_t n, dgnn_dtype
     };
     if (dt == DGNN_F32) {
         if constexpr (FIN <= 64 && FOUT <= 64 && FOUT % 32 == 0)
-            hipLaunchKernelGGL((xw_f32_staged_kernel<FIN, FOUT, true>), grid(xw_f32_staged_kernel<FIN, FOUT, true>), dim3(kThreads), 0, s,
-                               static_cast<const float *>(x), static_cast<const float *>(w), nullptr, static_cast<float *>(out), n, n_tiles, 0);
+            hipLaunchKernelGGL((xw_f32_staged_kernel<FIN, FOUT, true>), grid(xw_f32_staged_kernel<FIN, FOUT, true>), dim3(kThreads), 0, s, b, n, n_tiles, 0, 1);
         else
             return DGNN_ERR_SHAPE;
     } else {
         if constexpr (FIN % 32 == 0 && FOUT % 32 == 0 && FIN + FOUT <= 128)
-            hipLaunchKernelGGL((xw_bf16_staged_kernel<FIN, FOUT, true>), grid(xw_bf16_staged_kernel<FIN, FOUT, true>), dim3(kThreads), 0, s,
-                               static_cast<const uint16_t *>(x), static_cast<const uint16_t *>(w), nullptr, static_cast<uint16_t *>(out), n,
-                               n_tiles, 0);
+            hipLaunchKernelGGL((xw_bf16_staged_kernel<FIN, FOUT, true>), grid(xw_bf16_staged_kernel<FIN, FOUT, true>), dim3(kThreads), 0, s, b, n, n_tiles, 0, 1);
         else
             return DGNN_ERR_SHAPE;
     }
@@ -472,51 +501,65 @@ int launch_concat_out(int32_t f_out, const void *x, const void *w, void *out, in
 }
 
 template <int FIN>
-int launch_out(int32_t f_out, const void *x, const void *w, int wt, const float *row_scale, void *h, int64_t n,
-               dgnn_dtype dt, hipStream_t s) {
+int launch_out(int32_t f_out, int count, const Batch &b, int wt, int relu, int64_t n, dgnn_dtype dt, hipStream_t s) {
     switch (f_out) {
-        case 16: return launch<FIN, 16>(x, w, wt, row_scale, h, n, dt, s);
-        case 32: return launch<FIN, 32>(x, w, wt, row_scale, h, n, dt, s);
-        case 64: return launch<FIN, 64>(x, w, wt, row_scale, h, n, dt, s);
-        case 128: return launch<FIN, 128>(x, w, wt, row_scale, h, n, dt, s);
+        case 16: return launch<FIN, 16>(count, b, wt, relu, n, dt, s);
+        case 32: return launch<FIN, 32>(count, b, wt, relu, n, dt, s);
+        case 64: return launch<FIN, 64>(count, b, wt, relu, n, dt, s);
+        case 128: return launch<FIN, 128>(count, b, wt, relu, n, dt, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
 
-}  // namespace
-
-namespace {
-
-int transform(const void *x, int64_t n, int32_t f_in, const void *w, int wt, int32_t f_out, const float *row_scale,
-              void *h, dgnn_dtype dt, void *stream) {
-    if (!x || !w || !h) return DGNN_ERR_NULL;
-    if (n <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
+int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int wt, int relu, int32_t f_out, dgnn_dtype dt, void *stream) {
+    for (int k = 0; k < count; ++k)
+        if (!items[k].x || !items[k].w || !items[k].h) return DGNN_ERR_NULL;
+    if (n <= 0 || count <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n)) return DGNN_ERR_OVERFLOW;
-    if (!aligned16(x) || !aligned16(h)) return DGNN_ERR_ALIGN;
-    if (x == h) return DGNN_ERR_ALIAS;
-    hipStream_t s = (hipStream_t)stream;
-    switch (f_in) {
-        case 16: return launch_out<16>(f_out, x, w, wt, row_scale, h, n, dt, s);
-        case 32: return launch_out<32>(f_out, x, w, wt, row_scale, h, n, dt, s);
-        case 64: return launch_out<64>(f_out, x, w, wt, row_scale, h, n, dt, s);
-        case 128: return launch_out<128>(f_out, x, w, wt, row_scale, h, n, dt, s);
-        default: return DGNN_ERR_SHAPE;
+    for (int k = 0; k < count; ++k) {
+        if (!aligned16(items[k].x) || !aligned16(items[k].h)) return DGNN_ERR_ALIGN;
+        if (items[k].x == items[k].h) return DGNN_ERR_ALIAS;
     }
+    hipStream_t s = (hipStream_t)stream;
+    for (int done = 0; done < count; done += kMaxBatch) {
+        const int m = std::min(count - done, kMaxBatch);
+        Batch b;
+        for (int k = 0; k < m; ++k) b.item[k] = Item{items[done + k].x, items[done + k].w, items[done + k].row_scale, items[done + k].h};
+        int rc;
+        switch (f_in) {
+            case 16: rc = launch_out<16>(f_out, m, b, wt, relu, n, dt, s); break;
+            case 32: rc = launch_out<32>(f_out, m, b, wt, relu, n, dt, s); break;
+            case 64: rc = launch_out<64>(f_out, m, b, wt, relu, n, dt, s); break;
+            default: rc = launch_out<128>(f_out, m, b, wt, relu, n, dt, s); break;
+        }
+        if (rc != DGNN_OK) return rc;
+    }
+    return DGNN_OK;
 }
 
 }  // namespace
 
 extern "C" int dgnn_feature_transform(const void *x, int64_t n, int32_t f_in, const void *w, int32_t f_out,
                                       const float *row_scale, void *h, dgnn_dtype dt, void *stream) {
-    return transform(x, n, f_in, w, 0, f_out, row_scale, h, dt, stream);
+    const dgnn_transform_item item{x, w, row_scale, h};
+    return transform(1, &item, n, f_in, 0, 0, f_out, dt, stream);
 }
 
 // dX = G W^T: the same product with W read transposed while it is parked in LDS; the contraction runs over
 // the columns of W, so the kernel's inner width is f_out and its outer width f_in.
 extern "C" int dgnn_input_grad(const void *g, int64_t n, int32_t f_out, const void *w, int32_t f_in,
                                const float *row_scale, void *dx, dgnn_dtype dt, void *stream) {
-    return transform(g, n, f_out, w, 1, f_in, row_scale, dx, dt, stream);
+    const dgnn_transform_item item{g, w, row_scale, dx};
+    return transform(1, &item, n, f_out, 1, 0, f_in, dt, stream);
+}
+
+// The products of several timesteps in one launch.
+extern "C" int dgnn_feature_transform_batch(int32_t count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int32_t f_out,
+                                            uint32_t flags, dgnn_dtype dt, void *stream) {
+    if (count > 0 && !items) return DGNN_ERR_NULL;
+    if (flags & ~DGNN_RELU) return DGNN_ERR_SHAPE;
+    return transform(count, items, n, f_in, 0, (flags & DGNN_RELU) ? 1 : 0, f_out, dt, stream);
 }
 
 // Y = relu([X | X W]): the dense transform with the skip connection of the CD-GCN layer's GCN operation (Section

@@ -45,6 +45,19 @@ constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: all vector memory loa
 enum : int32_t { kLeft = 1, kLeftClosed = 2, kRight = 4 };
 struct RangeRec { int32_t flags, row_last, pad0, pad1; };
 
+// One aggregation of a launch; blockIdx.y says which (a launch may take the aggregations of several timesteps).
+struct Item {
+    const int32_t *rowptr, *colidx;
+    const float *dinv, *vals;
+    const char *h;
+    char *z;
+    RangeRec *recs;
+    float *carry;
+    int32_t nnz, range_len, n_ranges, pad;
+};
+constexpr int kMaxBatch = 32;        // what fits the kernel arguments comfortably
+struct Batch { Item item[kMaxBatch]; };
+
 // ---- 16-byte feature pieces: 4 fp32 or 8 bf16, accumulated in fp32 -------------------------
 template <bool BF16> struct Piece;
 template <> struct Piece<false> {
@@ -102,7 +115,7 @@ __device__ __forceinline__ void zero_row(char *z, int64_t row) {
 // LPR: lanes per feature row.  SCALE_V: multiply every gathered row by a per-entry factor: dinv of its
 // column, or the entry's own value when the snapshot carries values (otherwise H already carries the factor).
 template <int LPR, bool BF16, bool SCALE_V>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void spmm_stream_kernel(
+__device__ __forceinline__ void spmm_stream(
     int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ dinv, const char *__restrict__ h, char *__restrict__ z, int relu,
     RangeRec *__restrict__ recs, float *__restrict__ carry, const float *__restrict__ vals) {
@@ -463,32 +476,73 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) v
             if (rowptr[k] == rowptr[k + 1]) zero_row<BF16, LPR>(z, k);
 }
 
-// Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries
-// of the following ranges until the one that closes the row.
+template <int LPR, bool BF16, bool SCALE_V>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void spmm_stream_kernel(int n, int relu, Batch batch) {
+    const Item &it = batch.item[blockIdx.y];
+    spmm_stream<LPR, BF16, SCALE_V>(n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
+                                    as_global(it.h), as_global(it.z), relu, as_global(it.recs), as_global(it.carry), as_global(it.vals));
+}
+
+// Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries of the following
+// ranges up to the one that holds the row's end (known from the row pointers).  A row over more than kOwnPieces ranges is
+// added up by the whole wavefront, its lane groups taking every G-th piece, so that a hub row is not one chain of dependent
+// loads (R-MAT, 2^20 vertices, 16 M entries: 31 -> 5 us; 2^18 vertices: 25 -> 5 us).  The order of the sum depends on the
+// row's extent alone.
+constexpr int kOwnPieces = 4;
+
 template <int LPR, bool BF16>
-__global__ __launch_bounds__(256) void spmm_carry_kernel(int ranges, const RangeRec *__restrict__ recs,
-                                                         const float *__restrict__ carry,
-                                                         const float *__restrict__ dinv, char *__restrict__ z, int relu) {
+__global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) {
     constexpr int NV = Piece<BF16>::kVals;
     constexpr int F = LPR * NV;
-    constexpr int G = 256 / LPR;
-    const int tid = threadIdx.x;
-    const int sub = tid % LPR;
-    const int t = blockIdx.x * G + tid / LPR;
-    if (t >= ranges) return;
-    const RangeRec rec = recs[t];
-    if (!(rec.flags & kRight)) return;
-    float acc[NV];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) acc[q] = carry[((int64_t)t * 2 + 1) * F + sub * NV + q];
-    for (int j = t + 1; j < ranges; ++j) {
-        const int fj = recs[j].flags;
-        if (!(fj & kLeft)) break;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q] += carry[(int64_t)j * 2 * F + sub * NV + q];
-        if (fj & kLeftClosed) break;
+    constexpr int G = kWave / LPR;
+    const Item &item = batch.item[blockIdx.y];
+    const float *__restrict__ carry = as_global(item.carry), *__restrict__ dinv = as_global(item.dinv);
+    const RangeRec *__restrict__ recs = as_global(item.recs);
+    const int32_t *__restrict__ rowptr = as_global(item.rowptr);
+    char *__restrict__ z = as_global(item.z);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int sub = lane % LPR, g = lane / LPR;
+    const int first = (blockIdx.x * 256 + threadIdx.x) / kWave * G;     // the wavefront's records
+    const int t = first + g;
+    int row = -1, last = 0;
+    if (t < item.n_ranges) {
+        const RangeRec rec = recs[t];
+        if (rec.flags & kRight) {
+            row = rec.row_last;
+            last = min((rowptr[row + 1] - 1) / item.range_len, item.n_ranges - 1);
+        }
     }
-    finish_row<BF16, NV>(z, (int64_t)rec.row_last, LPR * 16, sub, dinv, relu, acc);
+    auto left = [&](int j, int q) { return carry[(int64_t)j * 2 * F + sub * NV + q]; };
+    const bool own = row >= 0 && last - t <= kOwnPieces;
+    if (own) {
+        float acc[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q] = carry[((int64_t)t * 2 + 1) * F + sub * NV + q];
+        for (int j = t + 1; j <= last; ++j)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) acc[q] += left(j, q);
+        finish_row<BF16, NV>(z, (int64_t)row, LPR * 16, sub, dinv, relu, acc);
+    }
+    for (uint64_t todo = __ballot(row >= 0 && !own && sub == 0); todo; todo &= todo - 1) {
+        const int src = __builtin_ctzll(todo);
+        const int tt = first + src / LPR, rr = __shfl(row, src, kWave), ll = __shfl(last, src, kWave);
+        float acc[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q] = 0.0f;
+#pragma unroll 4
+        for (int j = tt + 1 + g; j <= ll; j += G)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) acc[q] += left(j, q);
+#pragma unroll
+        for (int d = LPR; d < kWave; d <<= 1)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) acc[q] += __shfl_xor(acc[q], d, kWave);
+        if (g == 0) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) acc[q] += carry[((int64_t)tt * 2 + 1) * F + sub * NV + q];
+            finish_row<BF16, NV>(z, (int64_t)rr, LPR * 16, sub, dinv, relu, acc);
+        }
+    }
 }
 
 struct Workspace {
@@ -528,21 +582,19 @@ size_t workspace_layout(int64_t nnz, int32_t f, Workspace *ws, void *base, int64
     return total;
 }
 
+// The aggregations of one launch pair; grid.x follows from the longest, the others leave early.
 template <int LPR, bool BF16>
-int launch(int64_t n, int64_t nnz, int range_len, const int32_t *rowptr, const int32_t *colidx, const float *dinv, bool scale_v,
-           const void *h, void *z, int relu, const Workspace &ws, hipStream_t s, const float *vals = nullptr) {
+int launch(int64_t n, int count, const Batch &b, bool scale_v, int relu, hipStream_t s) {
     constexpr int G = 256 / LPR;
-    const int ranges = (int)((nnz + range_len - 1) / range_len);
+    int ranges = 0;
+    for (int k = 0; k < count; ++k) ranges = std::max(ranges, b.item[k].n_ranges);
     const int grid = (ranges + kXcds * kXcdChunk - 1) / (kXcds * kXcdChunk) * (kXcds * kXcdChunk);   // whole chunk rounds
     if (scale_v)
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, true>), dim3(grid), dim3(kWave), 0, s, (int)n, (int)nnz, range_len, ranges,
-                           rowptr, colidx, dinv, static_cast<const char *>(h), static_cast<char *>(z), relu, ws.recs, ws.carry, vals);
+        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, true>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
     else
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, false>), dim3(grid), dim3(kWave), 0, s, (int)n, (int)nnz, range_len, ranges,
-                           rowptr, colidx, dinv, static_cast<const char *>(h), static_cast<char *>(z), relu, ws.recs, ws.carry, vals);
+        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, false>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
     DGNN_RETURN_IF_LAUNCH_FAILED();
-    hipLaunchKernelGGL((spmm_carry_kernel<LPR, BF16>), dim3((ranges + G - 1) / G), dim3(256), 0, s, ranges, ws.recs,
-                       ws.carry, dinv, static_cast<char *>(z), relu);
+    hipLaunchKernelGGL((spmm_carry_kernel<LPR, BF16>), dim3((ranges + G - 1) / G, count), dim3(256), 0, s, relu, b);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
@@ -565,6 +617,19 @@ int range_length_of_call(int64_t nnz, int32_t f, dgnn_dtype dt, int64_t max_rang
     return range_length(nnz, (kWave / lpr) * kPer, max_ranges);
 }
 
+int launch_width(int64_t n, int count, const Batch &b, bool scale_v, int32_t f, dgnn_dtype dt, int relu, hipStream_t s) {
+    const int lpr = dt == DGNN_F32 ? f / 4 : f / 8;   // lanes per feature row, 16 bytes each
+    const bool bf = dt == DGNN_BF16;
+    switch (lpr) {
+        case 2: return launch<2, true>(n, count, b, scale_v, relu, s);
+        case 4: return bf ? launch<4, true>(n, count, b, scale_v, relu, s) : launch<4, false>(n, count, b, scale_v, relu, s);
+        case 8: return bf ? launch<8, true>(n, count, b, scale_v, relu, s) : launch<8, false>(n, count, b, scale_v, relu, s);
+        case 16: return bf ? launch<16, true>(n, count, b, scale_v, relu, s) : launch<16, false>(n, count, b, scale_v, relu, s);
+        case 32: return launch<32, false>(n, count, b, scale_v, relu, s);
+        default: return DGNN_ERR_SHAPE;
+    }
+}
+
 int spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *colidx, const float *dinv, const float *vals,
          const void *h, int32_t f, void *z, dgnn_dtype dt, uint32_t flags, uint32_t allowed, void *ws, size_t ws_bytes,
          void *stream, int64_t max_ranges = 0) {
@@ -577,24 +642,14 @@ int spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *colidx, c
     // max_ranges > 0: the records of exactly this call, laid out for its own number of ranges
     const int range_len = range_length_of_call(nnz, f, dt, max_ranges);
     if (range_len <= 0) return DGNN_ERR_CAPACITY;
+    const int64_t ranges = (nnz + range_len - 1) / range_len;
     Workspace w;
-    if (ws_bytes < workspace_layout(nnz, f, &w, ws, max_ranges > 0 ? (nnz + range_len - 1) / range_len : 0)) return DGNN_ERR_CAPACITY;
-    hipStream_t s = (hipStream_t)stream;
-    const int relu = (flags & DGNN_RELU) ? 1 : 0;
+    if (ws_bytes < workspace_layout(nnz, f, &w, ws, max_ranges > 0 ? ranges : 0)) return DGNN_ERR_CAPACITY;
     const bool scale_v = vals != nullptr || (dinv != nullptr && !(flags & DGNN_H_PRESCALED));
-    const int lpr = dt == DGNN_F32 ? f / 4 : f / 8;   // lanes per feature row, 16 bytes each
-    const bool bf = dt == DGNN_BF16;
-    switch (lpr) {
-        case 2: return launch<2, true>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals);
-        case 4: return bf ? launch<4, true>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals)
-                          : launch<4, false>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals);
-        case 8: return bf ? launch<8, true>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals)
-                          : launch<8, false>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals);
-        case 16: return bf ? launch<16, true>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals)
-                           : launch<16, false>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals);
-        case 32: return launch<32, false>(n, nnz, range_len, rowptr, colidx, dinv, scale_v, h, z, relu, w, s, vals);
-        default: return DGNN_ERR_SHAPE;
-    }
+    Batch b;
+    b.item[0] = Item{rowptr, colidx, dinv, vals, static_cast<const char *>(h), static_cast<char *>(z), w.recs, w.carry, (int32_t)nnz,
+                     range_len, (int32_t)ranges, 0};
+    return launch_width(n, 1, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -603,6 +658,62 @@ extern "C" int dgnn_spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const in
                          const void *h, int32_t f, void *z, dgnn_dtype dt, uint32_t flags,
                          void *ws, size_t ws_bytes, void *stream) {
     return spmm(n, nnz, rowptr, colidx, dinv, nullptr, h, f, z, dt, flags, DGNN_RELU | DGNN_H_PRESCALED, ws, ws_bytes, stream);
+}
+
+// ---- the aggregations of several timesteps in one launch pair: on small snapshots one of them leaves most of the chip
+// idle, and every launch costs as long as the aggregation itself
+extern "C" int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, size_t *bytes) {
+    if (!bytes) return DGNN_ERR_NULL;
+    if (count <= 0 || nnz < 0 || !supported_width(f)) return DGNN_ERR_SHAPE;
+    if (!fits_index(nnz)) return DGNN_ERR_OVERFLOW;
+    // the shortest range any storage type uses at this width is one sub-tile; no call has more ranges than this
+    const int64_t shortest = kWave / (f / 4) * kPer;
+    const int64_t ranges = std::min<int64_t>((nnz + shortest - 1) / shortest, std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange));
+    *bytes = (size_t)count * workspace_layout(nnz, f, nullptr, nullptr, ranges + 1);
+    return DGNN_OK;
+}
+
+extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *items, int32_t f, dgnn_dtype dt, uint32_t flags,
+                               void *ws, size_t ws_bytes, void *stream) {
+    if (!items || !ws) return DGNN_ERR_NULL;
+    if (n <= 0 || count <= 0 || !supported_width(f) || (flags & ~(DGNN_RELU | DGNN_H_PRESCALED))) return DGNN_ERR_SHAPE;
+    if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
+    if (!fits_index(n + 1)) return DGNN_ERR_OVERFLOW;
+    if (!aligned16(ws)) return DGNN_ERR_ALIGN;
+    const bool weighted = items[0].val != nullptr;
+    for (int k = 0; k < count; ++k) {
+        const dgnn_spmm_item &it = items[k];
+        if (!it.rowptr || !it.colidx || !it.h || !it.z) return DGNN_ERR_NULL;
+        if (it.nnz <= 0 || (it.val != nullptr) != weighted) return DGNN_ERR_SHAPE;
+        // as in dgnn_spmm_weighted: with values the normalisation is in the rows of h or there is none
+        if (weighted && (it.dinv != nullptr) != ((flags & DGNN_H_PRESCALED) != 0)) return DGNN_ERR_SHAPE;
+        if (!fits_index(it.nnz)) return DGNN_ERR_OVERFLOW;
+        if (!aligned16(it.h) || !aligned16(it.z)) return DGNN_ERR_ALIGN;
+        if (it.h == it.z) return DGNN_ERR_ALIAS;
+    }
+    char *base = static_cast<char *>(ws);
+    for (int done = 0; done < count; done += kMaxBatch) {
+        const int m = std::min(count - done, kMaxBatch);
+        Batch b;
+        for (int k = 0; k < m; ++k) {
+            const dgnn_spmm_item &it = items[done + k];
+            const int range_len = range_length_of_call(it.nnz, f, dt);
+            const int64_t ranges = (it.nnz + range_len - 1) / range_len;
+            Workspace w;
+            const size_t size = workspace_layout(it.nnz, f, &w, base, ranges);
+            if ((size_t)(base - static_cast<char *>(ws)) + size > ws_bytes) return DGNN_ERR_CAPACITY;
+            base += size;
+            b.item[k] = Item{it.rowptr, it.colidx, it.dinv, it.val, static_cast<const char *>(it.h), static_cast<char *>(it.z), w.recs, w.carry,
+                             (int32_t)it.nnz, range_len, (int32_t)ranges, 0};
+        }
+        // whether a per-entry factor is gathered is the launch's choice, not the item's
+        const bool scale_v = weighted || (b.item[0].dinv != nullptr && !(flags & DGNN_H_PRESCALED));
+        for (int k = 1; k < m; ++k)
+            if ((b.item[k].dinv != nullptr) != (b.item[0].dinv != nullptr)) return DGNN_ERR_SHAPE;
+        const int rc = launch_width(n, m, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
+        if (rc != DGNN_OK) return rc;
+    }
+    return DGNN_OK;
 }
 
 // ---- the same aggregation for callers that cannot allocate: its carry records live in a file-scope device array ----

@@ -17,6 +17,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
+from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, pointers, steps_together
 
 
 @dataclass
@@ -88,13 +89,19 @@ class BlockRunner:
         dt = blk.x[0].dtype
         cap = max(blk.nnz)
         self.cap = cap
-        # CSR slots: slot 2 keeps A_1 for the whole life of the block (so a pass can be repeated), slots
-        # 0 and 1 are used alternately by A_2, A_3, ...: A_{t-1} is read while A_t is written
-        self.rowptr = [torch.empty(n + 1, dtype=torch.int32, device=dev) for _ in range(3)]
-        self.colidx = [torch.empty(cap, dtype=torch.int32, device=dev) for _ in range(3)]
-        self.dinv = [torch.empty(n, dtype=torch.float32, device=dev) for _ in range(3)]
-        self.h = torch.empty((n, f), dtype=dt, device=dev)
-        self.z_mid = torch.empty((n, f), dtype=dt, device=dev) if blk.layers > 1 else None
+        # CSR slots: slot 2 keeps A_1 for the whole life of the block (so a pass can be repeated), slots 0 and 1 are used
+        # alternately by A_2, A_3, ...: A_{t-1} is read while A_t is written.  Where the whole block is rebuilt in one go
+        # every timestep but the last two has a slot of its own behind these
+        self.series = self._series_pays()
+        self.together = steps_together(n * f * blk.x[0].element_size(), blk.T) if self.series else 1
+        slots = max(blk.T, 3) if self.series else 3
+        self.rowptr = [torch.empty(n + 1, dtype=torch.int32, device=dev) for _ in range(slots)]
+        self.colidx = [torch.empty(cap, dtype=torch.int32, device=dev) for _ in range(slots)]
+        self.dinv = [torch.empty(n, dtype=torch.float32, device=dev) for _ in range(slots)]
+        self.h_batch = torch.empty((self.together, n, f), dtype=dt, device=dev)
+        self.h = self.h_batch[0]
+        self.z_mid_batch = torch.empty((self.together, n, f), dtype=dt, device=dev) if blk.layers > 1 else None
+        self.z_mid = self.z_mid_batch[0] if blk.layers > 1 else None
         self.keep_all_z = bool(blk.window) if keep_all_z is None else keep_all_z
         zt = blk.T if self.keep_all_z else 1
         self.z = torch.empty((zt, n, f), dtype=dt, device=dev)
@@ -106,6 +113,7 @@ class BlockRunner:
         self.ws_spmm = torch.empty(ws_s, dtype=torch.uint8, device=dev)
         self.status = torch.zeros(blk.T + 1, dtype=torch.int32, device=dev)
         self.timer: Optional[StageTimer] = None
+        self._tables = None             # of the calls that take several timesteps, made by the first pass that uses them
         # staging for difference lists that arrive from pinned host memory (two sets, used alternately)
         self.stage = None
         if blk.pinned is not None:
@@ -119,16 +127,22 @@ class BlockRunner:
     def _stage(self, name: str):
         return self.timer.stage(name) if self.timer is not None else contextlib.nullcontext()
 
-    @staticmethod
-    def slot_of(t: int) -> int:
+    def _series_pays(self) -> bool:
+        """Whether a pass over resident lists rebuilds all snapshots first (dgnn_delta_rebuild_series) and then takes the
+        GCN steps of several timesteps together."""
+        return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES
+
+    def slot_of(self, t: int) -> int:
+        if self.series and 1 < t < self.blk.T - 1:
+            return t + 1
         return 2 if t == 1 else t % 2
 
     def load_first(self) -> None:
         """Place A_1 in its slot and derive its dinv (outside any timed region: A_1 is sent whole)."""
-        blk = self.blk
-        self.rowptr[2].copy_(blk.rowptr1)
-        self.colidx[2][: blk.nnz[0]].copy_(blk.colidx1)
-        B.csr_dinv(self.rowptr[2], self.dinv[2])
+        blk, slot = self.blk, self.slot_of(1)
+        self.rowptr[slot].copy_(blk.rowptr1)
+        self.colidx[slot][: blk.nnz[0]].copy_(blk.colidx1)
+        B.csr_dinv(self.rowptr[slot], self.dinv[slot])
 
     def rebuild(self, t: int, lists, validate: bool = False) -> None:
         """A_t from A_{t-1} and the difference lists of step t (t >= 2)."""
@@ -193,6 +207,10 @@ class BlockRunner:
             self._run_overlapped(first, validate, on_snapshot, pinned=False, prefetch_next=False)
             return
         self.begin_pass()
+        if self.series and not validate and on_snapshot is None and self.timer is None:
+            self._run_series(first)
+            self.mix()
+            return
         for t in range(1, blk.T + 1):
             if t >= 2:
                 self.rebuild(t, blk.deltas[t - 2], validate)
@@ -202,6 +220,64 @@ class BlockRunner:
             if on_snapshot is not None:
                 on_snapshot(t, self.slot_of(t))
         self.mix()
+
+    # ------------------------------------------------------------------ several timesteps per call
+    def _make_tables(self):
+        blk, dev = self.blk, self.dev
+        n, f, T, L, m = blk.n, blk.f, blk.T, blk.layers, self.together
+        dt = blk.x[0].dtype
+        tb = type("Tables", (), {})()
+        order = [self.slot_of(t) for t in range(1, T + 1)]
+        rowptr, colidx, dinv = ([side[k] for k in order] for side in (self.rowptr, self.colidx, self.dinv))
+        tb.series = SeriesTable(rowptr[1:], colidx[1:], dinv[1:])
+        tb.x = Frames((n, f), dt, "x")
+        tb.w = [Frames((f, f), dt, "w") for _ in range(L)]
+        # frames that nobody keeps (keep_all_z off) still need a place while their neighbours are being formed
+        spare = torch.empty((m, n, f), dtype=dt, device=dev) if not self.keep_all_z and T > 1 and m > 1 else self.z
+        z = [self.z[t] if self.keep_all_z else self.z[0] if (m == 1 or t == T - 1) else spare[t % m] for t in range(T)]
+        tb.spare = spare
+        h = pointers([self.h_batch[t % m] for t in range(T)])
+        mid = pointers([self.z_mid_batch[t % m] for t in range(T)]) if L > 1 else None
+        tb.transform, tb.spmm = [], []
+        for layer in range(L):
+            a, b = TransformTable(T), SpmmTable(T)
+            if layer > 0:
+                a.column(a.X, mid)
+            a.column(a.SCALE, pointers(dinv))
+            a.column(a.H, h)
+            b.column(b.ROWPTR, pointers(rowptr))
+            b.column(b.COLIDX, pointers(colidx))
+            b.column(b.DINV, pointers(dinv))
+            b.column(b.H, h)
+            b.column(b.Z, pointers(z) if layer == L - 1 else mid)
+            b.column(b.NNZ, blk.nnz)
+            tb.transform.append(a)
+            tb.spmm.append(b)
+        tb.ws = torch.empty(B.spmm_batch_workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
+        return tb
+
+    def _run_series(self, first: int) -> None:
+        """All snapshots, then the GCN steps `together` timesteps at a time; the same kernels on the same operands as one
+        step after the other, bit for bit."""
+        blk = self.blk
+        if self._tables is None:
+            self._tables = self._make_tables()
+        tb, n, f, T, m = self._tables, blk.n, blk.f, blk.T, self.together
+        stream = torch.cuda.current_stream(self.dev).cuda_stream
+        dt = B._dtype_code(self.h)
+        one = self.slot_of(1)
+        tb.series.lists(blk.deltas)
+        B.delta_rebuild_series(n, self.rowptr[one], self.colidx[one], blk.nnz[0], T - 1, tb.series.at(), self.cap, stream)
+        a0 = tb.transform[0]
+        a0.column(a0.X, tb.x.addresses(blk.x[:T]))
+        for layer in range(blk.layers):
+            a = tb.transform[layer]
+            a.column(a.W, tb.w[layer].addresses([w[layer] for w in blk.w_t] if blk.w_t is not None else [blk.w[layer]]))
+        for t in range(first - 1, T, m):
+            k = min(m, T - t)
+            for layer in range(blk.layers):
+                B.feature_transform_batch(k, tb.transform[layer].at(t), n, f, f, 0, dt, stream)
+                B.spmm_batch(n, k, tb.spmm[layer].at(t), f, dt, B.DGNN_RELU | B.DGNN_H_PRESCALED, tb.ws, stream)
 
     def _run_overlapped(self, first: int, validate: bool, on_snapshot, pinned: bool, prefetch_next: bool) -> None:
         """The same pass on two streams: the rebuild of A_t, whatever a subclass does to A_t (snapshot_ready) and the
@@ -370,6 +446,9 @@ class SmoothedRunner(BlockRunner):
     def stored_entries(self) -> int:
         """Entries of the current smoothed snapshot (reads the device: waits for the stream)."""
         return int(self.cur[0][-1])
+
+    def _series_pays(self) -> bool:
+        return False
 
     def slot_of(self, t: int) -> int:                   # a ring: A_{t-life} is still there when S_t is formed
         return t % (self.life + 1)

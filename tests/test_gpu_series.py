@@ -1,0 +1,101 @@
+"""The calls that take several timesteps at once against the calls that take one: snapshots rebuilt as a series bit for bit
+those of step-by-step rebuilds, batched products and aggregations bit for bit the single ones."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2109_07893_amd as dg
+from dtdg_synth import WORKLOADS, DynamicGraph
+from dtdg_synth.blocks import make_block
+from paper_2109_07893_amd import binding as B
+from paper_2109_07893_amd.batch import SeriesTable, SpmmTable, TransformTable, pointers
+from paper_2109_07893_amd.pipeline import BlockRunner
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def graph(kind, n, deg, T, dels, adds, seed=11):
+    return replace(WORKLOADS["c2" if kind == "er" else "c5"], name=kind, n=n, T=T, avg_deg=float(deg), n_draws=n * deg,
+                   del_frac=dels, add_frac=adds, seed=seed)
+
+
+# stretches of 1536 entries that grow by a third before they leave the LDS, groups of four steps, launches of 32 steps
+@pytest.mark.parametrize("kind,n,deg,T,dels,adds", [
+    ("er", 7, 3, 5, 0.2, 0.2), ("er", 257, 4, 40, 0.1, 0.1), ("er", 1536, 1, 3, 0.0, 0.5), ("rmat", 1024, 20, 12, 0.05, 0.05),
+    ("er", 300, 8, 6, 0.0, 0.5), ("er", 2000, 6, 10, 0.05, 0.4), ("er", 5000, 30, 5, 0.5, 0.9), ("er", 4001, 10, 5, 0.6, 0.0),
+    ("rmat", 1 << 14, 16, 34, 0.03, 0.03)])
+def test_series_equals_step_by_step(kind, n, deg, T, dels, adds):
+    g = DynamicGraph(graph(kind, n, deg, T, dels, adds), device=DEV)
+    rp, ci = g.csr()
+    steps = [g.advance() for _ in range(T - 1)]
+    nnz = [int(ci.numel())]
+    for d in steps:
+        nnz.append(nnz[-1] + d[0].numel() - d[2].numel())
+    cap = max(nnz)
+    got = ([torch.full((n + 1,), -7, dtype=torch.int32, device=DEV) for _ in steps],
+           [torch.full((cap,), -7, dtype=torch.int32, device=DEV) for _ in steps], [torch.zeros(n, device=DEV) for _ in steps])
+    table = SeriesTable(*got)
+    table.lists(steps)
+    B.delta_rebuild_series(n, rp, ci, nnz[0], len(steps), table.at(), cap, torch.cuda.current_stream().cuda_stream)
+    longest = max(max(d[0].numel(), d[2].numel()) for d in steps) + 1
+    ws = torch.empty(dg.delta_rebuild_workspace(n, cap, longest, longest), dtype=torch.uint8, device=DEV)
+    for k, (ar, ac, dr, dc) in enumerate(steps):
+        rp2, ci2, dinv2 = torch.empty_like(rp), torch.empty(cap, dtype=torch.int32, device=DEV), torch.empty(n, device=DEV)
+        dg.delta_rebuild(rp, ci, nnz[k], ar, ac, ar.numel(), dr, dc, dr.numel(), rp2, ci2, dinv2, ws)
+        assert torch.equal(rp2, got[0][k]) and torch.equal(ci2[: nnz[k + 1]], got[1][k][: nnz[k + 1]]), k
+        assert bool((got[1][k][nnz[k + 1]:] == -7).all()) and torch.equal(dinv2, got[2][k]), k
+        rp, ci = rp2, ci2
+
+
+@pytest.mark.parametrize("dtype,f", [(torch.float32, 16), (torch.float32, 64), (torch.bfloat16, 32), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("count", [1, 3, 33])
+def test_batched_products_and_aggregations_equal_single_ones(dtype, f, count):
+    """33 items: one more than a launch takes.  Snapshots of different sizes, hub rows over many ranges among them."""
+    torch.manual_seed(count)
+    n, dt = 1 << 11, (B.DGNN_F32 if dtype == torch.float32 else B.DGNN_BF16)
+    snaps = [DynamicGraph(graph("rmat", n, 4 + 12 * (k % 3), 2, 0, 0, seed=k), device=DEV).csr() for k in range(count)]
+    x = [torch.randn(n, f, device=DEV).to(dtype) for _ in range(count)]
+    w = [(torch.randn(f, f, device=DEV) / f ** 0.5).to(dtype) for _ in range(count)]
+    dinv = [torch.empty(n, device=DEV) for _ in range(count)]
+    for (rp, _), d in zip(snaps, dinv):
+        dg.csr_dinv(rp, d)
+    h, z, h1, z1 = (torch.zeros(count, n, f, dtype=dtype, device=DEV) for _ in range(4))
+    nnz = [int(ci.numel()) for _, ci in snaps]
+    a, b = TransformTable(count), SpmmTable(count)
+    for k, col in ((a.X, x), (a.W, w), (a.SCALE, dinv), (a.H, list(h))):
+        a.column(k, pointers(col))
+    for k, col in ((b.ROWPTR, [s[0] for s in snaps]), (b.COLIDX, [s[1] for s in snaps]), (b.DINV, dinv), (b.H, list(h)), (b.Z, list(z))):
+        b.column(k, pointers(col))
+    b.column(b.NNZ, nnz)
+    ws = torch.empty(B.spmm_batch_workspace(count, max(nnz), f), dtype=torch.uint8, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.feature_transform_batch(count, a.at(), n, f, f, 0, dt, stream)
+    B.spmm_batch(n, count, b.at(), f, dt, B.DGNN_RELU | B.DGNN_H_PRESCALED, ws, stream)
+    ws1 = torch.empty(dg.spmm_workspace(n, max(nnz), f), dtype=torch.uint8, device=DEV)
+    for k in range(count):
+        dg.feature_transform(x[k], w[k], h1[k], row_scale=dinv[k])
+        dg.spmm(snaps[k][0], snaps[k][1], nnz[k], dinv[k], h1[k], z1[k], ws1, flags=dg.DGNN_RELU | dg.DGNN_H_PRESCALED)
+    assert torch.equal(h, h1) and torch.equal(z, z1)
+    a.column(a.SCALE, 0)
+    B.feature_transform_batch(count, a.at(), n, f, f, B.DGNN_RELU, dt, stream)
+    dg.feature_transform(x[0], w[0], h1[0])
+    assert torch.equal(h[0].float(), torch.relu(h1[0].float()))
+
+
+@pytest.mark.parametrize("name,n,T,keep", [("c1", 1000, 8, None), ("c2", 20_000, 7, True), ("c3", 1 << 12, 5, False), ("c4", 3_001, 35, None)])
+def test_pass_with_batched_steps_equals_the_pass_step_by_step(name, n, T, keep):
+    wl = WORKLOADS[name] if WORKLOADS[name].n == n else WORKLOADS[name].scaled(n, T=T)
+    runner = BlockRunner(make_block(wl, DEV, gen_device="cpu", T=T), keep_all_z=keep)
+    assert runner.series
+    runner.load_first()
+    runner.run_resident(validate=True)                   # validation goes step by step
+    want = runner.z.clone()
+    for first in (1, 2):
+        runner.z.fill_(float("nan"))
+        runner.run_resident(first=first)
+        torch.cuda.synchronize()
+        if first == 1 or not runner.blk.window:
+            assert torch.equal(runner.z[first - 1 if runner.keep_all_z else 0:], want[first - 1 if runner.keep_all_z else 0:])
