@@ -96,6 +96,8 @@ def algorithmic_bytes(blk, stage, t=None):
         return 4 * blk.nnz[t - 1] + 8 * n + 2 * s * n * f
     if stage == "relu_backward":   # gradient in, activation in, masked gradient out
         return 3 * s * n * f + 4 * n
+    if stage == "weight_grad" and blk.layers == 1:      # aggregated features, gradient, activation (the ReLU's mask) in
+        return 3 * s * n * f + s * f * f
     if stage in ("weight_grad", "input_grad"):
         return 2 * s * n * f + s * f * f
     raise KeyError(stage)
@@ -596,12 +598,12 @@ def training_step(args, wl, blk, dev):
     from paper_2109_07893_amd.pipeline import StageTimer
     from paper_2109_07893_amd.training import make_trainer
     # The whole series in one block if its activations and gradients fit next to the inputs (the upstream
-    # gradient and three more tensors of T x N x F); otherwise the paper's gradient checkpointing: blocks of
+    # gradient and four more tensors of T x N x F); otherwise the paper's gradient checkpointing: blocks of
     # timesteps, a forward pass that keeps only the hand-over, then per block a rerun and the backward pass.
     from paper_2109_07893_amd.training import CheckpointedTrainer
     frame = blk.n * blk.f * blk.x[0].element_size()
     free_bytes, _ = torch.cuda.mem_get_info(dev)
-    fit = int((0.85 * free_bytes - blk.T * frame) // (3 * frame))
+    fit = int((0.85 * free_bytes - blk.T * frame) // (4 * frame))
     n_blocks = 1 if fit >= blk.T else -(-blk.T // max(fit, 2))
     g_y = torch.empty((blk.T, blk.n, blk.f), dtype=blk.x[0].dtype, device=dev)
     for t in range(1, blk.T + 1):
@@ -654,7 +656,7 @@ def training_step(args, wl, blk, dev):
     edges = sum(blk.nnz)
     return {"ms_per_step": ms, "value": edges / (ms * 1e-3), "unit": "edges/s",
             "what": f"forward keeping activations + backward over t=1..{blk.T} ({'directed: second chain of transposed snapshots' if directed else 'undirected: the snapshot is its own transpose'}); "
-                    "weight gradients of every layer, reverse rebuilds with exchanged lists"
+                    "weight gradients of every layer; reverse rebuilds with exchanged lists where gradients travel through an aggregation"
                     + (f"; gradient checkpointing over {n_blocks} blocks: every block's forward pass runs twice" if n_blocks > 1 else ""),
             "checkpoint_blocks": n_blocks,
             "edges_per_step": edges, "stages": stages}

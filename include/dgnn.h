@@ -228,7 +228,13 @@ typedef struct {
     void *h;
 } dgnn_transform_item;
 
-/* dgnn_feature_transform for `count` products of the same shape and storage type.  flags: 0 or DGNN_RELU (the ReLU of the result). */
+/* Flags of dgnn_feature_transform_batch: DGNN_RELU (the ReLU of the result), and */
+#define DGNN_W_TRANSPOSED 4u     /* w is [f_out][f_in]: the products of dgnn_input_grad */
+
+/*
+ * dgnn_feature_transform for `count` products of the same shape and storage type.  w NULL in all items (f_in = f_out, no
+ * flags): only the rows are scaled, h = diag(row_scale) x.
+ */
 int dgnn_feature_transform_batch(int32_t count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int32_t f_out,
                                  uint32_t flags, dgnn_dtype dt, void *stream);
 
@@ -456,6 +462,21 @@ int dgnn_weight_grad_workspace(int32_t f_in, int32_t f_out, size_t *bytes);
  */
 int dgnn_weight_grad(const void *x, const void *g, int64_t n, int32_t f_in, int32_t f_out, float *dw,
                      int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream);
+
+/* One gradient of dgnn_weight_grad_batch: dw = x^T g, or, with z given, x^T (z > 0 ? g : 0); z in all items or in none. */
+typedef struct {
+    const void *x, *g, *z;
+    float *dw;
+} dgnn_weight_grad_item;
+
+/*
+ * dgnn_weight_grad for `count` gradients over n rows each (one weight per timestep, or one item over the rows of several
+ * timesteps).  With z = the layer's output the gradient passes its ReLU on the way in: with x = A~ X and g = dL/dZ this is
+ * the gradient of W for a layer evaluated as Z = sigma((A~ X) W), X^T A~^T G_P = (A~ X)^T G_P: no aggregation going back.
+ * Workspace as dgnn_weight_grad.
+ */
+int dgnn_weight_grad_batch(int32_t count, const dgnn_weight_grad_item *items, int64_t n, int32_t f_in, int32_t f_out,
+                           int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream);
 
 /*
  * Gradient of the input of H = X W: dx = G W^T, or diag(row_scale) G W^T.

@@ -66,9 +66,9 @@ class SeriesTable(Table):
 
     def __init__(self, rowptr, colidx, dinv):
         super().__init__(len(rowptr), 9)
-        self.column(6, pointers(rowptr)) if rowptr else None
-        self.column(7, pointers(colidx)) if colidx else None
-        self.column(8, pointers(dinv)) if dinv else None
+        for k, tensors in ((6, rowptr), (7, colidx), (8, dinv)):
+            if tensors:
+                self.column(k, pointers(tensors))
         self.seen, self.kept = Seen(), None
 
     def lists(self, deltas) -> None:
@@ -97,6 +97,14 @@ class SpmmTable(Table):
 
     def __init__(self, rows: int):
         super().__init__(rows, 7)
+
+
+class WeightGradTable(Table):
+    """dgnn_weight_grad_item: x, g, z, dw."""
+    X, G, Z, DW = range(4)
+
+    def __init__(self, rows: int):
+        super().__init__(rows, 4)
 
 
 class Frames:

@@ -21,6 +21,7 @@ DGNN_VALIDATE = 1
 DGNN_UPDATES_SORTED = 2
 DGNN_RELU = 1
 DGNN_H_PRESCALED = 2
+DGNN_W_TRANSPOSED = 4
 
 EXPORTS = (
     "dgnn_strerror", "dgnn_csr_validate", "dgnn_csr_dinv", "dgnn_delta_h2d", "dgnn_delta_rebuild_workspace",
@@ -28,7 +29,7 @@ EXPORTS = (
     "dgnn_spmm_static", "dgnn_mproduct",
     "dgnn_delta_rebuild_weighted", "dgnn_spmm_weighted", "dgnn_csr_combine_workspace", "dgnn_csr_combine", "dgnn_csr_weighted_dinv_workspace", "dgnn_csr_weighted_dinv", "dgnn_concat_relu", "dgnn_transform_concat_relu", "dgnn_lstm_cell", "dgnn_lstm_step", "dgnn_lstm_cell_backward", "dgnn_lstm_step_backward", "dgnn_concat_relu_backward", "dgnn_bias_grad_workspace", "dgnn_bias_grad", "dgnn_add",
     "dgnn_csr_transpose_workspace", "dgnn_csr_transpose", "dgnn_coo_transpose_workspace", "dgnn_coo_transpose",
-    "dgnn_delta_rebuild_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch",
+    "dgnn_delta_rebuild_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
     "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
 )
 
@@ -105,6 +106,7 @@ def load_library():
     lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp]
     lib.dgnn_feature_transform_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _u32, ctypes.c_int, _vp]
     lib.dgnn_spmm_batch_workspace.argtypes = [_i32, _i64, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_weight_grad_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _i32, ctypes.c_int, _vp, _sz, _vp]
     lib.dgnn_spmm_batch.argtypes = [_i64, _i32, _vp, _i32, ctypes.c_int, _u32, _vp, _sz, _vp]
     lib.dgnn_mproduct.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, ctypes.c_int, _vp]
     lib.dgnn_mproduct_backward.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, ctypes.c_int, _vp]
@@ -307,6 +309,11 @@ def spmm_batch_workspace(count: int, nnz: int, f: int) -> int:
 
 def spmm_batch(n: int, count: int, table: int, f: int, dt: int, flags: int, ws: torch.Tensor, stream) -> None:
     _check(load_library().dgnn_spmm_batch(n, count, table, f, dt, flags, _ptr(ws), ws.numel() * ws.element_size(), stream), "dgnn_spmm_batch")
+
+
+def weight_grad_batch(count: int, table: int, n: int, f_in: int, f_out: int, accumulate: bool, dt: int, ws: torch.Tensor, stream) -> None:
+    _check(load_library().dgnn_weight_grad_batch(count, table, n, f_in, f_out, int(accumulate), dt, _ptr(ws), ws.numel() * ws.element_size(),
+                                                 stream), "dgnn_weight_grad_batch")
 
 
 def delta_rebuild_weighted(rowptr_prev, colidx_prev, val_prev, nnz_prev: int, add, dele, upd,

@@ -5,6 +5,7 @@
 //     G_P = G_Z where Z > 0, else 0              relu_backward_kernel (can fold a row scale in)
 //     G_H = A~^T G_P                              the aggregation kernel on the transposed snapshot
 //     dW  = X^T G_H                               wgrad_kernel + wgrad_reduce_kernel   (this file)
+//         = (A~ X)^T G_P                          the same, with the mask folded in: no aggregation going back
 //     dX  = G_H W^T                               the X W kernels with W read transposed
 //
 // dW = X^T G_H contracts over the N rows, so it reads both matrices once (HBM-bound, 2 s N F bytes) and
@@ -28,6 +29,14 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// One gradient of a launch; blockIdx.y says which.  z (may be null): only rows' elements with z > 0 let g through.
+struct Item {
+    const void *x, *g, *z;
+    float *dw;
+};
+constexpr int kMaxBatch = 32;
+struct Batch { Item item[kMaxBatch]; };
+
 constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kStepRows = 16;        // rows per step: eight fp32 MFMAs of depth 2, or one bf16 MFMA of depth 16
@@ -49,14 +58,16 @@ struct Split {
     static_assert(TI * TJ == TPW && GI * TI == NI && GJ * TJ == NJ && RS * GROUPS == kWavesPerBlock, "tile split");
 };
 
-template <int FIN, int FOUT, bool BF16>
-__global__ __launch_bounds__(kThreads) void wgrad_kernel(const void *__restrict__ xv, const void *__restrict__ gv, int64_t n,
-                                                         int64_t n_steps, float *__restrict__ partial) {
+// MASKED: G is taken where Z > 0 only (the gradient through the ReLU, which then needs no pass of its own).
+template <int FIN, int FOUT, bool BF16, bool MASKED>
+__device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *__restrict__ gv, const void *__restrict__ zv, int64_t n,
+                                      int64_t n_steps, float *__restrict__ partial) {
     using S = Split<FIN, FOUT>;
     typedef typename std::conditional<BF16, uint16_t, float>::type Elem;
     typedef typename std::conditional<BF16, uint32_t, float>::type Raw;
     const Elem *x = static_cast<const Elem *>(xv);
     const Elem *g = static_cast<const Elem *>(gv);
+    const Elem *z = static_cast<const Elem *>(zv);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int i = lane & 31, hh = lane >> 5;
     const int group = wave % S::GROUPS, rs = wave / S::GROUPS;
@@ -76,7 +87,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const void *__restrict_
     // depth-16 MFMA takes rows (8 h + e).
     auto row_of = [&](int64_t step, int e) { return step * kStepRows + (BF16 ? 8 * hh + e : 2 * e + hh); };
     // Loads are unconditional (addresses clamped into the matrices); what lies outside is zeroed when used.
-    Raw xa_next[S::TI][8], gb_next[S::TJ][8];
+    Raw xa_next[S::TI][8], gb_next[S::TJ][8], zb_next[MASKED ? S::TJ : 1][8];
     auto fetch = [&](int64_t step) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -84,7 +95,11 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const void *__restrict_
 #pragma unroll
             for (int ti = 0; ti < S::TI; ++ti) xa_next[ti][e] = x[row * FIN + std::min((it0 + ti) * 32 + i, FIN - 1)];
 #pragma unroll
-            for (int tj = 0; tj < S::TJ; ++tj) gb_next[tj][e] = g[row * FOUT + std::min((jt0 + tj) * 32 + i, FOUT - 1)];
+            for (int tj = 0; tj < S::TJ; ++tj) {
+                const int64_t at = row * FOUT + std::min((jt0 + tj) * 32 + i, FOUT - 1);
+                gb_next[tj][e] = g[at];
+                if (MASKED) zb_next[tj][e] = z[at];
+            }
         }
     };
     if (me < n_steps) fetch(me);
@@ -96,7 +111,12 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const void *__restrict_
 #pragma unroll
             for (int ti = 0; ti < S::TI; ++ti) xa[ti][e] = (row_ok && (it0 + ti) * 32 + i < FIN) ? xa_next[ti][e] : Raw(0);
 #pragma unroll
-            for (int tj = 0; tj < S::TJ; ++tj) gb[tj][e] = (row_ok && (jt0 + tj) * 32 + i < FOUT) ? gb_next[tj][e] : Raw(0);
+            for (int tj = 0; tj < S::TJ; ++tj) {
+                bool ok = row_ok && (jt0 + tj) * 32 + i < FOUT;
+                if constexpr (MASKED && BF16) ok = ok && zb_next[tj][e] - 1u < 0x7fffu;      // a positive bf16: sign clear, not zero
+                if constexpr (MASKED && !BF16) ok = ok && zb_next[tj][e] > 0.0f;
+                gb[tj][e] = ok ? gb_next[tj][e] : Raw(0);
+            }
         }
         fetch(std::min(step + workers, n_steps - 1));      // the next step's rows travel while this one is multiplied
         __builtin_amdgcn_sched_barrier(0);                  // ... so the loads must stay ahead of the multiplications
@@ -144,12 +164,20 @@ __global__ __launch_bounds__(kThreads) void wgrad_kernel(const void *__restrict_
             }
 }
 
+template <int FIN, int FOUT, bool BF16, bool MASKED>
+__global__ __launch_bounds__(kThreads) void wgrad_kernel(Batch batch, int64_t n, int64_t n_steps, float *__restrict__ partial) {
+    const Item &it = batch.item[blockIdx.y];
+    wgrad<FIN, FOUT, BF16, MASKED>(as_global(it.x), as_global(it.g), as_global(it.z), n, n_steps,
+                                   partial + (int64_t)blockIdx.y * gridDim.x * Split<FIN, FOUT>::RS * FIN * FOUT);
+}
+
 // dw[e] = (accumulate ? dw[e] : 0) + sum over the workers' partial results: sixteen wavefronts take a slice of
 // the workers each (in worker order), then the sixteen slice sums are added in slice order: a fixed order.
 constexpr int kReduceSlices = 16;
-__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(const float *__restrict__ partial, int workers,
-                                                                            int elems, float *__restrict__ dw,
-                                                                            int accumulate) {
+__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, const float *__restrict__ partial, int workers,
+                                                                            int elems, int accumulate) {
+    float *__restrict__ dw = as_global(batch.item[blockIdx.y].dw);
+    partial += (int64_t)blockIdx.y * workers * elems;
     __shared__ float s_sum[kReduceSlices][kWave];
     const int lane = threadIdx.x & (kWave - 1), slice = threadIdx.x / kWave;
     const int e = blockIdx.x * kWave + lane;
@@ -198,40 +226,41 @@ __global__ __launch_bounds__(kThreads) void relu_backward_kernel(const uintx4 *_
     __builtin_nontemporal_store(o, out + p);
 }
 
-template <int FIN, int FOUT, bool BF16>
-int launch_wgrad(const void *x, const void *g, int64_t n, float *dw, int accumulate, float *partial, hipStream_t s) {
+template <int FIN, int FOUT, bool BF16, bool MASKED>
+int launch_wgrad(int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     using S = Split<FIN, FOUT>;
     const int64_t n_steps = (n + kStepRows - 1) / kStepRows;
     const int64_t needed = (n_steps + S::RS - 1) / S::RS;
-    const int64_t blocks = std::min<int64_t>(std::min<int64_t>(needed, resident_workgroups(wgrad_kernel<FIN, FOUT, BF16>, kThreads, 512)), kMaxBlocks);
-    hipLaunchKernelGGL((wgrad_kernel<FIN, FOUT, BF16>), dim3((unsigned)blocks), dim3(kThreads), 0, s, x, g, n, n_steps, partial);
+    // the items of a launch share the workspace (one partial result per row worker) and the device
+    const int64_t most = std::min<int64_t>(resident_workgroups(wgrad_kernel<FIN, FOUT, BF16, MASKED>, kThreads, 512), kMaxBlocks);
+    const int64_t blocks = std::min<int64_t>(needed, std::max<int64_t>(1, most / count));
+    hipLaunchKernelGGL((wgrad_kernel<FIN, FOUT, BF16, MASKED>), dim3((unsigned)blocks, (unsigned)count), dim3(kThreads), 0, s, b, n, n_steps, partial);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     constexpr int elems = FIN * FOUT;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((elems + kWave - 1) / kWave), dim3(kReduceSlices * kWave), 0, s, partial,
-                       (int)(blocks * S::RS), elems, dw, accumulate);
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((elems + kWave - 1) / kWave, (unsigned)count), dim3(kReduceSlices * kWave), 0, s, b, partial,
+                       (int)(blocks * S::RS), elems, accumulate);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
 
-template <int FIN, bool BF16>
-int wgrad_out(int32_t f_out, const void *x, const void *g, int64_t n, float *dw, int accumulate, float *partial, hipStream_t s) {
+template <int FIN, bool BF16, bool MASKED>
+int wgrad_out(int32_t f_out, int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     switch (f_out) {
-        case 16: return launch_wgrad<FIN, 16, BF16>(x, g, n, dw, accumulate, partial, s);
-        case 32: return launch_wgrad<FIN, 32, BF16>(x, g, n, dw, accumulate, partial, s);
-        case 64: return launch_wgrad<FIN, 64, BF16>(x, g, n, dw, accumulate, partial, s);
-        case 128: return launch_wgrad<FIN, 128, BF16>(x, g, n, dw, accumulate, partial, s);
+        case 16: return launch_wgrad<FIN, 16, BF16, MASKED>(count, b, n, accumulate, partial, s);
+        case 32: return launch_wgrad<FIN, 32, BF16, MASKED>(count, b, n, accumulate, partial, s);
+        case 64: return launch_wgrad<FIN, 64, BF16, MASKED>(count, b, n, accumulate, partial, s);
+        case 128: return launch_wgrad<FIN, 128, BF16, MASKED>(count, b, n, accumulate, partial, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
 
-template <bool BF16>
-int wgrad_in(int32_t f_in, int32_t f_out, const void *x, const void *g, int64_t n, float *dw, int accumulate, float *partial,
-             hipStream_t s) {
+template <bool BF16, bool MASKED>
+int wgrad_in(int32_t f_in, int32_t f_out, int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     switch (f_in) {
-        case 16: return wgrad_out<16, BF16>(f_out, x, g, n, dw, accumulate, partial, s);
-        case 32: return wgrad_out<32, BF16>(f_out, x, g, n, dw, accumulate, partial, s);
-        case 64: return wgrad_out<64, BF16>(f_out, x, g, n, dw, accumulate, partial, s);
-        case 128: return wgrad_out<128, BF16>(f_out, x, g, n, dw, accumulate, partial, s);
+        case 16: return wgrad_out<16, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
+        case 32: return wgrad_out<32, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
+        case 64: return wgrad_out<64, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
+        case 128: return wgrad_out<128, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
@@ -246,20 +275,41 @@ extern "C" int dgnn_weight_grad_workspace(int32_t f_in, int32_t f_out, size_t *b
     return DGNN_OK;
 }
 
-extern "C" int dgnn_weight_grad(const void *x, const void *g, int64_t n, int32_t f_in, int32_t f_out, float *dw,
-                                int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream) {
-    if (!x || !g || !dw || !ws) return DGNN_ERR_NULL;
-    if (n <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
+extern "C" int dgnn_weight_grad_batch(int32_t count, const dgnn_weight_grad_item *items, int64_t n, int32_t f_in, int32_t f_out,
+                                      int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream) {
+    if (!items || !ws) return DGNN_ERR_NULL;
+    for (int k = 0; k < count; ++k)
+        if (!items[k].x || !items[k].g || !items[k].dw) return DGNN_ERR_NULL;
+    if (n <= 0 || count <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n)) return DGNN_ERR_OVERFLOW;
-    if (!aligned16(x) || !aligned16(g) || !aligned16(ws)) return DGNN_ERR_ALIGN;
+    const bool masked = items[0].z != nullptr;
+    for (int k = 0; k < count; ++k) {
+        if ((items[k].z != nullptr) != masked) return DGNN_ERR_SHAPE;
+        if (!aligned16(items[k].x) || !aligned16(items[k].g) || !aligned16(items[k].z)) return DGNN_ERR_ALIGN;
+    }
+    if (!aligned16(ws)) return DGNN_ERR_ALIGN;
     size_t need = 0;
     dgnn_weight_grad_workspace(f_in, f_out, &need);
     if (ws_bytes < need) return DGNN_ERR_CAPACITY;
     hipStream_t s = (hipStream_t)stream;
     float *partial = static_cast<float *>(ws);
-    return dt == DGNN_BF16 ? wgrad_in<true>(f_in, f_out, x, g, n, dw, accumulate ? 1 : 0, partial, s)
-                           : wgrad_in<false>(f_in, f_out, x, g, n, dw, accumulate ? 1 : 0, partial, s);
+    for (int done = 0; done < count; done += kMaxBatch) {
+        const int m = std::min(count - done, kMaxBatch);
+        Batch b;
+        for (int k = 0; k < m; ++k) b.item[k] = Item{items[done + k].x, items[done + k].g, items[done + k].z, items[done + k].dw};
+        const int acc = accumulate ? 1 : 0;
+        const int rc = dt == DGNN_BF16 ? (masked ? wgrad_in<true, true>(f_in, f_out, m, b, n, acc, partial, s) : wgrad_in<true, false>(f_in, f_out, m, b, n, acc, partial, s))
+                                       : (masked ? wgrad_in<false, true>(f_in, f_out, m, b, n, acc, partial, s) : wgrad_in<false, false>(f_in, f_out, m, b, n, acc, partial, s));
+        if (rc != DGNN_OK) return rc;
+    }
+    return DGNN_OK;
+}
+
+extern "C" int dgnn_weight_grad(const void *x, const void *g, int64_t n, int32_t f_in, int32_t f_out, float *dw,
+                                int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream) {
+    const dgnn_weight_grad_item item{x, g, nullptr, dw};
+    return dgnn_weight_grad_batch(1, &item, n, f_in, f_out, accumulate, dt, ws, ws_bytes, stream);
 }
 
 extern "C" int dgnn_relu_backward(const void *g, const void *z, const float *row_scale, void *out, int64_t n, int32_t f,

@@ -511,9 +511,38 @@ int launch_out(int32_t f_out, int count, const Batch &b, int wt, int relu, int64
     }
 }
 
-int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int wt, int relu, int32_t f_out, dgnn_dtype dt, void *stream) {
+// h = diag(row_scale) x, one 16-byte piece per lane (a copy where an item has no scale).
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void row_scale_kernel(Batch batch, int64_t pieces, int pieces_per_row) {
+    constexpr int NV = Pack<BF16>::kVals;
+    const Item &it = batch.item[blockIdx.y];
+    const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (p >= pieces) return;
+    const float *scale = as_global(it.row_scale);
+    const float sc = scale ? scale[p / pieces_per_row] : 1.0f;
+    float v[NV];
+    Pack<BF16>::unpack(v, __builtin_nontemporal_load(as_global(static_cast<const uintx4 *>(it.x)) + p));
+#pragma unroll
+    for (int e = 0; e < NV; ++e) v[e] *= sc;
+    as_global(static_cast<uintx4 *>(it.h))[p] = Pack<BF16>::pack(v);       // gathered next: stays in the caches
+}
+
+int row_scale(int count, const Batch &b, int64_t n, int32_t f, dgnn_dtype dt, hipStream_t s) {
+    const int per_row = f * (dt == DGNN_F32 ? 4 : 2) / 16;
+    const int64_t pieces = n * per_row;
+    const dim3 grid((unsigned)((pieces + kThreads - 1) / kThreads), (unsigned)count);
+    if (dt == DGNN_F32) hipLaunchKernelGGL(row_scale_kernel<false>, grid, dim3(kThreads), 0, s, b, pieces, per_row);
+    else hipLaunchKernelGGL(row_scale_kernel<true>, grid, dim3(kThreads), 0, s, b, pieces, per_row);
+    DGNN_RETURN_IF_LAUNCH_FAILED();
+    return DGNN_OK;
+}
+
+int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int wt, int relu, int32_t f_out, dgnn_dtype dt, void *stream,
+              bool single_w) {
     for (int k = 0; k < count; ++k)
-        if (!items[k].x || !items[k].w || !items[k].h) return DGNN_ERR_NULL;
+        if (!items[k].x || !items[k].h || (items[k].w == nullptr) != (items[0].w == nullptr)) return DGNN_ERR_NULL;
+    if (!single_w && count > 0 && !items[0].w && f_in != f_out) return DGNN_ERR_SHAPE;
+    if (single_w && !items[0].w) return DGNN_ERR_NULL;
     if (n <= 0 || count <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n)) return DGNN_ERR_OVERFLOW;
@@ -527,6 +556,11 @@ int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_
         Batch b;
         for (int k = 0; k < m; ++k) b.item[k] = Item{items[done + k].x, items[done + k].w, items[done + k].row_scale, items[done + k].h};
         int rc;
+        if (!items[0].w) {
+            rc = row_scale(m, b, n, f_in, dt, s);
+            if (rc != DGNN_OK) return rc;
+            continue;
+        }
         switch (f_in) {
             case 16: rc = launch_out<16>(f_out, m, b, wt, relu, n, dt, s); break;
             case 32: rc = launch_out<32>(f_out, m, b, wt, relu, n, dt, s); break;
@@ -543,7 +577,7 @@ int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_
 extern "C" int dgnn_feature_transform(const void *x, int64_t n, int32_t f_in, const void *w, int32_t f_out,
                                       const float *row_scale, void *h, dgnn_dtype dt, void *stream) {
     const dgnn_transform_item item{x, w, row_scale, h};
-    return transform(1, &item, n, f_in, 0, 0, f_out, dt, stream);
+    return transform(1, &item, n, f_in, 0, 0, f_out, dt, stream, true);
 }
 
 // dX = G W^T: the same product with W read transposed while it is parked in LDS; the contraction runs over
@@ -551,15 +585,15 @@ extern "C" int dgnn_feature_transform(const void *x, int64_t n, int32_t f_in, co
 extern "C" int dgnn_input_grad(const void *g, int64_t n, int32_t f_out, const void *w, int32_t f_in,
                                const float *row_scale, void *dx, dgnn_dtype dt, void *stream) {
     const dgnn_transform_item item{g, w, row_scale, dx};
-    return transform(1, &item, n, f_out, 1, 0, f_in, dt, stream);
+    return transform(1, &item, n, f_out, 1, 0, f_in, dt, stream, true);
 }
 
 // The products of several timesteps in one launch.
 extern "C" int dgnn_feature_transform_batch(int32_t count, const dgnn_transform_item *items, int64_t n, int32_t f_in, int32_t f_out,
                                             uint32_t flags, dgnn_dtype dt, void *stream) {
     if (count > 0 && !items) return DGNN_ERR_NULL;
-    if (flags & ~DGNN_RELU) return DGNN_ERR_SHAPE;
-    return transform(count, items, n, f_in, 0, (flags & DGNN_RELU) ? 1 : 0, f_out, dt, stream);
+    if (flags & ~(DGNN_RELU | DGNN_W_TRANSPOSED)) return DGNN_ERR_SHAPE;
+    return transform(count, items, n, f_in, (flags & DGNN_W_TRANSPOSED) ? 1 : 0, (flags & DGNN_RELU) ? 1 : 0, f_out, dt, stream, false);
 }
 
 // Y = relu([X | X W]): the dense transform with the skip connection of the CD-GCN layer's GCN operation (Section

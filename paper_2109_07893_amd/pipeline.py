@@ -113,7 +113,7 @@ class BlockRunner:
         self.ws_spmm = torch.empty(ws_s, dtype=torch.uint8, device=dev)
         self.status = torch.zeros(blk.T + 1, dtype=torch.int32, device=dev)
         self.timer: Optional[StageTimer] = None
-        self._tables = None             # of the calls that take several timesteps, made by the first pass that uses them
+        self._tables = self._make_tables() if self.series else None
         # staging for difference lists that arrive from pinned host memory (two sets, used alternately)
         self.stage = None
         if blk.pinned is not None:
@@ -253,6 +253,7 @@ class BlockRunner:
             b.column(b.NNZ, blk.nnz)
             tb.transform.append(a)
             tb.spmm.append(b)
+        tb.series.lists(blk.deltas)
         tb.ws = torch.empty(B.spmm_batch_workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
         return tb
 
@@ -260,8 +261,6 @@ class BlockRunner:
         """All snapshots, then the GCN steps `together` timesteps at a time; the same kernels on the same operands as one
         step after the other, bit for bit."""
         blk = self.blk
-        if self._tables is None:
-            self._tables = self._make_tables()
         tb, n, f, T, m = self._tables, blk.n, blk.f, blk.T, self.together
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         dt = B._dtype_code(self.h)

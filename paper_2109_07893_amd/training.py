@@ -2,25 +2,33 @@
 Checkpoint": a block is run forward, keeping its activations, and gradients then travel through it in
 the reverse direction).  Like pipeline.py this owns buffers and the order of library calls only:
 
-    forward    t = 1..T:   A_t by dgnn_delta_rebuild (t >= 2), per layer H = X W, Z = relu(A~_t H) -- every
-                           Z is kept; then Y = Z x_1 M
-    backward   G = G_Y x_1 M^T (dgnn_mproduct_backward), then t = T..1:
-                   per layer, last to first:   G_P = dinv * (Z > 0 ? G : 0)      dgnn_relu_backward
-                                               G_H = A~_t^T G_P                  dgnn_spmm on the transposed snapshot
-                                               dW += X^T G_H                     dgnn_weight_grad
-                                               G   = G_H W^T  (if a layer lies below)   dgnn_input_grad
-                   A_{t-1} from A_t by dgnn_delta_rebuild with the added and deleted lists exchanged
+    forward    A_2 .. A_T (dgnn_delta_rebuild_series, or dgnn_delta_rebuild per step on large snapshots), then per timestep
+                   first layer    P = A~_t X,  Z = relu(P W)                     both kept
+                   other layers   H = Z_below W,  Z = relu(A~_t H)               Z kept
+               then Y = Z x_1 M
+    backward   G = G_Y x_1 M^T (dgnn_mproduct_backward), then per timestep, last layer to first:
+                   other layers   G_P = dinv * (Z > 0 ? G : 0)                   dgnn_relu_backward
+                                  G_H = A~_t^T G_P                               dgnn_spmm on the transposed snapshot
+                                  dW += Z_below^T G_H,  G = G_H W^T              dgnn_weight_grad, dgnn_input_grad
+                   first layer    dW += P^T (Z > 0 ? G : 0)                      dgnn_weight_grad_batch
 
-For a directed workload the transposed snapshots are a second dynamic graph, rebuilt the same way from the
-difference lists sorted by (col, row).  Nothing here computes: every step runs in the HIP kernels.
+The first layer's weight gradient is X^T A~^T G_P = (A~ X)^T G_P: with A~ X kept from the forward pass it needs no aggregation
+and no transposed snapshot, which leaves a one-layer step with half the gathers.  Where dL/dX is wanted (a layer lies below)
+the aggregation is needed anyway, and the first layer is treated like the others.
+
+For a directed workload the transposed snapshots, where needed, are a second dynamic graph, rebuilt the same way from the
+difference lists sorted by (col, row).  Timesteps are enqueued together while their frames are small (batch.py).  Nothing here
+computes: every step runs in the HIP kernels.
 """
 from __future__ import annotations
 
+import contextlib
 from typing import List, Optional, Tuple
 
 import torch
 
 from . import binding as B
+from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
 from .pipeline import BlockInputs, BlockRunner
 
 
@@ -34,7 +42,8 @@ class _Chain:
         count = slots if self.per_step else 3
         self.rowptr = [torch.empty(n + 1, dtype=torch.int32, device=dev) for _ in range(count)]
         self.colidx = [torch.empty(cap, dtype=torch.int32, device=dev) for _ in range(count)]
-        self.dinv = [torch.empty(n, dtype=torch.float32, device=dev) if with_dinv else None for _ in range(count)]
+        self.dinv_all = torch.empty((count, n), dtype=torch.float32, device=dev) if with_dinv else None
+        self.dinv = [self.dinv_all[k] if with_dinv else None for k in range(count)]
         self.load_first(rowptr1, colidx1)
 
     def load_first(self, rowptr1, colidx1) -> None:
@@ -49,6 +58,162 @@ class _Chain:
         if self.per_step:
             return t - 1
         return 2 if t == 1 else t % 2
+
+    def slots_of(self, T: int) -> List[int]:
+        return [self.slot_of(t) for t in range(1, T + 1)]
+
+
+class GcnStack:
+    """The GCN layers of a training step over T snapshots, forward and backward, from tables of the snapshots' arrays (a
+    value per stored entry where `vals` is given); T frames of activations are kept.  What differs between the trainers is
+    where the snapshots come from."""
+
+    def __init__(self, blk: BlockInputs, cap: int, rowptr, colidx, dinv, vals=None, transposed=None, want_dx: bool = False,
+                 stage=None, together: Optional[int] = None):
+        dev, dt = blk.rowptr1.device, blk.x[0].dtype
+        n, f, T, L = blk.n, blk.f, blk.T, blk.layers
+        self.n, self.f, self.L, self.T_max, self.dev, self.dt = n, f, L, T, dev, B._dtype_code(blk.x[0])
+        self.stage, self.want_dx, self.weighted = stage, want_dx, vals is not None
+        self.together = m = together or steps_together(n * f * blk.x[0].element_size(), T)
+        self.z = torch.empty((L, T, n, f), dtype=dt, device=dev)
+        self.p0 = None if want_dx else torch.empty((T, n, f), dtype=dt, device=dev)      # A~_t X_t
+        # rows of X are scaled by dinv in a pass of their own, or dinv is gathered with them (see GATHERED_DINV_ROWS);
+        # bf16 rows always take the latter, which spares them a rounding; with values there is one factor per entry already
+        self.prescale = not want_dx and (self.weighted or (blk.x[0].dtype == torch.float32 and n > GATHERED_DINV_ROWS))
+        aggregated = L - 1 if not want_dx else L                                         # layers that need A~^T going back
+        self.needs_transposed = aggregated > 0
+        buffers = aggregated > 0 or self.prescale
+        self.h = torch.empty((m, n, f), dtype=dt, device=dev) if buffers else None       # H going forward, G_H going back
+        self.gp = torch.empty((m, n, f), dtype=dt, device=dev) if aggregated > 0 else None
+        self.g_mid = torch.empty((m, n, f), dtype=dt, device=dev) if L > 1 else None
+        self.dx = torch.empty((T, n, f), dtype=dt, device=dev) if want_dx else None
+        self.ws_spmm = torch.empty(B.spmm_batch_workspace(m, cap, f), dtype=torch.uint8, device=dev)
+        self.ws_wgrad = torch.empty(B.weight_grad_workspace(f, f), dtype=torch.uint8, device=dev)
+        self.x, self.w = Frames((n, f), dt, "x"), [Frames((f, f), dt, "w") for _ in range(L)]
+
+        h = pointers([self.h[t % m] for t in range(T)]) if buffers else None
+        z = [pointers(self.z[layer]) for layer in range(L)]
+        p0 = pointers(self.p0) if self.p0 is not None else None
+        snapshot = (pointers(rowptr), pointers(colidx), pointers(dinv), pointers(vals) if vals is not None else 0)
+
+        def spmm_table(arrays, src, dst):
+            b = SpmmTable(T)
+            for k, col in enumerate(arrays):
+                b.column(k, col)
+            b.column(b.H, src)
+            b.column(b.Z, dst)
+            return b
+        self.transform, self.spmm = [], []
+        self.scaled = None
+        for layer in range(L):
+            a = TransformTable(T)
+            if layer == 0 and not want_dx:
+                if self.prescale:
+                    self.scaled = TransformTable(T)
+                    self.scaled.column(a.SCALE, snapshot[2])
+                    self.scaled.column(a.H, h)
+                a.column(a.X, p0)
+                a.column(a.H, z[0])
+                self.spmm.append(spmm_table(snapshot, h if self.prescale else 0, p0))
+            else:
+                if layer > 0:
+                    a.column(a.X, z[layer - 1])
+                a.column(a.SCALE, snapshot[2])
+                a.column(a.H, h)
+                self.spmm.append(spmm_table(snapshot, h, z[layer]))
+            self.transform.append(a)
+        self.spmm_t = None
+        if aggregated > 0:
+            rp_t, ci_t, val_t = transposed if transposed is not None else (rowptr, colidx, vals)
+            arrays = (pointers(rp_t), pointers(ci_t), snapshot[2], pointers(val_t) if val_t is not None else 0)
+            self.spmm_t = spmm_table(arrays, pointers([self.gp[t % m] for t in range(T)]), h)
+            self.input = TransformTable(T)                  # with one weight per timestep: G_H W_t^T
+            self.input.column(TransformTable.X, h)
+        self.wgrad = WeightGradTable(T)
+
+    def bind(self, blk: BlockInputs, nnz) -> None:
+        """The frames, weights and entry counts of the coming pass."""
+        T = blk.T
+        rows = slice(0, T)
+        for b in self.spmm + ([self.spmm_t] if self.spmm_t is not None else []):
+            b.column(b.NNZ, nnz[:T], rows)
+        x = self.x.addresses(blk.x[:T])
+        if self.want_dx:
+            self.transform[0].column(TransformTable.X, x, rows)
+        elif self.prescale:
+            self.scaled.column(TransformTable.X, x, rows)
+        else:
+            self.spmm[0].column(SpmmTable.H, x, rows)
+        for layer in range(self.L):
+            w = self.w[layer].addresses([w[layer] for w in blk.w_t[:T]] if blk.w_t is not None else [blk.w[layer]])
+            self.transform[layer].column(TransformTable.W, w, rows)
+
+    def forward(self, t: int, k: int, stream) -> None:
+        """All layers of timesteps t .. t + k - 1 (0-based), their snapshots resident."""
+        n, f, dt = self.n, self.f, self.dt
+        for layer in range(self.L):
+            first = layer == 0 and not self.want_dx
+            if first and self.prescale:
+                with self.stage("feature_transform"):
+                    B.feature_transform_batch(k, self.scaled.at(t), n, f, f, 0, dt, stream)
+            if not first:
+                with self.stage("feature_transform"):
+                    B.feature_transform_batch(k, self.transform[layer].at(t), n, f, f, 0, dt, stream)
+            flags = (0 if first else B.DGNN_RELU) | (0 if first and not self.prescale else B.DGNN_H_PRESCALED)
+            with self.stage("spmm_weighted" if self.weighted else "spmm"):
+                B.spmm_batch(n, k, self.spmm[layer].at(t), f, dt, flags, self.ws_spmm, stream)
+            if first:
+                with self.stage("feature_transform"):
+                    B.feature_transform_batch(k, self.transform[0].at(t), n, f, f, B.DGNN_RELU, dt, stream)
+
+    def _weight_grad(self, blk, t, k, layer, x, g, masked, dw, dw_t, accumulate, stream) -> None:
+        n, f, dt, a = self.n, self.f, self.dt, self.wgrad
+        with self.stage("weight_grad"):
+            if dw_t is None:                       # one weight for all timesteps: one product over all their rows
+                a.words[0] = (x.data_ptr(), g.data_ptr(), self.z[layer, t].data_ptr() if masked else 0, dw[layer].data_ptr())
+                B.weight_grad_batch(1, a.at(), k * n, f, f, accumulate, dt, self.ws_wgrad, stream)
+            else:
+                step = n * f * x.element_size()
+                for j in range(k):
+                    a.words[j] = (x.data_ptr() + j * step if x.dim() == 3 else 0, g.data_ptr() + j * step,
+                                  self.z[layer, t + j].data_ptr() if masked else 0, dw_t[t + j][layer].data_ptr())
+                B.weight_grad_batch(k, a.at(), n, f, f, False, dt, self.ws_wgrad, stream)
+
+    def backward(self, blk: BlockInputs, t: int, k: int, g_top: torch.Tensor, dinv: torch.Tensor, dw, dw_t, accumulate: bool, stream) -> None:
+        """Gradients of timesteps t .. t + k - 1; g_top [k, n, f] = dL/dZ of the last layer, dinv [k, n]."""
+        n, f, dt = self.n, self.f, self.dt
+        flat = (k * n, f)
+        g = g_top
+        for layer in range(self.L - 1, -1, -1):
+            if layer == 0 and not self.want_dx:
+                self._weight_grad(blk, t, k, 0, self.p0[t:t + k], g, True, dw, dw_t, accumulate, stream)
+                return
+            with self.stage("relu_backward"):
+                B.relu_backward(g.view(flat), self.z[layer, t:t + k].view(flat), self.gp[:k].view(flat), row_scale=dinv.view(-1))
+            with self.stage("spmm_weighted_transposed" if self.weighted else "spmm_transposed"):
+                B.spmm_batch(n, k, self.spmm_t.at(t), f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
+            if layer > 0:
+                self._weight_grad(blk, t, k, layer, self.z[layer - 1, t:t + k], self.h, False, dw, dw_t, accumulate, stream)
+            else:                                  # the frames of X are tensors of their own
+                for j in range(k):
+                    with self.stage("weight_grad"):
+                        B.weight_grad(blk.x[t + j], self.h[j], dw_t[t + j][0] if dw_t is not None else dw[0], self.ws_wgrad,
+                                      accumulate=dw_t is None and (accumulate or j > 0))
+            dst = self.g_mid[:k] if layer > 0 else self.dx[t:t + k]
+            with self.stage("input_grad"):
+                if blk.w_t is None:
+                    B.input_grad(self.h[:k].view(flat), blk.w[layer], dst.view(flat))
+                else:
+                    rows = slice(t, t + k)
+                    self.input.column(TransformTable.W, self.transform[layer].words[rows, TransformTable.W], rows)
+                    self.input.column(TransformTable.H, pointers(dst), rows)
+                    B.feature_transform_batch(k, self.input.at(t), n, f, f, B.DGNN_W_TRANSPOSED, dt, stream)
+            g = dst
+
+
+# Vertices up to which the aggregation of X gathers dinv along with the rows instead of finding them scaled: the factors (4
+# bytes per vertex) then fit in every L2 beside what the gather itself keeps there, and the pass that scales the rows is saved.
+GATHERED_DINV_ROWS = 1 << 19
 
 
 class BlockTrainer:
@@ -71,30 +236,35 @@ class BlockTrainer:
         # keep_snapshots: every A_t (and A_t^T) of the block stays resident (T index arrays instead of three), so the
         # backward pass rebuilds nothing; without, the snapshots are rebuilt in reverse, as gradient checkpointing
         # has it.  4 nnz bytes per snapshot and chain: 9.6 GB for c5's eight, a matter of course in 288 GB.
-        self.keep_snapshots = keep_snapshots
-        slots = T if keep_snapshots else None
+        self.series = cap <= SERIES_ENTRIES        # all snapshots in one go: they are resident then in any case
+        self.keep_snapshots = keep_snapshots or self.series
+        slots = T if self.keep_snapshots else None
         self.a = _Chain(n, cap, dev, blk.rowptr1, blk.colidx1, with_dinv=True, slots=slots)
         self.at = None
-        if directed:
+        if directed and needs_transposed(blk, want_dx):
             assert transposed_first is not None and transposed_deltas is not None
             self.at = _Chain(n, cap, dev, transposed_first[0], transposed_first[1], with_dinv=False, slots=slots)
             self.t_deltas = transposed_deltas
-        self.z = torch.empty((L, T, n, f), dtype=dt, device=dev)          # activations of the block
+        self.timer = None
+        arrays = [[side[k] for k in self.a.slots_of(T)] for side in (self.a.rowptr, self.a.colidx, self.a.dinv)]
+        back = None if self.at is None else ([self.at.rowptr[k] for k in self.at.slots_of(T)], [self.at.colidx[k] for k in self.at.slots_of(T)], None)
+        self.stack = GcnStack(blk, cap, *arrays, transposed=back, want_dx=want_dx, stage=self._stage, together=None if self.series else 1)
+        self.z, self.dx = self.stack.z, self.stack.dx                     # activations of the block
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
         self.g = None                                                     # dL/dZ of the last layer, if g_y must be kept
-        self.h = torch.empty((n, f), dtype=dt, device=dev)                # H going forward, G_H going back
-        self.gp = torch.empty((n, f), dtype=dt, device=dev)
-        self.g_mid = torch.empty((n, f), dtype=dt, device=dev) if L > 1 else None
-        self.dx = torch.empty((T, n, f), dtype=dt, device=dev) if want_dx else None
         self.dw = [torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)]
         # with one weight per timestep (Section "EvolveGCN") every timestep has a gradient of its own
         self.dw_t = ([[torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)] for _ in range(T)]
                      if blk.w_t is not None else None)
         max_list = max([int(d[0].numel()) for d in blk.deltas] + [int(d[2].numel()) for d in blk.deltas] + [1, max_list or 0])
         self.ws_rebuild = torch.empty(B.delta_rebuild_workspace(n, cap, max_list, max_list), dtype=torch.uint8, device=dev)
-        self.ws_spmm = torch.empty(B.spmm_workspace(n, cap, f), dtype=torch.uint8, device=dev)
-        self.ws_wgrad = torch.empty(B.weight_grad_workspace(f, f), dtype=torch.uint8, device=dev)
-        self.timer = None
+        self.tables = None
+        if self.series:
+            def table(chain):          # one step more than the block has: the next block's first snapshot (see forward)
+                return SeriesTable(chain.rowptr[1:] + chain.rowptr[:1], chain.colidx[1:] + chain.colidx[:1], chain.dinv[1:] + chain.dinv[:1])
+            self.tables = [(self.a, table(self.a))] + ([(self.at, table(self.at))] if self.at is not None else [])
+            for (_, tb), (_, lists, _) in zip(self.tables, self._chains()):
+                tb.lists(lists)
 
     def rebind(self, blk: BlockInputs, t0: int = 0, z_before: Optional[torch.Tensor] = None,
                transposed_first=None, transposed_deltas=None) -> None:
@@ -102,12 +272,11 @@ class BlockTrainer:
         assert blk.T <= self.T_max and max(blk.nnz) <= self.cap and blk.n == self.blk.n and blk.f == self.blk.f
         self.blk, self.t0, self.z_before = blk, t0, z_before
         self.a.load_first(blk.rowptr1, blk.colidx1)
-        if self.directed:
+        if self.at is not None:
             self.at.load_first(*transposed_first)
             self.t_deltas = transposed_deltas
 
     def _stage(self, name):
-        import contextlib
         return self.timer.stage(name) if self.timer is not None else contextlib.nullcontext()
 
     def _rebuild(self, chain: _Chain, lists, nnz_src: int, src_t: int, dst_t: int, reverse: bool) -> None:
@@ -119,23 +288,47 @@ class BlockTrainer:
             B.delta_rebuild(chain.rowptr[s], chain.colidx[s], nnz_src, ar, ac, int(ar.numel()), dr, dc, int(dr.numel()),
                             chain.rowptr[d], chain.colidx[d], chain.dinv[d], self.ws_rebuild)
 
+    def _chains(self, after=None):
+        """(chain, difference lists of the block's steps, what follows: (lists, rowptr, colidx) or None)."""
+        steps = self.blk.T - 1
+        out = [(self.a, self.blk.deltas[:steps], after[0] if after is not None else None)]
+        if self.at is not None:
+            out.append((self.at, self.t_deltas[:steps], after[1] if after is not None else None))
+        return out
+
     # ------------------------------------------------------------------ forward, keeping activations
-    def forward(self) -> torch.Tensor:
-        blk = self.blk
-        for t in range(1, blk.T + 1):
-            if t >= 2:
-                self._rebuild(self.a, blk.deltas[t - 2], blk.nnz[t - 2], t - 1, t, reverse=False)
-                if self.directed:
-                    self._rebuild(self.at, self.t_deltas[t - 2], blk.nnz[t - 2], t - 1, t, reverse=False)
-            slot = self.a.slot_of(t)
-            cur = blk.x[t - 1]
-            for layer in range(blk.layers):
-                with self._stage("feature_transform"):
-                    B.feature_transform(cur, blk.weight(t, layer), self.h, row_scale=self.a.dinv[slot])
-                with self._stage("spmm"):
-                    B.spmm(self.a.rowptr[slot], self.a.colidx[slot], blk.nnz[t - 1], self.a.dinv[slot], self.h,
-                           self.z[layer, t - 1], self.ws_spmm, flags=B.DGNN_RELU | B.DGNN_H_PRESCALED)
-                cur = self.z[layer, t - 1]
+    def forward(self, after=None) -> torch.Tensor:
+        """`after`: the snapshot behind the block is wanted too, [(lists, rowptr, colidx)] for A and, where a transposed
+        chain is kept, for A^T."""
+        blk, stack = self.blk, self.stack
+        stream = torch.cuda.current_stream(self.dev).cuda_stream
+        if self.series:
+            for (chain, table), (_, lists, extra) in zip(self.tables, self._chains(after)):
+                steps = len(lists)
+                if extra is not None:                      # behind a block of full length only: the table's last row
+                    assert steps == self.T_max - 1
+                    lists = list(lists) + [extra[0]]
+                    table.column(6, extra[1].data_ptr(), steps)
+                    table.column(7, extra[2].data_ptr(), steps)
+                    table.column(8, 0, steps)
+                table.lists(lists)
+                if lists:
+                    with self._stage("delta_rebuild"):
+                        B.delta_rebuild_series(blk.n, chain.rowptr[0], chain.colidx[0], blk.nnz[0], len(lists), table.at(), self.cap, stream)
+        stack.bind(blk, blk.nnz)
+        m = stack.together
+        for t in range(0, blk.T, m):
+            if not self.series and t > 0:
+                for chain, lists, _ in self._chains():
+                    self._rebuild(chain, lists[t - 1], blk.nnz[t - 1], t, t + 1, reverse=False)
+            stack.forward(t, min(m, blk.T - t), stream)
+        if not self.series and after is not None:
+            for chain, _, (lists, rowptr, colidx) in self._chains(after):
+                slot = chain.slot_of(blk.T)
+                ar, ac, dr, dc = lists
+                with self._stage("delta_rebuild"):
+                    B.delta_rebuild(chain.rowptr[slot], chain.colidx[slot], blk.nnz[-1], ar, ac, int(ar.numel()), dr, dc, int(dr.numel()),
+                                    rowptr, colidx, None, self.ws_rebuild)
         top = self.z[blk.layers - 1, : blk.T]
         if blk.window:
             with self._stage("mproduct"):
@@ -146,11 +339,12 @@ class BlockTrainer:
     # ------------------------------------------------------------------ backward
     def backward(self, g_y: torch.Tensor, overwrite: bool = False, g_after: Optional[torch.Tensor] = None,
                  accumulate: bool = False) -> None:
-        """g_y [T, n, f] = dL/dY.  Must follow forward() (A_T and, if directed, A_T^T are resident).
+        """g_y [T, n, f] = dL/dY.  Must follow forward() (A_T and, where needed, A_T^T are resident).
         With overwrite the adjoint of the M-transform is taken in place, on g_y itself; g_after = upstream
         gradient of the (up to w-1) timesteps after this block; accumulate adds to dw instead of replacing it."""
-        blk = self.blk
-        L, T = blk.layers, blk.T
+        blk, stack = self.blk, self.stack
+        T = blk.T
+        stream = torch.cuda.current_stream(self.dev).cuda_stream
         if blk.window:
             if overwrite:
                 g_top = g_y
@@ -162,36 +356,23 @@ class BlockTrainer:
                 B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
         else:
             g_top = g_y
-        first_call = [not accumulate] * L
-        for t in range(T, 0, -1):
-            slot = self.a.slot_of(t)
-            tc = self.at if self.directed else self.a           # the chain that holds (A_t + I)^T
-            dinv = self.a.dinv[slot]
-            g_in = g_top[t - 1]
-            for layer in range(L - 1, -1, -1):
-                with self._stage("relu_backward"):
-                    B.relu_backward(g_in, self.z[layer, t - 1], self.gp, row_scale=dinv)
-                with self._stage("spmm_transposed"):
-                    B.spmm(tc.rowptr[slot], tc.colidx[slot], blk.nnz[t - 1], dinv, self.gp, self.h, self.ws_spmm,
-                           flags=B.DGNN_H_PRESCALED)
-                below = blk.x[t - 1] if layer == 0 else self.z[layer - 1, t - 1]
-                with self._stage("weight_grad"):
-                    if self.dw_t is not None:
-                        B.weight_grad(below, self.h, self.dw_t[t - 1][layer], self.ws_wgrad)
-                    else:
-                        B.weight_grad(below, self.h, self.dw[layer], self.ws_wgrad, accumulate=not first_call[layer])
-                first_call[layer] = False
-                if layer > 0:
-                    with self._stage("input_grad"):
-                        B.input_grad(self.h, blk.weight(t, layer), self.g_mid)
-                    g_in = self.g_mid
-                elif self.dx is not None:
-                    with self._stage("input_grad"):
-                        B.input_grad(self.h, blk.weight(t, 0), self.dx[t - 1])
-            if t >= 3 and not self.keep_snapshots:   # A_{t-1} from A_t: the same rebuild with the two lists exchanged (A_1 was kept)
-                self._rebuild(self.a, blk.deltas[t - 2], blk.nnz[t - 1], t, t - 1, reverse=True)
-                if self.directed:
-                    self._rebuild(self.at, self.t_deltas[t - 2], blk.nnz[t - 1], t, t - 1, reverse=True)
+        # one layer, one weight, nothing to aggregate: the rows of all timesteps in one product
+        whole = not stack.needs_transposed and self.dw_t is None and T * blk.n < (1 << 31) - 65536
+        m = T if whole else stack.together
+        last = (T - 1) // m * m
+        for t in range(last, -1, -m):
+            k = min(m, T - t)
+            slot = self.a.slot_of(t + 1)
+            stack.backward(blk, t, k, g_top[t:t + k], self.a.dinv_all[slot:slot + k] if self.a.per_step else self.a.dinv_all[slot:slot + 1],
+                           self.dw, self.dw_t, accumulate or t != last, stream)
+            if stack.needs_transposed and t >= 2 and not self.keep_snapshots:   # A_{t-1} from A_t: the lists exchanged (A_1 was kept)
+                for chain, lists, _ in self._chains():
+                    self._rebuild(chain, lists[t - 1], blk.nnz[t], t + 1, t, reverse=True)
+
+
+def needs_transposed(blk: BlockInputs, want_dx: bool = False) -> bool:
+    """Whether gradients travel through an aggregation at all (the first layer's weight gradient does not, see above)."""
+    return blk.layers > 1 or want_dx
 
 
 def capture_training_step(tr: "BlockTrainer", g_y: torch.Tensor) -> "torch.cuda.CUDAGraph":
@@ -229,8 +410,8 @@ def make_smoothed_trainer(wl, blk: BlockInputs, life: int) -> "SmoothedTrainer":
 def make_trainer(wl, blk: BlockInputs, want_dx: bool = False, keep_snapshots: bool = False) -> BlockTrainer:
     """Trainer for a block; for a directed workload the transposed first snapshot and lists are prepared here."""
     directed = wl.graph != "er"
-    if not directed:
-        return BlockTrainer(blk, False, want_dx=want_dx, keep_snapshots=keep_snapshots)
+    if not directed or not needs_transposed(blk, want_dx):
+        return BlockTrainer(blk, directed, want_dx=want_dx, keep_snapshots=keep_snapshots)
     first, t_deltas = transposed_inputs(blk)
     return BlockTrainer(blk, True, transposed_first=first, transposed_deltas=t_deltas, want_dx=want_dx,
                         keep_snapshots=keep_snapshots)
@@ -251,17 +432,18 @@ class CheckpointedTrainer:
         dev = series.rowptr1.device
         # first snapshot of every block: block 0 has it, the others are filled in by the forward pass
         self.first = [(series.rowptr1, series.colidx1)] + [
-            (torch.empty_like(series.rowptr1), torch.empty(series.nnz[a], dtype=torch.int32, device=dev))
+            (torch.empty_like(series.rowptr1), torch.empty(max(series.nnz), dtype=torch.int32, device=dev))
             for a, _ in self.bounds[1:]]
         self.t_first, self.t_deltas = None, None
-        if self.directed:
+        if self.directed and needs_transposed(series):
             (rp_t, tc), self.t_deltas = transposed_inputs(series)
-            self.t_first = [(rp_t, tc)] + [(torch.empty_like(rp_t), torch.empty(series.nnz[a], dtype=torch.int32, device=dev))
+            self.t_first = [(rp_t, tc)] + [(torch.empty_like(rp_t), torch.empty(max(series.nnz), dtype=torch.int32, device=dev))
                                            for a, _ in self.bounds[1:]]
         self.pi: List[Optional[torch.Tensor]] = [None] * len(self.bounds)   # frames handed to block b
+        self.resident: Optional[int] = None                                 # the block whose activations the trainer holds
         longest_list = max([int(d[0].numel()) for d in series.deltas] + [int(d[2].numel()) for d in series.deltas] + [1])
         self.trainer = BlockTrainer(self._block(0), self.directed,       # block 0 is as long as any
-                                    transposed_first=self.t_first[0] if self.directed else None,
+                                    transposed_first=self.t_first[0] if self.t_first is not None else None,
                                     transposed_deltas=self._t_deltas(*self.bounds[0]),
                                     cap=max(series.nnz), max_list=longest_list)
         self.dw = self.trainer.dw
@@ -271,18 +453,17 @@ class CheckpointedTrainer:
         a, e = self.bounds[b]
         nnz = list(s.nnz[a:e])
         blk = BlockInputs(n=s.n, T=e - a, f=s.f, layers=s.layers, window=s.window, rowptr1=self.first[b][0],
-                          colidx1=self.first[b][1], deltas=s.deltas[a:e - 1], x=s.x[a:e], w=s.w,
+                          colidx1=self.first[b][1][: nnz[0]], deltas=s.deltas[a:e - 1], x=s.x[a:e], w=s.w,
                           w_t=s.w_t[a:e] if s.w_t is not None else None, nnz=nnz)
         return blk
 
     def _t_deltas(self, a: int, e: int):
-        return self.t_deltas[a:e - 1] if self.directed else None
+        return self.t_deltas[a:e - 1] if self.t_deltas is not None else None
 
     def _bind(self, b: int) -> None:
         a, e = self.bounds[b]
-        self.trainer.rebind(self._block(b), t0=a, z_before=self.pi[b],
-                            transposed_first=self.t_first[b] if self.directed else None,
-                            transposed_deltas=self._t_deltas(a, e))
+        t_first = None if self.t_first is None else (self.t_first[b][0], self.t_first[b][1][: self.series.nnz[a]])
+        self.trainer.rebind(self._block(b), t0=a, z_before=self.pi[b], transposed_first=t_first, transposed_deltas=self._t_deltas(a, e))
 
     def forward(self, on_block=None) -> None:
         """Block by block; on_block(b, a, e, y) sees the block's output frames before they are overwritten."""
@@ -290,27 +471,22 @@ class CheckpointedTrainer:
         w1 = max(s.window - 1, 0)
         for b, (a, e) in enumerate(self.bounds):
             self._bind(b)
-            y = tr.forward()
+            after = None
+            if b + 1 < len(self.bounds):          # the next block's first snapshot (the paper sends it whole; here it is one more rebuild)
+                after = [(s.deltas[e - 1],) + self.first[b + 1]]
+                if self.t_first is not None:
+                    after.append((self.t_deltas[e - 1],) + self.t_first[b + 1])
+            y = tr.forward(after)
             if on_block is not None:
                 on_block(b, a, e, y)
-            if b + 1 < len(self.bounds):
-                if w1:
-                    top = tr.z[s.layers - 1, : e - a]
-                    keep = min(w1, e)                       # frames of the series so far that the window reaches
-                    own = top[max(e - a - keep, 0):]
-                    if own.shape[0] < keep:                 # a block shorter than the window: older frames come along
-                        own = torch.cat([self.pi[b][-(keep - own.shape[0]):], own])
-                    self.pi[b + 1] = own.clone()
-                # the next block's first snapshot (the paper sends it whole; here it is one more rebuild)
-                slot = tr.a.slot_of(e - a)
-                ar, ac, dr, dc = s.deltas[e - 1]
-                B.delta_rebuild(tr.a.rowptr[slot], tr.a.colidx[slot], s.nnz[e - 1], ar, ac, int(ar.numel()), dr, dc,
-                                int(dr.numel()), self.first[b + 1][0], self.first[b + 1][1], None, tr.ws_rebuild)
-                if self.directed:
-                    ar, ac, dr, dc = self.t_deltas[e - 1]
-                    B.delta_rebuild(tr.at.rowptr[slot], tr.at.colidx[slot], s.nnz[e - 1], ar, ac, int(ar.numel()), dr,
-                                    dc, int(dr.numel()), self.t_first[b + 1][0], self.t_first[b + 1][1], None,
-                                    tr.ws_rebuild)
+            if b + 1 < len(self.bounds) and w1:
+                top = tr.z[s.layers - 1, : e - a]
+                keep = min(w1, e)                       # frames of the series so far that the window reaches
+                own = top[max(e - a - keep, 0):]
+                if own.shape[0] < keep:                 # a block shorter than the window: older frames come along
+                    own = torch.cat([self.pi[b][-(keep - own.shape[0]):], own])
+                self.pi[b + 1] = own.clone()
+        self.resident = len(self.bounds) - 1
 
     def backward(self, g_y: torch.Tensor) -> None:
         """g_y [T, n, f] for the whole series.  Must follow forward()."""
@@ -319,8 +495,10 @@ class CheckpointedTrainer:
         last = len(self.bounds) - 1
         for b in range(last, -1, -1):
             a, e = self.bounds[b]
-            self._bind(b)
-            tr.forward()                                                    # the rerun
+            if self.resident != b:                      # the last block's activations are still there from the forward pass
+                self._bind(b)
+                tr.forward()                                                # the rerun
+            self.resident = None
             after = g_y[e:min(e + w1, s.T)] if (w1 and e < s.T) else None
             tr.backward(g_y[a:e], g_after=after, accumulate=b != last)
 

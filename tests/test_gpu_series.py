@@ -99,3 +99,46 @@ def test_pass_with_batched_steps_equals_the_pass_step_by_step(name, n, T, keep):
         torch.cuda.synchronize()
         if first == 1 or not runner.blk.window:
             assert torch.equal(runner.z[first - 1 if runner.keep_all_z else 0:], want[first - 1 if runner.keep_all_z else 0:])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("f_in,f_out,n", [(16, 16, 1), (32, 64, 333), (128, 128, 1000), (64, 16, 5000)])
+def test_weight_gradient_through_the_relu(dtype, f_in, f_out, n):
+    """x^T (z > 0 ? g : 0) in one call against the mask applied beforehand; zeros and negative zeros do not pass."""
+    from paper_2109_07893_amd.batch import WeightGradTable
+    torch.manual_seed(n)
+    x, g, z = (torch.randn(2, n, f, device=DEV).to(dtype) for f in (f_in, f_out, f_out))
+    z[:, ::3] = 0.0
+    z[:, 1::7] = -0.0
+    dw = torch.full((2, f_in, f_out), float("nan"), device=DEV)
+    ws = torch.empty(B.weight_grad_workspace(f_in, f_out), dtype=torch.uint8, device=DEV)
+    table = WeightGradTable(2)
+    for k, t in ((table.X, x), (table.G, g), (table.Z, z), (table.DW, dw)):
+        table.column(k, pointers(list(t)))
+    B.weight_grad_batch(2, table.at(), n, f_in, f_out, False, B._dtype_code(x), ws, torch.cuda.current_stream().cuda_stream)
+    want = x.double().transpose(1, 2).contiguous() @ torch.where(z > 0, g, torch.zeros_like(g)).double()
+    assert torch.allclose(dw.double(), want, rtol=1e-4, atol=1e-4 * float(want.abs().max()) + 1e-6)
+
+
+@pytest.mark.parametrize("name,layers", [("c1", 1), ("c1", 2), ("c3", 1), ("c3", 2), ("c4", 1)])
+@pytest.mark.parametrize("what", ["SERIES_ENTRIES", "GATHERED_DINV_ROWS"])
+def test_trainer_on_both_sides_of_its_size_rules(name, layers, what, monkeypatch):
+    """The trainer at small sizes with the rules for large ones: rebuilds step by step, rows of X scaled beforehand."""
+    from dtdg_synth import gradient
+    from paper_2109_07893_amd import training
+    wl = replace(WORKLOADS[name] if name == "c1" else WORKLOADS[name].scaled(1 << 11, T=5), layers=layers, window=3 if layers == 2 else 0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV) + 1.0
+    out = []
+    for patched in (False, True):
+        if patched:
+            monkeypatch.setattr(training, what, 0)
+        tr = training.make_trainer(wl, blk)
+        assert tr.series == (not patched or what != "SERIES_ENTRIES")
+        y = tr.forward()
+        tr.backward(g_y.to(y.dtype))
+        torch.cuda.synchronize()
+        out.append((y.double().clone(), [d.double().clone() for d in tr.dw]))
+    tol = 1e-5 if wl.dtype != "bf16" else 1e-2
+    for a, b in zip([out[0][0]] + out[0][1], [out[1][0]] + out[1][1]):
+        assert float((a - b).norm()) <= tol * float(b.norm())
