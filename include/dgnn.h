@@ -581,6 +581,23 @@ int dgnn_bias_grad(const void *g, int64_t n, int32_t f, float *db, int accumulat
                    size_t ws_bytes, void *stream);
 
 /*
+ * EvolveGCN's weight recurrence (Section "EvolveGCN"), all timesteps in one call: a_t = W_{t-1} U_x + W_{t-1} U_h + b,
+ * (W_t, C_t) = the cell of dgnn_lstm_cell, C_0 = 0.  w0 [f][f2], u_x, u_h [f2][4 f2], bias [4 f2] or NULL, w [T][f][f2] = W_1 .. W_T,
+ * c [T + 1][f][f2] = C_0 .. C_T, all fp32; f a feature width, f2 16 or 32.  The two products are formed as W (U_x + U_h).
+ */
+int dgnn_evolve_weights(const float *w0, const float *u_x, const float *u_h, const float *bias, int32_t T, int32_t f, int32_t f2,
+                        float *w, float *c, void *stream);
+
+/*
+ * Its adjoint: dw = HOST array of T device pointers to dL/dW_t [f][f2] -> dw0 [f][f2], du_x = du_h [f2][4 f2], db [4 f2] (the
+ * gate pre-activations are recomputed).  Sums have a fixed order.  ws: at least dgnn_evolve_weights_backward_workspace() bytes.
+ */
+int dgnn_evolve_weights_backward_workspace(int32_t f, int32_t f2, size_t *bytes);
+int dgnn_evolve_weights_backward(const float *w0, const float *u_x, const float *u_h, const float *bias, int32_t T, int32_t f, int32_t f2,
+                                 const float *w, const float *c, const float *const *dw, float *dw0, float *du_x, float *du_h,
+                                 float *db, void *ws, size_t ws_bytes, void *stream);
+
+/*
  * out = a + b for [n, f] tensors of one storage type (the sum is formed in fp32 and rounded once): a gradient that
  * reaches a tensor along two paths.  out may be a or b.  f a feature width.  Errors: NULL, SHAPE, OVERFLOW, ALIGN.
  */

@@ -30,6 +30,7 @@ EXPORTS = (
     "dgnn_delta_rebuild_weighted", "dgnn_spmm_weighted", "dgnn_csr_combine_workspace", "dgnn_csr_combine", "dgnn_csr_weighted_dinv_workspace", "dgnn_csr_weighted_dinv", "dgnn_concat_relu", "dgnn_transform_concat_relu", "dgnn_lstm_cell", "dgnn_lstm_step", "dgnn_lstm_cell_backward", "dgnn_lstm_step_backward", "dgnn_concat_relu_backward", "dgnn_bias_grad_workspace", "dgnn_bias_grad", "dgnn_add",
     "dgnn_csr_transpose_workspace", "dgnn_csr_transpose", "dgnn_coo_transpose_workspace", "dgnn_coo_transpose",
     "dgnn_delta_rebuild_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
+    "dgnn_evolve_weights", "dgnn_evolve_weights_backward_workspace", "dgnn_evolve_weights_backward",
     "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
 )
 
@@ -106,6 +107,9 @@ def load_library():
     lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp]
     lib.dgnn_feature_transform_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _u32, ctypes.c_int, _vp]
     lib.dgnn_spmm_batch_workspace.argtypes = [_i32, _i64, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_evolve_weights.argtypes = [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp]
+    lib.dgnn_evolve_weights_backward_workspace.argtypes = [_i32, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_evolve_weights_backward.argtypes = [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
     lib.dgnn_weight_grad_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _i32, ctypes.c_int, _vp, _sz, _vp]
     lib.dgnn_spmm_batch.argtypes = [_i64, _i32, _vp, _i32, ctypes.c_int, _u32, _vp, _sz, _vp]
     lib.dgnn_mproduct.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, ctypes.c_int, _vp]
@@ -314,6 +318,37 @@ def spmm_batch(n: int, count: int, table: int, f: int, dt: int, flags: int, ws: 
 def weight_grad_batch(count: int, table: int, n: int, f_in: int, f_out: int, accumulate: bool, dt: int, ws: torch.Tensor, stream) -> None:
     _check(load_library().dgnn_weight_grad_batch(count, table, n, f_in, f_out, int(accumulate), dt, _ptr(ws), ws.numel() * ws.element_size(),
                                                  stream), "dgnn_weight_grad_batch")
+
+
+def evolve_weights(w0, u_x, u_h, bias, w, c) -> None:
+    """W_1 .. W_T in w [T, f, f2], C_0 .. C_T in c [T + 1, f, f2]."""
+    T, f, f2 = w.shape
+    for t in (w0, u_x, u_h, bias, w, c):
+        _need(t, torch.float32, "evolve_weights tensors")
+    if tuple(w0.shape) != (f, f2) or tuple(u_x.shape) != (f2, 4 * f2) or tuple(u_h.shape) != (f2, 4 * f2) or bias.numel() != 4 * f2 or tuple(c.shape) != (T + 1, f, f2):
+        raise ValueError("shape mismatch in evolve_weights")
+    _check(load_library().dgnn_evolve_weights(_ptr(w0), _ptr(u_x), _ptr(u_h), _ptr(bias), T, f, f2, _ptr(w), _ptr(c), _stream(w)),
+           "dgnn_evolve_weights")
+
+
+def evolve_weights_backward_workspace(f: int, f2: int) -> int:
+    out = _sz(0)
+    _check(load_library().dgnn_evolve_weights_backward_workspace(f, f2, ctypes.byref(out)), "dgnn_evolve_weights_backward_workspace")
+    return int(out.value)
+
+
+def evolve_weights_backward(w0, u_x, u_h, bias, w, c, dw, dw0, du_x, du_h, db, ws) -> None:
+    """dw = list of T gradients dL/dW_t; leaves dL/dW_0, dL/dU_x, dL/dU_h, dL/db."""
+    T, f, f2 = w.shape
+    if len(dw) != T:
+        raise ValueError("one gradient per timestep")
+    for t in dw:
+        if tuple(t.shape) != (f, f2) or t.dtype != torch.float32:
+            raise ValueError("dL/dW_t must be float32 of W's shape")
+    table = (_vp * T)(*[_ptr(t) for t in dw])
+    _check(load_library().dgnn_evolve_weights_backward(_ptr(w0), _ptr(u_x), _ptr(u_h), _ptr(bias), T, f, f2, _ptr(w), _ptr(c), table, _ptr(dw0),
+                                                       _ptr(du_x), _ptr(du_h), _ptr(db), _ptr(ws), ws.numel() * ws.element_size(), _stream(w)),
+           "dgnn_evolve_weights_backward")
 
 
 def delta_rebuild_weighted(rowptr_prev, colidx_prev, val_prev, nnz_prev: int, add, dele, upd,

@@ -142,3 +142,27 @@ def test_trainer_on_both_sides_of_its_size_rules(name, layers, what, monkeypatch
     tol = 1e-5 if wl.dtype != "bf16" else 1e-2
     for a, b in zip([out[0][0]] + out[0][1], [out[1][0]] + out[1][1]):
         assert float((a - b).norm()) <= tol * float(b.norm())
+
+
+@pytest.mark.parametrize("f,f2,T", [(16, 16, 1), (32, 32, 3), (64, 16, 5), (128, 32, 2), (16, 32, 130)])
+def test_weight_recurrence_and_its_adjoint(f, f2, T):
+    """All widths the one-launch recurrence takes; 130 steps: three launches of the adjoint."""
+    import oracle
+    from helpers import to_f64
+    from paper_2109_07893_amd.evolve import EvolvingWeights
+    gen = torch.Generator().manual_seed(T)
+    w0 = torch.randn((f, f2), generator=gen) / f2 ** 0.5
+    u_x, u_h = (torch.randn((f2, 4 * f2), generator=gen) / f2 ** 0.5 for _ in range(2))
+    bias = torch.randn(4 * f2, generator=gen) * 0.1
+    dw = [torch.randn((f, f2), generator=gen) for _ in range(T)]
+    ev = EvolvingWeights(w0.to(DEV), u_x.to(DEV), u_h.to(DEV), bias.to(DEV), T)
+    w_t = ev.forward()
+    ev.backward([d.to(DEV) for d in dw])
+    torch.cuda.synchronize()
+    args = [to_f64(x) for x in (w0, u_x, u_h, bias)]
+    ws, _ = oracle.evolve_weights(*args, T)
+    for t in range(T):
+        assert np.abs(to_f64(w_t[t]) - ws[t]).max() <= 1e-4, t
+    want = oracle.evolve_weights_backward(*args, [to_f64(d) for d in dw])
+    for got, exp in zip((ev.du_x, ev.du_h, ev.db, ev.dw0), want):
+        assert np.abs(to_f64(got) - exp).max() <= 2e-4 * np.abs(exp).max()
