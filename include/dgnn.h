@@ -564,6 +564,33 @@ int dgnn_lstm_step_backward(const void *y, int32_t f_y, const void *h_prev, cons
                             void *stream);
 
 /*
+ * The LSTM over T timesteps in one call: h [T][n][hidden] = h_1 .. h_T from h0, c0 [n][hidden] and y [T][n][f_y]; widths,
+ * layouts and arithmetic as dgnn_lstm_step (which is T = 1).  keep_c = 0: c [n][hidden] receives the last cell state (it may be
+ * c0); else c [T][n][hidden] receives c_1 .. c_T.
+ */
+int dgnn_lstm_series(const void *y, int32_t f_y, const void *h0, const void *w_x, const void *w_h, const float *bias, const void *c0,
+                     void *c, int32_t keep_c, void *h, int64_t n, int32_t T, int32_t hidden, dgnn_dtype dt, void *stream);
+
+/*
+ * Its adjoint, for the CD-GCN layer's Y = relu(Y0 o Y1) with Y1 as wide as the state (f_y = 2 hidden; fp32 hidden 16 or 32,
+ * bf16 hidden 32).  h, c [T][n][hidden] as the forward call left them (keep_c), g_h [T][n][hidden] = dL/dh_t of the loss itself.
+ *   da [T][n][4 hidden]   gradient of the gate pre-activations
+ *   dy1 [T][n][hidden]    da W_x^T in Y1's columns where Y1 > 0, else 0: the gradient of Y0 W
+ *   dh, dc [n][hidden] fp32  in (carried != 0) dL/dh_T and dL/dc_T from the steps behind this series, out dL/dh_0 and dL/dc_0
+ */
+int dgnn_lstm_series_backward(const void *y, int32_t f_y, const void *h0, const void *h, const void *w_x, const void *w_h, const float *bias,
+                              const void *c0, const void *c, const void *g_h, void *da, void *dy1, float *dh, float *dc, int32_t carried,
+                              int64_t n, int32_t T, int32_t hidden, dgnn_dtype dt, void *stream);
+
+/*
+ * dw_x = sum_t y_t^T da_t, dw_h = sum_t h_{t-1}^T da_t, db = column sums of da (or added to them) in one pass over da; shapes as
+ * dgnn_lstm_series_backward.  The sums have a fixed order.
+ */
+int dgnn_lstm_weight_grad_workspace(int32_t f_y, int32_t hidden, size_t *bytes);
+int dgnn_lstm_weight_grad(const void *y, int32_t f_y, const void *h0, const void *h, const void *da, int64_t n, int32_t T, int32_t hidden,
+                          float *dw_x, float *dw_h, float *db, int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream);
+
+/*
  * Adjoint of dgnn_concat_relu: dy, y [n, f0 + f1] (y = the forward output); d0 [n, f0] and d1 [n, f1] receive the
  * two column blocks of dy where y > 0, zero elsewhere.  d0 may be NULL (the gradient with respect to Y0's own block
  * is needed only when a layer lies below).  Errors as dgnn_concat_relu.

@@ -23,6 +23,10 @@ BATCH_BYTES = 64 << 20
 # 4.5 / 12.7 us, 1.7 M 8.0 / 14.7 us, 17 M 65 / 53 us).
 SERIES_ENTRIES = 1 << 22
 
+# Vertices up to which the aggregation of X gathers dinv along with the rows instead of finding them scaled: the factors (4
+# bytes per vertex) then fit in every L2 beside what the gather itself keeps there, and the pass that scales the rows is saved.
+GATHERED_DINV_ROWS = 1 << 19
+
 
 def steps_together(frame_bytes: int, T: int) -> int:
     return max(1, min(T, BATCH_BYTES // max(frame_bytes, 1)))

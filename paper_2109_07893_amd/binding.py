@@ -30,6 +30,7 @@ EXPORTS = (
     "dgnn_delta_rebuild_weighted", "dgnn_spmm_weighted", "dgnn_csr_combine_workspace", "dgnn_csr_combine", "dgnn_csr_weighted_dinv_workspace", "dgnn_csr_weighted_dinv", "dgnn_concat_relu", "dgnn_transform_concat_relu", "dgnn_lstm_cell", "dgnn_lstm_step", "dgnn_lstm_cell_backward", "dgnn_lstm_step_backward", "dgnn_concat_relu_backward", "dgnn_bias_grad_workspace", "dgnn_bias_grad", "dgnn_add",
     "dgnn_csr_transpose_workspace", "dgnn_csr_transpose", "dgnn_coo_transpose_workspace", "dgnn_coo_transpose",
     "dgnn_delta_rebuild_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
+    "dgnn_lstm_series", "dgnn_lstm_series_backward", "dgnn_lstm_weight_grad_workspace", "dgnn_lstm_weight_grad",
     "dgnn_evolve_weights", "dgnn_evolve_weights_backward_workspace", "dgnn_evolve_weights_backward",
     "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
 )
@@ -107,6 +108,10 @@ def load_library():
     lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp]
     lib.dgnn_feature_transform_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _u32, ctypes.c_int, _vp]
     lib.dgnn_spmm_batch_workspace.argtypes = [_i32, _i64, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_lstm_series.argtypes = [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp, _i64, _i32, _i32, ctypes.c_int, _vp]
+    lib.dgnn_lstm_series_backward.argtypes = [_vp, _i32] + [_vp] * 12 + [_i32, _i64, _i32, _i32, ctypes.c_int, _vp]
+    lib.dgnn_lstm_weight_grad_workspace.argtypes = [_i32, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_lstm_weight_grad.argtypes = [_vp, _i32, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _i32, ctypes.c_int, _vp, _sz, _vp]
     lib.dgnn_evolve_weights.argtypes = [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp]
     lib.dgnn_evolve_weights_backward_workspace.argtypes = [_i32, _i32, ctypes.POINTER(_sz)]
     lib.dgnn_evolve_weights_backward.argtypes = [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
@@ -318,6 +323,56 @@ def spmm_batch(n: int, count: int, table: int, f: int, dt: int, flags: int, ws: 
 def weight_grad_batch(count: int, table: int, n: int, f_in: int, f_out: int, accumulate: bool, dt: int, ws: torch.Tensor, stream) -> None:
     _check(load_library().dgnn_weight_grad_batch(count, table, n, f_in, f_out, int(accumulate), dt, _ptr(ws), ws.numel() * ws.element_size(),
                                                  stream), "dgnn_weight_grad_batch")
+
+
+def lstm_series(y, h0, w_x, w_h, bias, c0, c, h) -> None:
+    """h_1 .. h_T in h [T, n, hidden] from y [T, n, f_y]; c [n, hidden] (the last state; may be c0) or [T, n, hidden] (every one)."""
+    T, n, f_y = y.shape
+    hidden = h0.shape[1]
+    keep = c.dim() == 3
+    if (tuple(h.shape) != (T, n, hidden) or tuple(c0.shape) != (n, hidden) or tuple(c.shape) != ((T, n, hidden) if keep else (n, hidden))
+            or tuple(w_x.shape) != (f_y, 4 * hidden) or tuple(w_h.shape) != (hidden, 4 * hidden)):
+        raise ValueError("shape mismatch in lstm_series")
+    if bias is not None:
+        _need(bias, torch.float32, "bias")
+    _check(load_library().dgnn_lstm_series(_ptr(y), f_y, _ptr(h0), _ptr(w_x), _ptr(w_h), _ptr(bias), _ptr(c0), _ptr(c), int(keep), _ptr(h), n, T,
+                                           hidden, _dtype_code(y), _stream(y)), "dgnn_lstm_series")
+
+
+def lstm_series_backward_supported(y: torch.Tensor, hidden: int) -> bool:
+    return lstm_step_backward_supported(y, hidden) and y.shape[-1] == 2 * hidden
+
+
+def lstm_series_backward(y, h0, h, w_x, w_h, bias, c0, c, g_h, da, dy1, dh, dc, carried: bool) -> None:
+    T, n, f_y = y.shape
+    hidden = h0.shape[1]
+    _need(dh, torch.float32, "dh"); _need(dc, torch.float32, "dc")
+    for t in (h, c, g_h, dy1):
+        if tuple(t.shape) != (T, n, hidden) or t.dtype != y.dtype:
+            raise ValueError("state tensors must be [T, n, hidden]")
+    if tuple(da.shape) != (T, n, 4 * hidden) or da.dtype != y.dtype or dh.numel() < n * hidden or dc.numel() < n * hidden:
+        raise ValueError("shape mismatch in lstm_series_backward")
+    _check(load_library().dgnn_lstm_series_backward(_ptr(y), f_y, _ptr(h0), _ptr(h), _ptr(w_x), _ptr(w_h), _ptr(bias), _ptr(c0), _ptr(c), _ptr(g_h),
+                                                    _ptr(da), _ptr(dy1), _ptr(dh), _ptr(dc), int(carried), n, T, hidden, _dtype_code(y), _stream(y)),
+           "dgnn_lstm_series_backward")
+
+
+def lstm_weight_grad_workspace(f_y: int, hidden: int) -> int:
+    out = _sz(0)
+    _check(load_library().dgnn_lstm_weight_grad_workspace(f_y, hidden, ctypes.byref(out)), "dgnn_lstm_weight_grad_workspace")
+    return int(out.value)
+
+
+def lstm_weight_grad(y, h0, h, da, dw_x, dw_h, db, ws, accumulate: bool = False) -> None:
+    T, n, f_y = y.shape
+    hidden = h0.shape[1]
+    for t in (dw_x, dw_h, db):
+        _need(t, torch.float32, "weight gradients")
+    if tuple(dw_x.shape) != (f_y, 4 * hidden) or tuple(dw_h.shape) != (hidden, 4 * hidden) or tuple(da.shape) != (T, n, 4 * hidden):
+        raise ValueError("shape mismatch in lstm_weight_grad")
+    _check(load_library().dgnn_lstm_weight_grad(_ptr(y), f_y, _ptr(h0), _ptr(h), _ptr(da), n, T, hidden, _ptr(dw_x), _ptr(dw_h), _ptr(db),
+                                                int(accumulate), _dtype_code(y), _ptr(ws), ws.numel() * ws.element_size(), _stream(y)),
+           "dgnn_lstm_weight_grad")
 
 
 def evolve_weights(w0, u_x, u_h, bias, w, c) -> None:
@@ -556,7 +611,7 @@ def lstm_cell_backward(gates_x, gates_h, bias, c_prev, dh_a, dh_b, dc_next, da, 
 
 def lstm_step_backward_supported(y: torch.Tensor, hidden: int) -> bool:
     widths = {torch.float32: (16, 32), torch.bfloat16: (32,)}.get(y.dtype, ())
-    return hidden in widths and y.shape[1] in (hidden, 2 * hidden)
+    return hidden in widths and y.shape[-1] in (hidden, 2 * hidden)
 
 
 def lstm_step_backward(y, h_prev, w_x, w_h, bias, c_prev, dh_a, dh_b, dc_next, da, dc_prev) -> None:
@@ -615,7 +670,7 @@ def add(a: torch.Tensor, b: torch.Tensor, out: torch.Tensor) -> None:
 
 def lstm_step_supported(y: torch.Tensor, hidden: int) -> bool:
     widths = (16, 32) if y.dtype == torch.float32 else (32, 64) if y.dtype == torch.bfloat16 else ()
-    return hidden in widths and y.shape[1] in (hidden, 2 * hidden)
+    return hidden in widths and y.shape[-1] in (hidden, 2 * hidden)
 
 
 def lstm_step(y, h_prev, w_x, w_h, bias, c, h_next) -> None:

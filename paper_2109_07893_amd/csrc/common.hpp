@@ -130,6 +130,13 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
     return u >> 16;
 }
 
+// Two at once, as one word (the first in the low half): one conversion instruction, the same rounding.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
+}
+
 // ---- 16-byte pieces of feature rows: 4 fp32 or 8 bf16 values, unpacked to and packed from fp32 ------------
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 

@@ -28,7 +28,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
+from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
 from .pipeline import BlockInputs, BlockRunner
 
 
@@ -209,11 +209,6 @@ class GcnStack:
                     self.input.column(TransformTable.H, pointers(dst), rows)
                     B.feature_transform_batch(k, self.input.at(t), n, f, f, B.DGNN_W_TRANSPOSED, dt, stream)
             g = dst
-
-
-# Vertices up to which the aggregation of X gathers dinv along with the rows instead of finding them scaled: the factors (4
-# bytes per vertex) then fit in every L2 beside what the gather itself keeps there, and the pass that scales the rows is saved.
-GATHERED_DINV_ROWS = 1 << 19
 
 
 class BlockTrainer:

@@ -400,3 +400,66 @@ def test_two_layer_cdgcn_training_step(case, keep):
         for name, got, want in zip(("dW", "dW_x", "dW_h", "db"), (tr.dw, tr.dw_x, tr.dw_h, tr.db), grads[layer]):
             err = np.abs(to_f64(got) - want).max()
             assert err <= 3e-4 * np.abs(want).max(), f"{case} layer {layer + 1} {name}: max err {err:.3e} against max |.| {np.abs(want).max():.3e}"
+
+
+@pytest.mark.parametrize("dtype,hidden,f_y", [(torch.float32, 32, 64), (torch.float32, 16, 16), (torch.bfloat16, 32, 32), (torch.bfloat16, 64, 128)])
+@pytest.mark.parametrize("n,T", [(1, 3), (33, 1), (1000, 5), (70_003, 2)])
+@pytest.mark.parametrize("keep_c", [False, True])
+def test_lstm_series(dtype, hidden, f_y, n, T, keep_c):
+    """A series in one call against the oracle's cell step by step; 70 003 vertices: more tiles than resident wavefronts."""
+    y = randn((T, n, f_y), n + T, dtype)
+    h0, c0 = randn((n, hidden), 1, dtype), randn((n, hidden), 2, dtype)
+    w_x, w_h = (randn((f_y, 4 * hidden), 3) / f_y ** 0.5).to(dtype), (randn((hidden, 4 * hidden), 4) / hidden ** 0.5).to(dtype)
+    bias = randn((4 * hidden,), 5) * 0.1
+    h = torch.full((T, n, hidden), float("nan"), dtype=dtype, device=DEV)
+    cd = c0.to(DEV)
+    c = torch.full((T, n, hidden), float("nan"), dtype=dtype, device=DEV) if keep_c else cd
+    dg.lstm_series(y.to(DEV), h0.to(DEV), w_x.to(DEV), w_h.to(DEV), bias.to(DEV), cd, c, h)
+    hw, cw = to_f64(h0), to_f64(c0)
+    for t in range(T):
+        hw, cw = oracle.lstm_cell(to_f64(y[t]), hw, cw, to_f64(w_x), to_f64(w_h), to_f64(bias))
+        assert_close(to_f64(h[t]), hw, dtype, f"h_{t + 1}", stores=2 * (t + 1))
+        if keep_c:
+            assert_close(to_f64(c[t]), cw, dtype, f"c_{t + 1}", stores=2 * (t + 1))
+    assert_close(to_f64(c[-1] if keep_c else cd), cw, dtype, "c_T", stores=2 * T)
+
+
+@pytest.mark.parametrize("dtype,hidden", [(torch.float32, 32), (torch.float32, 16), (torch.bfloat16, 32)])
+@pytest.mark.parametrize("n,T,cut", [(1, 3, 1), (33, 2, 0), (1000, 5, 2), (70_003, 2, 0)])
+def test_lstm_series_backward(dtype, hidden, n, T, cut):
+    """The adjoint of a series, in one call or cut into two, and the weight gradients of all its steps; the ReLU's mask on Y1."""
+    f_y = 2 * hidden
+    y = randn((T, n, f_y), n + T, dtype)
+    h0, c0, g_h = randn((n, hidden), 1, dtype), randn((n, hidden), 2, dtype), randn((T, n, hidden), 6, dtype)
+    w_x, w_h = (randn((f_y, 4 * hidden), 3) / f_y ** 0.5).to(dtype), (randn((hidden, 4 * hidden), 4) / hidden ** 0.5).to(dtype)
+    bias = randn((4 * hidden,), 5) * 0.1
+    dev = [t.to(DEV) for t in (y, h0, c0, g_h, w_x, w_h, bias)]
+    yd, h0d, c0d, gd, wxd, whd, bd = dev
+    h, c = (torch.empty((T, n, hidden), dtype=dtype, device=DEV) for _ in range(2))
+    dg.lstm_series(yd, h0d, wxd, whd, bd, c0d, c, h)
+    da, dy1 = torch.full((T, n, 4 * hidden), float("nan"), dtype=dtype, device=DEV), torch.full((T, n, hidden), float("nan"), dtype=dtype, device=DEV)
+    dh, dc = torch.empty((n, hidden), device=DEV), torch.empty((n, hidden), device=DEV)
+    dw_x, dw_h, db = torch.zeros((f_y, 4 * hidden), device=DEV), torch.zeros((hidden, 4 * hidden), device=DEV), torch.zeros(4 * hidden, device=DEV)
+    ws = torch.empty(dg.binding.lstm_weight_grad_workspace(f_y, hidden), dtype=torch.uint8, device=DEV)
+    for a, e in ((cut, T), (0, cut)):
+        if a == e:
+            continue
+        hp, cp = (h0d, c0d) if a == 0 else (h[a - 1], c[a - 1])
+        dg.lstm_series_backward(yd[a:e], hp, h[a:e], wxd, whd, bd, cp, c[a:e], gd[a:e], da[a:e], dy1[a:e], dh, dc, carried=e != T)
+        dg.lstm_weight_grad(yd[a:e], hp, h[a:e], da[a:e], dw_x, dw_h, db, ws, accumulate=e != T)
+    hs, cs = [to_f64(h0)] + [to_f64(t) for t in h], [to_f64(c0)] + [to_f64(t) for t in c]
+    wx, wh, b = to_f64(w_x), to_f64(w_h), to_f64(bias)
+    d_h, d_c = np.zeros((n, hidden)), np.zeros((n, hidden))
+    want = [np.zeros_like(wx), np.zeros_like(wh), np.zeros_like(b)]
+    for t in range(T - 1, -1, -1):
+        yt = to_f64(y[t])
+        d_a, _, _, d_c = oracle.lstm_cell_backward(yt, hs[t], cs[t], wx, wh, b, to_f64(g_h[t]) + d_h, d_c)[:4]
+        d_h = d_a @ wh.T
+        assert_close(to_f64(da[t]), d_a, dtype, f"da_{t + 1}", stores=2 * (T - t))
+        assert_close(to_f64(dy1[t]), (d_a @ wx.T)[:, hidden:] * (yt[:, hidden:] > 0), dtype, f"dY1_{t + 1}", stores=2 * (T - t))
+        want[0] += yt.T @ d_a
+        want[1] += hs[t].T @ d_a
+        want[2] += d_a.sum(axis=0)
+    tol = 2e-4 if dtype == torch.float32 else 2e-2
+    for got, exp in zip((dh, dc, dw_x, dw_h, db), [d_h, d_c] + want):
+        assert np.abs(to_f64(got) - exp).max() <= tol * np.abs(exp).max() + 1e-6
