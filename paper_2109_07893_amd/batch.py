@@ -23,9 +23,11 @@ BATCH_BYTES = 64 << 20
 # 4.5 / 12.7 us, 1.7 M 8.0 / 14.7 us, 17 M 65 / 53 us).
 SERIES_ENTRIES = 1 << 22
 
-# Vertices up to which the aggregation of X gathers dinv along with the rows instead of finding them scaled: the factors (4
-# bytes per vertex) then fit in every L2 beside what the gather itself keeps there, and the pass that scales the rows is saved.
-GATHERED_DINV_ROWS = 1 << 19
+# Vertices up to which the aggregation of X gathers dinv with the rows instead of finding them scaled by a pass of their own.
+# The pass costs per byte of X, the gather per entry, and far more once the factors (4 bytes per vertex, 1 MB here) leave an
+# L2 of 4 MB to the rows no more: per aggregation of 128-byte rows, gather against pass, 2^16 vertices 8 / 6 us, 2^18
+# 15 / 15, 2^19 37 / 27, 2^20 130 / 49; of 256-byte rows 2^18 17 / 24, 2^19 62 / 52, 2^20 200 / 98.
+GATHERED_DINV_ROWS = 1 << 18
 
 
 def steps_together(frame_bytes: int, T: int) -> int:

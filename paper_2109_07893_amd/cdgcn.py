@@ -42,7 +42,7 @@ class CdgcnLayer(BlockRunner):
         assert tuple(w_x.shape) == (f + f_out, 4 * hidden) and tuple(w_h.shape) == (hidden, 4 * hidden)
         # the right-hand D^(-1/2) of A~: gathered with the rows of X, or, where the factors no longer fit beside them in the
         # caches, put into the rows by a pass of its own
-        self.prescale = dt == torch.float32 and n > GATHERED_DINV_ROWS
+        self.prescale = n > GATHERED_DINV_ROWS
         self.xs = torch.empty((m, n, f), dtype=dt, device=dev) if self.prescale else None
         self.y0_batch = torch.empty((m, n, f), dtype=dt, device=dev)
         self.y_batch = torch.empty((m, n, f + f_out), dtype=dt, device=dev)

@@ -40,6 +40,7 @@ constexpr int kTargetWaves = 65536;  // ranges shrink on small inputs so that ab
 constexpr int kLongestRange = 8192;  // what a caller with little room for records may stretch a range to
 constexpr int kXcds = 8;             // accelerator dies of an MI355X, each with its own L2
 constexpr int kXcdChunk = 16;        // consecutive ranges that go to the same XCD
+constexpr int kMaxSlices = 2;        // of the columns, see slices_of
 constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: all vector memory loads returned, other counters untouched
 
 enum : int32_t { kLeft = 1, kLeftClosed = 2, kRight = 4 };
@@ -103,20 +104,20 @@ __device__ __forceinline__ void finish_row(char *z, int64_t row, int row_bytes, 
     Piece<BF16>::store(z + row * row_bytes + sub * 16, out);
 }
 
-template <bool BF16, int LPR>
+template <int LPR, int SLICES, bool BF16>
 __device__ __forceinline__ void zero_row(char *z, int64_t row) {
     constexpr int NV = Piece<BF16>::kVals;
     float zero[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) zero[q] = 0.0f;
-    for (int s = 0; s < LPR; ++s) Piece<BF16>::store(z + row * (LPR * 16) + s * 16, zero);
+    for (int s = 0; s < LPR; ++s) Piece<BF16>::store(z + row * (LPR * SLICES * 16) + s * 16, zero);
 }
 
 // LPR: lanes per feature row.  SCALE_V: multiply every gathered row by a per-entry factor: dinv of its
 // column, or the entry's own value when the snapshot carries values (otherwise H already carries the factor).
-template <int LPR, bool BF16, bool SCALE_V>
+template <int LPR, int SLICES, bool BF16, bool SCALE_V>
 __device__ __forceinline__ void spmm_stream(
-    int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int range, int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ dinv, const char *__restrict__ h, char *__restrict__ z, int relu,
     RangeRec *__restrict__ recs, float *__restrict__ carry, const float *__restrict__ vals) {
     typedef typename Piece<BF16>::Raw Raw;
@@ -125,7 +126,7 @@ __device__ __forceinline__ void spmm_stream(
     constexpr int G = kWave / LPR;          // lane groups per wavefront
     constexpr int SUB = G * kPer;           // entries per sub-tile
     constexpr int CPL = kPer / LPR;         // column indices held by one lane
-    constexpr int kRowBytes = LPR * 16;
+    constexpr int kRowBytes = LPR * SLICES * 16;   // from a row to the next; h, z, recs and carry are the slice's own
     constexpr int kRowCap = SUB + kWave;    // most rows a sub-tile can need: one per entry, plus the bounding one
     constexpr int ROUNDS = kRowCap / kWave;
 
@@ -136,13 +137,6 @@ __device__ __forceinline__ void spmm_stream(
 
     const int lane = threadIdx.x;
     const int sub = lane % LPR, g = lane / LPR, gbase = lane - sub;
-    // Workgroups are dealt to the eight XCDs in turn, and each XCD has an L2 of its own.  Ranges are handed
-    // out in chunks of kXcdChunk consecutive ones per XCD, so that rows which lie close together (and in a
-    // graph with locality gather the same rows of H) meet in one L2, while every XCD still gets a share of
-    // every part of the matrix (parts differ in cost per entry when row lengths are clustered).
-    const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
-    const int range = ((slot / kXcdChunk) * kXcds + xcd) * kXcdChunk + slot % kXcdChunk;
-    if (range >= n_ranges) return;
     // the host's count may be an upper bound (a snapshot whose size only the device knows): the last row pointer decides
     nnz = min(nnz, rowptr[n]);
     const int e_begin = (int)((int64_t)range * range_len);
@@ -153,7 +147,7 @@ __device__ __forceinline__ void spmm_stream(
     const int e_end = (int)min((int64_t)e_begin + range_len, (int64_t)nnz);
     int k_cur = max(wave_find_row(rowptr, n, e_begin, lane), 0);   // a row with rowptr <= e_begin
     if (range == 0)                          // rows without entries ahead of the first stored entry
-        for (int k = lane; k < k_cur; k += kWave) zero_row<BF16, LPR>(z, k);
+        for (int k = lane; k < k_cur; k += kWave) zero_row<LPR, SLICES, BF16>(z, k);
 
     // the row that is still open at the end of a sub-tile is carried on in the lanes of group 0
     float run[NV];
@@ -227,7 +221,7 @@ __device__ __forceinline__ void spmm_stream(
         // rows without entries give zero output (none exist when every row holds its diagonal)
 #pragma unroll 1
         for (int t = lane; t + 1 < staged; t += kWave)
-            if (k_cur + t + 1 <= n && s_rp[t] == s_rp[t + 1]) zero_row<BF16, LPR>(z, k_cur + t);
+            if (k_cur + t + 1 <= n && s_rp[t] == s_rp[t + 1]) zero_row<LPR, SLICES, BF16>(z, k_cur + t);
         if (t0 > 0) {                                    // rows without entries were stepped over: restage from the row of e
             k_cur += t0;
             fetch_rows(k_cur);
@@ -473,14 +467,26 @@ __device__ __forceinline__ void spmm_stream(
     }
     if (e_end == nnz)                                    // rows without entries beyond the last staged window
         for (int k = k_win + staged_last - 1 + lane; k < n; k += kWave)
-            if (rowptr[k] == rowptr[k + 1]) zero_row<BF16, LPR>(z, k);
+            if (rowptr[k] == rowptr[k + 1]) zero_row<LPR, SLICES, BF16>(z, k);
 }
 
-template <int LPR, bool BF16, bool SCALE_V>
+// Workgroups are dealt to the eight XCDs in turn, and each XCD has an L2 of its own.  Ranges are handed out in chunks of
+// kXcdChunk consecutive ones per XCD, so that rows which lie close together (and in a graph with locality gather the same
+// rows of H) meet in one L2, while every XCD still gets a share of every part of the matrix (parts differ in cost per entry
+// when row lengths are clustered).  With SLICES > 1 an XCD takes one slice of the columns of H only (see slices_of): each
+// range is then walked by SLICES wavefronts, on SLICES different XCDs.
+template <int LPR, int SLICES, bool BF16, bool SCALE_V>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void spmm_stream_kernel(int n, int relu, Batch batch) {
+    constexpr int kGroups = kXcds / SLICES;                             // XCDs per slice
     const Item &it = batch.item[blockIdx.y];
-    spmm_stream<LPR, BF16, SCALE_V>(n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
-                                    as_global(it.h), as_global(it.z), relu, as_global(it.recs), as_global(it.carry), as_global(it.vals));
+    const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds, slice = xcd % SLICES;
+    const int range = ((slot / kXcdChunk) * kGroups + xcd / SLICES) * kXcdChunk + slot % kXcdChunk;
+    if (range >= it.n_ranges) return;
+    constexpr int F = LPR * Piece<BF16>::kVals;                         // columns of a slice
+    spmm_stream<LPR, SLICES, BF16, SCALE_V>(range, n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
+                                            as_global(it.h) + slice * LPR * 16, as_global(it.z) + slice * LPR * 16, relu,
+                                            as_global(it.recs) + slice * it.n_ranges, as_global(it.carry) + (int64_t)slice * it.n_ranges * 2 * F,
+                                            as_global(it.vals));
 }
 
 // Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries of the following
@@ -490,16 +496,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) v
 // row's extent alone.
 constexpr int kOwnPieces = 4;
 
-template <int LPR, bool BF16>
+template <int LPR, int SLICES, bool BF16>
 __global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) {
     constexpr int NV = Piece<BF16>::kVals;
     constexpr int F = LPR * NV;
     constexpr int G = kWave / LPR;
     const Item &item = batch.item[blockIdx.y];
-    const float *__restrict__ carry = as_global(item.carry), *__restrict__ dinv = as_global(item.dinv);
-    const RangeRec *__restrict__ recs = as_global(item.recs);
+    const int slice = blockIdx.z;
+    const float *__restrict__ carry = as_global(item.carry) + (int64_t)slice * item.n_ranges * 2 * F, *__restrict__ dinv = as_global(item.dinv);
+    const RangeRec *__restrict__ recs = as_global(item.recs) + slice * item.n_ranges;
     const int32_t *__restrict__ rowptr = as_global(item.rowptr);
-    char *__restrict__ z = as_global(item.z);
+    char *__restrict__ z = as_global(item.z) + slice * LPR * 16;
     const int lane = threadIdx.x & (kWave - 1);
     const int sub = lane % LPR, g = lane / LPR;
     const int first = (blockIdx.x * 256 + threadIdx.x) / kWave * G;     // the wavefront's records
@@ -521,7 +528,7 @@ __global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) 
         for (int j = t + 1; j <= last; ++j)
 #pragma unroll
             for (int q = 0; q < NV; ++q) acc[q] += left(j, q);
-        finish_row<BF16, NV>(z, (int64_t)row, LPR * 16, sub, dinv, relu, acc);
+        finish_row<BF16, NV>(z, (int64_t)row, LPR * SLICES * 16, sub, dinv, relu, acc);
     }
     for (uint64_t todo = __ballot(row >= 0 && !own && sub == 0); todo; todo &= todo - 1) {
         const int src = __builtin_ctzll(todo);
@@ -540,7 +547,7 @@ __global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) 
         if (g == 0) {
 #pragma unroll
             for (int q = 0; q < NV; ++q) acc[q] += carry[((int64_t)tt * 2 + 1) * F + sub * NV + q];
-            finish_row<BF16, NV>(z, (int64_t)rr, LPR * 16, sub, dinv, relu, acc);
+            finish_row<BF16, NV>(z, (int64_t)rr, LPR * SLICES * 16, sub, dinv, relu, acc);
         }
     }
 }
@@ -572,7 +579,7 @@ size_t workspace_layout(int64_t nnz, int32_t f, Workspace *ws, void *base, int64
     // exact_ranges: the number of ranges of one particular call (a caller that knows the call and has little room)
     const int64_t ranges = exact_ranges > 0 ? exact_ranges
                                             : std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange) + 1;
-    const size_t o_carry = round_up((size_t)ranges * sizeof(RangeRec), 256);
+    const size_t o_carry = round_up((size_t)ranges * kMaxSlices * sizeof(RangeRec), 256);
     const size_t total = o_carry + round_up((size_t)ranges * 2 * f * sizeof(float), 256);
     if (ws) {
         char *b = static_cast<char *>(base);
@@ -583,21 +590,28 @@ size_t workspace_layout(int64_t nnz, int32_t f, Workspace *ws, void *base, int64
 }
 
 // The aggregations of one launch pair; grid.x follows from the longest, the others leave early.
-template <int LPR, bool BF16>
+template <int LPR, int SLICES, bool BF16>
 int launch(int64_t n, int count, const Batch &b, bool scale_v, int relu, hipStream_t s) {
-    constexpr int G = 256 / LPR;
+    constexpr int G = 256 / LPR, kRound = kXcds / SLICES * kXcdChunk;   // ranges per round of chunks over the XCDs
     int ranges = 0;
     for (int k = 0; k < count; ++k) ranges = std::max(ranges, b.item[k].n_ranges);
-    const int grid = (ranges + kXcds * kXcdChunk - 1) / (kXcds * kXcdChunk) * (kXcds * kXcdChunk);   // whole chunk rounds
+    const int grid = (ranges + kRound - 1) / kRound * kXcds * kXcdChunk;
     if (scale_v)
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, true>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
+        hipLaunchKernelGGL((spmm_stream_kernel<LPR, SLICES, BF16, true>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
     else
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, BF16, false>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
+        hipLaunchKernelGGL((spmm_stream_kernel<LPR, SLICES, BF16, false>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
     DGNN_RETURN_IF_LAUNCH_FAILED();
-    hipLaunchKernelGGL((spmm_carry_kernel<LPR, BF16>), dim3((ranges + G - 1) / G, count), dim3(256), 0, s, relu, b);
+    hipLaunchKernelGGL((spmm_carry_kernel<LPR, SLICES, BF16>), dim3((ranges + G - 1) / G, count, SLICES), dim3(256), 0, s, relu, b);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
+
+// Into how many slices of columns an aggregation is cut, one group of XCDs per slice: an L2 then holds that slice of H only,
+// as if it were so much larger, and a lane group stays at 16 lanes.  Rows of 512 bytes in two slices of 256: uniform graph of
+// 32 K vertices 45 -> 36 us, R-MAT 2^20 1.10 -> 0.91 ms, uniform 2^20 (no reuse either way) 1.34 ms both.  Not for rows of 256
+// bytes: every entry's bookkeeping is done once per slice, which costs power-law graphs more (7 %) than the L2 gives back, and
+// below 128 bytes, the L2's line, nothing is saved at all (twice the time).
+int slices_of(int32_t f, dgnn_dtype dt) { return f * (dt == DGNN_F32 ? 4 : 2) > 256 ? 2 : 1; }
 
 }  // namespace
 
@@ -613,19 +627,18 @@ namespace {
 
 // Entries per range of one call for this snapshot, width and storage type (max_ranges as in range_length).
 int range_length_of_call(int64_t nnz, int32_t f, dgnn_dtype dt, int64_t max_ranges = 0) {
-    const int lpr = dt == DGNN_F32 ? f / 4 : f / 8;
+    const int lpr = (dt == DGNN_F32 ? f / 4 : f / 8) / slices_of(f, dt);
     return range_length(nnz, (kWave / lpr) * kPer, max_ranges);
 }
 
 int launch_width(int64_t n, int count, const Batch &b, bool scale_v, int32_t f, dgnn_dtype dt, int relu, hipStream_t s) {
-    const int lpr = dt == DGNN_F32 ? f / 4 : f / 8;   // lanes per feature row, 16 bytes each
     const bool bf = dt == DGNN_BF16;
-    switch (lpr) {
-        case 2: return launch<2, true>(n, count, b, scale_v, relu, s);
-        case 4: return bf ? launch<4, true>(n, count, b, scale_v, relu, s) : launch<4, false>(n, count, b, scale_v, relu, s);
-        case 8: return bf ? launch<8, true>(n, count, b, scale_v, relu, s) : launch<8, false>(n, count, b, scale_v, relu, s);
-        case 16: return bf ? launch<16, true>(n, count, b, scale_v, relu, s) : launch<16, false>(n, count, b, scale_v, relu, s);
-        case 32: return launch<32, false>(n, count, b, scale_v, relu, s);
+    if (slices_of(f, dt) == 2) return launch<16, 2, false>(n, count, b, scale_v, relu, s);      // fp32, 128 columns
+    switch (bf ? f / 8 : f / 4) {   // lanes per feature row, 16 bytes each
+        case 2: return launch<2, 1, true>(n, count, b, scale_v, relu, s);
+        case 4: return bf ? launch<4, 1, true>(n, count, b, scale_v, relu, s) : launch<4, 1, false>(n, count, b, scale_v, relu, s);
+        case 8: return bf ? launch<8, 1, true>(n, count, b, scale_v, relu, s) : launch<8, 1, false>(n, count, b, scale_v, relu, s);
+        case 16: return bf ? launch<16, 1, true>(n, count, b, scale_v, relu, s) : launch<16, 1, false>(n, count, b, scale_v, relu, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
@@ -667,7 +680,7 @@ extern "C" int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, 
     if (count <= 0 || nnz < 0 || !supported_width(f)) return DGNN_ERR_SHAPE;
     if (!fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // the shortest range any storage type uses at this width is one sub-tile; no call has more ranges than this
-    const int64_t shortest = kWave / (f / 4) * kPer;
+    const int64_t shortest = kWave / (f / 4) * kPer;              // (slices make sub-tiles longer)
     const int64_t ranges = std::min<int64_t>((nnz + shortest - 1) / shortest, std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange));
     *bytes = (size_t)count * workspace_layout(nnz, f, nullptr, nullptr, ranges + 1);
     return DGNN_OK;
@@ -762,7 +775,7 @@ extern "C" int dgnn_spmm_static(int64_t n, int64_t nnz, const int32_t *rowptr, c
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n + 1) || !fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // as many ranges as the array has room for records of: ranges grow longer where the usual ones would be too many
-    const int64_t max_ranges = (int64_t)((kStaticScratchBytes - 512) / (sizeof(RangeRec) + 2 * (size_t)f * sizeof(float)));
+    const int64_t max_ranges = (int64_t)((kStaticScratchBytes - 512) / (kMaxSlices * sizeof(RangeRec) + 2 * (size_t)f * sizeof(float)));
     if (range_length_of_call(nnz, f, dt, max_ranges) <= 0) return DGNN_ERR_CAPACITY;
     void *ptr = nullptr;
     const int rc = static_scratch(&ptr);
