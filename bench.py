@@ -451,7 +451,7 @@ def smoothing_steps(args, wl, blk, dev, life=4):
     # as many timesteps as fit beside the inputs: activations, M-transformed output and two gradient tensors per frame,
     # index and value arrays per smoothed snapshot (twice for a directed workload)
     free, _ = torch.cuda.mem_get_info(dev)
-    per_t = 4 * blk.n * blk.f * blk.x[0].element_size() * max(blk.layers, 1) + 2 * 8 * int(max(blk.nnz) * 1.3)
+    per_t = 5 * blk.n * blk.f * blk.x[0].element_size() * max(blk.layers, 1) + 2 * 8 * int(max(blk.nnz) * 1.3)
     t_fit = max(2, min(blk.T, int(0.6 * free / per_t)))
     if t_fit < blk.T:
         from paper_2109_07893_amd.pipeline import BlockInputs

@@ -221,6 +221,29 @@ typedef struct {
 int dgnn_delta_rebuild_series(int64_t n, const int32_t *rowptr_first, const int32_t *colidx_first, int64_t nnz_first,
                               int32_t steps, const dgnn_series_step *step, int64_t cap, void *stream);
 
+/* One step of dgnn_smooth_series: its difference lists and where S_t goes (dinv may be NULL). */
+typedef struct {
+    const int32_t *add_row, *add_col, *del_row, *del_col;
+    int64_t n_add, n_del;
+    int32_t *rowptr, *colidx;
+    float *val, *dinv;
+} dgnn_smooth_step;
+
+/*
+ * The smoothed snapshots S_2 .. S_{steps+1} from S_1 = A_1 and the difference lists of the RAW series, and their normalisation:
+ * what dgnn_delta_rebuild, dgnn_csr_combine (alpha 1, beta -1, A_out from step `life` on, diag_value) and
+ * dgnn_csr_weighted_dinv give step by step, bit for bit, in four launches for all steps; no raw snapshot is formed.
+ *   steps: at most DGNN_SERIES_STEPS; life: 1 .. 32 snapshots are summed; step[k].colidx / val: `capacity` entries each, all
+ *   arrays different from each other and from A_1's.  step[k].dinv is that of S with every snapshot holding its diagonal.
+ *   d_status [steps] or NULL: 0, or DGNN_BAD_CAPACITY where S_t does not fit (rowptr[n] then holds the size needed, and what
+ *   lies beyond the capacity is not written).  Lists and preconditions as in dgnn_delta_rebuild, without its validation.
+ * Enqueue-only.  Errors: NULL, SHAPE, OVERFLOW, CAPACITY (workspace), ALIAS, ALIGN, HIP.
+ */
+int dgnn_smooth_series_workspace(int64_t nnz_first, int32_t steps, size_t *bytes);
+int dgnn_smooth_series(int64_t n, const int32_t *rowptr_first, const int32_t *colidx_first, int64_t nnz_first, int32_t steps,
+                       const dgnn_smooth_step *step, int32_t life, float diag_value, int64_t capacity, int32_t *d_status,
+                       void *ws, size_t ws_bytes, void *stream);
+
 /* One product of dgnn_feature_transform_batch: h = diag(row_scale) x w (row_scale may be NULL). */
 typedef struct {
     const void *x, *w;
@@ -247,7 +270,10 @@ typedef struct {
     int64_t nnz;
 } dgnn_spmm_item;
 
-/* dgnn_spmm (dgnn_spmm_weighted) for `count` snapshots of n vertices, same results bit for bit.  nnz: the largest of the items'. */
+/*
+ * dgnn_spmm (dgnn_spmm_weighted) for `count` snapshots of n vertices, same results bit for bit.  nnz: the largest of the items'.
+ * With values and dinv, rows of h that are not DGNN_H_PRESCALED are scaled as they are gathered.
+ */
 int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, size_t *bytes);
 int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *items, int32_t f, dgnn_dtype dt, uint32_t flags,
                     void *ws, size_t ws_bytes, void *stream);

@@ -1,4 +1,4 @@
-"""Tables for the library calls that take several timesteps at once (dgnn_delta_rebuild_series,
+"""Tables for the library calls that take several timesteps at once (dgnn_delta_rebuild_series, dgnn_smooth_series,
 dgnn_feature_transform_batch, dgnn_spmm_batch).  A table is a numpy array of 64-bit words laid out like the C structs of
 include/dgnn.h: device pointers and counts; the drivers fill it once and refresh, per pass, the columns a caller may have
 replaced (features, weights, difference lists)."""
@@ -67,14 +67,12 @@ class Table:
         self.words[rows, k] = values
 
 
-class SeriesTable(Table):
-    """dgnn_series_step: add_row, add_col, del_row, del_col, n_add, n_del, rowptr, colidx, dinv."""
+class StepsTable(Table):
+    """What the two series calls have in common: the difference lists of a step, add_row, add_col, del_row, del_col, n_add,
+    n_del, before the arrays it leads to."""
 
-    def __init__(self, rowptr, colidx, dinv):
-        super().__init__(len(rowptr), 9)
-        for k, tensors in ((6, rowptr), (7, colidx), (8, dinv)):
-            if tensors:
-                self.column(k, pointers(tensors))
+    def __init__(self, rows: int, words: int):
+        super().__init__(rows, words)
         self.seen, self.kept = Seen(), None
 
     def lists(self, deltas) -> None:
@@ -87,6 +85,28 @@ class SeriesTable(Table):
                 B._need(t, torch.int32, "difference list")
                 assert t.is_contiguous()
             self.words[k, :6] = [t.data_ptr() if t.numel() else 0 for t in d] + [d[0].numel(), d[2].numel()]
+
+
+class SeriesTable(StepsTable):
+    """dgnn_series_step: the lists, then rowptr, colidx, dinv."""
+
+    def __init__(self, rowptr, colidx, dinv):
+        super().__init__(len(rowptr), 9)
+        for k, tensors in ((6, rowptr), (7, colidx), (8, dinv)):
+            if tensors:
+                self.column(k, pointers(tensors))
+
+
+class SmoothTable(StepsTable):
+    """dgnn_smooth_step: the lists, then rowptr, colidx, val, dinv."""
+
+    def __init__(self, snapshots, dinv):
+        super().__init__(len(snapshots), 10)
+        for k in range(3):
+            if len(snapshots):
+                self.column(6 + k, pointers([s[k] for s in snapshots]))
+        if len(snapshots) and dinv is not None:
+            self.column(9, pointers(dinv))
 
 
 class TransformTable(Table):

@@ -137,6 +137,25 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
 
+// First index in [lo, hi) whose key, get(index), is not below `key` (keys ascending): four ways per round, because a round
+// is a trip to memory (or to the LDS) that nothing hides.
+template <typename Get>
+__device__ __forceinline__ int lower4(int lo, int hi, uint64_t key, Get get) {
+    int len = hi - lo;                         // the answer lies in [lo, lo + len]
+    while (len > 3) {
+        const int q = len >> 2;
+        const uint64_t k1 = get(lo + q), k2 = get(lo + 2 * q), k3 = get(lo + 3 * q);
+        const int below = (k1 < key ? 1 : 0) + (k2 < key ? 1 : 0) + (k3 < key ? 1 : 0);
+        len = below == 3 ? len - 3 * q - 1 : below == 0 ? q : q - 1;
+        lo += below == 0 ? 0 : below * q + 1;
+    }
+    while (len > 0 && get(lo) < key) { ++lo; --len; }
+    return lo;
+}
+__device__ __forceinline__ int lower_key(const int32_t *__restrict__ row, const int32_t *__restrict__ col, int lo, int hi, uint64_t key) {
+    return lower4(lo, hi, key, [=](int i) { return ((uint64_t)(uint32_t)row[i] << 32) | (uint32_t)col[i]; });
+}
+
 // ---- 16-byte pieces of feature rows: 4 fp32 or 8 bf16 values, unpacked to and packed from fp32 ------------
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 

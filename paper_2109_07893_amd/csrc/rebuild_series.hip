@@ -40,25 +40,6 @@ struct Series {
     dgnn_series_step s[kSteps];
 };
 
-// First index in [lo, hi) whose key, get(index), is not below `key` (keys ascending): four ways per round, because a round
-// is a trip to memory (or to the LDS) that nothing hides.
-template <typename Get>
-__device__ __forceinline__ int lower4(int lo, int hi, uint64_t key, Get get) {
-    int len = hi - lo;                         // the answer lies in [lo, lo + len]
-    while (len > 3) {
-        const int q = len >> 2;
-        const uint64_t k1 = get(lo + q), k2 = get(lo + 2 * q), k3 = get(lo + 3 * q);
-        const int below = (k1 < key ? 1 : 0) + (k2 < key ? 1 : 0) + (k3 < key ? 1 : 0);
-        len = below == 3 ? len - 3 * q - 1 : below == 0 ? q : q - 1;
-        lo += below == 0 ? 0 : below * q + 1;
-    }
-    while (len > 0 && get(lo) < key) { ++lo; --len; }
-    return lo;
-}
-__device__ __forceinline__ int lower_key(const int32_t *__restrict__ row, const int32_t *__restrict__ col, int lo, int hi, uint64_t key) {
-    return lower4(lo, hi, key, [=](int i) { return ((uint64_t)(uint32_t)row[i] << 32) | (uint32_t)col[i]; });
-}
-
 // rowptr_t[r] = rowptr_1[r] + sum over the steps so far of (#added - #deleted with row < r); all steps of the launch.
 __global__ __launch_bounds__(kRowTile) void series_rowptr_kernel(Series P) {
     __shared__ __attribute__((aligned(16))) int s_cnt[kSteps][kCountLd];   // net entries per row, then their exclusive sums

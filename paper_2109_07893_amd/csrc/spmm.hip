@@ -54,7 +54,7 @@ struct Item {
     char *z;
     RangeRec *recs;
     float *carry;
-    int32_t nnz, range_len, n_ranges, pad;
+    int32_t nnz, range_len, n_ranges, gather_dinv;   // gather_dinv: rows of h are scaled as they are gathered
 };
 constexpr int kMaxBatch = 32;        // what fits the kernel arguments comfortably
 struct Batch { Item item[kMaxBatch]; };
@@ -119,7 +119,7 @@ template <int LPR, int SLICES, bool BF16, bool SCALE_V>
 __device__ __forceinline__ void spmm_stream(
     int range, int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ dinv, const char *__restrict__ h, char *__restrict__ z, int relu,
-    RangeRec *__restrict__ recs, float *__restrict__ carry, const float *__restrict__ vals) {
+    RangeRec *__restrict__ recs, float *__restrict__ carry, const float *__restrict__ vals, bool gather_dinv) {
     typedef typename Piece<BF16>::Raw Raw;
     constexpr int NV = Piece<BF16>::kVals;
     constexpr int F = LPR * NV;
@@ -172,8 +172,8 @@ __device__ __forceinline__ void spmm_stream(
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
                 const int idx = e0 + g * kPer + sub * CPL + i;
-                // an explicit value per stored entry (one coalesced stream), else dinv of the entry's column
-                d_next[i] = idx < e_end ? (vals ? vals[idx] : dinv[c_next[i]]) : 0.0f;
+                // an explicit value per stored entry (one coalesced stream) and / or dinv of the entry's column
+                d_next[i] = idx < e_end ? (vals ? vals[idx] : 1.0f) * (gather_dinv ? dinv[c_next[i]] : 1.0f) : 0.0f;
             }
         }
     };
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) v
     spmm_stream<LPR, SLICES, BF16, SCALE_V>(range, n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
                                             as_global(it.h) + slice * LPR * 16, as_global(it.z) + slice * LPR * 16, relu,
                                             as_global(it.recs) + slice * it.n_ranges, as_global(it.carry) + (int64_t)slice * it.n_ranges * 2 * F,
-                                            as_global(it.vals));
+                                            as_global(it.vals), it.gather_dinv != 0);
 }
 
 // Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries of the following
@@ -661,7 +661,7 @@ int spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *colidx, c
     const bool scale_v = vals != nullptr || (dinv != nullptr && !(flags & DGNN_H_PRESCALED));
     Batch b;
     b.item[0] = Item{rowptr, colidx, dinv, vals, static_cast<const char *>(h), static_cast<char *>(z), w.recs, w.carry, (int32_t)nnz,
-                     range_len, (int32_t)ranges, 0};
+                     range_len, (int32_t)ranges, dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0};
     return launch_width(n, 1, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
 }
 
@@ -698,8 +698,7 @@ extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *i
         const dgnn_spmm_item &it = items[k];
         if (!it.rowptr || !it.colidx || !it.h || !it.z) return DGNN_ERR_NULL;
         if (it.nnz <= 0 || (it.val != nullptr) != weighted) return DGNN_ERR_SHAPE;
-        // as in dgnn_spmm_weighted: with values the normalisation is in the rows of h or there is none
-        if (weighted && (it.dinv != nullptr) != ((flags & DGNN_H_PRESCALED) != 0)) return DGNN_ERR_SHAPE;
+        if (weighted && !it.dinv && (flags & DGNN_H_PRESCALED)) return DGNN_ERR_SHAPE;
         if (!fits_index(it.nnz)) return DGNN_ERR_OVERFLOW;
         if (!aligned16(it.h) || !aligned16(it.z)) return DGNN_ERR_ALIGN;
         if (it.h == it.z) return DGNN_ERR_ALIAS;
@@ -717,7 +716,7 @@ extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *i
             if ((size_t)(base - static_cast<char *>(ws)) + size > ws_bytes) return DGNN_ERR_CAPACITY;
             base += size;
             b.item[k] = Item{it.rowptr, it.colidx, it.dinv, it.val, static_cast<const char *>(it.h), static_cast<char *>(it.z), w.recs, w.carry,
-                             (int32_t)it.nnz, range_len, (int32_t)ranges, 0};
+                             (int32_t)it.nnz, range_len, (int32_t)ranges, it.dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0};
         }
         // whether a per-entry factor is gathered is the launch's choice, not the item's
         const bool scale_v = weighted || (b.item[0].dinv != nullptr && !(flags & DGNN_H_PRESCALED));

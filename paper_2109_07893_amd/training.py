@@ -28,7 +28,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
+from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
 from .pipeline import BlockInputs, BlockRunner
 
 
@@ -76,11 +76,15 @@ class GcnStack:
         self.stage, self.want_dx, self.weighted = stage, want_dx, vals is not None
         self.together = m = together or steps_together(n * f * blk.x[0].element_size(), T)
         self.z = torch.empty((L, T, n, f), dtype=dt, device=dev)
-        self.p0 = None if want_dx else torch.empty((T, n, f), dtype=dt, device=dev)      # A~_t X_t
+        # A~_t X_t, from which the first layer's weight gradient follows without an aggregation.  With values and further layers
+        # above, where the transposed snapshots are resident anyway, the first layer is aggregated like the others: A~ (X W) rounds
+        # less than (A~ X) W before the ReLU decides, and what it decides passes through all layers going back
+        aggregate_first = want_dx or (self.weighted and L > 1)
+        self.p0 = None if aggregate_first else torch.empty((T, n, f), dtype=dt, device=dev)
         # rows of X are scaled by dinv in a pass of their own, or dinv is gathered with them (see GATHERED_DINV_ROWS);
-        # bf16 rows always take the latter, which spares them a rounding; with values there is one factor per entry already
-        self.prescale = not want_dx and (self.weighted or (blk.x[0].dtype == torch.float32 and n > GATHERED_DINV_ROWS))
-        aggregated = L - 1 if not want_dx else L                                         # layers that need A~^T going back
+        # bf16 rows always take the latter, which spares them a rounding
+        self.prescale = not aggregate_first and blk.x[0].dtype == torch.float32 and n > GATHERED_DINV_ROWS
+        aggregated = L if aggregate_first else L - 1                                     # layers that need A~^T going back
         self.needs_transposed = aggregated > 0
         buffers = aggregated > 0 or self.prescale
         self.h = torch.empty((m, n, f), dtype=dt, device=dev) if buffers else None       # H going forward, G_H going back
@@ -107,7 +111,7 @@ class GcnStack:
         self.scaled = None
         for layer in range(L):
             a = TransformTable(T)
-            if layer == 0 and not want_dx:
+            if layer == 0 and self.p0 is not None:
                 if self.prescale:
                     self.scaled = TransformTable(T)
                     self.scaled.column(a.SCALE, snapshot[2])
@@ -138,7 +142,7 @@ class GcnStack:
         for b in self.spmm + ([self.spmm_t] if self.spmm_t is not None else []):
             b.column(b.NNZ, nnz[:T], rows)
         x = self.x.addresses(blk.x[:T])
-        if self.want_dx:
+        if self.p0 is None:
             self.transform[0].column(TransformTable.X, x, rows)
         elif self.prescale:
             self.scaled.column(TransformTable.X, x, rows)
@@ -152,7 +156,7 @@ class GcnStack:
         """All layers of timesteps t .. t + k - 1 (0-based), their snapshots resident."""
         n, f, dt = self.n, self.f, self.dt
         for layer in range(self.L):
-            first = layer == 0 and not self.want_dx
+            first = layer == 0 and self.p0 is not None
             if first and self.prescale:
                 with self.stage("feature_transform"):
                     B.feature_transform_batch(k, self.scaled.at(t), n, f, f, 0, dt, stream)
@@ -165,6 +169,12 @@ class GcnStack:
             if first:
                 with self.stage("feature_transform"):
                     B.feature_transform_batch(k, self.transform[0].at(t), n, f, f, B.DGNN_RELU, dt, stream)
+
+    def steps_back(self, dw_t, T: int) -> int:
+        """Timesteps that backward takes at a time: with one layer, one weight and nothing to aggregate the rows of all of them
+        in one product."""
+        whole = not self.needs_transposed and dw_t is None and T * self.n < (1 << 31) - 65536
+        return T if whole else self.together
 
     def _weight_grad(self, blk, t, k, layer, x, g, masked, dw, dw_t, accumulate, stream) -> None:
         n, f, dt, a = self.n, self.f, self.dt, self.wgrad
@@ -185,7 +195,7 @@ class GcnStack:
         flat = (k * n, f)
         g = g_top
         for layer in range(self.L - 1, -1, -1):
-            if layer == 0 and not self.want_dx:
+            if layer == 0 and self.p0 is not None:
                 self._weight_grad(blk, t, k, 0, self.p0[t:t + k], g, True, dw, dw_t, accumulate, stream)
                 return
             with self.stage("relu_backward"):
@@ -199,6 +209,8 @@ class GcnStack:
                     with self.stage("weight_grad"):
                         B.weight_grad(blk.x[t + j], self.h[j], dw_t[t + j][0] if dw_t is not None else dw[0], self.ws_wgrad,
                                       accumulate=dw_t is None and (accumulate or j > 0))
+            if layer == 0 and not self.want_dx:
+                return
             dst = self.g_mid[:k] if layer > 0 else self.dx[t:t + k]
             with self.stage("input_grad"):
                 if blk.w_t is None:
@@ -351,9 +363,7 @@ class BlockTrainer:
                 B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
         else:
             g_top = g_y
-        # one layer, one weight, nothing to aggregate: the rows of all timesteps in one product
-        whole = not stack.needs_transposed and self.dw_t is None and T * blk.n < (1 << 31) - 65536
-        m = T if whole else stack.together
+        m = stack.steps_back(self.dw_t, T)
         last = (T - 1) // m * m
         for t in range(last, -1, -m):
             k = min(m, T - t)
@@ -396,8 +406,8 @@ def transposed_inputs(blk: BlockInputs):
 
 def make_smoothed_trainer(wl, blk: BlockInputs, life: int) -> "SmoothedTrainer":
     directed = wl.graph != "er"
-    if not directed:
-        return SmoothedTrainer(blk, life, False)
+    if not directed or not needs_transposed(blk):
+        return SmoothedTrainer(blk, life, directed)
     first, deltas = transposed_inputs(blk)
     return SmoothedTrainer(blk, life, True, transposed_first=first, transposed_deltas=deltas)
 
@@ -522,12 +532,12 @@ class _Ring:
 
 class SmoothedTrainer:
     """A training step on SMOOTHED snapshots (Section "Smoothening the Input Graphs": the graphs TM-GCN and EvolveGCN
-    are trained on), with the smoothing done on the device.  Forward: the raw A_t by dgnn_delta_rebuild,
-    S_t = S_{t-1} + A_t - A_{t-life} by dgnn_csr_combine, its normalisation by dgnn_csr_weighted_dinv, then per layer
-    H = X W and Z = relu(D^(-1/2) S_t D^(-1/2) H) with the counts as values (dgnn_spmm_weighted).  Every S_t stays
-    resident (index and value arrays of all T smoothed snapshots: 21 GB at c5's size; and as many again for the
-    transposed ones of a directed workload), so the backward pass needs no graph work at all: it is the one of
-    BlockTrainer with the weighted aggregation on S_t^T.  Buffers and call order only."""
+    are trained on), with the smoothing done on the device: every S_t and its normalisation by dgnn_smooth_series, or, for
+    series longer than one such call takes, the raw A_t by dgnn_delta_rebuild, S_t = S_{t-1} + A_t - A_{t-life} by
+    dgnn_csr_combine and its normalisation by dgnn_csr_weighted_dinv.  The layers are those of BlockTrainer with the counts as
+    values.  Every S_t stays resident (index and value arrays of all T smoothed snapshots: 21 GB at c5's size; and as many
+    again for the transposed ones, where a directed workload has more than one layer), so the backward pass needs no graph
+    work at all.  Buffers and call order only."""
 
     def __init__(self, blk: BlockInputs, life: int, directed: bool,
                  transposed_first: Optional[Tuple[torch.Tensor, torch.Tensor]] = None,
@@ -544,39 +554,46 @@ class SmoothedTrainer:
         max_del = max([int(d[2].numel()) for d in blk.deltas] + [0])
         max_list = max([int(d[0].numel()) for d in blk.deltas] + [max_del, 1])
         self.cap_s = cap + life * max_del                  # the window's union: A_t and what the window's steps deleted
-        self.raw = _Ring(n, cap, dev, life + 1, with_dinv=False)
-        self.raw_t = _Ring(n, cap, dev, life + 1, with_dinv=False) if directed else None
-        self.t_first, self.t_deltas = transposed_first, transposed_deltas
-        if directed:
+        self.series = T - 1 <= B.DGNN_SERIES_STEPS and life <= 32 and blk.nnz[0] > 0
+        transposed = directed and needs_transposed(blk)
+        if transposed:
             assert transposed_first is not None and transposed_deltas is not None
+        self.t_first, self.t_deltas = transposed_first, transposed_deltas
+        ones = torch.ones(blk.nnz[0], dtype=torch.float32, device=dev)       # S_1 = A_1, every entry counted once
 
-        def smoothed_slots():
-            return [(torch.empty(n + 1, dtype=torch.int32, device=dev), torch.empty(self.cap_s, dtype=torch.int32, device=dev),
-                     torch.empty(self.cap_s, dtype=torch.float32, device=dev)) for _ in range(T)]
-        self.s = smoothed_slots()
-        self.st = smoothed_slots() if directed else self.s
-        self.s_nnz = [0] * T
+        def smoothed(rowptr1, colidx1):
+            return [(rowptr1, colidx1, ones)] + [
+                (torch.empty(n + 1, dtype=torch.int32, device=dev), torch.empty(self.cap_s, dtype=torch.int32, device=dev),
+                 torch.empty(self.cap_s, dtype=torch.float32, device=dev)) for _ in range(T - 1)]
+        self.s = smoothed(blk.rowptr1, blk.colidx1)
+        self.st = smoothed(*transposed_first) if transposed else self.s
+        # what the calls that take S_t are told about its size: an upper bound (the count is its last row pointer)
+        self.s_nnz = [blk.nnz[0]] + [self.cap_s] * (T - 1)
         self.dinv_s = torch.empty((T, n), dtype=torch.float32, device=dev)
-        self.z = torch.empty((L, T, n, f), dtype=dt, device=dev)
+        self.timer = None
+        arrays = [[s[k] for s in self.s] for k in range(3)]
+        back = [[s[k] for s in self.st] for k in range(3)] if transposed else None
+        self.stack = GcnStack(blk, max(self.cap_s, blk.nnz[0]), arrays[0], arrays[1], self.dinv_s, vals=arrays[2], transposed=back, stage=self._stage)
+        self.z = self.stack.z
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
         self.g = None
-        self.h = torch.empty((n, f), dtype=dt, device=dev)
-        self.gp = torch.empty((n, f), dtype=dt, device=dev)
-        self.g_mid = torch.empty((n, f), dtype=dt, device=dev) if L > 1 else None
         self.dw = [torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)]
         # with one weight per timestep (Section "EvolveGCN") every timestep has a gradient of its own
         self.dw_t = ([[torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)] for _ in range(T)]
                      if blk.w_t is not None else None)
-        self.ws_rebuild = torch.empty(B.delta_rebuild_workspace(n, cap, max_list, max_list), dtype=torch.uint8, device=dev)
-        self.ws_combine = torch.empty(B.csr_combine_workspace(self.cap_s), dtype=torch.uint8, device=dev)
-        self.ws_dinv = torch.empty(B.csr_weighted_dinv_workspace(self.cap_s), dtype=torch.uint8, device=dev)
-        self.ws_spmm = torch.empty(B.spmm_workspace(n, self.cap_s, f), dtype=torch.uint8, device=dev)
-        self.ws_wgrad = torch.empty(B.weight_grad_workspace(f, f), dtype=torch.uint8, device=dev)
-        self.status = torch.zeros(T + 1, dtype=torch.int32, device=dev)     # per timestep: what dgnn_csr_combine found
-        self.timer = None
+        self.status = torch.zeros(T + 1, dtype=torch.int32, device=dev)     # per timestep: whether S_t fitted its arrays
+        if self.series:
+            self.table = SmoothTable(self.s[1:], list(self.dinv_s[1:]))
+            self.table_t = SmoothTable(self.st[1:], None) if transposed else None
+            self.ws_smooth = torch.empty(B.smooth_series_workspace(blk.nnz[0], T - 1), dtype=torch.uint8, device=dev)
+        else:
+            self.raw = _Ring(n, cap, dev, life + 1, with_dinv=False)
+            self.raw_t = _Ring(n, cap, dev, life + 1, with_dinv=False) if transposed else None
+            self.ws_rebuild = torch.empty(B.delta_rebuild_workspace(n, cap, max_list, max_list), dtype=torch.uint8, device=dev)
+            self.ws_combine = torch.empty(B.csr_combine_workspace(self.cap_s), dtype=torch.uint8, device=dev)
+            self.ws_dinv = torch.empty(B.csr_weighted_dinv_workspace(self.cap_s), dtype=torch.uint8, device=dev)
 
     def _stage(self, name):
-        import contextlib
         return self.timer.stage(name) if self.timer is not None else contextlib.nullcontext()
 
     def _advance(self, ring: _Ring, lists, t: int) -> None:
@@ -587,8 +604,7 @@ class SmoothedTrainer:
                             ring.rowptr[d], ring.colidx[d], None, self.ws_rebuild)
 
     def _smooth(self, ring: _Ring, store, t: int) -> None:
-        """store[t-1] <- S_t (t >= 2) from store[t-2], A_t and A_{t-life}.  Its number of stored entries stays on the
-        device (the last row pointer); the calls that take S_t are given the capacity as an upper bound."""
+        """store[t-1] <- S_t (t >= 2) from store[t-2], A_t and A_{t-life}."""
         blk = self.blk
         prev = store[t - 2] + (self.s_nnz[t - 2],)
         a_out = ring.snapshot(t - self.life, blk.nnz[t - self.life - 1]) if t - self.life >= 1 else None
@@ -596,37 +612,39 @@ class SmoothedTrainer:
             B.csr_combine(prev, ring.snapshot(t, blk.nnz[t - 1]), 1.0, a_out, -1.0, store[t - 1], self.ws_combine,
                           diag_value=self.diag_value, status=self.status[t:t + 1])
 
-    def forward(self) -> torch.Tensor:
+    def _snapshots(self, stream) -> None:
+        """S_1 .. S_T (and their transposes, where needed) with their normalisation."""
         blk = self.blk
+        with self._stage("csr_weighted_dinv"):
+            B.csr_dinv(blk.rowptr1, self.dinv_s[0])
+        if self.series:
+            for table, store, lists in ((self.table, self.s, blk.deltas), (self.table_t, self.st, self.t_deltas)):
+                if table is not None and blk.T > 1:
+                    table.lists(lists)
+                    with self._stage("smooth_series"):
+                        B.smooth_series(blk.n, store[0][0], store[0][1], blk.nnz[0], blk.T - 1, table.at(), self.life, self.diag_value,
+                                        self.cap_s, self.status[2:], self.ws_smooth, stream)
+            return
         self.raw.load_first(blk.rowptr1, blk.colidx1)
-        if self.directed:
+        if self.raw_t is not None:
             self.raw_t.load_first(*self.t_first)
-        for t in range(1, blk.T + 1):
-            if t == 1:                                  # S_1 = A_1, every entry counted once
-                for store, (rp1, ci1) in ((self.s, (blk.rowptr1, blk.colidx1)),) + (((self.st, self.t_first),) if self.directed else ()):
-                    store[0][0].copy_(rp1)
-                    store[0][1][: blk.nnz[0]].copy_(ci1)
-                    store[0][2][: blk.nnz[0]].fill_(1.0)
-                self.s_nnz[0] = blk.nnz[0]
-            else:
-                self._advance(self.raw, blk.deltas[t - 2], t)
-                self._smooth(self.raw, self.s, t)
-                if self.directed:
-                    self._advance(self.raw_t, self.t_deltas[t - 2], t)
-                    self._smooth(self.raw_t, self.st, t)
-                self.s_nnz[t - 1] = self.cap_s           # an upper bound: the kernels read the count from the last row pointer
-            rp, ci, val = self.s[t - 1]
-            nnz = self.s_nnz[t - 1]
+        for t in range(2, blk.T + 1):
+            self._advance(self.raw, blk.deltas[t - 2], t)
+            self._smooth(self.raw, self.s, t)
+            if self.raw_t is not None:
+                self._advance(self.raw_t, self.t_deltas[t - 2], t)
+                self._smooth(self.raw_t, self.st, t)
+            rp, _, val = self.s[t - 1]
             with self._stage("csr_weighted_dinv"):
-                B.csr_weighted_dinv(rp, val, nnz, self.dinv_s[t - 1], self.ws_dinv)
-            cur = blk.x[t - 1]
-            for layer in range(blk.layers):
-                with self._stage("feature_transform"):
-                    B.feature_transform(cur, blk.weight(t, layer), self.h, row_scale=self.dinv_s[t - 1])
-                with self._stage("spmm_weighted"):
-                    B.spmm_weighted(rp, ci, val, nnz, self.h, self.z[layer, t - 1], self.ws_spmm,
-                                    flags=B.DGNN_RELU | B.DGNN_H_PRESCALED, dinv=self.dinv_s[t - 1])
-                cur = self.z[layer, t - 1]
+                B.csr_weighted_dinv(rp, val, self.s_nnz[t - 1], self.dinv_s[t - 1], self.ws_dinv)
+
+    def forward(self) -> torch.Tensor:
+        blk, stack = self.blk, self.stack
+        stream = torch.cuda.current_stream(self.dev).cuda_stream
+        self._snapshots(stream)
+        stack.bind(blk, self.s_nnz)
+        for t in range(0, blk.T, stack.together):
+            stack.forward(t, min(stack.together, blk.T - t), stream)
         top = self.z[blk.layers - 1]
         if blk.window:
             with self._stage("mproduct"):
@@ -636,8 +654,9 @@ class SmoothedTrainer:
 
     def backward(self, g_y: torch.Tensor) -> None:
         """g_y [T, n, f] = dL/dY.  Must follow forward()."""
-        blk = self.blk
-        L, T = blk.layers, blk.T
+        blk, stack = self.blk, self.stack
+        T = blk.T
+        stream = torch.cuda.current_stream(self.dev).cuda_stream
         if blk.window:
             if self.g is None:
                 self.g = torch.empty_like(g_y)
@@ -646,24 +665,8 @@ class SmoothedTrainer:
             g_top = self.g
         else:
             g_top = g_y
-        first_call = [True] * L
-        for t in range(T, 0, -1):
-            rp, ci, val = self.st[t - 1]                 # S_t^T (S_t itself for an undirected workload)
-            nnz, dinv = self.s_nnz[t - 1], self.dinv_s[t - 1]
-            g_in = g_top[t - 1]
-            for layer in range(L - 1, -1, -1):
-                with self._stage("relu_backward"):
-                    B.relu_backward(g_in, self.z[layer, t - 1], self.gp, row_scale=dinv)
-                with self._stage("spmm_weighted_transposed"):
-                    B.spmm_weighted(rp, ci, val, nnz, self.gp, self.h, self.ws_spmm, flags=B.DGNN_H_PRESCALED, dinv=dinv)
-                below = blk.x[t - 1] if layer == 0 else self.z[layer - 1, t - 1]
-                with self._stage("weight_grad"):
-                    if self.dw_t is not None:
-                        B.weight_grad(below, self.h, self.dw_t[t - 1][layer], self.ws_wgrad)
-                    else:
-                        B.weight_grad(below, self.h, self.dw[layer], self.ws_wgrad, accumulate=not first_call[layer])
-                first_call[layer] = False
-                if layer > 0:
-                    with self._stage("input_grad"):
-                        B.input_grad(self.h, blk.weight(t, layer), self.g_mid)
-                    g_in = self.g_mid
+        m = stack.steps_back(self.dw_t, T)
+        last = (T - 1) // m * m
+        for t in range(last, -1, -m):
+            k = min(m, T - t)
+            stack.backward(blk, t, k, g_top[t:t + k], self.dinv_s[t:t + k], self.dw, self.dw_t, t != last, stream)

@@ -10,7 +10,7 @@ import paper_2109_07893_amd as dg
 from dtdg_synth import WORKLOADS, DynamicGraph
 from dtdg_synth.blocks import make_block
 from paper_2109_07893_amd import binding as B
-from paper_2109_07893_amd.batch import SeriesTable, SpmmTable, TransformTable, pointers
+from paper_2109_07893_amd.batch import SeriesTable, SmoothTable, SpmmTable, TransformTable, pointers
 from paper_2109_07893_amd.pipeline import BlockRunner
 
 pytestmark = pytest.mark.gpu
@@ -48,6 +48,76 @@ def test_series_equals_step_by_step(kind, n, deg, T, dels, adds):
         assert torch.equal(rp2, got[0][k]) and torch.equal(ci2[: nnz[k + 1]], got[1][k][: nnz[k + 1]]), k
         assert bool((got[1][k][nnz[k + 1]:] == -7).all()) and torch.equal(dinv2, got[2][k]), k
         rp, ci = rp2, ci2
+
+
+def toggled_series(n, places, T, dels, adds, seed):
+    """A_1 (the diagonal and half of `places`, off-diagonal keys row * n + column) and difference lists that take entries out
+    and put them back: of the absent places `adds` per step, of the present ones `dels`."""
+    rng = np.random.default_rng(seed)
+    present = rng.random(places.size) < 0.5 if adds < 1 else np.zeros(places.size, bool)
+    def split(keys):
+        keys = np.sort(keys)
+        return [torch.from_numpy((k).astype(np.int32)).to(DEV) for k in (keys // n, keys % n)]
+    first = np.sort(np.concatenate([np.arange(n, dtype=np.int64) * (n + 1), places[present]]))
+    rp = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(first // n, minlength=n), out=rp[1:])
+    steps = []
+    for _ in range(T - 1):
+        flip = rng.random(places.size) < np.where(present, dels, adds if adds < 1 else adds / places.size)
+        steps.append(tuple(split(places[flip & ~present])) + tuple(split(places[flip & present])))
+        present = present ^ flip
+    return torch.from_numpy(rp).to(DEV), torch.from_numpy((first % n).astype(np.int32)).to(DEV), steps
+
+
+# entries that come back while they are remembered; stretches of 1536 entries; a gap between two entries of A_1 into which more
+# than the LDS holds, or more than 512 per step, is added, so that the keys have to be halved; the longest window and series
+@pytest.mark.parametrize("n,rows,T,life,dels,adds,diag", [
+    (1, 1, 3, 2, 0.0, 0.0, 1.0), (40, 40, 8, 3, 0.3, 0.3, 1.0), (40, 40, 33, 32, 0.2, 0.1, 1.0), (130, 130, 9, 1, 0.1, 0.1, 1.0),
+    (300, 300, 6, 4, 0.02, 0.02, 0.0), (1537, 1, 5, 2, 0.1, 0.0, 0.5), (9000, 1, 6, 3, 0.1, 400, 1.0), (9000, 2, 5, 4, 0.3, 4000, 1.0),
+    (5000, 3, 3, 2, 0.0, 900, 2.0), (2000, 70, 5, 5, 0.05, 0.05, 1.0)])
+def test_smoothed_series_equals_step_by_step(n, rows, T, life, dels, adds, diag):
+    where = np.arange(rows, dtype=np.int64) * max(1, n // rows)
+    places = (where[:, None] * n + np.arange(n, dtype=np.int64)[None, :]).reshape(-1)
+    places = places[places % (n + 1) != 0]
+    rp, ci, steps = toggled_series(n, places, T, dels, adds, seed=n + T)
+    nnz = [int(ci.numel())]
+    for d in steps:
+        nnz.append(nnz[-1] + d[0].numel() - d[2].numel())
+    cap = max(nnz) + life * max(d[2].numel() for d in steps)
+    def room():
+        return torch.full((n + 1,), -7, dtype=torch.int32, device=DEV), torch.full((cap,), -7, dtype=torch.int32, device=DEV), torch.zeros(cap, device=DEV)
+    got, dinv = [room() for _ in steps], torch.zeros(T - 1, n, device=DEV)
+    status = torch.full((T - 1,), -1, dtype=torch.int32, device=DEV)
+    table = SmoothTable(got, list(dinv))
+    table.lists(steps)
+    ws = torch.empty(B.smooth_series_workspace(nnz[0], T - 1), dtype=torch.uint8, device=DEV)
+    B.smooth_series(n, rp, ci, nnz[0], T - 1, table.at(), life, diag, cap, status, ws, torch.cuda.current_stream().cuda_stream)
+    assert int(status.abs().sum()) == 0
+    longest = max(max(d[0].numel(), d[2].numel()) for d in steps) + 1
+    ws = torch.empty(dg.delta_rebuild_workspace(n, max(nnz), longest, longest), dtype=torch.uint8, device=DEV)
+    ws_c = torch.empty(dg.csr_combine_workspace(cap), dtype=torch.uint8, device=DEV)
+    ws_d = torch.empty(dg.csr_weighted_dinv_workspace(cap), dtype=torch.uint8, device=DEV)
+    raw, s = [(rp, ci, nnz[0])], (rp, ci, None, nnz[0])
+    for k, (ar, ac, dr, dc) in enumerate(steps):
+        rp2, ci2 = torch.empty_like(rp), torch.empty(max(nnz), dtype=torch.int32, device=DEV)
+        dg.delta_rebuild(raw[-1][0], raw[-1][1], nnz[k], ar, ac, ar.numel(), dr, dc, dr.numel(), rp2, ci2, None, ws)
+        raw.append((rp2, ci2, nnz[k + 1]))
+        out, d = room(), torch.empty(n, device=DEV)
+        dg.csr_combine(s, raw[-1], 1.0, raw[k + 1 - life] if k + 1 >= life else None, -1.0, out, ws_c, diag_value=diag)
+        dg.csr_weighted_dinv(out[0], out[2], cap, d, ws_d)
+        m = int(out[0][n])
+        for a, b in zip(got[k], out):
+            assert torch.equal(a[: n + 1 if a is got[k][0] else m], b[: n + 1 if a is got[k][0] else m]), k
+        assert bool((got[k][1][m:] == -7).all()) and torch.equal(dinv[k], d), k
+        s = out + (cap,)
+    # arrays that are too small: said so, and nothing written behind them
+    small = [(r, c[:max(1, int(r[n]) // 2)], v[:max(1, int(r[n]) // 2)]) for r, c, v in got]
+    keep = [c[max(1, int(r[n]) // 2):].clone() for r, c, v in got]
+    room_left = min(int(c.numel()) for _, c, _ in small)
+    ws = torch.empty(B.smooth_series_workspace(nnz[0], T - 1), dtype=torch.uint8, device=DEV)
+    B.smooth_series(n, rp, ci, nnz[0], T - 1, table.at(), life, diag, room_left, status, ws, torch.cuda.current_stream().cuda_stream)
+    assert all(bool(x) == (int(r[n]) > room_left) for x, (r, _, _) in zip(status, got))
+    assert all(torch.equal(c[max(1, int(r[n]) // 2):], k) for (r, c, v), k in zip(got, keep))
 
 
 @pytest.mark.parametrize("dtype,f", [(torch.float32, 16), (torch.float32, 64), (torch.bfloat16, 32), (torch.bfloat16, 128)])
