@@ -202,7 +202,7 @@ int dgnn_mproduct(const void *z, void *y, int64_t T, int64_t n, int32_t f, int32
  */
 
 /* The most steps dgnn_delta_rebuild_series takes per launch; longer series are cut into launches of that many. */
-#define DGNN_SERIES_STEPS 32
+#define DGNN_SERIES_STEPS 31
 
 /* One step of a series: its difference lists (as in dgnn_delta_rebuild) and the arrays its snapshot goes to (dinv may be NULL). */
 typedef struct {
@@ -214,12 +214,14 @@ typedef struct {
 
 /*
  * A_2 .. A_{steps+1} from A_1 and the difference lists of the steps (Section "Graph-difference Based Input Transfer"): what
- * `steps` calls of dgnn_delta_rebuild give, bit for bit, in two launches per DGNN_SERIES_STEPS steps.  Every snapshot needs
+ * `steps` calls of dgnn_delta_rebuild give, bit for bit, in one or two launches per DGNN_SERIES_STEPS steps.  Every snapshot needs
  * rowptr and colidx arrays of its own (each colidx of `cap` entries, at least the stored entries of the densest snapshot),
- * different from A_1's; lists and preconditions as in dgnn_delta_rebuild, without its validation.  No workspace.
+ * different from A_1's; lists and preconditions as in dgnn_delta_rebuild, without its validation.
+ *   ws: scratch of dgnn_delta_rebuild_series_workspace() bytes for these lists (it looks at the tables' counts only).
  */
+int dgnn_delta_rebuild_series_workspace(int64_t nnz_first, int32_t steps, const dgnn_series_step *step, size_t *bytes);
 int dgnn_delta_rebuild_series(int64_t n, const int32_t *rowptr_first, const int32_t *colidx_first, int64_t nnz_first,
-                              int32_t steps, const dgnn_series_step *step, int64_t cap, void *stream);
+                              int32_t steps, const dgnn_series_step *step, int64_t cap, void *ws, size_t ws_bytes, void *stream);
 
 /* One step of dgnn_smooth_series: its difference lists and where S_t goes (dinv may be NULL). */
 typedef struct {
@@ -237,9 +239,10 @@ typedef struct {
  *   arrays different from each other and from A_1's.  step[k].dinv is that of S with every snapshot holding its diagonal.
  *   d_status [steps] or NULL: 0, or DGNN_BAD_CAPACITY where S_t does not fit (rowptr[n] then holds the size needed, and what
  *   lies beyond the capacity is not written).  Lists and preconditions as in dgnn_delta_rebuild, without its validation.
+ *   ws: scratch of dgnn_smooth_series_workspace() bytes; added: entries of all added lists together.
  * Enqueue-only.  Errors: NULL, SHAPE, OVERFLOW, CAPACITY (workspace), ALIAS, ALIGN, HIP.
  */
-int dgnn_smooth_series_workspace(int64_t nnz_first, int32_t steps, size_t *bytes);
+int dgnn_smooth_series_workspace(int64_t nnz_first, int64_t added, int32_t steps, size_t *bytes);
 int dgnn_smooth_series(int64_t n, const int32_t *rowptr_first, const int32_t *colidx_first, int64_t nnz_first, int32_t steps,
                        const dgnn_smooth_step *step, int32_t life, float diag_value, int64_t capacity, int32_t *d_status,
                        void *ws, size_t ws_bytes, void *stream);

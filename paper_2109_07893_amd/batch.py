@@ -17,10 +17,10 @@ from . import binding as B
 # still in the cache when it is gathered.
 BATCH_BYTES = 64 << 20
 
-# Stored entries up to which a block's snapshots are rebuilt as a series.  A workgroup of the series kernel walks its stretch
-# through all steps, 2.3 us a step, where one rebuild after the other pays two launches, 13 us a step; with more entries
-# the step-by-step merge, whose wavefronts stream, is the faster one (per step, series / step by step: 11 thousand entries
-# 4.5 / 12.7 us, 1.7 M 8.0 / 14.7 us, 17 M 65 / 53 us).
+# Stored entries up to which a block's snapshots are rebuilt as a series.  Its set-up takes 9 us per million entries, which
+# the launches it saves, 13 us a step, make up for; per further step it is as fast as the step-by-step merge (per step, series /
+# step by step: 11 thousand entries, 7 steps 2.0 / 13.8 us; 1.7 M, 15 steps 5.3 / 15.6 us; 17 M, 15 steps 48 / 54 us, 3 steps
+# 85 / 62 us), and it keeps every snapshot in an array of its own.
 SERIES_ENTRIES = 1 << 22
 
 # Vertices up to which the aggregation of X gathers dinv with the rows instead of finding them scaled by a pass of their own.
@@ -95,6 +95,21 @@ class SeriesTable(StepsTable):
         for k, tensors in ((6, rowptr), (7, colidx), (8, dinv)):
             if tensors:
                 self.column(k, pointers(tensors))
+        self.ws = None
+
+    def prepare(self, lists, nnz: int, dev) -> None:
+        """The difference lists of the coming calls, behind a first snapshot of nnz entries."""
+        if not self.seen.same(lists) or self.ws is None:
+            self.seen.ids = None
+            self.lists(lists)
+            size = B.delta_rebuild_series_workspace(nnz, len(lists), self.at())
+            if self.ws is None or self.ws.numel() < size:
+                self.ws = torch.empty(size, dtype=torch.uint8, device=dev)
+
+    def rebuild(self, n: int, rowptr, colidx, nnz: int, lists, cap: int, stream) -> None:
+        """All snapshots behind (rowptr, colidx) with its nnz entries."""
+        self.prepare(lists, nnz, rowptr.device)
+        B.delta_rebuild_series(n, rowptr, colidx, nnz, len(lists), self.at(), cap, self.ws, stream)
 
 
 class SmoothTable(StepsTable):

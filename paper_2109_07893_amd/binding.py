@@ -19,7 +19,7 @@ _LIB_PATH = os.path.join(_CSRC, "libdgnn.so")
 DGNN_F32, DGNN_BF16 = 0, 1
 DGNN_VALIDATE = 1
 DGNN_UPDATES_SORTED = 2
-DGNN_SERIES_STEPS = 32
+DGNN_SERIES_STEPS = 31
 DGNN_RELU = 1
 DGNN_H_PRESCALED = 2
 DGNN_W_TRANSPOSED = 4
@@ -30,7 +30,7 @@ EXPORTS = (
     "dgnn_spmm_static", "dgnn_mproduct",
     "dgnn_delta_rebuild_weighted", "dgnn_spmm_weighted", "dgnn_csr_combine_workspace", "dgnn_csr_combine", "dgnn_csr_weighted_dinv_workspace", "dgnn_csr_weighted_dinv", "dgnn_concat_relu", "dgnn_transform_concat_relu", "dgnn_lstm_cell", "dgnn_lstm_step", "dgnn_lstm_cell_backward", "dgnn_lstm_step_backward", "dgnn_concat_relu_backward", "dgnn_bias_grad_workspace", "dgnn_bias_grad", "dgnn_add",
     "dgnn_csr_transpose_workspace", "dgnn_csr_transpose", "dgnn_coo_transpose_workspace", "dgnn_coo_transpose",
-    "dgnn_delta_rebuild_series", "dgnn_smooth_series_workspace", "dgnn_smooth_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
+    "dgnn_delta_rebuild_series_workspace", "dgnn_delta_rebuild_series", "dgnn_smooth_series_workspace", "dgnn_smooth_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
     "dgnn_lstm_series", "dgnn_lstm_series_backward", "dgnn_lstm_weight_grad_workspace", "dgnn_lstm_weight_grad",
     "dgnn_evolve_weights", "dgnn_evolve_weights_backward_workspace", "dgnn_evolve_weights_backward",
     "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
@@ -106,8 +106,9 @@ def load_library():
     lib.dgnn_spmm.argtypes = [_i64, _i64, _vp, _vp, _vp, _vp, _i32, _vp, ctypes.c_int, _u32, _vp, _sz, _vp]
     lib.dgnn_spmm_static_limit.argtypes = [ctypes.POINTER(_sz)]
     lib.dgnn_spmm_static.argtypes = [_i64, _i64, _vp, _vp, _vp, _vp, _i32, _vp, ctypes.c_int, _u32, _vp]
-    lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp]
-    lib.dgnn_smooth_series_workspace.argtypes = [_i64, _i32, ctypes.POINTER(_sz)]
+    lib.dgnn_delta_rebuild_series_workspace.argtypes = [_i64, _i32, _vp, ctypes.POINTER(_sz)]
+    lib.dgnn_delta_rebuild_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i64, _vp, _sz, _vp]
+    lib.dgnn_smooth_series_workspace.argtypes = [_i64, _i64, _i32, ctypes.POINTER(_sz)]
     lib.dgnn_smooth_series.argtypes = [_i64, _vp, _vp, _i64, _i32, _vp, _i32, ctypes.c_float, _i64, _vp, _vp, _sz, _vp]
     lib.dgnn_feature_transform_batch.argtypes = [_i32, _vp, _i64, _i32, _i32, _u32, ctypes.c_int, _vp]
     lib.dgnn_spmm_batch_workspace.argtypes = [_i32, _i64, _i32, ctypes.POINTER(_sz)]
@@ -303,15 +304,21 @@ def mproduct(z: torch.Tensor, y: torch.Tensor, w: int, m_band: Optional[torch.Te
 
 
 # ---- several timesteps per call: tables of structs (batch.py) instead of tensors, checked by their owner -------------------
-def delta_rebuild_series(n: int, rowptr_first: torch.Tensor, colidx_first: torch.Tensor, nnz_first: int, steps: int, table: int, cap: int,
-                         stream) -> None:
-    _check(load_library().dgnn_delta_rebuild_series(n, _ptr(rowptr_first), _ptr(colidx_first), nnz_first, steps, table, cap, stream),
-           "dgnn_delta_rebuild_series")
-
-
-def smooth_series_workspace(nnz_first: int, steps: int) -> int:
+def delta_rebuild_series_workspace(nnz_first: int, steps: int, table: int) -> int:
     out = _sz(0)
-    _check(load_library().dgnn_smooth_series_workspace(nnz_first, steps, ctypes.byref(out)), "dgnn_smooth_series_workspace")
+    _check(load_library().dgnn_delta_rebuild_series_workspace(nnz_first, steps, table, ctypes.byref(out)), "dgnn_delta_rebuild_series_workspace")
+    return int(out.value)
+
+
+def delta_rebuild_series(n: int, rowptr_first: torch.Tensor, colidx_first: torch.Tensor, nnz_first: int, steps: int, table: int, cap: int,
+                         ws: torch.Tensor, stream) -> None:
+    _check(load_library().dgnn_delta_rebuild_series(n, _ptr(rowptr_first), _ptr(colidx_first), nnz_first, steps, table, cap, _ptr(ws),
+                                                    ws.numel() * ws.element_size(), stream), "dgnn_delta_rebuild_series")
+
+
+def smooth_series_workspace(nnz_first: int, added: int, steps: int) -> int:
+    out = _sz(0)
+    _check(load_library().dgnn_smooth_series_workspace(nnz_first, added, steps, ctypes.byref(out)), "dgnn_smooth_series_workspace")
     return int(out.value)
 
 

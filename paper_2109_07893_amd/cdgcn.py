@@ -80,11 +80,9 @@ class CdgcnLayer(BlockRunner):
     def rebuild_all(self) -> None:
         """Every snapshot of the block (where the block is small enough to be rebuilt in one go)."""
         blk, one = self.blk, self.slot_of(1)
-        table = self._tables.series
-        table.lists(blk.deltas)
         with self._stage("delta_rebuild"):
-            B.delta_rebuild_series(blk.n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.T - 1, table.at(), self.cap,
-                                   torch.cuda.current_stream(self.dev).cuda_stream)
+            self._tables.series.rebuild(blk.n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.deltas[:blk.T - 1], self.cap,
+                                        torch.cuda.current_stream(self.dev).cuda_stream)
 
     def _bind(self) -> None:
         scaled, b = self._aggregations

@@ -253,7 +253,7 @@ class BlockRunner:
             b.column(b.NNZ, blk.nnz)
             tb.transform.append(a)
             tb.spmm.append(b)
-        tb.series.lists(blk.deltas)
+        tb.series.prepare(blk.deltas[:T - 1], blk.nnz[0], dev)
         tb.ws = torch.empty(B.spmm_batch_workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
         return tb
 
@@ -265,8 +265,7 @@ class BlockRunner:
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         dt = B._dtype_code(self.h)
         one = self.slot_of(1)
-        tb.series.lists(blk.deltas)
-        B.delta_rebuild_series(n, self.rowptr[one], self.colidx[one], blk.nnz[0], T - 1, tb.series.at(), self.cap, stream)
+        tb.series.rebuild(n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.deltas[:T - 1], self.cap, stream)
         a0 = tb.transform[0]
         a0.column(a0.X, tb.x.addresses(blk.x[:T]))
         for layer in range(blk.layers):

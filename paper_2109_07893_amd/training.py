@@ -258,7 +258,7 @@ class BlockTrainer:
         self.stack = GcnStack(blk, cap, *arrays, transposed=back, want_dx=want_dx, stage=self._stage, together=None if self.series else 1)
         self.z, self.dx = self.stack.z, self.stack.dx                     # activations of the block
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
-        self.g = None                                                     # dL/dZ of the last layer, if g_y must be kept
+        self.g = self.g_top = None                                        # dL/dZ of the last layer, if g_y must be kept; wherever it is
         self.dw = [torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)]
         # with one weight per timestep (Section "EvolveGCN") every timestep has a gradient of its own
         self.dw_t = ([[torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)] for _ in range(T)]
@@ -271,7 +271,7 @@ class BlockTrainer:
                 return SeriesTable(chain.rowptr[1:] + chain.rowptr[:1], chain.colidx[1:] + chain.colidx[:1], chain.dinv[1:] + chain.dinv[:1])
             self.tables = [(self.a, table(self.a))] + ([(self.at, table(self.at))] if self.at is not None else [])
             for (_, tb), (_, lists, _) in zip(self.tables, self._chains()):
-                tb.lists(lists)
+                tb.prepare(lists, blk.nnz[0], dev)
 
     def rebind(self, blk: BlockInputs, t0: int = 0, z_before: Optional[torch.Tensor] = None,
                transposed_first=None, transposed_deltas=None) -> None:
@@ -318,10 +318,9 @@ class BlockTrainer:
                     table.column(6, extra[1].data_ptr(), steps)
                     table.column(7, extra[2].data_ptr(), steps)
                     table.column(8, 0, steps)
-                table.lists(lists)
                 if lists:
                     with self._stage("delta_rebuild"):
-                        B.delta_rebuild_series(blk.n, chain.rowptr[0], chain.colidx[0], blk.nnz[0], len(lists), table.at(), self.cap, stream)
+                        table.rebuild(blk.n, chain.rowptr[0], chain.colidx[0], blk.nnz[0], lists, self.cap, stream)
         stack.bind(blk, blk.nnz)
         m = stack.together
         for t in range(0, blk.T, m):
@@ -363,6 +362,7 @@ class BlockTrainer:
                 B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
         else:
             g_top = g_y
+        self.g_top = g_top
         m = stack.steps_back(self.dw_t, T)
         last = (T - 1) // m * m
         for t in range(last, -1, -m):
@@ -373,6 +373,24 @@ class BlockTrainer:
             if stack.needs_transposed and t >= 2 and not self.keep_snapshots:   # A_{t-1} from A_t: the lists exchanged (A_1 was kept)
                 for chain, lists, _ in self._chains():
                     self._rebuild(chain, lists[t - 1], blk.nnz[t], t + 1, t, reverse=True)
+
+
+    @property
+    def h(self) -> torch.Tensor:
+        """The first layer's G_H = A~_1^T G_P of the block's first timestep, the last one that backward() takes.  Where the step
+        aggregates this gradient itself it is still in the buffer; where it does not (see above) this inspection does."""
+        if self.stack.p0 is None:
+            return self.stack.h[0]
+        blk, slot = self.blk, self.a.slot_of(1)
+        assert self.g_top is not None and blk.layers == 1, "after backward() of a one-layer block"
+        rowptr, colidx, dinv = self.a.rowptr[slot], self.a.colidx[slot], self.a.dinv[slot]
+        if self.directed:
+            rowptr, colidx = B.csr_transpose(rowptr, colidx, blk.nnz[0])
+        g_p, g_h = torch.empty_like(self.g_top[0]), torch.empty_like(self.g_top[0])
+        B.relu_backward(self.g_top[0], self.z[0, 0], g_p, row_scale=dinv)
+        ws = torch.empty(B.spmm_workspace(blk.n, blk.nnz[0], blk.f), dtype=torch.uint8, device=self.dev)
+        B.spmm(rowptr, colidx, blk.nnz[0], dinv, g_p, g_h, ws, flags=B.DGNN_H_PRESCALED)
+        return g_h
 
 
 def needs_transposed(blk: BlockInputs, want_dx: bool = False) -> bool:
@@ -585,7 +603,7 @@ class SmoothedTrainer:
         if self.series:
             self.table = SmoothTable(self.s[1:], list(self.dinv_s[1:]))
             self.table_t = SmoothTable(self.st[1:], None) if transposed else None
-            self.ws_smooth = torch.empty(B.smooth_series_workspace(blk.nnz[0], T - 1), dtype=torch.uint8, device=dev)
+            self.ws_smooth = torch.empty(B.smooth_series_workspace(blk.nnz[0], sum(int(d[0].numel()) for d in blk.deltas), T - 1), dtype=torch.uint8, device=dev)
         else:
             self.raw = _Ring(n, cap, dev, life + 1, with_dinv=False)
             self.raw_t = _Ring(n, cap, dev, life + 1, with_dinv=False) if transposed else None

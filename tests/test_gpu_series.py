@@ -22,11 +22,11 @@ def graph(kind, n, deg, T, dels, adds, seed=11):
                    del_frac=dels, add_frac=adds, seed=seed)
 
 
-# stretches of 1536 entries that grow by a third before they leave the LDS, groups of four steps, launches of 32 steps
+# stretches of up to 1536 entries and what all steps add to them, launches of 31 steps
 @pytest.mark.parametrize("kind,n,deg,T,dels,adds", [
     ("er", 7, 3, 5, 0.2, 0.2), ("er", 257, 4, 40, 0.1, 0.1), ("er", 1536, 1, 3, 0.0, 0.5), ("rmat", 1024, 20, 12, 0.05, 0.05),
     ("er", 300, 8, 6, 0.0, 0.5), ("er", 2000, 6, 10, 0.05, 0.4), ("er", 5000, 30, 5, 0.5, 0.9), ("er", 4001, 10, 5, 0.6, 0.0),
-    ("rmat", 1 << 14, 16, 34, 0.03, 0.03)])
+    ("rmat", 1 << 14, 16, 34, 0.03, 0.03), ("er", 30_000, 40, 3, 0.02, 0.02), ("rmat", 1 << 15, 40, 33, 0.01, 0.05)])
 def test_series_equals_step_by_step(kind, n, deg, T, dels, adds):
     g = DynamicGraph(graph(kind, n, deg, T, dels, adds), device=DEV)
     rp, ci = g.csr()
@@ -38,8 +38,7 @@ def test_series_equals_step_by_step(kind, n, deg, T, dels, adds):
     got = ([torch.full((n + 1,), -7, dtype=torch.int32, device=DEV) for _ in steps],
            [torch.full((cap,), -7, dtype=torch.int32, device=DEV) for _ in steps], [torch.zeros(n, device=DEV) for _ in steps])
     table = SeriesTable(*got)
-    table.lists(steps)
-    B.delta_rebuild_series(n, rp, ci, nnz[0], len(steps), table.at(), cap, torch.cuda.current_stream().cuda_stream)
+    table.rebuild(n, rp, ci, nnz[0], steps, cap, torch.cuda.current_stream().cuda_stream)
     longest = max(max(d[0].numel(), d[2].numel()) for d in steps) + 1
     ws = torch.empty(dg.delta_rebuild_workspace(n, cap, longest, longest), dtype=torch.uint8, device=DEV)
     for k, (ar, ac, dr, dc) in enumerate(steps):
@@ -70,9 +69,9 @@ def toggled_series(n, places, T, dels, adds, seed):
 
 
 # entries that come back while they are remembered; stretches of 1536 entries; a gap between two entries of A_1 into which more
-# than the LDS holds, or more than 512 per step, is added, so that the keys have to be halved; the longest window and series
+# than the LDS holds is added, so that the keys have to be halved; the longest window and series
 @pytest.mark.parametrize("n,rows,T,life,dels,adds,diag", [
-    (1, 1, 3, 2, 0.0, 0.0, 1.0), (40, 40, 8, 3, 0.3, 0.3, 1.0), (40, 40, 33, 32, 0.2, 0.1, 1.0), (130, 130, 9, 1, 0.1, 0.1, 1.0),
+    (1, 1, 3, 2, 0.0, 0.0, 1.0), (40, 40, 8, 3, 0.3, 0.3, 1.0), (40, 40, 32, 32, 0.2, 0.1, 1.0), (130, 130, 9, 1, 0.1, 0.1, 1.0),
     (300, 300, 6, 4, 0.02, 0.02, 0.0), (1537, 1, 5, 2, 0.1, 0.0, 0.5), (9000, 1, 6, 3, 0.1, 400, 1.0), (9000, 2, 5, 4, 0.3, 4000, 1.0),
     (5000, 3, 3, 2, 0.0, 900, 2.0), (2000, 70, 5, 5, 0.05, 0.05, 1.0)])
 def test_smoothed_series_equals_step_by_step(n, rows, T, life, dels, adds, diag):
@@ -90,7 +89,7 @@ def test_smoothed_series_equals_step_by_step(n, rows, T, life, dels, adds, diag)
     status = torch.full((T - 1,), -1, dtype=torch.int32, device=DEV)
     table = SmoothTable(got, list(dinv))
     table.lists(steps)
-    ws = torch.empty(B.smooth_series_workspace(nnz[0], T - 1), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(B.smooth_series_workspace(nnz[0], sum(d[0].numel() for d in steps), T - 1), dtype=torch.uint8, device=DEV)
     B.smooth_series(n, rp, ci, nnz[0], T - 1, table.at(), life, diag, cap, status, ws, torch.cuda.current_stream().cuda_stream)
     assert int(status.abs().sum()) == 0
     longest = max(max(d[0].numel(), d[2].numel()) for d in steps) + 1
@@ -114,7 +113,7 @@ def test_smoothed_series_equals_step_by_step(n, rows, T, life, dels, adds, diag)
     small = [(r, c[:max(1, int(r[n]) // 2)], v[:max(1, int(r[n]) // 2)]) for r, c, v in got]
     keep = [c[max(1, int(r[n]) // 2):].clone() for r, c, v in got]
     room_left = min(int(c.numel()) for _, c, _ in small)
-    ws = torch.empty(B.smooth_series_workspace(nnz[0], T - 1), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(B.smooth_series_workspace(nnz[0], sum(d[0].numel() for d in steps), T - 1), dtype=torch.uint8, device=DEV)
     B.smooth_series(n, rp, ci, nnz[0], T - 1, table.at(), life, diag, room_left, status, ws, torch.cuda.current_stream().cuda_stream)
     assert all(bool(x) == (int(r[n]) > room_left) for x, (r, _, _) in zip(status, got))
     assert all(torch.equal(c[max(1, int(r[n]) // 2):], k) for (r, c, v), k in zip(got, keep))
