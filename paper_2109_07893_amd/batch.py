@@ -38,19 +38,7 @@ def pointers(tensors: Sequence[Optional[torch.Tensor]]) -> List[int]:
     return [0 if t is None else t.data_ptr() for t in tensors]
 
 
-class Seen:
-    """Whether a list of tensors (or tuples of them) holds the objects it held before; the checks of shape, type and layout
-    that a call makes are only repeated when it does not."""
-
-    def __init__(self):
-        self.ids = None
-
-    def same(self, objects) -> bool:
-        ids = [id(o) for o in objects]
-        if ids == self.ids:
-            return True
-        self.ids = ids
-        return False
+_numel, _data_ptr, _is_contiguous = torch.Tensor.numel, torch.Tensor.data_ptr, torch.Tensor.is_contiguous
 
 
 class Table:
@@ -59,6 +47,7 @@ class Table:
     def __init__(self, rows: int, words: int):
         self.words = np.zeros((max(rows, 1), words), dtype=np.int64)
         self.base, self.stride = self.words.ctypes.data, words * 8
+        self.bound = {}
 
     def at(self, row: int = 0) -> int:
         return self.base + row * self.stride
@@ -67,24 +56,42 @@ class Table:
         self.words[rows, k] = values
 
 
+    def refresh(self, k: int, values: List[int], rows: int) -> None:
+        """The first `rows` entries of a column that is bound anew for every pass; written where the values differ."""
+        if self.bound.get(k) != values:
+            self.words[:rows, k] = values
+            self.bound[k] = list(values)
+
+
 class StepsTable(Table):
     """What the two series calls have in common: the difference lists of a step, add_row, add_col, del_row, del_col, n_add,
     n_del, before the arrays it leads to."""
 
-    def __init__(self, rows: int, words: int):
-        super().__init__(rows, words)
-        self.seen, self.kept = Seen(), None
+    entered = None                                   # the rows as they stand
 
-    def lists(self, deltas) -> None:
-        """The difference lists of the steps, (add_row, add_col, del_row, del_col) each."""
-        if self.seen.same(deltas):
-            return
-        self.kept = list(deltas)                     # the objects compared by identity must stay alive
-        for k, d in enumerate(deltas):
-            for t in d:
+    def lists(self, deltas) -> List[int]:
+        """The difference lists of the steps, (add_row, add_col, del_row, del_col) each, checked and entered anew for every
+        call; returns the counts (n_add, n_del of every step)."""
+        flat = [t for d in deltas for t in d]
+        if not all(map(_is_contiguous, flat)):
+            raise AssertionError("dgnn takes contiguous tensors")
+        for t in flat:
+            if t.dtype is not torch.int32:
                 B._need(t, torch.int32, "difference list")
-                assert t.is_contiguous()
-            self.words[k, :6] = [t.data_ptr() if t.numel() else 0 for t in d] + [d[0].numel(), d[2].numel()]
+        count, at = list(map(_numel, flat)), list(map(_data_ptr, flat))
+        adds, dels = count[0::4], count[2::4]
+        if count[1::4] != adds or count[3::4] != dels:
+            assert all(c >= r for c, r in zip(count[1::4] + count[3::4], adds + dels)), "a difference list has fewer columns than rows"
+        if 0 in count:                               # an empty list has no address
+            at = [p if count[k & ~1] else 0 for k, p in enumerate(at)]
+        rows = [at, adds, dels]
+        if flat and rows != self.entered:
+            steps = len(adds)
+            self.words[:steps, :4] = np.array(at, dtype=np.int64).reshape(steps, 4)
+            self.words[:steps, 4] = adds
+            self.words[:steps, 5] = dels
+            self.entered = rows
+        return [c for pair in zip(adds, dels) for c in pair]
 
 
 class SeriesTable(StepsTable):
@@ -95,20 +102,26 @@ class SeriesTable(StepsTable):
         for k, tensors in ((6, rowptr), (7, colidx), (8, dinv)):
             if tensors:
                 self.column(k, pointers(tensors))
-        self.ws = None
+        self.ws, self.sized_for = None, None
 
-    def prepare(self, lists, nnz: int, dev) -> None:
-        """The difference lists of the coming calls, behind a first snapshot of nnz entries."""
-        if not self.seen.same(lists) or self.ws is None:
-            self.seen.ids = None
-            self.lists(lists)
+    def prepare(self, lists, nnz: int, dev) -> List[int]:
+        """The difference lists of the coming call, behind a first snapshot of nnz entries; returns their counts."""
+        counts = self.lists(lists)
+        if self.sized_for != (nnz, counts):          # what the workspace depends on
             size = B.delta_rebuild_series_workspace(nnz, len(lists), self.at())
             if self.ws is None or self.ws.numel() < size:
                 self.ws = torch.empty(size, dtype=torch.uint8, device=dev)
+            self.sized_for = (nnz, counts)
+        return counts
 
-    def rebuild(self, n: int, rowptr, colidx, nnz: int, lists, cap: int, stream) -> None:
-        """All snapshots behind (rowptr, colidx) with its nnz entries."""
-        self.prepare(lists, nnz, rowptr.device)
+    def rebuild(self, n: int, rowptr, colidx, nnz: int, lists, cap: int, stream, leads_to=()) -> None:
+        """All snapshots behind (rowptr, colidx) with its nnz entries; leads_to: how many entries the caller will take those
+        behind the first steps to have."""
+        counts = self.prepare(lists, nnz, rowptr.device)
+        have = nnz
+        for k, want in enumerate(leads_to):
+            have += counts[2 * k] - counts[2 * k + 1]
+            assert have == want, "difference lists and entry counts disagree"
         B.delta_rebuild_series(n, rowptr, colidx, nnz, len(lists), self.at(), cap, self.ws, stream)
 
 
@@ -149,16 +162,28 @@ class WeightGradTable(Table):
 
 
 class Frames:
-    """Checks of a list of per-timestep tensors, made when the list's objects change, and their addresses."""
+    """Addresses of a list of per-timestep tensors, after the checks that a call on each of them would make."""
 
     def __init__(self, shape, dtype, name: str):
-        self.shape, self.dtype, self.name = tuple(shape), dtype, name
-        self.seen, self.kept = Seen(), None
+        self.shape, self.dtype, self.name = torch.Size(shape), dtype, name
 
     def addresses(self, tensors) -> List[int]:
-        if not self.seen.same(tensors):
-            self.kept = list(tensors)
-            for t in tensors:
-                if tuple(t.shape) != self.shape or t.dtype != self.dtype or not t.is_contiguous():
-                    raise ValueError(f"{self.name}: expected contiguous {self.dtype} tensors of shape {self.shape}")
-        return [t.data_ptr() for t in tensors]
+        shape, dtype = self.shape, self.dtype
+        for t in tensors:
+            if t.shape != shape or t.dtype is not dtype or not t.is_contiguous():
+                raise ValueError(f"{self.name}: expected contiguous {dtype} tensors of shape {tuple(shape)}")
+        return list(map(_data_ptr, tensors))
+
+
+def upstream_frames(g, T: int, n: int, f: int, dtype, window: int = 0) -> torch.Tensor:
+    """The gradients [T, n, f] handed to a backward pass, whose rows go to the kernels by address.  Without a window, which
+    takes them whole in any case, frames of their own (a list, or a tensor that is strided over the timesteps) are brought
+    together."""
+    if not isinstance(g, torch.Tensor):
+        g = torch.stack([g[t] for t in range(T)])
+    if g.dim() != 3 or g.shape[0] < T or g.shape[1] != n or g.shape[2] != f or g.dtype is not dtype or not g.is_cuda:
+        raise ValueError(f"upstream gradients: expected a {dtype} device tensor of shape {(T, n, f)}")
+    if not g.is_contiguous():
+        assert not window and g[0].is_contiguous(), "dgnn takes contiguous tensors"
+        g = g[:T].contiguous()
+    return g

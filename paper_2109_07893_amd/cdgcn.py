@@ -15,7 +15,7 @@ from typing import Optional
 import torch
 
 from . import binding as B
-from .batch import GATHERED_DINV_ROWS, Frames, SpmmTable, TransformTable, pointers
+from .batch import GATHERED_DINV_ROWS, Frames, SpmmTable, TransformTable, pointers, upstream_frames
 from .pipeline import BlockInputs, BlockRunner
 
 # Bytes of gate gradients (N x 4 hidden per timestep) that one call of the adjoint leaves for the weight gradients behind it.
@@ -67,7 +67,6 @@ class CdgcnLayer(BlockRunner):
         b.column(b.COLIDX, pointers([self.colidx[k] for k in order]))
         b.column(b.DINV, dinv)
         b.column(b.Z, pointers(y0))
-        b.column(b.NNZ, blk.nnz)
         self.x_frames = Frames((blk.n, blk.f), blk.x[0].dtype, "x")
         if self.prescale:
             xs = pointers([self.xs[t % self.together] for t in range(blk.T)])
@@ -82,15 +81,16 @@ class CdgcnLayer(BlockRunner):
         blk, one = self.blk, self.slot_of(1)
         with self._stage("delta_rebuild"):
             self._tables.series.rebuild(blk.n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.deltas[:blk.T - 1], self.cap,
-                                        torch.cuda.current_stream(self.dev).cuda_stream)
+                                        torch.cuda.current_stream(self.dev).cuda_stream, blk.nnz[1:blk.T])
 
     def _bind(self) -> None:
         scaled, b = self._aggregations
         x = self.x_frames.addresses(self.blk.x[: self.blk.T])
+        b.refresh(b.NNZ, self.blk.nnz[: self.blk.T], self.blk.T)
         if self.prescale:
-            scaled.column(scaled.X, x)
+            scaled.refresh(scaled.X, x, self.blk.T)
         else:
-            b.column(b.H, x)
+            b.refresh(b.H, x, self.blk.T)
 
     def gcn_steps(self, t: int, k: int, y0: torch.Tensor, y: torch.Tensor) -> None:
         """Y0 (where the tables say; y0 is that place) and Y of timesteps t .. t + k - 1 (0-based), their snapshots resident."""
@@ -131,6 +131,21 @@ class CdgcnLayer(BlockRunner):
             with self._stage("lstm_cell"):
                 B.lstm_cell(self.gx, self.gh, self.bias, c0, c_to, self.h_all[t + j])
             c0 = c_to
+
+    def _gcn_of_one(self, t: int, y0: torch.Tensor, y: torch.Tensor) -> None:
+        """Y0 and Y of timestep t (1-based) recomputed into the first place of the batch buffers."""
+        scaled, b = self._aggregations
+        kept = b.words[t - 1, b.Z]
+        b.words[t - 1, b.Z] = y0.data_ptr()
+        self.gcn_steps(t - 1, 1, y0, y)
+        b.words[t - 1, b.Z] = kept
+
+    def step(self, t: int) -> None:
+        """Timestep t (1-based) alone, its snapshot resident: h_t from h_{t-1}, the state c in place."""
+        self._bind()
+        y0, y = self.y0_batch[:1], self.y_batch[:1]
+        self._gcn_of_one(t, y0, y)
+        self.lstm_steps(t - 1, 1, y, self.c, self.c)
 
     def run(self) -> torch.Tensor:
         """The whole block from the initial state (h, c) = 0; returns h_t for t = 1..T."""
@@ -264,6 +279,7 @@ class CdgcnTrainer(CdgcnLayer):
 
     def backward(self, g_h: torch.Tensor) -> None:
         """g_h [T, n, hidden] = dL/dh_t.  Must follow forward() (A_T resident)."""
+        g_h = upstream_frames(g_h, self.blk.T, self.blk.n, self.hidden, self.h_all.dtype)
         if self.back_fused:
             self._backward_stretches(g_h)
         else:
@@ -343,11 +359,3 @@ class CdgcnTrainer(CdgcnLayer):
                     self._rebuild_transposed(t, t - 1, blk.nnz[t - 1], reverse=True)
             first = False
             self._rebuild_backwards(t)
-
-    def _gcn_of_one(self, t: int, y0: torch.Tensor, y: torch.Tensor) -> None:
-        """Y0 and Y of timestep t (1-based) recomputed into the first place of the batch buffers."""
-        scaled, b = self._aggregations
-        kept = b.words[t - 1, b.Z]
-        b.words[t - 1, b.Z] = y0.data_ptr()
-        self.gcn_steps(t - 1, 1, y0, y)
-        b.words[t - 1, b.Z] = kept

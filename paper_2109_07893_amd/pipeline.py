@@ -130,6 +130,8 @@ class BlockRunner:
     def _series_pays(self) -> bool:
         """Whether a pass over resident lists rebuilds all snapshots first (dgnn_delta_rebuild_series) and then takes the
         GCN steps of several timesteps together."""
+        if any(getattr(type(self), name) is not getattr(BlockRunner, name) for name in ("rebuild", "transform_first", "gcn", "snapshot_ready")):
+            return False                    # a subclass that does something of its own per snapshot is asked for every one
         return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES
 
     def slot_of(self, t: int) -> int:
@@ -234,7 +236,6 @@ class BlockRunner:
         tb.w = [Frames((f, f), dt, "w") for _ in range(L)]
         # frames that nobody keeps (keep_all_z off) still need a place while their neighbours are being formed
         spare = torch.empty((m, n, f), dtype=dt, device=dev) if not self.keep_all_z and T > 1 and m > 1 else self.z
-        z = [self.z[t] if self.keep_all_z else self.z[0] if (m == 1 or t == T - 1) else spare[t % m] for t in range(T)]
         tb.spare = spare
         h = pointers([self.h_batch[t % m] for t in range(T)])
         mid = pointers([self.z_mid_batch[t % m] for t in range(T)]) if L > 1 else None
@@ -249,13 +250,27 @@ class BlockRunner:
             b.column(b.COLIDX, pointers(colidx))
             b.column(b.DINV, pointers(dinv))
             b.column(b.H, h)
-            b.column(b.Z, pointers(z) if layer == L - 1 else mid)
-            b.column(b.NNZ, blk.nnz)
+            if layer < L - 1:
+                b.column(b.Z, mid)
             tb.transform.append(a)
             tb.spmm.append(b)
         tb.series.prepare(blk.deltas[:T - 1], blk.nnz[0], dev)
         tb.ws = torch.empty(B.spmm_batch_workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
         return tb
+
+    def _bind_frames(self, tb) -> None:
+        """Where the frames of this pass go, and the entries of its snapshots: z and nnz may be others than in the last one."""
+        blk, T, m = self.blk, self.blk.T, self.together
+        z = self.z
+        if z.shape != (T if self.keep_all_z else 1, blk.n, blk.f) or z.dtype is not self.h.dtype or not z.is_contiguous():
+            raise ValueError("z: expected a contiguous tensor with a frame per kept timestep")
+        step, at, top = blk.n * blk.f * z.element_size(), z.data_ptr(), tb.spmm[-1]
+        if self.keep_all_z:
+            top.refresh(top.Z, [at + t * step for t in range(T)], T)
+        else:
+            top.refresh(top.Z, [at if (m == 1 or t == T - 1) else tb.spare.data_ptr() + (t % m) * step for t in range(T)], T)
+        for b in tb.spmm:
+            b.refresh(b.NNZ, blk.nnz[:T], T)
 
     def _run_series(self, first: int) -> None:
         """All snapshots, then the GCN steps `together` timesteps at a time; the same kernels on the same operands as one
@@ -265,12 +280,13 @@ class BlockRunner:
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         dt = B._dtype_code(self.h)
         one = self.slot_of(1)
-        tb.series.rebuild(n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.deltas[:T - 1], self.cap, stream)
+        tb.series.rebuild(n, self.rowptr[one], self.colidx[one], blk.nnz[0], blk.deltas[:T - 1], self.cap, stream, blk.nnz[1:T])
         a0 = tb.transform[0]
-        a0.column(a0.X, tb.x.addresses(blk.x[:T]))
+        self._bind_frames(tb)
+        a0.refresh(a0.X, tb.x.addresses(blk.x[:T]), T)
         for layer in range(blk.layers):
             a = tb.transform[layer]
-            a.column(a.W, tb.w[layer].addresses([w[layer] for w in blk.w_t] if blk.w_t is not None else [blk.w[layer]]))
+            a.refresh(a.W, tb.w[layer].addresses([w[layer] for w in blk.w_t] if blk.w_t is not None else [blk.w[layer]]), T)
         for t in range(first - 1, T, m):
             k = min(m, T - t)
             for layer in range(blk.layers):

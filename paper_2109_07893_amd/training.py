@@ -28,7 +28,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together
+from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers, steps_together, upstream_frames
 from .pipeline import BlockInputs, BlockRunner
 
 
@@ -138,19 +138,18 @@ class GcnStack:
     def bind(self, blk: BlockInputs, nnz) -> None:
         """The frames, weights and entry counts of the coming pass."""
         T = blk.T
-        rows = slice(0, T)
         for b in self.spmm + ([self.spmm_t] if self.spmm_t is not None else []):
-            b.column(b.NNZ, nnz[:T], rows)
+            b.refresh(b.NNZ, nnz[:T], T)
         x = self.x.addresses(blk.x[:T])
         if self.p0 is None:
-            self.transform[0].column(TransformTable.X, x, rows)
+            self.transform[0].refresh(TransformTable.X, x, T)
         elif self.prescale:
-            self.scaled.column(TransformTable.X, x, rows)
+            self.scaled.refresh(TransformTable.X, x, T)
         else:
-            self.spmm[0].column(SpmmTable.H, x, rows)
+            self.spmm[0].refresh(SpmmTable.H, x, T)
         for layer in range(self.L):
             w = self.w[layer].addresses([w[layer] for w in blk.w_t[:T]] if blk.w_t is not None else [blk.w[layer]])
-            self.transform[layer].column(TransformTable.W, w, rows)
+            self.transform[layer].refresh(TransformTable.W, w, T)
 
     def forward(self, t: int, k: int, stream) -> None:
         """All layers of timesteps t .. t + k - 1 (0-based), their snapshots resident."""
@@ -320,7 +319,7 @@ class BlockTrainer:
                     table.column(8, 0, steps)
                 if lists:
                     with self._stage("delta_rebuild"):
-                        table.rebuild(blk.n, chain.rowptr[0], chain.colidx[0], blk.nnz[0], lists, self.cap, stream)
+                        table.rebuild(blk.n, chain.rowptr[0], chain.colidx[0], blk.nnz[0], lists, self.cap, stream, blk.nnz[1:])
         stack.bind(blk, blk.nnz)
         m = stack.together
         for t in range(0, blk.T, m):
@@ -350,6 +349,7 @@ class BlockTrainer:
         gradient of the (up to w-1) timesteps after this block; accumulate adds to dw instead of replacing it."""
         blk, stack = self.blk, self.stack
         T = blk.T
+        g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         if blk.window:
             if overwrite:
@@ -638,7 +638,9 @@ class SmoothedTrainer:
         if self.series:
             for table, store, lists in ((self.table, self.s, blk.deltas), (self.table_t, self.st, self.t_deltas)):
                 if table is not None and blk.T > 1:
-                    table.lists(lists)
+                    size = B.smooth_series_workspace(blk.nnz[0], sum(table.lists(lists[:blk.T - 1])[::2]), blk.T - 1)
+                    if self.ws_smooth.numel() < size:
+                        self.ws_smooth = torch.empty(size, dtype=torch.uint8, device=self.dev)
                     with self._stage("smooth_series"):
                         B.smooth_series(blk.n, store[0][0], store[0][1], blk.nnz[0], blk.T - 1, table.at(), self.life, self.diag_value,
                                         self.cap_s, self.status[2:], self.ws_smooth, stream)
@@ -674,6 +676,7 @@ class SmoothedTrainer:
         """g_y [T, n, f] = dL/dY.  Must follow forward()."""
         blk, stack = self.blk, self.stack
         T = blk.T
+        g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         if blk.window:
             if self.g is None:

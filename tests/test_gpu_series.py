@@ -235,3 +235,83 @@ def test_weight_recurrence_and_its_adjoint(f, f2, T):
     want = oracle.evolve_weights_backward(*args, [to_f64(d) for d in dw])
     for got, exp in zip((ev.du_x, ev.du_h, ev.db, ev.dw0), want):
         assert np.abs(to_f64(got) - exp).max() <= 2e-4 * np.abs(exp).max()
+
+
+def moved(t):
+    """The same tensor object over other memory; what it lay in before is cleared."""
+    old, new = t.view(-1), t.clone()
+    t.set_(new)
+    old.zero_()
+
+
+def test_tensors_that_move_between_passes():
+    """Nothing is kept of a call's tensors but the objects: features, lists, weights and frames that lie elsewhere in the next
+    pass are found there."""
+    blk = make_block(replace(WORKLOADS["c1"], layers=2), DEV, gen_device="cpu")
+    runner = BlockRunner(blk)
+    runner.load_first()
+    runner.run_resident()
+    want, want_rp = runner.z.clone(), runner.rowptr[runner.slot_of(blk.T)].clone()
+    for t in [t for d in blk.deltas for t in d if t.numel()] + list(blk.x) + list(blk.w):
+        moved(t)
+    runner.z = torch.full_like(runner.z, float("nan"))
+    runner.run_resident()
+    torch.cuda.synchronize()
+    assert torch.equal(runner.z, want) and torch.equal(runner.rowptr[runner.slot_of(blk.T)], want_rp)
+    blk.x[0] = blk.x[0].double()
+    with pytest.raises(ValueError):
+        runner.run_resident()
+
+
+def test_runner_whose_subclass_acts_per_snapshot():
+    seen = []
+
+    class Watching(BlockRunner):
+        def snapshot_ready(self, t):
+            seen.append(t)
+
+    runner = Watching(make_block(WORKLOADS["c1"], DEV, gen_device="cpu"))
+    runner.load_first()
+    runner.run_resident()
+    assert seen == list(range(1, runner.blk.T + 1))
+
+
+@pytest.mark.parametrize("smoothed", [False, True])
+def test_upstream_gradients_in_other_forms(smoothed):
+    """Frames strided over the timesteps, and more of them than the block has, are taken; another type or place is refused."""
+    from paper_2109_07893_amd import training
+    wl = WORKLOADS["c3"].scaled(1 << 11, T=4)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    tr = training.make_smoothed_trainer(wl, blk, 2) if smoothed else training.make_trainer(wl, blk)
+    g = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    spread = torch.empty((wl.T + 1, 2, wl.n, wl.f), device=DEV)
+    spread[: wl.T, 0] = g
+    out = []
+    for form in (g, spread[:, 0], list(g)):
+        tr.forward()
+        tr.backward(form)
+        torch.cuda.synchronize()
+        out.append(tr.dw[0].clone())
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+    for form in (g.double(), g.cpu(), g[:, :-1], g.transpose(1, 2).contiguous().transpose(1, 2)):
+        with pytest.raises((ValueError, AssertionError)):
+            tr.backward(form)
+
+
+def test_cdgcn_layer_timestep_by_timestep():
+    from paper_2109_07893_amd.cdgcn import CdgcnLayer
+    gen = torch.Generator().manual_seed(3)
+    wl = WORKLOADS["c1"]
+    blk = make_block(wl, DEV, gen_device="cpu")
+    w, w_x, w_h = (torch.randn(s, generator=gen).mul_(0.2).to(DEV) for s in ((16, 16), (32, 64), (16, 64)))
+    layer = CdgcnLayer(blk, w, w_x, w_h, None, 16)
+    layer.load_first()
+    want = layer.run().clone()
+    layer.h_all.zero_()
+    layer.c.zero_()
+    for t in range(1, blk.T + 1):
+        if t >= 2:
+            layer.rebuild(t, blk.deltas[t - 2])
+        layer.step(t)
+    torch.cuda.synchronize()
+    assert torch.allclose(layer.h_all, want, rtol=1e-6, atol=1e-6)       # the same sums; a launch per step rounds the state alike
