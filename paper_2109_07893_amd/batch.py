@@ -23,6 +23,11 @@ BATCH_BYTES = 64 << 20
 # 85 / 62 us), and it keeps every snapshot in an array of its own.
 SERIES_ENTRIES = 1 << 22
 
+# ... and the bytes its snapshots may take together.  A series of many dense snapshots on few vertices holds far more in them than
+# in its features (10 000 steps of 4 M entries: 160 GB, where the step-by-step rebuild needs three slots), so a long one is
+# rebuilt step by step again; 33 snapshots of 4 M entries and 2^20 vertices take 0.8 GB.
+SERIES_BYTES = 16 << 30
+
 # Vertices up to which the aggregation of X gathers dinv with the rows instead of finding them scaled by a pass of their own.
 # The pass costs per byte of X, the gather per entry, and far more once the factors (4 bytes per vertex, 1 MB here) leave an
 # L2 of 4 MB to the rows no more: per aggregation of 128-byte rows, gather against pass, 2^16 vertices 8 / 6 us, 2^18
@@ -32,6 +37,10 @@ GATHERED_DINV_ROWS = 1 << 18
 
 def steps_together(frame_bytes: int, T: int) -> int:
     return max(1, min(T, BATCH_BYTES // max(frame_bytes, 1)))
+
+
+def snapshots_fit(T: int, n: int, cap: int) -> bool:
+    return T * (4 * cap + 8 * n) <= SERIES_BYTES
 
 
 def pointers(tensors: Sequence[Optional[torch.Tensor]]) -> List[int]:

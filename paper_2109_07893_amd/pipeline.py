@@ -17,7 +17,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, pointers, steps_together
+from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, pointers, snapshots_fit, steps_together
 
 
 @dataclass
@@ -132,7 +132,7 @@ class BlockRunner:
         GCN steps of several timesteps together."""
         if any(getattr(type(self), name) is not getattr(BlockRunner, name) for name in ("rebuild", "transform_first", "gcn", "snapshot_ready")):
             return False                    # a subclass that does something of its own per snapshot is asked for every one
-        return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES
+        return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES and snapshots_fit(self.blk.T, self.blk.n, self.cap)
 
     def slot_of(self, t: int) -> int:
         if self.series and 1 < t < self.blk.T - 1:

@@ -315,3 +315,29 @@ def test_cdgcn_layer_timestep_by_timestep():
         layer.step(t)
     torch.cuda.synchronize()
     assert torch.allclose(layer.h_all, want, rtol=1e-6, atol=1e-6)       # the same sums; a launch per step rounds the state alike
+
+
+def test_long_series_of_dense_snapshots_go_step_by_step(monkeypatch):
+    """Snapshots that would take too many bytes together: three slots again, the same frames and gradients."""
+    from dtdg_synth import gradient
+    from paper_2109_07893_amd import batch, training
+    wl = replace(WORKLOADS["c1"], layers=2)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV)
+    bytes_of_all = wl.T * (4 * max(blk.nnz) + 8 * wl.n)
+    z, dw = [], []
+    for limit in (bytes_of_all, bytes_of_all - 1):
+        monkeypatch.setattr(batch, "SERIES_BYTES", limit)
+        runner, tr = BlockRunner(blk, keep_all_z=True), training.make_trainer(wl, blk)
+        assert runner.series == tr.series == (limit == bytes_of_all)
+        assert len(runner.rowptr) == (wl.T if runner.series else 3)
+        runner.load_first()
+        runner.run_resident()
+        tr.forward()
+        tr.backward(g_y)
+        torch.cuda.synchronize()
+        z.append(runner.z.clone())
+        dw.append([d.double().clone() for d in tr.dw])
+    assert torch.equal(z[0], z[1])
+    for a, b in zip(*dw):                                   # sums over timesteps in another order
+        assert float((a - b).norm()) <= 1e-5 * float(b.norm())
