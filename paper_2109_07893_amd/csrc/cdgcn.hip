@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kLstmThreads) void lstm_step_backward_f32_kernel(
     }
 }
 
-// The adjoint for bf16 storage, hidden = 32: products as in lstm_step_bf16_kernel, the cell's backward formulas in fp32
+// The adjoint for bf16 storage, hidden = 32: products as in the bf16 form of lstm_series_kernel, the cell's backward formulas in fp32
 // on the accumulators; the two summands of dL/dh stay apart until they are added in fp32.
 template <int FY>
 __global__ __launch_bounds__(kLstmThreads) void lstm_step_backward_bf16_kernel(
