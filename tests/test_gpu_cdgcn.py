@@ -463,3 +463,19 @@ def test_lstm_series_backward(dtype, hidden, n, T, cut):
     tol = 2e-4 if dtype == torch.float32 else 2e-2
     for got, exp in zip((dh, dc, dw_x, dw_h, db), [d_h, d_c] + want):
         assert np.abs(to_f64(got) - exp).max() <= tol * np.abs(exp).max() + 1e-6
+
+
+# steps of 16 rows: all whole, one in which the states change from h_0 to h, a ragged last one, both at once, fewer rows than a step
+@pytest.mark.parametrize("n,T", [(16, 3), (24, 2), (7, 2), (21, 1), (1, 1), (1, 40), (5, 13), (4099, 3), (20_000, 2)])
+@pytest.mark.parametrize("dtype,hidden", [(torch.float32, 16), (torch.float32, 32), (torch.bfloat16, 32)])
+def test_parameter_gradients_of_the_lstm_at_the_edges_of_its_steps(dtype, hidden, n, T):
+    f_y, rows = 2 * hidden, n * T
+    y, h0, h, da = (randn(s, k + n, dtype).to(DEV) for k, s in enumerate([(T, n, f_y), (n, hidden), (T, n, hidden), (T, n, 4 * hidden)]))
+    dw_x, dw_h, db = (torch.empty(s, device=DEV) for s in ((f_y, 4 * hidden), (hidden, 4 * hidden), (4 * hidden,)))
+    ws = torch.empty(dg.binding.lstm_weight_grad_workspace(f_y, hidden), dtype=torch.uint8, device=DEV)
+    dg.lstm_weight_grad(y, h0, h, da, dw_x, dw_h, db, ws)
+    g, before = to_f64(da).reshape(rows, -1), np.concatenate([to_f64(h0)[None], to_f64(h)[:-1]]).reshape(rows, -1)
+    for got, left in ((dw_x, to_f64(y).reshape(rows, -1)), (dw_h, before), (db, np.ones((rows, 1)))):
+        # fp32 sums of exact products (bf16) or once-rounded ones: an error of 2^-24 per term and addition of the magnitudes
+        bound = (min(rows, 4096) + 2) * 2.0 ** -24 * (np.abs(left).T @ np.abs(g)) + 1e-30
+        assert np.all(np.abs(to_f64(got).reshape(bound.shape) - left.T @ g) <= bound)
