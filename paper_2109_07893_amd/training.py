@@ -3,7 +3,7 @@ Checkpoint": a block is run forward, keeping its activations, and gradients then
 the reverse direction).  Like pipeline.py this owns buffers and the order of library calls only:
 
     forward    A_2 .. A_T (dgnn_delta_rebuild_series, or dgnn_delta_rebuild per step on large snapshots), then per timestep
-                   first layer    P = A~_t X,  Z = relu(P W)                     both kept
+                   first layer    P = A~_t X,  Z = relu(P W)                     both kept (fp32)
                    other layers   H = Z_below W,  Z = relu(A~_t H)               Z kept
                then Y = Z x_1 M
     backward   G = G_Y x_1 M^T (dgnn_mproduct_backward), then per timestep, last layer to first:
@@ -14,7 +14,8 @@ the reverse direction).  Like pipeline.py this owns buffers and the order of lib
 
 The first layer's weight gradient is X^T A~^T G_P = (A~ X)^T G_P: with A~ X kept from the forward pass it needs no aggregation
 and no transposed snapshot, which leaves a one-layer step with half the gathers.  Where dL/dX is wanted (a layer lies below)
-the aggregation is needed anyway, and the first layer is treated like the others.
+the aggregation is needed anyway, and the first layer is treated like the others; so it is where frames are stored in bf16 (see
+first_layer_keeps_aggregated).
 
 For a directed workload the transposed snapshots, where needed, are a second dynamic graph, rebuilt the same way from the
 difference lists sorted by (col, row).  Timesteps are enqueued together while their frames are small (batch.py).  Nothing here
@@ -76,15 +77,12 @@ class GcnStack:
         self.stage, self.want_dx, self.weighted = stage, want_dx, vals is not None
         self.together = m = together or steps_together(n * f * blk.x[0].element_size(), T)
         self.z = torch.empty((L, T, n, f), dtype=dt, device=dev)
-        # A~_t X_t, from which the first layer's weight gradient follows without an aggregation.  With values and further layers
-        # above, where the transposed snapshots are resident anyway, the first layer is aggregated like the others: A~ (X W) rounds
-        # less than (A~ X) W before the ReLU decides, and what it decides passes through all layers going back
-        aggregate_first = want_dx or (self.weighted and L > 1)
-        self.p0 = None if aggregate_first else torch.empty((T, n, f), dtype=dt, device=dev)
-        # rows of X are scaled by dinv in a pass of their own, or dinv is gathered with them (see GATHERED_DINV_ROWS);
-        # bf16 rows always take the latter, which spares them a rounding
-        self.prescale = not aggregate_first and blk.x[0].dtype == torch.float32 and n > GATHERED_DINV_ROWS
-        aggregated = L if aggregate_first else L - 1                                     # layers that need A~^T going back
+        # A~_t X_t, from which the first layer's weight gradient follows without an aggregation
+        keep_p0 = first_layer_keeps_aggregated(blk, want_dx, self.weighted)
+        self.p0 = torch.empty((T, n, f), dtype=dt, device=dev) if keep_p0 else None
+        # rows of X are scaled by dinv in a pass of their own, or dinv is gathered with them (see GATHERED_DINV_ROWS)
+        self.prescale = keep_p0 and n > GATHERED_DINV_ROWS
+        aggregated = L - 1 if keep_p0 else L                                             # layers that need A~^T going back
         self.needs_transposed = aggregated > 0
         buffers = aggregated > 0 or self.prescale
         self.h = torch.empty((m, n, f), dtype=dt, device=dev) if buffers else None       # H going forward, G_H going back
@@ -203,11 +201,11 @@ class GcnStack:
                 B.spmm_batch(n, k, self.spmm_t.at(t), f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
             if layer > 0:
                 self._weight_grad(blk, t, k, layer, self.z[layer - 1, t:t + k], self.h, False, dw, dw_t, accumulate, stream)
-            else:                                  # the frames of X are tensors of their own
-                for j in range(k):
+            else:                                  # the frames of X are tensors of their own, added up from the last one on
+                for j in range(k - 1, -1, -1):
                     with self.stage("weight_grad"):
                         B.weight_grad(blk.x[t + j], self.h[j], dw_t[t + j][0] if dw_t is not None else dw[0], self.ws_wgrad,
-                                      accumulate=dw_t is None and (accumulate or j > 0))
+                                      accumulate=dw_t is None and (accumulate or j < k - 1))
             if layer == 0 and not self.want_dx:
                 return
             dst = self.g_mid[:k] if layer > 0 else self.dx[t:t + k]
@@ -393,9 +391,17 @@ class BlockTrainer:
         return g_h
 
 
-def needs_transposed(blk: BlockInputs, want_dx: bool = False) -> bool:
-    """Whether gradients travel through an aggregation at all (the first layer's weight gradient does not, see above)."""
-    return blk.layers > 1 or want_dx
+def first_layer_keeps_aggregated(blk: BlockInputs, want_dx: bool = False, weighted: bool = False) -> bool:
+    """Whether the first layer is evaluated as relu((A~ X) W) with A~ X kept, so that its weight gradient needs no aggregation.
+    Only in fp32: a bf16 A~ X is rounded once per row before the product and the ReLU see it, where the roundings of X W average
+    out over a row's neighbours (features that are all positive, 16 neighbours: dW 1.6 to 3.2 times as far from 64 bits).  And
+    not with values and further layers above, where the transposed snapshots are resident anyway."""
+    return blk.x[0].dtype == torch.float32 and not want_dx and not (weighted and blk.layers > 1)
+
+
+def needs_transposed(blk: BlockInputs, want_dx: bool = False, weighted: bool = False) -> bool:
+    """Whether gradients travel through an aggregation at all."""
+    return blk.layers > 1 or not first_layer_keeps_aggregated(blk, want_dx, weighted)
 
 
 def capture_training_step(tr: "BlockTrainer", g_y: torch.Tensor) -> "torch.cuda.CUDAGraph":
@@ -424,7 +430,7 @@ def transposed_inputs(blk: BlockInputs):
 
 def make_smoothed_trainer(wl, blk: BlockInputs, life: int) -> "SmoothedTrainer":
     directed = wl.graph != "er"
-    if not directed or not needs_transposed(blk):
+    if not directed or not needs_transposed(blk, weighted=True):
         return SmoothedTrainer(blk, life, directed)
     first, deltas = transposed_inputs(blk)
     return SmoothedTrainer(blk, life, True, transposed_first=first, transposed_deltas=deltas)
@@ -573,7 +579,7 @@ class SmoothedTrainer:
         max_list = max([int(d[0].numel()) for d in blk.deltas] + [max_del, 1])
         self.cap_s = cap + life * max_del                  # the window's union: A_t and what the window's steps deleted
         self.series = T - 1 <= B.DGNN_SERIES_STEPS and life <= 32 and blk.nnz[0] > 0
-        transposed = directed and needs_transposed(blk)
+        transposed = directed and needs_transposed(blk, weighted=True)
         if transposed:
             assert transposed_first is not None and transposed_deltas is not None
         self.t_first, self.t_deltas = transposed_first, transposed_deltas

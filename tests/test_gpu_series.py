@@ -341,3 +341,41 @@ def test_long_series_of_dense_snapshots_go_step_by_step(monkeypatch):
     assert torch.equal(z[0], z[1])
     for a, b in zip(*dw):                                   # sums over timesteps in another order
         assert float((a - b).norm()) <= 1e-5 * float(b.norm())
+
+
+@pytest.mark.parametrize("graph_kind,smoothed", [("er", False), ("rmat", False), ("rmat", True)])
+def test_bf16_training_rounds_as_its_single_calls_do(graph_kind, smoothed):
+    """A bf16 step, bit for bit: X W rounded per row and aggregated, going back G_H rounded per row and multiplied by X, one
+    timestep after the other from the last one on.  (With A~ X rounded before the product, features of one sign leave the
+    gradients up to three times as far from 64 bits.)"""
+    from paper_2109_07893_amd import training
+    wl = replace(graph(graph_kind, 1 << 11, 12, 5, 0.02, 0.03), f=64, dtype="bf16", layers=1, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    blk.x = [x.abs() for x in blk.x]
+    tr = training.make_smoothed_trainer(wl, blk, 3) if smoothed else training.make_trainer(wl, blk, keep_snapshots=True)
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV).to(torch.bfloat16)
+    y = tr.forward()
+    tr.backward(g_y)
+    h, gp, z = (torch.empty_like(blk.x[0]) for _ in range(3))
+    dw = torch.zeros((wl.f, wl.f), device=DEV)
+    ws_w = torch.empty(dg.weight_grad_workspace(wl.f, wl.f), dtype=torch.uint8, device=DEV)
+    for t in range(wl.T - 1, -1, -1):
+        if smoothed:
+            (rp, ci, val), there, nnz, dinv = tr.s[t], tr.st[t], tr.s_nnz[t], tr.dinv_s[t]
+        else:
+            rp, ci, val, nnz, dinv = tr.a.rowptr[t], tr.a.colidx[t], None, blk.nnz[t], tr.a.dinv[t]
+            there = (tr.at.rowptr[t], tr.at.colidx[t]) if tr.at is not None else (rp, ci)
+        ws = torch.empty(dg.spmm_workspace(wl.n, nnz, wl.f), dtype=torch.uint8, device=DEV)
+
+        def aggregate(snapshot, src, dst, flags):
+            if val is None:
+                dg.spmm(snapshot[0], snapshot[1], nnz, dinv, src, dst, ws, flags=flags | dg.DGNN_H_PRESCALED)
+            else:
+                dg.spmm_weighted(*snapshot, nnz, src, dst, ws, flags=flags | dg.DGNN_H_PRESCALED, dinv=dinv)
+        dg.feature_transform(blk.x[t], blk.w[0], h, row_scale=dinv)
+        aggregate((rp, ci, val), h, z, dg.DGNN_RELU)
+        assert torch.equal(z, y[t]), t
+        dg.relu_backward(g_y[t], z, gp, row_scale=dinv)
+        aggregate(there, gp, h, 0)
+        dg.weight_grad(blk.x[t], h, dw, ws_w, accumulate=t < wl.T - 1)
+    assert torch.equal(dw, tr.dw[0])
