@@ -41,8 +41,8 @@ class CdgcnLayer(BlockRunner):
         self.w, self.w_x, self.w_h, self.bias, self.hidden, self.f_out = w, w_x, w_h, bias, hidden, f_out
         assert tuple(w_x.shape) == (f + f_out, 4 * hidden) and tuple(w_h.shape) == (hidden, 4 * hidden)
         # the right-hand D^(-1/2) of A~: gathered with the rows of X, or, where the factors no longer fit beside them in the
-        # caches, put into the rows by a pass of its own
-        self.prescale = n > GATHERED_DINV_ROWS
+        # caches, put into the rows by a pass of its own; bf16 rows always the latter, so that one size rounds as the next
+        self.prescale = dt == torch.bfloat16 or n > GATHERED_DINV_ROWS
         self.xs = torch.empty((m, n, f), dtype=dt, device=dev) if self.prescale else None
         self.y0_batch = torch.empty((m, n, f), dtype=dt, device=dev)
         self.y_batch = torch.empty((m, n, f + f_out), dtype=dt, device=dev)

@@ -2,12 +2,12 @@
 //
 // The recurrence runs per vertex, a = [Y_t | h_{t-1}] [W_x ; W_h] + b and the cell, so a wavefront that owns 32 vertices can
 // walk all timesteps by itself: [W_x ; W_h] is staged in LDS once per workgroup, h_{t-1} is in the tile buffer when it is
-// needed, c never leaves the registers.  Per step a wavefront forms the TRANSPOSED gate tiles on the matrix cores (W^T as
-// the A operand, the rows of [Y | h] as the B operand): column C = g * hidden + k of the pre-activations is gate g of state
-// element k, it lies in the 32-column tile C / 32, and lane (i, h) holds, for vertex i, the columns c of a tile with (c / 4) % 2
-// == h, four consecutive ones per four accumulator registers.  hidden is a multiple of 8, so the four gates of a state
-// element sit in the same lane: lane (i, h) owns state elements 8 m + 4 h + r of vertex i, and the cell works on the
-// accumulators.
+// needed, c stays in the registers (rounded to the storage type after every step).  Per step a wavefront forms the TRANSPOSED
+// gate tiles on the matrix cores (W^T as the A operand, the rows of [Y | h] as the B operand): column C = g * hidden + k of the
+// pre-activations is gate g of state element k, it lies in the 32-column tile C / 32, and lane (i, h) holds, for vertex i, the
+// columns c of a tile with (c / 4) % 2 == h, four consecutive ones per four accumulator registers.  hidden is a multiple of 8,
+// so the four gates of a state element sit in the same lane: lane (i, h) owns state elements 8 m + 4 h + r of vertex i, and the
+// cell works on the accumulators.
 //
 // Going back the same wavefront recomputes the gates of timestep t, turns the accumulators into da and multiplies them by the
 // rows of [W_x ; W_h] that are wanted, W da^T, straight from the registers: a lane's accumulators are half of the contraction
@@ -44,6 +44,7 @@ template <> struct Store<false> {
     static constexpr int kTilePad = 4;                 // elements of padding per tile row
     static __device__ __forceinline__ floatx4 load4(const float *p) { return *reinterpret_cast<const floatx4 *>(p); }
     static __device__ __forceinline__ void store4(float *p, floatx4 v) { *reinterpret_cast<floatx4 *>(p) = v; }
+    static __device__ __forceinline__ floatx4 rounded(floatx4 v) { return v; }
 };
 template <> struct Store<true> {
     typedef uint16_t Elem;
@@ -55,6 +56,10 @@ template <> struct Store<true> {
     }
     static __device__ __forceinline__ void store4(uint16_t *p, floatx4 v) {
         *reinterpret_cast<uint2 *>(p) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    }
+    static __device__ __forceinline__ floatx4 rounded(floatx4 v) {
+        const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
+        return floatx4{__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
     }
 };
 
@@ -223,6 +228,7 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
                     h_new[r] = fast_sigmoid(ao) * fast_tanh(cell[m][r]);
                 }
                 S::store4(&tile_lds[i * LDT + FY + k0], h_new);
+                cell[m] = S::rounded(cell[m]);          // as a launch per step would hand it on: results do not depend on how many share one
                 if (KEEP_C) S::store4(&tile_lds[i * LDT + k0], cell[m]);
             }
             wave_lds_sync();

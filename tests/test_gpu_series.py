@@ -379,3 +379,41 @@ def test_bf16_training_rounds_as_its_single_calls_do(graph_kind, smoothed):
         aggregate(there, gp, h, 0)
         dg.weight_grad(blk.x[t], h, dw, ws_w, accumulate=t < wl.T - 1)
     assert torch.equal(dw, tr.dw[0])
+
+
+@pytest.mark.parametrize("f_y,hidden", [(32, 32), (64, 32), (64, 64), (128, 64)])
+def test_bf16_lstm_does_not_depend_on_the_steps_per_launch(f_y, hidden):
+    """Every state is rounded to bf16 between two steps, whether or not they share a launch."""
+    gen = torch.Generator(device=DEV).manual_seed(hidden + f_y)
+    n, T = 333, 7
+    y, h0, c0 = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((T, n, f_y), (n, hidden), (n, hidden)))
+    w_x, w_h = (torch.randn(k, 4 * hidden, generator=gen, device=DEV).mul_(k ** -0.5).to(torch.bfloat16) for k in (f_y, hidden))
+    bias = torch.randn(4 * hidden, generator=gen, device=DEV) * 0.1
+    h, c, kept = torch.empty(T, n, hidden, dtype=y.dtype, device=DEV), torch.empty_like(c0), torch.empty(T, n, hidden, dtype=y.dtype, device=DEV)
+    dg.lstm_series(y, h0, w_x, w_h, bias, c0, c, h)
+    h_kept = torch.empty_like(h)
+    dg.lstm_series(y, h0, w_x, w_h, bias, c0, kept, h_kept)
+    state, prev, out = c0.clone(), h0, torch.empty_like(h)
+    for t in range(T):
+        dg.lstm_step(y[t], prev, w_x, w_h, bias, state, out[t])
+        prev = out[t]
+        assert torch.equal(kept[t], state), t
+    assert torch.equal(h, out) and torch.equal(h_kept, out) and torch.equal(c, state)
+
+
+def test_bf16_cdgcn_layer_does_not_depend_on_the_steps_per_launch():
+    from paper_2109_07893_amd.cdgcn import CdgcnLayer
+    gen = torch.Generator().manual_seed(4)
+    wl = replace(WORKLOADS["c1"], f=32, dtype="bf16")
+    blk = make_block(wl, DEV, gen_device="cpu")
+    w, w_x, w_h = (torch.randn(s, generator=gen).mul_(0.2).to(torch.bfloat16).to(DEV) for s in ((32, 32), (64, 128), (32, 128)))
+    layer = CdgcnLayer(blk, w, w_x, w_h, None, 32)
+    layer.load_first()
+    want, want_c = layer.run().clone(), layer.c.clone()
+    layer.h_all.zero_()
+    layer.c.zero_()
+    for t in range(1, blk.T + 1):
+        if t >= 2:
+            layer.rebuild(t, blk.deltas[t - 2])
+        layer.step(t)
+    assert torch.equal(layer.h_all, want) and torch.equal(layer.c, want_c)
