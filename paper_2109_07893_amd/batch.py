@@ -64,12 +64,12 @@ class Table:
     def column(self, k: int, values, rows: slice = slice(None)) -> None:
         self.words[rows, k] = values
 
-
     def refresh(self, k: int, values: List[int], rows: int) -> None:
-        """The first `rows` entries of a column that is bound anew for every pass; written where the values differ."""
-        if self.bound.get(k) != values:
+        """The first `rows` entries of a column that is bound anew for every pass (one value: for all of them); written where
+        they are not what the last pass wrote."""
+        if self.bound.get(k) != (rows, values):
             self.words[:rows, k] = values
-            self.bound[k] = list(values)
+            self.bound[k] = (rows, list(values))
 
 
 class StepsTable(Table):

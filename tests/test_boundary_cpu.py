@@ -366,3 +366,15 @@ int main(void) {
                            "-L", lib_dir, "-ldgnn", f"-Wl,-rpath,{lib_dir}", "-Wl,-rpath,/opt/rocm/lib"])
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and "boundary ok" in out.stdout, (out.returncode, out.stdout, out.stderr)
+
+
+def test_table_columns_follow_the_number_of_rows():
+    """One weight stands for all timesteps of a pass, however many the passes before had."""
+    from paper_2109_07893_amd.batch import Table
+    table = Table(8, 2)
+    for rows, value in ((4, 0xb), (8, 0xb), (3, 0xb), (8, 0xc), (2, 0xa), (8, 0xa)):
+        table.refresh(1, [value], rows)
+        assert (table.words[:rows, 1] == value).all(), (rows, value)
+    table.refresh(1, [1, 2, 3], 3)
+    table.refresh(1, [1, 2, 3, 4], 4)
+    assert table.words[:4, 1].tolist() == [1, 2, 3, 4] and not table.words[:, 0].any()

@@ -417,3 +417,23 @@ def test_bf16_cdgcn_layer_does_not_depend_on_the_steps_per_launch():
             layer.rebuild(t, blk.deltas[t - 2])
         layer.step(t)
     assert torch.equal(layer.h_all, want) and torch.equal(layer.c, want_c)
+
+
+def test_rebinding_to_blocks_of_other_lengths():
+    """A block, a shorter one with other weights, then one of full length again: every timestep takes the weights at hand."""
+    from paper_2109_07893_amd.training import BlockTrainer
+    wl = replace(graph("er", 700, 6, 6, 0.05, 0.05), f=32, layers=1, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+
+    def cut(T, w):
+        return replace(blk, T=T, deltas=blk.deltas[:T - 1], x=blk.x[:T], nnz=blk.nnz[:T], w=[w])
+    w = [torch.randn_like(blk.w[0]) for _ in range(2)]
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    tr = BlockTrainer(cut(6, w[0]), False)
+    for T, k in ((6, 0), (2, 1), (6, 1), (3, 0), (5, 0)):
+        part, fresh = cut(T, w[k]), BlockTrainer(cut(T, w[k]), False)
+        tr.rebind(part)
+        assert torch.equal(tr.forward(), fresh.forward()), (T, k)
+        for t in (tr, fresh):
+            t.backward(g_y[:T])
+        assert torch.equal(tr.dw[0], fresh.dw[0]), (T, k)
