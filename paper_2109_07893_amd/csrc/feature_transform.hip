@@ -541,7 +541,8 @@ int transform(int count, const dgnn_transform_item *items, int64_t n, int32_t f_
               bool single_w) {
     for (int k = 0; k < count; ++k)
         if (!items[k].x || !items[k].h || (items[k].w == nullptr) != (items[0].w == nullptr)) return DGNN_ERR_NULL;
-    if (!single_w && count > 0 && !items[0].w && f_in != f_out) return DGNN_ERR_SHAPE;
+    // without a product there is nothing that flags could ask of it
+    if (!single_w && count > 0 && !items[0].w && (f_in != f_out || wt || relu)) return DGNN_ERR_SHAPE;
     if (single_w && !items[0].w) return DGNN_ERR_NULL;
     if (n <= 0 || count <= 0 || !supported_width(f_in) || !supported_width(f_out)) return DGNN_ERR_SHAPE;
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;

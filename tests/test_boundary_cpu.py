@@ -368,6 +368,14 @@ int main(void) {
     assert out.returncode == 0 and "boundary ok" in out.stdout, (out.returncode, out.stdout, out.stderr)
 
 
+def test_products_without_a_weight_take_no_flags(lib):
+    """w NULL asks for the rows scaled and nothing else; a ReLU or a transposed w asked for beside it would be lost."""
+    items = (ctypes.c_uint64 * 4)(FAKE, 0, FAKE + 4096, FAKE + 8192)
+    for flags in (binding.DGNN_RELU, binding.DGNN_W_TRANSPOSED, binding.DGNN_RELU | binding.DGNN_W_TRANSPOSED):
+        assert lib.dgnn_feature_transform_batch(1, items, 10, 32, 32, flags, 0, None) == -2
+    assert lib.dgnn_feature_transform_batch(1, items, 10, 32, 64, 0, 0, None) == -2
+
+
 def test_table_columns_follow_the_number_of_rows():
     """One weight stands for all timesteps of a pass, however many the passes before had."""
     from paper_2109_07893_amd.batch import Table
