@@ -583,14 +583,14 @@ class SmoothedTrainer:
         if transposed:
             assert transposed_first is not None and transposed_deltas is not None
         self.t_first, self.t_deltas = transposed_first, transposed_deltas
-        ones = torch.ones(blk.nnz[0], dtype=torch.float32, device=dev)       # S_1 = A_1, every entry counted once
+        ones = torch.ones(cap, dtype=torch.float32, device=dev)              # S_1 = A_1, every entry counted once
 
-        def smoothed(rowptr1, colidx1):
-            return [(rowptr1, colidx1, ones)] + [
+        def smoothed():                                    # S_1's arrays are filled anew for every pass, as A_1 may lie elsewhere then
+            return [(torch.empty(n + 1, dtype=torch.int32, device=dev), torch.empty(cap, dtype=torch.int32, device=dev), ones)] + [
                 (torch.empty(n + 1, dtype=torch.int32, device=dev), torch.empty(self.cap_s, dtype=torch.int32, device=dev),
                  torch.empty(self.cap_s, dtype=torch.float32, device=dev)) for _ in range(T - 1)]
-        self.s = smoothed(blk.rowptr1, blk.colidx1)
-        self.st = smoothed(*transposed_first) if transposed else self.s
+        self.s = smoothed()
+        self.st = smoothed() if transposed else self.s
         # what the calls that take S_t are told about its size: an upper bound (the count is its last row pointer)
         self.s_nnz = [blk.nnz[0]] + [self.cap_s] * (T - 1)
         self.dinv_s = torch.empty((T, n), dtype=torch.float32, device=dev)
@@ -639,8 +639,14 @@ class SmoothedTrainer:
     def _snapshots(self, stream) -> None:
         """S_1 .. S_T (and their transposes, where needed) with their normalisation."""
         blk = self.blk
+        self.s_nnz[0] = blk.nnz[0]
+        firsts = [(self.s, blk.rowptr1, blk.colidx1)] + ([(self.st,) + tuple(self.t_first)] if self.st is not self.s else [])
+        for store, rowptr1, colidx1 in firsts:
+            rowptr, colidx, _ = store[0]
+            rowptr.copy_(rowptr1)
+            colidx[: blk.nnz[0]].copy_(colidx1[: blk.nnz[0]])
         with self._stage("csr_weighted_dinv"):
-            B.csr_dinv(blk.rowptr1, self.dinv_s[0])
+            B.csr_dinv(self.s[0][0], self.dinv_s[0])
         if self.series:
             for table, store, lists in ((self.table, self.s, blk.deltas), (self.table_t, self.st, self.t_deltas)):
                 if table is not None and blk.T > 1:

@@ -437,3 +437,29 @@ def test_rebinding_to_blocks_of_other_lengths():
         for t in (tr, fresh):
             t.backward(g_y[:T])
         assert torch.equal(tr.dw[0], fresh.dw[0]), (T, k)
+
+
+@pytest.mark.parametrize("T,layers", [(5, 1), (5, 2), (34, 2)])
+def test_smoothed_trainer_finds_its_first_snapshot_anew(T, layers):
+    """A_1 (and its transpose) lies elsewhere in the next pass, or comes from the host with 64-bit indices.  34 timesteps: more
+    than are smoothed in one call."""
+    from paper_2109_07893_amd import training
+    wl = replace(graph("rmat", 1 << 10, 8, T, 0.03, 0.03), f=16, layers=layers, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    tr = training.make_smoothed_trainer(wl, blk, 3)
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+
+    def step():
+        y = tr.forward().clone()
+        tr.backward(g_y)
+        torch.cuda.synchronize()
+        return [y] + [d.clone() for d in tr.dw]
+    want = step()
+    firsts = [blk.rowptr1, blk.colidx1] + (list(tr.t_first) if tr.t_first is not None else [])
+    for t in firsts:
+        moved(t)
+    assert all(torch.equal(a, b) for a, b in zip(step(), want))
+    blk.rowptr1, blk.colidx1 = blk.rowptr1.clone(), blk.colidx1.cpu().long()
+    for t in firsts[:2]:
+        t.zero_()
+    assert all(torch.equal(a, b) for a, b in zip(step(), want))
