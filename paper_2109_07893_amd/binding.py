@@ -400,9 +400,10 @@ def lstm_weight_grad(y, h0, h, da, dw_x, dw_h, db, ws, accumulate: bool = False)
 def evolve_weights(w0, u_x, u_h, bias, w, c) -> None:
     """W_1 .. W_T in w [T, f, f2], C_0 .. C_T in c [T + 1, f, f2]."""
     T, f, f2 = w.shape
-    for t in (w0, u_x, u_h, bias, w, c):
+    for t in (w0, u_x, u_h, w, c) + ((bias,) if bias is not None else ()):
         _need(t, torch.float32, "evolve_weights tensors")
-    if tuple(w0.shape) != (f, f2) or tuple(u_x.shape) != (f2, 4 * f2) or tuple(u_h.shape) != (f2, 4 * f2) or bias.numel() != 4 * f2 or tuple(c.shape) != (T + 1, f, f2):
+    if (tuple(w0.shape) != (f, f2) or tuple(u_x.shape) != (f2, 4 * f2) or tuple(u_h.shape) != (f2, 4 * f2) or tuple(c.shape) != (T + 1, f, f2)
+            or (bias is not None and bias.numel() != 4 * f2)):
         raise ValueError("shape mismatch in evolve_weights")
     _check(load_library().dgnn_evolve_weights(_ptr(w0), _ptr(u_x), _ptr(u_h), _ptr(bias), T, f, f2, _ptr(w), _ptr(c), _stream(w)),
            "dgnn_evolve_weights")

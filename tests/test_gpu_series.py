@@ -463,3 +463,16 @@ def test_smoothed_trainer_finds_its_first_snapshot_anew(T, layers):
     for t in firsts[:2]:
         t.zero_()
     assert all(torch.equal(a, b) for a, b in zip(step(), want))
+
+
+def test_weight_recurrence_without_a_bias():
+    from paper_2109_07893_amd.evolve import EvolvingWeights
+    w0, u_x, u_h = torch.randn(32, 16, device=DEV), torch.randn(16, 64, device=DEV), torch.randn(16, 64, device=DEV)
+    dw = [torch.randn(32, 16, device=DEV) for _ in range(4)]
+    out = []
+    for bias in (None, torch.zeros(64, device=DEV)):
+        ev = EvolvingWeights(w0, u_x, u_h, bias, 4)
+        ev.forward()
+        ev.backward(dw)
+        out.append((ev.w, ev.c, ev.dw0, ev.du_x, ev.du_h, ev.db))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
