@@ -168,7 +168,7 @@ int dgnn_spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *coli
 /*
  * dgnn_spmm for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments and same kernels as dgnn_spmm, but no workspace argument: the carry
- * records, (32 + 8 f) bytes per range of stored entries that one wavefront streams, live in a device array of fixed
+ * records, (16 + 8 f) bytes per range of stored entries that one wavefront streams, live in a device array of fixed
  * size inside the library (dgnn_spmm_static_limit() bytes, 32 MiB, held by every GPU the library runs on until the
  * process ends).  Where dgnn_spmm's ranges (2048 entries, fewer on small snapshots) would need more records than
  * the array holds, this call makes its ranges longer, up to 8192 entries: rows that a range's end cuts are then

@@ -40,7 +40,6 @@ constexpr int kTargetWaves = 65536;  // ranges shrink on small inputs so that ab
 constexpr int kLongestRange = 8192;  // what a caller with little room for records may stretch a range to
 constexpr int kXcds = 8;             // accelerator dies of an MI355X, each with its own L2
 constexpr int kXcdChunk = 16;        // consecutive ranges that go to the same XCD
-constexpr int kMaxSlices = 2;        // of the columns, see slices_of
 constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: all vector memory loads returned, other counters untouched
 
 enum : int32_t { kLeft = 1, kLeftClosed = 2, kRight = 4 };
@@ -119,14 +118,14 @@ template <int LPR, int SLICES, bool BF16, bool SCALE_V>
 __device__ __forceinline__ void spmm_stream(
     int range, int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ dinv, const char *__restrict__ h, char *__restrict__ z, int relu,
-    RangeRec *__restrict__ recs, float *__restrict__ carry, const float *__restrict__ vals, bool gather_dinv) {
+    RangeRec *__restrict__ recs, bool record, float *__restrict__ carry, const float *__restrict__ vals, bool gather_dinv) {
     typedef typename Piece<BF16>::Raw Raw;
     constexpr int NV = Piece<BF16>::kVals;
     constexpr int F = LPR * NV;
     constexpr int G = kWave / LPR;          // lane groups per wavefront
     constexpr int SUB = G * kPer;           // entries per sub-tile
     constexpr int CPL = kPer / LPR;         // column indices held by one lane
-    constexpr int kRowBytes = LPR * SLICES * 16;   // from a row to the next; h, z, recs and carry are the slice's own
+    constexpr int kRowBytes = LPR * SLICES * 16;   // from a row to the next; h, z and carry are the slice's own, recs are the same for all (one of them records)
     constexpr int kRowCap = SUB + kWave;    // most rows a sub-tile can need: one per entry, plus the bounding one
     constexpr int ROUNDS = kRowCap / kWave;
 
@@ -141,7 +140,7 @@ __device__ __forceinline__ void spmm_stream(
     nnz = min(nnz, rowptr[n]);
     const int e_begin = (int)((int64_t)range * range_len);
     if (e_begin >= nnz && range > 0) {                  // nothing stored here: a record that closes nothing and carries nothing
-        if (threadIdx.x == 0) recs[range] = RangeRec{0, 0, 0, 0};
+        if (threadIdx.x == 0 && record) recs[range] = RangeRec{0, 0, 0, 0};
         return;
     }
     const int e_end = (int)min((int64_t)e_begin + range_len, (int64_t)nnz);
@@ -463,7 +462,7 @@ __device__ __forceinline__ void spmm_stream(
                 range_flags |= kLeft;
             }
         }
-        if (lane == 0) recs[range] = RangeRec{range_flags, run_row, 0, 0};
+        if (lane == 0 && record) recs[range] = RangeRec{range_flags, run_row, 0, 0};
     }
     if (e_end == nnz)                                    // rows without entries beyond the last staged window
         for (int k = k_win + staged_last - 1 + lane; k < n; k += kWave)
@@ -485,7 +484,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) v
     constexpr int F = LPR * Piece<BF16>::kVals;                         // columns of a slice
     spmm_stream<LPR, SLICES, BF16, SCALE_V>(range, n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
                                             as_global(it.h) + slice * LPR * 16, as_global(it.z) + slice * LPR * 16, relu,
-                                            as_global(it.recs) + slice * it.n_ranges, as_global(it.carry) + (int64_t)slice * it.n_ranges * 2 * F,
+                                            as_global(it.recs), slice == 0, as_global(it.carry) + (int64_t)slice * it.n_ranges * 2 * F,
                                             as_global(it.vals), it.gather_dinv != 0);
 }
 
@@ -504,7 +503,7 @@ __global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) 
     const Item &item = batch.item[blockIdx.y];
     const int slice = blockIdx.z;
     const float *__restrict__ carry = as_global(item.carry) + (int64_t)slice * item.n_ranges * 2 * F, *__restrict__ dinv = as_global(item.dinv);
-    const RangeRec *__restrict__ recs = as_global(item.recs) + slice * item.n_ranges;
+    const RangeRec *__restrict__ recs = as_global(item.recs);
     const int32_t *__restrict__ rowptr = as_global(item.rowptr);
     char *__restrict__ z = as_global(item.z) + slice * LPR * 16;
     const int lane = threadIdx.x & (kWave - 1);
@@ -579,7 +578,7 @@ size_t workspace_layout(int64_t nnz, int32_t f, Workspace *ws, void *base, int64
     // exact_ranges: the number of ranges of one particular call (a caller that knows the call and has little room)
     const int64_t ranges = exact_ranges > 0 ? exact_ranges
                                             : std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange) + 1;
-    const size_t o_carry = round_up((size_t)ranges * kMaxSlices * sizeof(RangeRec), 256);
+    const size_t o_carry = round_up((size_t)ranges * sizeof(RangeRec), 256);
     const size_t total = o_carry + round_up((size_t)ranges * 2 * f * sizeof(float), 256);
     if (ws) {
         char *b = static_cast<char *>(base);
@@ -774,7 +773,7 @@ extern "C" int dgnn_spmm_static(int64_t n, int64_t nnz, const int32_t *rowptr, c
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n + 1) || !fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // as many ranges as the array has room for records of: ranges grow longer where the usual ones would be too many
-    const int64_t max_ranges = (int64_t)((kStaticScratchBytes - 512) / (kMaxSlices * sizeof(RangeRec) + 2 * (size_t)f * sizeof(float)));
+    const int64_t max_ranges = (int64_t)((kStaticScratchBytes - 512) / (sizeof(RangeRec) + 2 * (size_t)f * sizeof(float)));
     if (range_length_of_call(nnz, f, dt, max_ranges) <= 0) return DGNN_ERR_CAPACITY;
     void *ptr = nullptr;
     const int rc = static_scratch(&ptr);

@@ -386,3 +386,14 @@ def test_table_columns_follow_the_number_of_rows():
     table.refresh(1, [1, 2, 3], 3)
     table.refresh(1, [1, 2, 3, 4], 4)
     assert table.words[:4, 1].tolist() == [1, 2, 3, 4] and not table.words[:, 0].any()
+
+
+def test_spmm_static_takes_as_many_ranges_as_fit(lib):
+    """A record of 16 bytes and two partial rows per range of at most 8192 entries, whatever the width and type.  (The call
+    that fits gets past the size check and is refused for its misaligned h, or without a device.)"""
+    for f in (16, 32, 64, 128):
+        most = ((32 << 20) - 512) // (16 + 8 * f) * 8192
+        for dt in (0, 1):
+            def call(nnz):
+                return lib.dgnn_spmm_static(1 << 20, nnz, FAKE, FAKE, None, FAKE + 4, f, FAKE + 4096, dt, 0, None)
+            assert call(most) in (-6, -7) and call(most + 1) == -3, (f, dt)

@@ -119,7 +119,7 @@ def test_smoothed_series_equals_step_by_step(n, rows, T, life, dels, adds, diag)
     assert all(torch.equal(c[max(1, int(r[n]) // 2):], k) for (r, c, v), k in zip(got, keep))
 
 
-@pytest.mark.parametrize("dtype,f", [(torch.float32, 16), (torch.float32, 64), (torch.bfloat16, 32), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("dtype,f", [(torch.float32, 16), (torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 32), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("count", [1, 3, 33])
 def test_batched_products_and_aggregations_equal_single_ones(dtype, f, count):
     """33 items: one more than a launch takes.  Snapshots of different sizes, hub rows over many ranges among them."""
@@ -152,6 +152,35 @@ def test_batched_products_and_aggregations_equal_single_ones(dtype, f, count):
     B.feature_transform_batch(count, a.at(), n, f, f, B.DGNN_RELU, dt, stream)
     dg.feature_transform(x[0], w[0], h1[0])
     assert torch.equal(h[0].float(), torch.relu(h1[0].float()))
+
+
+@pytest.mark.parametrize("dtype,f", [(torch.float32, 32), (torch.float32, 128), (torch.bfloat16, 64)])
+@pytest.mark.parametrize("count", [2, 33])
+def test_batched_aggregations_with_values_equal_single_ones(dtype, f, count):
+    """Rows scaled beforehand, as dgnn_spmm_weighted; and (fp32) scaled as they are gathered: value times dinv per entry."""
+    torch.manual_seed(count)
+    n, dt = 1 << 11, (B.DGNN_F32 if dtype == torch.float32 else B.DGNN_BF16)
+    snaps = [DynamicGraph(graph("rmat", n, 4 + 12 * (k % 3), 2, 0, 0, seed=k), device=DEV).csr() for k in range(count)]
+    nnz = [int(ci.numel()) for _, ci in snaps]
+    val, dinv = [torch.rand(m, device=DEV) + 0.5 for m in nnz], [torch.rand(n, device=DEV) for _ in range(count)]
+    h = [torch.randn(n, f, device=DEV).to(dtype) for _ in range(count)]
+    z, z1 = (torch.zeros(count, n, f, dtype=dtype, device=DEV) for _ in range(2))
+    b = SpmmTable(count)
+    for k, col in ((b.ROWPTR, [s[0] for s in snaps]), (b.COLIDX, [s[1] for s in snaps]), (b.DINV, dinv), (b.VAL, val), (b.H, h), (b.Z, list(z))):
+        b.column(k, pointers(col))
+    b.column(b.NNZ, nnz)
+    ws = torch.empty(B.spmm_batch_workspace(count, max(nnz), f), dtype=torch.uint8, device=DEV)
+    ws1 = torch.empty(dg.spmm_workspace(n, max(nnz), f), dtype=torch.uint8, device=DEV)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.spmm_batch(n, count, b.at(), f, dt, B.DGNN_RELU | B.DGNN_H_PRESCALED, ws, stream)
+    for k, (rp, ci) in enumerate(snaps):
+        dg.spmm_weighted(rp, ci, val[k], nnz[k], h[k], z1[k], ws1, flags=dg.DGNN_RELU | dg.DGNN_H_PRESCALED, dinv=dinv[k])
+    assert torch.equal(z, z1)
+    if dtype == torch.float32:
+        B.spmm_batch(n, count, b.at(), f, dt, 0, ws, stream)
+        for k, (rp, ci) in enumerate(snaps):
+            dg.spmm_weighted(rp, ci, val[k] * dinv[k][ci.long()], nnz[k], h[k], z1[k], ws1)
+            assert torch.equal(z[k], z1[k] * dinv[k][:, None]), k
 
 
 @pytest.mark.parametrize("name,n,T,keep", [("c1", 1000, 8, None), ("c2", 20_000, 7, True), ("c3", 1 << 12, 5, False), ("c4", 3_001, 35, None)])

@@ -63,12 +63,12 @@ def test_two_calls_in_a_row_second_one_smaller(dtype, f):
 
 
 def test_more_ranges_than_the_scratch_array_has_records_for():
-    """8.8 M stored entries at width 128 in fp32: the usual ranges (192 entries at this size and width) would need 46
-    thousand records of 1040 bytes, half as many again as the array holds, so this entry point makes its ranges longer.  Rows cut by a range's end are then summed in other pieces than in
+    """8.8 M stored entries at width 128 in fp32: the usual ranges (256 entries at this size and width) would need 34
+    thousand records of 1040 bytes, more than the array holds, so this entry point makes its ranges longer.  Rows cut by a range's end are then summed in other pieces than in
     dgnn_spmm: same result within the rounding of the sums, and within the bound against the oracle."""
     n, f = 1 << 19, 128
     rp, ci = power_law_snapshot(n, [(3, 50_000), (77_777, 9_000)], seed=9)
-    assert (16 + 8 * f) * (ci.size // 192) > dg.spmm_static_limit()
+    assert (16 + 8 * f) * (ci.size // 256) > dg.spmm_static_limit()
     h = torch.randn((n, f), generator=torch.Generator().manual_seed(5))
     z_ws, z_static = both_ways(rp, ci, h, dg.DGNN_RELU)
     assert_close(to_f64(z_static), to_f64(z_ws), torch.float32, "dgnn_spmm_static against dgnn_spmm")
