@@ -24,6 +24,7 @@ computes: every step runs in the HIP kernels.
 from __future__ import annotations
 
 import contextlib
+import weakref
 from typing import List, Optional, Tuple
 
 import torch
@@ -62,6 +63,13 @@ class _Chain:
 
     def slots_of(self, T: int) -> List[int]:
         return [self.slot_of(t) for t in range(1, T + 1)]
+
+
+def _stage_of(trainer):
+    """trainer._stage for the stack that it owns, which does not own it in turn: a trainer that is let go gives its memory back
+    at once and not when the garbage collector comes by."""
+    owner = weakref.ref(trainer)
+    return lambda name: owner()._stage(name)
 
 
 class GcnStack:
@@ -252,7 +260,7 @@ class BlockTrainer:
         self.timer = None
         arrays = [[side[k] for k in self.a.slots_of(T)] for side in (self.a.rowptr, self.a.colidx, self.a.dinv)]
         back = None if self.at is None else ([self.at.rowptr[k] for k in self.at.slots_of(T)], [self.at.colidx[k] for k in self.at.slots_of(T)], None)
-        self.stack = GcnStack(blk, cap, *arrays, transposed=back, want_dx=want_dx, stage=self._stage, together=None if self.series else 1)
+        self.stack = GcnStack(blk, cap, *arrays, transposed=back, want_dx=want_dx, stage=_stage_of(self), together=None if self.series else 1)
         self.z, self.dx = self.stack.z, self.stack.dx                     # activations of the block
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
         self.g = self.g_top = None                                        # dL/dZ of the last layer, if g_y must be kept; wherever it is
@@ -597,7 +605,7 @@ class SmoothedTrainer:
         self.timer = None
         arrays = [[s[k] for s in self.s] for k in range(3)]
         back = [[s[k] for s in self.st] for k in range(3)] if transposed else None
-        self.stack = GcnStack(blk, max(self.cap_s, blk.nnz[0]), arrays[0], arrays[1], self.dinv_s, vals=arrays[2], transposed=back, stage=self._stage)
+        self.stack = GcnStack(blk, max(self.cap_s, blk.nnz[0]), arrays[0], arrays[1], self.dinv_s, vals=arrays[2], transposed=back, stage=_stage_of(self))
         self.z = self.stack.z
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
         self.g = None

@@ -505,3 +505,38 @@ def test_weight_recurrence_without_a_bias():
         ev.backward(dw)
         out.append((ev.w, ev.c, ev.dw0, ev.du_x, ev.du_h, ev.db))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("kind", ["runner", "trainer", "smoothed", "checkpointed", "cdgcn"])
+def test_memory_comes_back_with_the_last_reference(kind):
+    """No driver holds itself: its buffers are free when it goes, without the garbage collector."""
+    import gc
+    from paper_2109_07893_amd import training
+    from paper_2109_07893_amd.cdgcn import CdgcnTrainer
+    wl = replace(graph("er", 2000, 6, 4, 0.05, 0.05), f=32, layers=2, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    weights = [torch.randn(s, device=DEV) for s in ((32, 32), (64, 128), (32, 128))]
+    gc.collect()
+    gc.disable()
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated(DEV)
+        if kind == "runner":
+            driver = BlockRunner(blk)
+            driver.load_first()
+            driver.run_resident()
+        elif kind == "cdgcn":
+            driver = CdgcnTrainer(blk, *weights, None, 32)
+            driver.load_first()
+        else:
+            driver = {"trainer": training.make_trainer, "smoothed": lambda w, b: training.make_smoothed_trainer(w, b, 2),
+                      "checkpointed": lambda w, b: training.CheckpointedTrainer(w, b, 2)}[kind](wl, blk)
+        if kind != "runner":
+            driver.forward()
+            driver.backward(g_y)
+        assert torch.cuda.memory_allocated(DEV) > before
+        del driver
+        assert torch.cuda.memory_allocated(DEV) == before
+    finally:
+        gc.enable()
