@@ -26,6 +26,7 @@
 // and 234 us); moving a stretch's entries to their new places in every step instead took 32 and 125 us.  Five smoothed snapshots
 // of 4.4 M entries 162 us, 340 us when the entries moved, 940 us one after the other.
 #include <algorithm>
+#include <cstddef>
 
 #include "common.hpp"
 
@@ -78,7 +79,7 @@ __device__ __forceinline__ void copy_lists(const Series &P, Lists &lists, int la
 
 struct RowPart {
     Lists lists;
-    int net[kSteps][kCountLd];               // entries per row, added less deleted, then (raw) their exclusive sums
+    alignas(16) int net[kSteps][kCountLd];   // entries per row, added less deleted, then (raw) their exclusive sums
     int bound[kSteps][4];                    // of the tile: added begin, deleted begin, added end, deleted end
 };
 struct StretchPart {
@@ -87,7 +88,7 @@ struct StretchPart {
     uint32_t bits[kCap];
     union {
         struct {
-            int before[kCap + 4];            // added entries per slot, then their exclusive sums
+            alignas(16) int before[kCap + 4];   // added entries per slot, then their exclusive sums
             uint64_t added[kAddCap];         // by slot
         } build;
         struct {
@@ -102,6 +103,7 @@ struct StretchPart {
     int bound[2][2], total_add, total_del;   // row and column at either end
 };
 static_assert(kSteps < 32, "a word of bits, and places for the ends of the parts");
+static_assert(offsetof(RowPart, net) % 16 == 0 && kCountLd % 4 == 0 && offsetof(StretchPart, build.before) % 16 == 0, "taken four words at a time");
 
 // Row pointers and dinv of every raw snapshot, or dinv of every smoothed one, for a tile of rows.
 template <Mode MODE>
