@@ -216,7 +216,8 @@ typedef struct {
  * A_2 .. A_{steps+1} from A_1 and the difference lists of the steps (Section "Graph-difference Based Input Transfer"): what
  * `steps` calls of dgnn_delta_rebuild give, bit for bit, in one or two launches per DGNN_SERIES_STEPS steps.  Every snapshot needs
  * rowptr and colidx arrays of its own (each colidx of `cap` entries, at least the stored entries of the densest snapshot),
- * different from A_1's; lists and preconditions as in dgnn_delta_rebuild, without its validation.
+ * different from A_1's; lists and preconditions as in dgnn_delta_rebuild, without its validation (no step starts from a snapshot
+ * without entries: DGNN_ERR_SHAPE).
  *   ws: scratch of dgnn_delta_rebuild_series_workspace() bytes for these lists (it looks at the tables' counts only).
  */
 int dgnn_delta_rebuild_series_workspace(int64_t nnz_first, int32_t steps, const dgnn_series_step *step, size_t *bytes);

@@ -683,6 +683,7 @@ extern "C" int dgnn_delta_rebuild_series(int64_t n, const int32_t *rowptr_first,
     for (int k = 0; k < steps; ++k) {
         const dgnn_series_step &st = step[k];
         if (!st.rowptr || !st.colidx) return DGNN_ERR_NULL;
+        if (nnz == 0) return DGNN_ERR_SHAPE;             // a step from a snapshot without entries, which the single call refuses too
         if (st.n_add < 0 || st.n_del < 0) return DGNN_ERR_SHAPE;
         if ((st.n_add > 0 && (!st.add_row || !st.add_col)) || (st.n_del > 0 && (!st.del_row || !st.del_col))) return DGNN_ERR_NULL;
         if (!fits_index(nnz + st.n_add)) return DGNN_ERR_OVERFLOW;

@@ -397,3 +397,18 @@ def test_spmm_static_takes_as_many_ranges_as_fit(lib):
             def call(nnz):
                 return lib.dgnn_spmm_static(1 << 20, nnz, FAKE, FAKE, None, FAKE + 4, f, FAKE + 4096, dt, 0, None)
             assert call(most) in (-6, -7) and call(most + 1) == -3, (f, dt)
+
+
+@pytest.mark.parametrize("before", [1, 30, 31])
+def test_series_refuses_a_step_from_an_empty_snapshot(lib, before):
+    """... as the single call does; 31 steps in front of it: the next launch would begin with it."""
+    steps = before + 1
+    table = (ctypes.c_uint64 * (9 * steps))()
+    for k in range(steps):
+        n_add, n_del = (0, 20) if k == before - 1 else (5, 0) if k == before else (0, 0)
+        table[9 * k:9 * k + 9] = [FAKE, FAKE, FAKE, FAKE, n_add, n_del, FAKE + 64 * (2 * k + 1), FAKE + 64 * (2 * k + 2), 0]
+    call = lib.dgnn_delta_rebuild_series
+    assert call(10, FAKE, FAKE, 20, steps, table, 64, FAKE, 0, None) == -2
+    assert call(10, FAKE, FAKE, 20, before, table, 64, FAKE, 0, None) == -3      # up to the empty one: on to the workspace, which is too small
+    single = lib.dgnn_delta_rebuild(10, FAKE, FAKE, 0, FAKE, FAKE, 5, FAKE, FAKE, 0, FAKE + 64, FAKE + 128, 64, None, None, FAKE, 1 << 20, 0, None, None)
+    assert single == -2
