@@ -692,35 +692,38 @@ extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *i
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
     if (!fits_index(n + 1)) return DGNN_ERR_OVERFLOW;
     if (!aligned16(ws)) return DGNN_ERR_ALIGN;
-    const bool weighted = items[0].val != nullptr;
+    const bool weighted = items[0].val != nullptr, normalised = items[0].dinv != nullptr;
+    size_t needed = 0;
+    auto ranges_of = [&](const dgnn_spmm_item &it, int &range_len) {
+        range_len = range_length_of_call(it.nnz, f, dt);
+        return (it.nnz + range_len - 1) / range_len;
+    };
+    int range_len;
     for (int k = 0; k < count; ++k) {
         const dgnn_spmm_item &it = items[k];
         if (!it.rowptr || !it.colidx || !it.h || !it.z) return DGNN_ERR_NULL;
-        if (it.nnz <= 0 || (it.val != nullptr) != weighted) return DGNN_ERR_SHAPE;
+        if (it.nnz <= 0 || (it.val != nullptr) != weighted || (it.dinv != nullptr) != normalised) return DGNN_ERR_SHAPE;
         if (weighted && !it.dinv && (flags & DGNN_H_PRESCALED)) return DGNN_ERR_SHAPE;
         if (!fits_index(it.nnz)) return DGNN_ERR_OVERFLOW;
         if (!aligned16(it.h) || !aligned16(it.z)) return DGNN_ERR_ALIGN;
         if (it.h == it.z) return DGNN_ERR_ALIAS;
+        needed += workspace_layout(it.nnz, f, nullptr, nullptr, ranges_of(it, range_len));
     }
+    if (ws_bytes < needed) return DGNN_ERR_CAPACITY;
+    // whether a per-entry factor is gathered is the launch's choice, not the item's
+    const bool scale_v = weighted || (normalised && !(flags & DGNN_H_PRESCALED));
     char *base = static_cast<char *>(ws);
     for (int done = 0; done < count; done += kMaxBatch) {
         const int m = std::min(count - done, kMaxBatch);
         Batch b;
         for (int k = 0; k < m; ++k) {
             const dgnn_spmm_item &it = items[done + k];
-            const int range_len = range_length_of_call(it.nnz, f, dt);
-            const int64_t ranges = (it.nnz + range_len - 1) / range_len;
+            const int64_t ranges = ranges_of(it, range_len);
             Workspace w;
-            const size_t size = workspace_layout(it.nnz, f, &w, base, ranges);
-            if ((size_t)(base - static_cast<char *>(ws)) + size > ws_bytes) return DGNN_ERR_CAPACITY;
-            base += size;
+            base += workspace_layout(it.nnz, f, &w, base, ranges);
             b.item[k] = Item{it.rowptr, it.colidx, it.dinv, it.val, static_cast<const char *>(it.h), static_cast<char *>(it.z), w.recs, w.carry,
                              (int32_t)it.nnz, range_len, (int32_t)ranges, it.dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0};
         }
-        // whether a per-entry factor is gathered is the launch's choice, not the item's
-        const bool scale_v = weighted || (b.item[0].dinv != nullptr && !(flags & DGNN_H_PRESCALED));
-        for (int k = 1; k < m; ++k)
-            if ((b.item[k].dinv != nullptr) != (b.item[0].dinv != nullptr)) return DGNN_ERR_SHAPE;
         const int rc = launch_width(n, m, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
         if (rc != DGNN_OK) return rc;
     }

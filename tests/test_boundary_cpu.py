@@ -412,3 +412,20 @@ def test_series_refuses_a_step_from_an_empty_snapshot(lib, before):
     assert call(10, FAKE, FAKE, 20, before, table, 64, FAKE, 0, None) == -3      # up to the empty one: on to the workspace, which is too small
     single = lib.dgnn_delta_rebuild(10, FAKE, FAKE, 0, FAKE, FAKE, 5, FAKE, FAKE, 0, FAKE + 64, FAKE + 128, 64, None, None, FAKE, 1 << 20, 0, None, None)
     assert single == -2
+
+
+def test_batched_aggregations_are_checked_before_the_first_of_them(lib):
+    """Faults of the 33rd item, which a second launch would take: a dinv that the others have not, a workspace too small."""
+    def items(odd=None, count=33):
+        table = (ctypes.c_uint64 * (7 * count))()
+        for k in range(count):
+            table[7 * k:7 * k + 7] = [FAKE, FAKE, odd if odd is not None and k == 32 else 0, 0, FAKE, FAKE + 4096, 20]
+        return table
+    call = lib.dgnn_spmm_batch
+    assert call(10, 33, items(odd=FAKE), 32, 0, 0, FAKE, 1 << 24, None) == -2
+    need, whole = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    assert lib.dgnn_spmm_batch_workspace(1, 20, 32, ctypes.byref(need)) == 0 and need.value > 0
+    assert lib.dgnn_spmm_batch_workspace(33, 20, 32, ctypes.byref(whole)) == 0 and whole.value >= 33 * need.value
+    assert call(10, 33, items(), 32, 0, 0, FAKE, 1000, None) == -3
+    one = 256 + 256                                  # a record and two rows of 32 floats, each rounded up to 256 bytes
+    assert call(10, 33, items(), 32, 0, 0, FAKE, 33 * one - 1, None) == -3
