@@ -42,8 +42,9 @@ constexpr int kXcds = 8;             // accelerator dies of an MI355X, each with
 constexpr int kXcdChunk = 16;        // consecutive ranges that go to the same XCD
 constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: all vector memory loads returned, other counters untouched
 
-enum : int32_t { kLeft = 1, kLeftClosed = 2, kRight = 4 };
-struct RangeRec { int32_t flags, row_last, pad0, pad1; };
+// What a range leaves for the carry kernel: the row that begins in it and goes on behind it, or -1.  How far that row reaches,
+// and with it whose left carries are its pieces, follows from the row pointers.
+struct RangeRec { int32_t open_row, pad0, pad1, pad2; };
 
 // One aggregation of a launch; blockIdx.y says which (a launch may take the aggregations of several timesteps).
 struct Item {
@@ -140,7 +141,7 @@ __device__ __forceinline__ void spmm_stream(
     nnz = min(nnz, rowptr[n]);
     const int e_begin = (int)((int64_t)range * range_len);
     if (e_begin >= nnz && range > 0) {                  // nothing stored here: a record that closes nothing and carries nothing
-        if (threadIdx.x == 0 && record) recs[range] = RangeRec{0, 0, 0, 0};
+        if (threadIdx.x == 0 && record) recs[range] = RangeRec{-1, 0, 0, 0};
         return;
     }
     const int e_end = (int)min((int64_t)e_begin + range_len, (int64_t)nnz);
@@ -155,7 +156,7 @@ __device__ __forceinline__ void spmm_stream(
     bool running = false;       // such a row exists
     bool began_here = false;    // ... and it began inside this range
     int run_row = 0;
-    int range_flags = 0;
+    int open_row = -1;
     float *my_carry = carry + (int64_t)range * 2 * F;
 
     // column indices (and their dinv) of the coming sub-tile: lane holds entries e + 32 g + sub CPL + i
@@ -413,7 +414,6 @@ __device__ __forceinline__ void spmm_stream(
                     } else {                             // end of the row inherited from the previous range
 #pragma unroll
                         for (int q = 0; q < NV; ++q) my_carry[lane * NV + q] = run[q];
-                        range_flags |= kLeft | kLeftClosed;
                     }
                     running = false;
 #pragma unroll
@@ -455,14 +455,13 @@ __device__ __forceinline__ void spmm_stream(
             if (began_here) {                            // goes on in the next range
 #pragma unroll
                 for (int q = 0; q < NV; ++q) my_carry[F + lane * NV + q] = run[q];
-                range_flags |= kRight;
+                open_row = run_row;
             } else {                                     // the whole range lies inside one row
 #pragma unroll
                 for (int q = 0; q < NV; ++q) my_carry[lane * NV + q] = run[q];
-                range_flags |= kLeft;
             }
         }
-        if (lane == 0 && record) recs[range] = RangeRec{range_flags, run_row, 0, 0};
+        if (lane == 0 && record) recs[range] = RangeRec{open_row, 0, 0, 0};
     }
     if (e_end == nnz)                                    // rows without entries beyond the last staged window
         for (int k = k_win + staged_last - 1 + lane; k < n; k += kWave)
@@ -491,8 +490,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) v
 // Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries of the following
 // ranges up to the one that holds the row's end (known from the row pointers).  A row over more than kOwnPieces ranges is
 // added up by the whole wavefront, its lane groups taking every G-th piece, so that a hub row is not one chain of dependent
-// loads (R-MAT, 2^20 vertices, 16 M entries: 31 -> 5 us; 2^18 vertices: 25 -> 5 us).  The order of the sum depends on the
-// row's extent alone.
+// loads (R-MAT, 2^20 vertices, 16 M entries: 31 -> 5 us; 2^18 vertices: 25 -> 5 us).  The order of the sum depends on
+// the row's extent and the range length alone.
 constexpr int kOwnPieces = 4;
 
 template <int LPR, int SLICES, bool BF16>
@@ -512,11 +511,8 @@ __global__ __launch_bounds__(256) void spmm_carry_kernel(int relu, Batch batch) 
     const int t = first + g;
     int row = -1, last = 0;
     if (t < item.n_ranges) {
-        const RangeRec rec = recs[t];
-        if (rec.flags & kRight) {
-            row = rec.row_last;
-            last = min((rowptr[row + 1] - 1) / item.range_len, item.n_ranges - 1);
-        }
+        row = recs[t].open_row;
+        if (row >= 0) last = min((rowptr[row + 1] - 1) / item.range_len, item.n_ranges - 1);
     }
     auto left = [&](int j, int q) { return carry[(int64_t)j * 2 * F + sub * NV + q]; };
     const bool own = row >= 0 && last - t <= kOwnPieces;
