@@ -4,7 +4,6 @@ include/dgnn.h: device pointers and counts; the drivers fill it once and refresh
 replaced (features, weights, difference lists)."""
 from __future__ import annotations
 
-import ctypes
 from typing import List, Optional, Sequence
 
 import numpy as np

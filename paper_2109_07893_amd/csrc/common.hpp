@@ -152,9 +152,6 @@ __device__ __forceinline__ int lower4(int lo, int hi, uint64_t key, Get get) {
     while (len > 0 && get(lo) < key) { ++lo; --len; }
     return lo;
 }
-__device__ __forceinline__ int lower_key(const int32_t *__restrict__ row, const int32_t *__restrict__ col, int lo, int hi, uint64_t key) {
-    return lower4(lo, hi, key, [=](int i) { return ((uint64_t)(uint32_t)row[i] << 32) | (uint32_t)col[i]; });
-}
 
 // ---- 16-byte pieces of feature rows: 4 fp32 or 8 bf16 values, unpacked to and packed from fp32 ------------
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
