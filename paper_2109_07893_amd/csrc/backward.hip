@@ -113,7 +113,7 @@ __device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *_
 #pragma unroll
             for (int tj = 0; tj < S::TJ; ++tj) {
                 bool ok = row_ok && (jt0 + tj) * 32 + i < FOUT;
-                if constexpr (MASKED && BF16) ok = ok && zb_next[tj][e] - 1u < 0x7fffu;      // a positive bf16: sign clear, not zero
+                if constexpr (MASKED && BF16) ok = ok && zb_next[tj][e] - 1u < 0x7f80u;      // a positive bf16: sign clear, not zero, no NaN
                 if constexpr (MASKED && !BF16) ok = ok && zb_next[tj][e] > 0.0f;
                 gb[tj][e] = ok ? gb_next[tj][e] : Raw(0);
             }

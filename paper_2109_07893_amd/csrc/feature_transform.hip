@@ -410,9 +410,11 @@ __device__ __forceinline__ void xw_bf16_staged(const uint16_t *__restrict__ x, c
                 const int64_t piece = tile * (32 * OUTW / 8) + q * kWave + lane;
                 if (piece * 8 < n * OUTW) {
                     uintx4 v = *reinterpret_cast<const uintx4 *>(&tile_lds[(e / OUTW) * LDT + e % OUTW]);
-                    if (CONCAT || relu) {      // a bf16 with its sign bit set becomes zero (a negative zero too)
+                    if (CONCAT || relu) {      // a bf16 with its sign bit set becomes zero (a negative zero too); a NaN where fmaxf drops it
+                        constexpr uint32_t kMost = CONCAT ? 0x7fffu : 0x7f80u;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = ((v[c] & 0x8000u) ? 0u : (v[c] & 0xffffu)) | ((v[c] & 0x80000000u) ? 0u : (v[c] & 0xffff0000u));
+                        for (int c = 0; c < 4; ++c)
+                            v[c] = ((v[c] & 0xffffu) > kMost ? 0u : (v[c] & 0xffffu)) | ((v[c] >> 16) > kMost ? 0u : (v[c] & 0xffff0000u));
                     }
                     __builtin_nontemporal_store(v, reinterpret_cast<uintx4 *>(h) + piece);
                 }

@@ -10,7 +10,7 @@ import paper_2109_07893_amd as dg
 from dtdg_synth import WORKLOADS, DynamicGraph
 from dtdg_synth.blocks import make_block
 from paper_2109_07893_amd import binding as B
-from paper_2109_07893_amd.batch import SeriesTable, SmoothTable, SpmmTable, TransformTable, pointers
+from paper_2109_07893_amd.batch import SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers
 from paper_2109_07893_amd.pipeline import BlockRunner
 
 pytestmark = pytest.mark.gpu
@@ -540,3 +540,34 @@ def test_memory_comes_back_with_the_last_reference(kind):
         assert torch.cuda.memory_allocated(DEV) == before
     finally:
         gc.enable()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("f", [16, 32, 128])
+def test_a_nan_does_not_pass_the_relu(dtype, f):
+    """The dense transform's ReLU gives 0 for a NaN of either sign, as the aggregation's does, and the gradient's mask is 0 there;
+    infinities are ordinary values."""
+    n, nan = 100, float("nan")
+    x = torch.randn(n, f, device=DEV).to(dtype)
+    x[3, 0], x[40, 1], x[41, 1] = nan, -nan, nan
+    w, h = torch.eye(f, device=DEV).to(dtype), torch.empty_like(x)
+    a = TransformTable(1)
+    a.words[0] = (x.data_ptr(), w.data_ptr(), 0, h.data_ptr())
+    dt = B.DGNN_F32 if dtype == torch.float32 else B.DGNN_BF16
+    B.feature_transform_batch(1, a.at(), n, f, f, B.DGNN_RELU, dt, torch.cuda.current_stream().cuda_stream)
+    want = torch.relu(x)
+    want[[3, 40, 41]] = 0                                # a row with a NaN in it is all NaN behind the product
+    assert torch.equal(h, want)
+    z = torch.randn(n, f, device=DEV).to(dtype)
+    g = torch.randn(n, f, device=DEV).to(dtype)
+    z[5, :4] = torch.tensor([nan, -nan, float("inf"), -float("inf")], device=DEV).to(dtype)
+    x = torch.randn(n, f, device=DEV).to(dtype)
+    out, ws = [], torch.empty(dg.weight_grad_workspace(f, f), dtype=torch.uint8, device=DEV)
+    for mask in (z, torch.nan_to_num(z, nan=0.0)):
+        dw, table = torch.empty(f, f, device=DEV), WeightGradTable(1)
+        table.words[0] = (x.data_ptr(), g.data_ptr(), mask.data_ptr(), dw.data_ptr())
+        B.weight_grad_batch(1, table.at(), n, f, f, False, dt, ws, torch.cuda.current_stream().cuda_stream)
+        out.append(dw)
+    assert torch.equal(*out) and bool(torch.isfinite(out[0]).all())
+    exp = x.double().T @ torch.where(torch.nan_to_num(z, nan=0.0) > 0, g, torch.zeros_like(g)).double()
+    assert float((out[0] - exp).abs().max()) <= 1e-4 * n ** 0.5 * float(exp.abs().max())
