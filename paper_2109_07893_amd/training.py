@@ -388,12 +388,13 @@ class BlockTrainer:
         if self.stack.p0 is None:
             return self.stack.h[0]
         blk, slot = self.blk, self.a.slot_of(1)
-        assert self.g_top is not None and blk.layers == 1, "after backward() of a one-layer block"
+        assert self.g_top is not None, "after backward()"
+        g = self.g_top[0] if blk.layers == 1 else self.stack.g_mid[0]       # dL/dZ of the first layer and timestep
         rowptr, colidx, dinv = self.a.rowptr[slot], self.a.colidx[slot], self.a.dinv[slot]
         if self.directed:
             rowptr, colidx = B.csr_transpose(rowptr, colidx, blk.nnz[0])
-        g_p, g_h = torch.empty_like(self.g_top[0]), torch.empty_like(self.g_top[0])
-        B.relu_backward(self.g_top[0], self.z[0, 0], g_p, row_scale=dinv)
+        g_p, g_h = torch.empty_like(g), torch.empty_like(g)
+        B.relu_backward(g, self.z[0, 0], g_p, row_scale=dinv)
         ws = torch.empty(B.spmm_workspace(blk.n, blk.nnz[0], blk.f), dtype=torch.uint8, device=self.dev)
         B.spmm(rowptr, colidx, blk.nnz[0], dinv, g_p, g_h, ws, flags=B.DGNN_H_PRESCALED)
         return g_h

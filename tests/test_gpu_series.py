@@ -571,3 +571,27 @@ def test_a_nan_does_not_pass_the_relu(dtype, f):
     assert torch.equal(*out) and bool(torch.isfinite(out[0]).all())
     exp = x.double().T @ torch.where(torch.nan_to_num(z, nan=0.0) > 0, g, torch.zeros_like(g)).double()
     assert float((out[0] - exp).abs().max()) <= 1e-4 * n ** 0.5 * float(exp.abs().max())
+
+
+@pytest.mark.parametrize("graph_kind", ["er", "rmat"])
+@pytest.mark.parametrize("layers", [1, 2, 3])
+def test_gradient_in_front_of_the_first_product(graph_kind, layers):
+    """BlockTrainer.h after a step: A~_1^T of the first layer's masked gradient, whatever the number of layers."""
+    from paper_2109_07893_amd import training
+    wl = replace(graph(graph_kind, 512, 6, 4, 0.05, 0.05), f=16, layers=layers, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    tr = training.make_trainer(wl, blk)
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    tr.forward()
+    tr.backward(g_y)
+    n, rows = wl.n, torch.repeat_interleave(torch.arange(wl.n, device=DEV), blk.rowptr1.diff())
+    a = torch.zeros((n, n), dtype=torch.float64, device=DEV)
+    a[rows, blk.colidx1.long()] = 1.0
+    d = a.sum(1).rsqrt()
+    a = d[:, None] * a * d[None, :]
+    g = g_y[0].double()
+    for layer in range(layers - 1, -1, -1):
+        g = a.T @ torch.where(tr.z[layer, 0] > 0, g, torch.zeros_like(g))
+        if layer > 0:
+            g = g @ blk.w[layer].double().T
+    assert float((tr.h - g).abs().max()) <= 1e-4 * float(g.abs().max())
