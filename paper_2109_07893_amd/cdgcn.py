@@ -46,6 +46,7 @@ class CdgcnLayer(BlockRunner):
         self.xs = torch.empty((m, n, f), dtype=dt, device=dev) if self.prescale else None
         self.y0_batch = torch.empty((m, n, f), dtype=dt, device=dev)
         self.y_batch = torch.empty((m, n, f + f_out), dtype=dt, device=dev)
+        self.y0, self.y = self.y0_batch[0], self.y_batch[0]                     # of the timestep that form_y is asked for
         self.lstm_fused = fused and B.lstm_step_supported(self.y_batch, hidden)
         self.y1 = self.gx = self.gh = None
         if not (fused and B.transform_concat_relu_supported(self.y0_batch[0], f_out)):
@@ -76,6 +77,12 @@ class CdgcnLayer(BlockRunner):
         self.ws_batch = torch.empty(B.spmm_batch_workspace(self.together, self.cap, blk.f), dtype=torch.uint8, device=self.dev)
         return scaled, b
 
+    def _overrides(self, name: str) -> bool:
+        return getattr(type(self), name) is not getattr(CdgcnLayer, name)
+
+    def _series_pays(self) -> bool:
+        return super()._series_pays() and not (self._overrides("step") or self._overrides("form_y"))     # ... is asked for every timestep
+
     def rebuild_all(self) -> None:
         """Every snapshot of the block (where the block is small enough to be rebuilt in one go)."""
         blk, one = self.blk, self.slot_of(1)
@@ -103,8 +110,19 @@ class CdgcnLayer(BlockRunner):
                 B.feature_transform_batch(k, scaled.at(t), n, f, f, 0, dt, stream)
         with self._stage("spmm"):
             B.spmm_batch(n, k, b.at(t), f, dt, B.DGNN_H_PRESCALED if self.prescale else 0, self.ws_batch, stream)
-        rows = k * n
-        y0, y = y0.view(rows, f), y.view(rows, f + self.f_out)
+        if self._overrides("form_y"):
+            self.y0, self.y = y0[0], y[0]
+            self.form_y()
+        else:
+            self._form(k, y0, y)
+
+    def form_y(self) -> None:
+        """Y = relu(Y0 o Y0 W) of one timestep from self.y0 into self.y."""
+        self._form(1, self.y0, self.y)
+
+    def _form(self, k: int, y0: torch.Tensor, y: torch.Tensor) -> None:
+        rows = k * self.blk.n
+        y0, y = y0.view(rows, self.blk.f), y.view(rows, self.blk.f + self.f_out)
         if self.y1 is None:
             with self._stage("transform_concat_relu"):
                 B.transform_concat_relu(y0, self.w, y)
@@ -150,6 +168,13 @@ class CdgcnLayer(BlockRunner):
     def run(self) -> torch.Tensor:
         """The whole block from the initial state (h, c) = 0; returns h_t for t = 1..T."""
         blk, m = self.blk, self.together
+        if self._overrides("step"):
+            self.c.zero_()
+            for t in range(1, blk.T + 1):
+                if t >= 2:
+                    self.rebuild(t, blk.deltas[t - 2])
+                self.step(t)
+            return self.h_all
         self._bind()
         if self.series:
             self.rebuild_all()

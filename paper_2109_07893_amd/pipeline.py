@@ -130,7 +130,7 @@ class BlockRunner:
     def _series_pays(self) -> bool:
         """Whether a pass over resident lists rebuilds all snapshots first (dgnn_delta_rebuild_series) and then takes the
         GCN steps of several timesteps together."""
-        if any(getattr(type(self), name) is not getattr(BlockRunner, name) for name in ("rebuild", "transform_first", "gcn", "snapshot_ready")):
+        if any(getattr(type(self), name) is not getattr(BlockRunner, name) for name in ("rebuild", "transform_first", "gcn", "snapshot_ready", "slot_of")):
             return False                    # a subclass that does something of its own per snapshot is asked for every one
         return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES and snapshots_fit(self.blk.T, self.blk.n, self.cap)
 

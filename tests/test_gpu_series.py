@@ -595,3 +595,56 @@ def test_gradient_in_front_of_the_first_product(graph_kind, layers):
         if layer > 0:
             g = g @ blk.w[layer].double().T
     assert float((tr.h - g).abs().max()) <= 1e-4 * float(g.abs().max())
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_cdgcn_subclasses_are_asked_for_every_timestep(fused):
+    from paper_2109_07893_amd.cdgcn import CdgcnLayer, CdgcnTrainer
+    wl = replace(WORKLOADS["c1"], f=32)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    weights = [torch.randn(s, device=DEV) * 0.2 for s in ((32, 32), (64, 128), (32, 128))]
+    g_h = torch.randn((wl.T, wl.n, 32), device=DEV)
+    seen = []
+
+    class Steps(CdgcnLayer):
+        def step(self, t):
+            seen.append(t)
+            super().step(t)
+
+    class Forms:
+        def form_y(self):
+            seen.append(self.y.data_ptr())
+            super().form_y()
+
+    class FormsLayer(Forms, CdgcnLayer):
+        pass
+
+    class FormsTrainer(Forms, CdgcnTrainer):
+        pass
+
+    class SlotsOfItsOwn(BlockRunner):
+        def slot_of(self, t):
+            seen.append(t)
+            return super().slot_of(t)
+    plain = CdgcnLayer(blk, *weights, None, 32, fused=fused)
+    plain.load_first()
+    want = plain.run().clone()
+    for kind in (Steps, FormsLayer):
+        seen.clear()
+        layer = kind(blk, *weights, None, 32, fused=fused)
+        layer.load_first()
+        assert torch.equal(layer.run(), want) and len(seen) == wl.T, kind
+        assert kind is FormsLayer or seen == list(range(1, wl.T + 1))
+    for keep in (True, False):
+        grads = []
+        for kind in (CdgcnTrainer, FormsTrainer):
+            tr = kind(blk, *weights, None, 32, fused=fused, keep_activations=keep)
+            tr.load_first()
+            seen.clear()
+            assert torch.equal(tr.forward(), want)
+            tr.backward(g_h)
+            grads.append([g.clone() for g in (tr.dw, tr.dw_x, tr.dw_h, tr.db)])
+        assert len(seen) >= wl.T
+        for a, b in zip(*grads):
+            assert float((a - b).norm()) <= 1e-5 * float(a.norm())
+    assert not SlotsOfItsOwn(blk).series and BlockRunner(blk).series
