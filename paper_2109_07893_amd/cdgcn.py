@@ -20,9 +20,6 @@ from .pipeline import BlockInputs, BlockRunner
 
 # Bytes of gate gradients (N x 4 hidden per timestep) that one call of the adjoint leaves for the weight gradients behind it.
 GATE_BYTES = 1 << 30
-# Bytes of Y0 and Y of a whole block up to which a trainer keeps them also where it was asked to recompute them: recomputing
-# trades time for memory, and this is a three-hundredth of the device's.
-SMALL_ACTIVATIONS = 1 << 30
 
 
 class CdgcnLayer(BlockRunner):
@@ -189,8 +186,8 @@ class CdgcnLayer(BlockRunner):
 
 class CdgcnTrainer(CdgcnLayer):
     """Forward and backward over one block for the CD-GCN layer (Section "CD-GCN", trained as in Section "Gradient
-    Checkpoint": the forward pass keeps only the LSTM states (h_t, c_t) of every timestep, and Y0 and Y where they are kept or
-    small; the backward pass walks the timesteps in reverse, recomputing what was not kept):
+    Checkpoint": the forward pass keeps only the LSTM states (h_t, c_t) of every timestep, and Y0 and Y where they are asked
+    for; the backward pass walks the timesteps in reverse, recomputing what was not kept):
 
         a stretch of timesteps, last stretch first:
             (da, dY1, dh, dc) <- adjoint of the LSTM and of Y's ReLU               dgnn_lstm_series_backward
@@ -226,10 +223,14 @@ class CdgcnTrainer(CdgcnLayer):
         # With keep_activations the forward pass also keeps Y0 and Y of every timestep (N x (2F + F') per step: 6.4 GB
         # at c5's size, a matter of course in 288 GB) and the backward pass neither recomputes the GCN operation
         # nor needs the snapshots again; without, only the LSTM states are kept, as gradient checkpointing has it.
-        self.keep = keep_activations or T * n * (2 * f + f_out) * self.y_batch.element_size() <= SMALL_ACTIVATIONS
-        if self.keep:
+        # Where the batch buffers hold the whole block they are still there without being asked for.
+        self.keep = keep_activations or m >= T
+        if m >= T:
+            self.y0_all, self.y_all = self.y0_batch, self.y_batch
+        elif self.keep:
             self.y0_all = torch.empty((T, n, f), dtype=dt, device=dev)
             self.y_all = torch.empty((T, n, f + f_out), dtype=dt, device=dev)
+        if self.keep:
             self._aggregations = self._aggregation_tables(list(self.y0_all))
         self.c_all = torch.zeros((T + 1, n, hidden), dtype=dt, device=dev)     # c_0 = 0, c_t after step t
         self.dw = torch.zeros((f, f_out), dtype=torch.float32, device=dev)

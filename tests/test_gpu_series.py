@@ -648,3 +648,34 @@ def test_cdgcn_subclasses_are_asked_for_every_timestep(fused):
         for a, b in zip(*grads):
             assert float((a - b).norm()) <= 1e-5 * float(a.norm())
     assert not SlotsOfItsOwn(blk).series and BlockRunner(blk).series
+
+
+@pytest.mark.parametrize("dtype,f", [("f32", 32), ("f32", 16), ("bf16", 32)])
+@pytest.mark.parametrize("n,T", [(1000, 5), (30_001, 7)])
+def test_cdgcn_trainer_recomputes_what_it_was_not_asked_to_keep(dtype, f, n, T, monkeypatch):
+    """Y0 and Y take memory only where they are asked for, and the gradients agree; 30 001 vertices: three timesteps together,
+    several stretches going back."""
+    from paper_2109_07893_amd import batch
+    from paper_2109_07893_amd.cdgcn import CdgcnTrainer
+    wl = replace(graph("er", n, 6, T, 0.05, 0.05), f=f, dtype=dtype, layers=1, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    dt = blk.x[0].dtype
+    weights = [(torch.randn(s, device=DEV) * 0.2).to(dt) for s in ((f, f), (2 * f, 4 * f), (f, 4 * f))]
+    g_h = torch.randn((T, n, f), device=DEV).to(dt)
+    if n > 1000:
+        monkeypatch.setattr(batch, "BATCH_BYTES", 3 * n * f * weights[0].element_size())
+    out, held = [], []
+    for keep in (True, False):
+        before = torch.cuda.memory_allocated(DEV)
+        tr = CdgcnTrainer(blk, *weights, None, f, keep_activations=keep)
+        assert tr.together == (T if n == 1000 else 3)
+        tr.load_first()
+        held.append(torch.cuda.memory_allocated(DEV) - before)
+        h = tr.forward().clone()
+        tr.backward(g_h)
+        out.append([h] + [g.clone() for g in (tr.dw, tr.dw_x, tr.dw_h, tr.db)])
+        del tr
+    frames = n * 3 * f * weights[0].element_size()
+    assert held[0] - held[1] >= (0 if n == 1000 else T * frames) // 2 and torch.equal(out[0][0], out[1][0])
+    for a, b in zip(out[0][1:], out[1][1:]):
+        assert float((a - b).norm()) <= 2e-5 * float(a.norm())
