@@ -31,6 +31,8 @@ class CdgcnLayer(BlockRunner):
     def __init__(self, blk: BlockInputs, w: torch.Tensor, w_x: torch.Tensor, w_h: torch.Tensor,
                  bias: Optional[torch.Tensor], hidden: int, fused: bool = True):
         super().__init__(blk, keep_all_z=False)
+        if self.series:
+            self._widen()
         self.fused = fused            # one-kernel LSTM (and Y) where the library has the widths
         n, f, m = blk.n, blk.f, self.together
         f_out = w.shape[1]

@@ -91,17 +91,15 @@ class BlockRunner:
         self.cap = cap
         # CSR slots: slot 2 keeps A_1 for the whole life of the block (so a pass can be repeated), slots 0 and 1 are used
         # alternately by A_2, A_3, ...: A_{t-1} is read while A_t is written.  Where the whole block is rebuilt in one go
-        # every timestep but the last two has a slot of its own behind these
+        # every timestep but the last two has a slot of its own behind these, see _widen
         self.series = self._series_pays()
         self.together = steps_together(n * f * blk.x[0].element_size(), blk.T) if self.series else 1
-        slots = max(blk.T, 3) if self.series else 3
-        self.rowptr = [torch.empty(n + 1, dtype=torch.int32, device=dev) for _ in range(slots)]
-        self.colidx = [torch.empty(cap, dtype=torch.int32, device=dev) for _ in range(slots)]
-        self.dinv = [torch.empty(n, dtype=torch.float32, device=dev) for _ in range(slots)]
-        self.h_batch = torch.empty((self.together, n, f), dtype=dt, device=dev)
-        self.h = self.h_batch[0]
-        self.z_mid_batch = torch.empty((self.together, n, f), dtype=dt, device=dev) if blk.layers > 1 else None
-        self.z_mid = self.z_mid_batch[0] if blk.layers > 1 else None
+        self.rowptr, self.colidx, self.dinv = [], [], []
+        self._add_slots(3)
+        wide = self.series and blk.pinned is None
+        self.h_batch = torch.empty((self.together if wide else 1, n, f), dtype=dt, device=dev)
+        self.z_mid_batch = torch.empty_like(self.h_batch) if blk.layers > 1 else None
+        self.h, self.z_mid = self.h_batch[0], self.z_mid_batch[0] if blk.layers > 1 else None
         self.keep_all_z = bool(blk.window) if keep_all_z is None else keep_all_z
         zt = blk.T if self.keep_all_z else 1
         self.z = torch.empty((zt, n, f), dtype=dt, device=dev)
@@ -113,7 +111,9 @@ class BlockRunner:
         self.ws_spmm = torch.empty(ws_s, dtype=torch.uint8, device=dev)
         self.status = torch.zeros(blk.T + 1, dtype=torch.int32, device=dev)
         self.timer: Optional[StageTimer] = None
-        self._tables = self._make_tables() if self.series else None
+        self._tables = None
+        if wide:
+            self._widen()
         # staging for difference lists that arrive from pinned host memory (two sets, used alternately)
         self.stage = None
         if blk.pinned is not None:
@@ -134,8 +134,26 @@ class BlockRunner:
             return False                    # a subclass that does something of its own per snapshot is asked for every one
         return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES and snapshots_fit(self.blk.T, self.blk.n, self.cap)
 
+    def _add_slots(self, count: int) -> None:
+        n, dev = self.blk.n, self.dev
+        self.rowptr += [torch.empty(n + 1, dtype=torch.int32, device=dev) for _ in range(count)]
+        self.colidx += [torch.empty(self.cap, dtype=torch.int32, device=dev) for _ in range(count)]
+        self.dinv += [torch.empty(n, dtype=torch.float32, device=dev) for _ in range(count)]
+
+    def _widen(self) -> None:
+        """The further slots and buffers of a pass that takes several timesteps at a time: made with the runner, but for a block with
+        pinned lists with its first such pass: passes that copy the lists need three slots."""
+        blk, m = self.blk, self.together
+        if self._tables is not None:
+            return
+        self._add_slots(max(blk.T, 3) - 3)
+        if m > self.h_batch.shape[0]:                   # (h and z_mid stay where they are)
+            self.h_batch = torch.empty((m, blk.n, blk.f), dtype=self.h.dtype, device=self.dev)
+            self.z_mid_batch = torch.empty_like(self.h_batch) if blk.layers > 1 else None
+        self._tables = self._make_tables()
+
     def slot_of(self, t: int) -> int:
-        if self.series and 1 < t < self.blk.T - 1:
+        if len(self.rowptr) > 3 and 1 < t < self.blk.T - 1:
             return t + 1
         return 2 if t == 1 else t % 2
 
@@ -276,6 +294,7 @@ class BlockRunner:
         """All snapshots, then the GCN steps `together` timesteps at a time; the same kernels on the same operands as one
         step after the other, bit for bit."""
         blk = self.blk
+        self._widen()
         tb, n, f, T, m = self._tables, blk.n, blk.f, blk.T, self.together
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         dt = B._dtype_code(self.h)

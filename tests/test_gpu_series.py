@@ -679,3 +679,31 @@ def test_cdgcn_trainer_recomputes_what_it_was_not_asked_to_keep(dtype, f, n, T, 
     assert held[0] - held[1] >= (0 if n == 1000 else T * frames) // 2 and torch.equal(out[0][0], out[1][0])
     for a, b in zip(out[0][1:], out[1][1:]):
         assert float((a - b).norm()) <= 2e-5 * float(a.norm())
+
+
+@pytest.mark.parametrize("layers,window", [(1, 0), (2, 3)])
+def test_pinned_blocks_keep_three_slots_until_a_resident_pass(layers, window):
+    """Passes over pinned lists need three snapshots' arrays; passes of either kind, in any order, give the same frames."""
+    wl = replace(graph("er", 3000, 6, 9, 0.05, 0.05), f=16, layers=layers, window=window)
+    blk = make_block(wl, DEV, pinned=True)
+    plain = BlockRunner(replace(blk, pinned=None), keep_all_z=True)
+    plain.load_first()
+    plain.run_resident()
+    runner = BlockRunner(blk, keep_all_z=True)
+    assert runner.series and len(runner.rowptr) == 3 and len(plain.rowptr) == wl.T
+    runner.load_first()
+    for resident, overlap in ((False, False), (False, True), (True, True), (True, False), (False, False), (False, True), (True, False)):
+        runner.z.zero_()
+        (runner.run_resident if resident else runner.run_from_pinned)(overlap=overlap)
+        torch.cuda.synchronize()
+        assert torch.equal(runner.z, plain.z), (resident, overlap)
+        a, b = runner.slot_of(wl.T), plain.slot_of(wl.T)
+        assert torch.equal(runner.rowptr[a], plain.rowptr[b]) and torch.equal(runner.dinv[a], plain.dinv[b])
+    assert len(runner.rowptr) == wl.T
+    torch.cuda.synchronize()
+    graph_ = runner.capture()
+    for _ in range(3):
+        runner.z.zero_()
+        graph_.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(runner.z, plain.z)
