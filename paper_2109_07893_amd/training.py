@@ -25,6 +25,7 @@ from __future__ import annotations
 
 import contextlib
 import weakref
+from dataclasses import replace
 from typing import List, Optional, Tuple
 
 import torch
@@ -400,12 +401,19 @@ class BlockTrainer:
         return g_h
 
 
+# Bytes of A~ X over the timesteps of a block up to which it is kept.  It comes on top of what the step holds in any case (X, Z of
+# every layer, Y and the gradients, layers + 4 tensors of the same size at most); a block that fills the device's 288 GB without
+# it is to fit as well, and aggregates again on the way back.
+AGGREGATED_BYTES = 16 << 30
+
+
 def first_layer_keeps_aggregated(blk: BlockInputs, want_dx: bool = False, weighted: bool = False) -> bool:
     """Whether the first layer is evaluated as relu((A~ X) W) with A~ X kept, so that its weight gradient needs no aggregation.
     Only in fp32: a bf16 A~ X is rounded once per row before the product and the ReLU see it, where the roundings of X W average
     out over a row's neighbours (features that are all positive, 16 neighbours: dW 1.6 to 3.2 times as far from 64 bits).  And
     not with values and further layers above, where the transposed snapshots are resident anyway."""
-    return blk.x[0].dtype == torch.float32 and not want_dx and not (weighted and blk.layers > 1)
+    fits = blk.T * blk.n * blk.f * 4 <= AGGREGATED_BYTES
+    return blk.x[0].dtype == torch.float32 and fits and not want_dx and not (weighted and blk.layers > 1)
 
 
 def needs_transposed(blk: BlockInputs, want_dx: bool = False, weighted: bool = False) -> bool:
@@ -473,7 +481,7 @@ class CheckpointedTrainer:
             (torch.empty_like(series.rowptr1), torch.empty(max(series.nnz), dtype=torch.int32, device=dev))
             for a, _ in self.bounds[1:]]
         self.t_first, self.t_deltas = None, None
-        if self.directed and needs_transposed(series):
+        if self.directed and needs_transposed(replace(series, T=self.bounds[0][1])):
             (rp_t, tc), self.t_deltas = transposed_inputs(series)
             self.t_first = [(rp_t, tc)] + [(torch.empty_like(rp_t), torch.empty(max(series.nnz), dtype=torch.int32, device=dev))
                                            for a, _ in self.bounds[1:]]

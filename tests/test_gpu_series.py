@@ -219,9 +219,10 @@ def test_weight_gradient_through_the_relu(dtype, f_in, f_out, n):
 
 
 @pytest.mark.parametrize("name,layers", [("c1", 1), ("c1", 2), ("c3", 1), ("c3", 2), ("c4", 1)])
-@pytest.mark.parametrize("what", ["SERIES_ENTRIES", "GATHERED_DINV_ROWS"])
+@pytest.mark.parametrize("what", ["SERIES_ENTRIES", "GATHERED_DINV_ROWS", "AGGREGATED_BYTES"])
 def test_trainer_on_both_sides_of_its_size_rules(name, layers, what, monkeypatch):
-    """The trainer at small sizes with the rules for large ones: rebuilds step by step, rows of X scaled beforehand."""
+    """The trainer at small sizes with the rules for large ones: rebuilds step by step, rows of X scaled beforehand, A~ X
+    not kept."""
     from dtdg_synth import gradient
     from paper_2109_07893_amd import training
     wl = replace(WORKLOADS[name] if name == "c1" else WORKLOADS[name].scaled(1 << 11, T=5), layers=layers, window=3 if layers == 2 else 0)
@@ -233,6 +234,7 @@ def test_trainer_on_both_sides_of_its_size_rules(name, layers, what, monkeypatch
             monkeypatch.setattr(training, what, 0)
         tr = training.make_trainer(wl, blk)
         assert tr.series == (not patched or what != "SERIES_ENTRIES")
+        assert (tr.stack.p0 is not None) == (wl.dtype == "f32" and (not patched or what != "AGGREGATED_BYTES"))
         y = tr.forward()
         tr.backward(g_y.to(y.dtype))
         torch.cuda.synchronize()
@@ -707,3 +709,21 @@ def test_pinned_blocks_keep_three_slots_until_a_resident_pass(layers, window):
         graph_.replay()
         torch.cuda.synchronize()
         assert torch.equal(runner.z, plain.z)
+
+
+@pytest.mark.parametrize("graph_kind", ["er", "rmat"])
+def test_checkpointed_blocks_decide_by_their_own_length(graph_kind, monkeypatch):
+    """A~ X is kept where that of a block fits, whatever the length of the series."""
+    from paper_2109_07893_amd import training
+    wl = replace(graph(graph_kind, 1 << 10, 6, 9, 0.05, 0.05), f=16, layers=1, window=3)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    frame, grads = wl.n * wl.f * 4, []
+    for limit, keeps in ((5 * frame, True), (4 * frame, False)):
+        monkeypatch.setattr(training, "AGGREGATED_BYTES", limit)
+        tr = training.CheckpointedTrainer(wl, blk, 5)
+        assert (tr.trainer.stack.p0 is not None) == keeps
+        tr.forward()
+        tr.backward(g_y)
+        grads.append(tr.dw[0].clone())
+    assert float((grads[0] - grads[1]).norm()) <= 1e-5 * float(grads[0].norm())
