@@ -16,11 +16,13 @@ from . import binding as B
 # still in the cache when it is gathered.
 BATCH_BYTES = 64 << 20
 
-# Stored entries up to which a block's snapshots are rebuilt as a series.  Its set-up takes 9 us per million entries, which
-# the launches it saves, 13 us a step, make up for; per further step it is as fast as the step-by-step merge (per step, series /
-# step by step: 11 thousand entries, 7 steps 2.0 / 13.8 us; 1.7 M, 15 steps 5.3 / 15.6 us; 17 M, 15 steps 48 / 54 us, 3 steps
-# 85 / 62 us), and it keeps every snapshot in an array of its own.
+# Stored entries up to which a block's snapshots are rebuilt as a series, and how many of them a step must make up for.  The
+# set-up takes 9 us per million entries; a step saves one rebuild's launches and the products and aggregations of its timestep
+# a launch of their own, less the more entries there are.  Whole passes (32 columns, uniform graph), series / step by step in us:
+# one step 1.4 M entries 90 / 101, 2.0 M 123 / 124, 2.8 M 163 / 159, 4.0 M 224 / 212; two steps 2.8 M 221 / 244, 4.0 M 324 / 325;
+# nine steps 4.0 M 964 / 1123.  Above 2^22 the chip is full with one timestep (17 M, per step: 15 steps 48 / 54 us, 3 steps 85 / 62).
 SERIES_ENTRIES = 1 << 22
+SERIES_ENTRIES_PER_STEP = 1 << 21
 
 # ... and the bytes its snapshots may take together.  A series of many dense snapshots on few vertices holds far more in them than
 # in its features (10 000 steps of 4 M entries: 160 GB, where the step-by-step rebuild needs three slots), so a long one is
@@ -28,14 +30,20 @@ SERIES_ENTRIES = 1 << 22
 SERIES_BYTES = 16 << 30
 
 # Vertices up to which the aggregation of X gathers dinv with the rows instead of finding them scaled by a pass of their own.
-# The pass costs per byte of X, the gather per entry, and far more once the factors (4 bytes per vertex, 1 MB here) leave an
-# L2 of 4 MB to the rows no more: per aggregation of 128-byte rows, gather against pass, 2^16 vertices 8 / 6 us, 2^18
-# 15 / 15, 2^19 37 / 27, 2^20 130 / 49; of 256-byte rows 2^18 17 / 24, 2^19 62 / 52, 2^20 200 / 98.
+# The pass costs per byte of X and a launch, the gather per entry, and far more once the factors (4 bytes per vertex, 1 MB here)
+# leave an L2 of 4 MB to the rows no more.  Uniform graphs, timesteps together as batch.py has them, gather / pass in us per
+# aggregation: 128-byte rows, 16 entries per row 2^14 vertices 5.7 / 6.0, 2^16 19.1 / 18.6, 2^18 94 / 94, 2^19 216 / 201; 4 entries
+# per row 2^16 9.3 / 11.3, 2^18 40 / 47, 2^19 84 / 95; 512-byte rows, 16 entries 2^16 75 / 84, 2^18 361 / 369, 2^19 794 / 751.
+# (64-byte rows cross at 2^15 already, 2^18 82 / 75: a tenth, for which the rule takes no width.)
 GATHERED_DINV_ROWS = 1 << 18
 
 
 def steps_together(frame_bytes: int, T: int) -> int:
     return max(1, min(T, BATCH_BYTES // max(frame_bytes, 1)))
+
+
+def series_pays(T: int, cap: int) -> bool:
+    return cap <= max(T - 1, 1) * SERIES_ENTRIES_PER_STEP
 
 
 def snapshots_fit(T: int, n: int, cap: int) -> bool:

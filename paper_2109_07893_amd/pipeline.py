@@ -17,7 +17,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, pointers, snapshots_fit, steps_together
+from .batch import SERIES_ENTRIES, Frames, SeriesTable, SpmmTable, TransformTable, pointers, series_pays, snapshots_fit, steps_together
 
 
 @dataclass
@@ -132,7 +132,8 @@ class BlockRunner:
         GCN steps of several timesteps together."""
         if any(getattr(type(self), name) is not getattr(BlockRunner, name) for name in ("rebuild", "transform_first", "gcn", "snapshot_ready", "slot_of")):
             return False                    # a subclass that does something of its own per snapshot is asked for every one
-        return self.blk.T >= 2 and self.cap <= SERIES_ENTRIES and snapshots_fit(self.blk.T, self.blk.n, self.cap)
+        T, cap = self.blk.T, self.cap
+        return T >= 2 and cap <= SERIES_ENTRIES and series_pays(T, cap) and snapshots_fit(T, self.blk.n, cap)
 
     def _add_slots(self, count: int) -> None:
         n, dev = self.blk.n, self.dev

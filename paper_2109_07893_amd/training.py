@@ -31,7 +31,7 @@ from typing import List, Optional, Tuple
 import torch
 
 from . import binding as B
-from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers, snapshots_fit, steps_together, upstream_frames
+from .batch import GATHERED_DINV_ROWS, SERIES_ENTRIES, Frames, SeriesTable, SmoothTable, SpmmTable, TransformTable, WeightGradTable, pointers, series_pays, snapshots_fit, steps_together, upstream_frames
 from .pipeline import BlockInputs, BlockRunner
 
 
@@ -249,7 +249,7 @@ class BlockTrainer:
         # keep_snapshots: every A_t (and A_t^T) of the block stays resident (T index arrays instead of three), so the
         # backward pass rebuilds nothing; without, the snapshots are rebuilt in reverse, as gradient checkpointing
         # has it.  4 nnz bytes per snapshot and chain: 9.6 GB for c5's eight, a matter of course in 288 GB.
-        self.series = cap <= SERIES_ENTRIES and snapshots_fit(T, n, cap)     # all snapshots in one go: they are resident then in any case
+        self.series = cap <= SERIES_ENTRIES and series_pays(T, cap) and snapshots_fit(T, n, cap)     # all snapshots in one go: they are resident then in any case
         self.keep_snapshots = keep_snapshots or self.series
         slots = T if self.keep_snapshots else None
         self.a = _Chain(n, cap, dev, blk.rowptr1, blk.colidx1, with_dinv=True, slots=slots)

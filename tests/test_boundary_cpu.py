@@ -429,3 +429,16 @@ def test_batched_aggregations_are_checked_before_the_first_of_them(lib):
     assert call(10, 33, items(), 32, 0, 0, FAKE, 1000, None) == -3
     one = 256 + 256                                  # a record and two rows of 32 floats, each rounded up to 256 bytes
     assert call(10, 33, items(), 32, 0, 0, FAKE, 33 * one - 1, None) == -3
+
+
+def test_a_series_needs_steps_enough_for_its_set_up(lib):
+    """Blocks of one step are rebuilt as a series up to half the entries of longer ones."""
+    import torch
+    from paper_2109_07893_amd.batch import SERIES_ENTRIES, SERIES_ENTRIES_PER_STEP
+    from paper_2109_07893_amd.pipeline import BlockInputs, BlockRunner
+    lists = tuple(torch.zeros(1, dtype=torch.int32) for _ in range(4))
+    for T, cap, series in ((2, SERIES_ENTRIES_PER_STEP, True), (2, SERIES_ENTRIES_PER_STEP + 1, False), (3, SERIES_ENTRIES, True),
+                           (3, SERIES_ENTRIES + 1, False), (9, SERIES_ENTRIES, True), (1, 100, False)):
+        blk = BlockInputs(n=10, T=T, f=16, layers=1, window=0, rowptr1=torch.zeros(11, dtype=torch.int32), colidx1=torch.zeros(1, dtype=torch.int32),
+                          deltas=[lists] * (T - 1), x=[torch.zeros(10, 16)] * T, w=[torch.zeros(16, 16)], nnz=[cap] * T)
+        assert BlockRunner(blk).series == series, (T, cap)
