@@ -90,17 +90,24 @@ def algorithmic_bytes(blk, stage, t=None):
         return 2 * s * n * f + s * f * f
     if stage == "spmm":            # lower bound: every row of H fetched once
         return 4 * blk.nnz[t - 1] + 8 * n + 2 * s * n * f
-    if stage in ("mproduct", "mproduct_backward"):
+    if stage == "mproduct":
         return 2 * s * n * f * blk.T
-    if stage == "spmm_transposed":
-        return 4 * blk.nnz[t - 1] + 8 * n + 2 * s * n * f
-    if stage == "relu_backward":   # gradient in, activation in, masked gradient out
-        return 3 * s * n * f + 4 * n
-    if stage == "weight_grad" and blk.layers == 1:      # aggregated features, gradient, activation (the ReLU's mask) in
-        return 3 * s * n * f + s * f * f
-    if stage in ("weight_grad", "input_grad"):
-        return 2 * s * n * f + s * f * f
     raise KeyError(stage)
+
+
+def training_bytes(blk, stack, forwards):
+    """Bytes the method itself must move per stage of a training step, all calls together (a call may take several timesteps).
+    forwards: timesteps that go forward in a step (those of a block that is rerun count twice)."""
+    s, n, f, T, L = blk.x[0].element_size(), blk.n, blk.f, blk.T, blk.layers
+    frame, dense = s * n * f, 2 * s * n * f + s * f * f
+    kept = stack.p0 is not None                         # A~ X: the first layer needs no aggregation going back
+    back = L - 1 if kept else L
+    gather = sum(algorithmic_bytes(blk, "spmm", t) for t in range(1, T + 1)) / T
+    return {"feature_transform": forwards * (L * dense + (2 * frame + 4 * n if stack.prescale else 0)),     # X scaled by dinv beforehand
+            "spmm": forwards * L * gather, "spmm_transposed": T * back * gather,
+            "relu_backward": T * back * (3 * frame + 4 * n),          # gradient in, activation in, masked gradient out
+            "weight_grad": T * (L * dense + (frame if kept else 0)),  # ... the activation is read here where the mask is taken on the way
+            "input_grad": T * (L - 1) * dense, "mproduct": forwards * 2 * frame, "mproduct_backward": T * 2 * frame}
 
 
 STAGE_SOURCES = {"spmm": ("spmm.hip", "common.hpp"), "delta_rebuild": ("delta_rebuild.hip", "common.hpp"),
@@ -639,15 +646,10 @@ def training_step(args, wl, blk, dev):
     one_step()
     torch.cuda.synchronize()
     stages = {}
+    forwards = blk.T if n_blocks == 1 else sum(e - a for a, e in ck.bounds + ck.bounds[:-1])      # the last block is not rerun
+    needed = training_bytes(blk, timed.stack, forwards)
     for name, (calls, total_ms) in timed.timer.totals().items():
-        if name in ("mproduct", "mproduct_backward"):
-            byts = algorithmic_bytes(blk, name) / n_blocks          # a call mixes one block of the series
-        elif name == "delta_rebuild":
-            byts = None
-        elif name in ("spmm", "spmm_transposed"):
-            byts = sum(algorithmic_bytes(blk, name, t) for t in range(1, blk.T + 1)) / blk.T
-        else:
-            byts = algorithmic_bytes(blk, name, 1)
+        byts = needed.get(name, 0) / calls
         entry = {"calls_per_step": calls, "avg_ms": round(total_ms / calls, 4), "ms_per_step": round(total_ms, 4)}
         if byts:
             entry["algorithmic_bytes_per_call"] = int(byts)
@@ -657,7 +659,7 @@ def training_step(args, wl, blk, dev):
     return {"ms_per_step": ms, "value": edges / (ms * 1e-3), "unit": "edges/s",
             "what": f"forward keeping activations + backward over t=1..{blk.T} ({'directed: second chain of transposed snapshots' if directed else 'undirected: the snapshot is its own transpose'}); "
                     "weight gradients of every layer; reverse rebuilds with exchanged lists where gradients travel through an aggregation"
-                    + (f"; gradient checkpointing over {n_blocks} blocks: every block's forward pass runs twice" if n_blocks > 1 else ""),
+                    + (f"; gradient checkpointing over {n_blocks} blocks: every block's forward pass but the last one's runs twice" if n_blocks > 1 else ""),
             "checkpoint_blocks": n_blocks,
             "edges_per_step": edges, "stages": stages}
 
