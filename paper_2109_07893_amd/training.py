@@ -14,8 +14,8 @@ the reverse direction).  Like pipeline.py this owns buffers and the order of lib
 
 The first layer's weight gradient is X^T A~^T G_P = (A~ X)^T G_P: with A~ X kept from the forward pass it needs no aggregation
 and no transposed snapshot, which leaves a one-layer step with half the gathers.  Where dL/dX is wanted (a layer lies below)
-the aggregation is needed anyway, and the first layer is treated like the others; so it is where frames are stored in bf16 (see
-first_layer_keeps_aggregated).
+the aggregation is needed anyway, and the first layer is treated like the others; so it is where frames are stored in bf16 or
+A~ X of the block would take more than AGGREGATED_BYTES (see first_layer_keeps_aggregated).
 
 For a directed workload the transposed snapshots, where needed, are a second dynamic graph, rebuilt the same way from the
 difference lists sorted by (col, row).  Timesteps are enqueued together while their frames are small (batch.py).  Nothing here
