@@ -727,3 +727,34 @@ def test_checkpointed_blocks_decide_by_their_own_length(graph_kind, monkeypatch)
         tr.backward(g_y)
         grads.append(tr.dw[0].clone())
     assert float((grads[0] - grads[1]).norm()) <= 1e-5 * float(grads[0].norm())
+
+
+@pytest.mark.parametrize("kind", ["trainer", "checkpointed", "evolving", "cdgcn"])
+def test_trainers_find_moved_tensors(kind):
+    """Features, weights and difference lists that lie elsewhere in the next step are found there, forward and back."""
+    from paper_2109_07893_amd import training
+    from paper_2109_07893_amd.cdgcn import CdgcnTrainer
+    wl = replace(graph("rmat", 1 << 10, 8, 6, 0.05, 0.05), f=32, layers=1 if kind in ("cdgcn", "evolving") else 2, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.randn((wl.T, wl.n, wl.f), device=DEV)
+    weights = [torch.randn(s, device=DEV) * 0.2 for s in ((32, 32), (64, 128), (32, 128), (128,))]
+    if kind == "evolving":
+        blk.w_t = [[torch.randn(32, 32, device=DEV)] for _ in range(wl.T)]
+    if kind == "cdgcn":
+        tr = CdgcnTrainer(blk, *weights, 32)
+        tr.load_first()
+        lists = blk.deltas
+    else:
+        tr = training.CheckpointedTrainer(wl, blk, 3) if kind == "checkpointed" else training.make_trainer(wl, blk)
+        lists = list(blk.deltas) + list(getattr(tr, "t_deltas", None) or [])
+
+    def step():
+        tr.forward()
+        tr.backward(g_y)
+        torch.cuda.synchronize()
+        grads = [tr.dw, tr.dw_x, tr.dw_h, tr.db] if kind == "cdgcn" else [d[0] for d in tr.dw_t] if kind == "evolving" else tr.dw
+        return [g.clone() for g in grads]
+    want = step()
+    for t in [t for d in lists for t in d if t.numel()] + list(blk.x) + list(blk.w) + weights + [w[0] for w in blk.w_t or []]:
+        moved(t)
+    assert all(torch.equal(a, b) for a, b in zip(step(), want))
