@@ -412,7 +412,8 @@ def first_layer_keeps_aggregated(blk: BlockInputs, want_dx: bool = False, weight
     Only in fp32: a bf16 A~ X is rounded once per row before the product and the ReLU see it, where the roundings of X W average
     out over a row's neighbours (features that are all positive, 16 neighbours: dW 1.6 to 3.2 times as far from 64 bits).  In fp32
     both forms are at the rounding of the type: Z 1.1e-7 to 2.2e-7 either way with N(0, 1) features, 1.0e-7 to 2.2e-7 against
-    0.8e-7 to 1.7e-7 with positive ones; dW 0.6e-7 to 0.9e-7 against 0.5e-7 to 1.0e-7, where no ReLU's mask differs.  And not with values and further layers above, where the transposed snapshots are resident anyway."""
+    0.8e-7 to 1.7e-7 with positive ones; dW 0.6e-7 to 0.9e-7 against 0.5e-7 to 1.0e-7, where no ReLU's mask differs.
+    And not with values and further layers above, where the transposed snapshots are resident anyway."""
     fits = blk.T * blk.n * blk.f * 4 <= AGGREGATED_BYTES
     return blk.x[0].dtype == torch.float32 and fits and not want_dx and not (weighted and blk.layers > 1)
 
