@@ -57,6 +57,12 @@ __device__ __forceinline__ T *as_global(T *p) {
     return (T *)(__attribute__((address_space(1))) T *)p;
 }
 
+// The same for what no work of the kernel's own writes, read at an address that is the same in all lanes: through the scalar cache.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *as_constant(const T *p) {
+    return (const __attribute__((address_space(4))) T *)p;
+}
+
 // The `count` 32-bit words at p (the same in all lanes) behind a buffer descriptor: a load beyond them gives 0, a store
 // beyond them is dropped, so that no access needs a branch and the compiler can count the accesses in flight exactly.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int count) {

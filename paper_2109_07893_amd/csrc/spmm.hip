@@ -3,24 +3,28 @@
 // dinv[u] * dinv[v] and the kernel needs no value array:
 //     Z[u] = dinv[u] * sum_{v in row u} dinv[v] * H[v].
 //
-// The work is a gather of whole H rows (one 16-byte piece per lane, a lane group per row of H),
-// bound by how many independent row fetches are in flight, so it is split by ENTRIES, not by
-// rows, and every wavefront is an independent stream:
-//   - a wavefront owns a contiguous range of stored entries and walks it in sub-tiles; the row
-//     that holds the range's first entry is found once (64-ary search), afterwards rows simply
-//     follow on: a window of consecutive row pointers is staged in LDS and the row starts that
-//     fall into the sub-tile become a bit mask (one 32-bit word per lane group);
-//   - every lane group takes 32 consecutive entries, keeps eight gathers in flight while it adds
-//     up the previous eight, and closes its running sum wherever the mask has a bit: a row that
-//     begins and ends inside the group's 32 entries is finished and stored at once, a piece cut
-//     at either end is parked in LDS;
-//   - one lane group adds the parked pieces in entry order and carries a row that is still open
-//     into the next sub-tile in registers; only rows cut by the range itself leave a "left" or
-//     "right" carry in the workspace, which a second small kernel adds up, again in entry order;
-//   - column indices and row pointers of the next sub-tile are fetched while this one is summed.
+// The work is a gather of whole H rows (one 16-byte piece per lane, a lane group per row of H).  On large snapshots it is bound by
+// the rate at which L2 misses are served; where the rows lie in the L2s, by the vector memory units of the CUs (2.5 - 3.5 cycles
+// per cache line touched), so lines other than those of H count.  It is split by ENTRIES, not by rows, and every wavefront is
+// an independent stream:
+//   - a wavefront owns a contiguous range of stored entries and walks it in sub-tiles (up to 65536 sub-tiles: one per wavefront,
+//     which then needs 64 registers only).  The row that holds the range's first entry is found once, mostly by two scalar
+//     loads and one look at 64 row pointers; afterwards rows simply follow on;
+//   - the sub-tile's columns go to LDS as byte offsets, a lane group reads four of them at once; the rows with entries are listed
+//     in LDS, their starts become a bit mask (one 32-bit word per lane group);
+//   - every lane group takes 32 consecutive entries, keeps eight gathers in flight, each replaced as it is used, and where
+//     the mask has a bit puts its running sum away: a row that began inside the group's 32 entries is stored at once, a piece cut
+//     on the left is parked in LDS.  Where no group has a row start, an entry costs four additions, an address and a load;
+//   - the group where a cut row begins adds the parked pieces in entry order; a row still open goes on in group 0 of the next
+//     sub-tile; only rows cut by the range itself leave a "left" or "right" carry in the workspace, which a second small
+//     kernel adds up, again in entry order;
+//   - where a range has several sub-tiles, columns and row pointers of the next one are fetched while this one is summed.
 // Hub rows of power-law graphs are thereby spread over as many wavefronts as they have ranges,
 // short rows share a wavefront, and every sum has a fixed order: no floating-point atomics,
 // results repeat bit for bit.
+// Against the form with a search per lane group, a branch per entry and workgroup barriers, us per aggregation: uniform 50 K
+// vertices x 64 fp32 25.9 -> 17.0 (with slices of columns, see slices_of), 100 K 59.5 -> 50, R-MAT 2^18 x 32 fp32 with values 71 -> 52,
+// 2^23 (misses) 2250 both.
 #include <algorithm>
 #include <type_traits>
 
@@ -33,7 +37,9 @@ using namespace dgnn;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBatch = 8;            // gathers issued together by a lane group
-constexpr int kPer = 32;             // entries a lane group walks per sub-tile (one mask word)
+// Entries a lane group walks per sub-tile (one mask word; half of one where the groups are so many that the sub-tile's rows would
+// take the LDS of half the wavefronts).
+constexpr int per_group(int lanes_per_row) { return lanes_per_row == 2 ? 16 : 32; }
 constexpr int kMaxRange = 2048;      // entries streamed by one wavefront, at most: many short-lived wavefronts stream
                                      // faster than few long-lived ones (8192: +2.5 % on the largest workloads)
 constexpr int kTargetWaves = 65536;  // ranges shrink on small inputs so that about this many wavefronts exist (16384: +4 %)
@@ -55,38 +61,40 @@ struct Item {
     RangeRec *recs;
     float *carry;
     int32_t nnz, range_len, n_ranges, gather_dinv;   // gather_dinv: rows of h are scaled as they are gathered
+    float rows_per_entry;
 };
 constexpr int kMaxBatch = 32;        // what fits the kernel arguments comfortably
 struct Batch { Item item[kMaxBatch]; };
+
+struct RowRef { uint32_t at; float du; };   // a row that holds entries: where its result begins (FAR: its number), and its dinv
 
 // ---- 16-byte feature pieces: 4 fp32 or 8 bf16, accumulated in fp32 -------------------------
 template <bool BF16> struct Piece;
 template <> struct Piece<false> {
     static constexpr int kVals = 4;
     typedef floatx4 Raw;
-    static __device__ __forceinline__ void fma(float (&acc)[4], float s, Raw v) {
+    template <bool SCALE> static __device__ __forceinline__ void add(float (&acc)[4], float s, Raw v) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = fmaf(s, v[e], acc[e]);
+        for (int e = 0; e < 4; ++e) acc[e] = SCALE ? fmaf(s, v[e], acc[e]) : acc[e] + v[e];
     }
-    static __device__ __forceinline__ void store(void *p, const float (&acc)[4]) {
-        __builtin_nontemporal_store(floatx4{acc[0], acc[1], acc[2], acc[3]}, static_cast<floatx4 *>(p));   // written once, read by a later kernel
-    }
+    static __device__ __forceinline__ Raw pack(const float (&acc)[4]) { return Raw{acc[0], acc[1], acc[2], acc[3]}; }
 };
 template <> struct Piece<true> {
     static constexpr int kVals = 8;
     typedef uintx4 Raw;
-    static __device__ __forceinline__ void fma(float (&acc)[8], float s, Raw v) {
+    template <bool SCALE> static __device__ __forceinline__ void add(float (&acc)[8], float s, Raw v) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            acc[2 * e] = fmaf(s, __uint_as_float(v[e] << 16), acc[2 * e]);
-            acc[2 * e + 1] = fmaf(s, __uint_as_float(v[e] & 0xffff0000u), acc[2 * e + 1]);
+            const float lo = __uint_as_float(v[e] << 16), hi = __uint_as_float(v[e] & 0xffff0000u);
+            acc[2 * e] = SCALE ? fmaf(s, lo, acc[2 * e]) : acc[2 * e] + lo;
+            acc[2 * e + 1] = SCALE ? fmaf(s, hi, acc[2 * e + 1]) : acc[2 * e + 1] + hi;
         }
     }
-    static __device__ __forceinline__ void store(void *p, const float (&acc)[8]) {
-        uintx4 v;
+    static __device__ __forceinline__ Raw pack(const float (&acc)[8]) {
+        Raw v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = f32_to_bf16(acc[2 * e]) | (f32_to_bf16(acc[2 * e + 1]) << 16);
-        __builtin_nontemporal_store(v, static_cast<uintx4 *>(p));
+        for (int e = 0; e < 4; ++e) v[e] = pack_bf16(acc[2 * e], acc[2 * e + 1]);
+        return v;
     }
 };
 
@@ -101,390 +109,313 @@ __device__ __forceinline__ void finish_row(char *z, int64_t row, int row_bytes, 
         out[q] = acc[q] * du;
         if (relu) out[q] = fmaxf(out[q], 0.0f);
     }
-    Piece<BF16>::store(z + row * row_bytes + sub * 16, out);
+    __builtin_nontemporal_store(Piece<BF16>::pack(out), reinterpret_cast<typename Piece<BF16>::Raw *>(z + row * row_bytes + sub * 16));
 }
 
-template <int LPR, int SLICES, bool BF16>
+template <int LPR, int SLICES>
 __device__ __forceinline__ void zero_row(char *z, int64_t row) {
-    constexpr int NV = Piece<BF16>::kVals;
-    float zero[NV];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) zero[q] = 0.0f;
-    for (int s = 0; s < LPR; ++s) Piece<BF16>::store(z + row * (LPR * SLICES * 16) + s * 16, zero);
+    for (int s = 0; s < LPR; ++s) __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(z + row * (LPR * SLICES * 16) + s * 16));
 }
 
 // LPR: lanes per feature row.  SCALE_V: multiply every gathered row by a per-entry factor: dinv of its
 // column, or the entry's own value when the snapshot carries values (otherwise H already carries the factor).
-template <int LPR, int SLICES, bool BF16, bool SCALE_V>
+// FAR: H or Z reaches beyond the 4 GB that a 32-bit offset from its first byte spans.  ONE: the range is a single sub-tile.
+template <int LPR, int SLICES, bool BF16, bool SCALE_V, bool FAR, bool ONE>
 __device__ __forceinline__ void spmm_stream(
-    int range, int n, int nnz, int range_len, int n_ranges, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int range, int n, int nnz, int range_len, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ dinv, const char *__restrict__ h, char *__restrict__ z, int relu,
-    RangeRec *__restrict__ recs, bool record, float *__restrict__ carry, const float *__restrict__ vals, bool gather_dinv) {
+    RangeRec *__restrict__ recs, bool record, float *__restrict__ carry, const float *__restrict__ vals, bool gather_dinv, float rows_per_entry) {
     typedef typename Piece<BF16>::Raw Raw;
     constexpr int NV = Piece<BF16>::kVals;
     constexpr int F = LPR * NV;
     constexpr int G = kWave / LPR;          // lane groups per wavefront
+    constexpr int kPer = per_group(LPR);
     constexpr int SUB = G * kPer;           // entries per sub-tile
-    constexpr int CPL = kPer / LPR;         // column indices held by one lane
+    constexpr int CN = SUB / kWave;         // column indices fetched by one lane
     constexpr int kRowBytes = LPR * SLICES * 16;   // from a row to the next; h, z and carry are the slice's own, recs are the same for all (one of them records)
-    constexpr int kRowCap = SUB + kWave;    // most rows a sub-tile can need: one per entry, plus the bounding one
-    constexpr int ROUNDS = kRowCap / kWave;
+    constexpr int kStride = kPer + 4;       // words from a group's offsets to the next group's: 16-byte reads of the groups fall on different banks
 
-    __shared__ int s_rp[kRowCap];           // row pointers of the staged rows
-    __shared__ float s_du[kRowCap];         // their dinv
-    __shared__ unsigned s_heads[G + 1];     // bit p of the mask: a row begins at entry e + p
-    __shared__ float s_part[G][2][F];       // [0]: a group's first piece when cut on the left, [1]: its last piece when cut on the right only
+    __shared__ __align__(16) uint32_t s_off[G * kStride];                  // where the rows of H that the entries name begin (FAR: their numbers)
+    __shared__ __align__(16) float s_val[SCALE_V ? G * kStride : 4];       // the entries' factors
+    __shared__ __align__(8) RowRef s_rows[SUB + 2];                        // the sub-tile's rows, those without entries left out
+    __shared__ unsigned s_heads[G + 1];     // bit p of word g: a row begins at entry kPer g + p; the last word: their disjunction
+    __shared__ __align__(16) float s_left[G][F];                           // a group's sum up to its first row start
 
     const int lane = threadIdx.x;
-    const int sub = lane % LPR, g = lane / LPR, gbase = lane - sub;
+    const int sub = lane % LPR, g = lane / LPR;
+    const uint32_t sub16 = sub * 16;
+    const int e_begin = (int)((int64_t)range * range_len);
     // the host's count may be an upper bound (a snapshot whose size only the device knows): the last row pointer decides
     nnz = min(nnz, rowptr[n]);
-    const int e_begin = (int)((int64_t)range * range_len);
-    if (e_begin >= nnz && range > 0) {                  // nothing stored here: a record that closes nothing and carries nothing
-        if (threadIdx.x == 0 && record) recs[range] = RangeRec{-1, 0, 0, 0};
+    if (e_begin >= nnz) {                               // nothing stored here: a record that closes nothing and carries nothing
+        if (lane == 0 && record) recs[range] = RangeRec{-1, 0, 0, 0};
+        if (range == 0)
+            for (int k = lane; k < n; k += kWave) zero_row<LPR, SLICES>(z, k);
         return;
     }
     const int e_end = (int)min((int64_t)e_begin + range_len, (int64_t)nnz);
-    int k_cur = max(wave_find_row(rowptr, n, e_begin, lane), 0);   // a row with rowptr <= e_begin
-    if (range == 0)                          // rows without entries ahead of the first stored entry
-        for (int k = lane; k < k_cur; k += kWave) zero_row<LPR, SLICES, BF16>(z, k);
+    float *my_carry = carry + (int64_t)range * 2 * F;
 
-    // the row that is still open at the end of a sub-tile is carried on in the lanes of group 0
+    // column indices (and factors) of the coming sub-tile, consecutive ones per load
+    int c_next[CN];
+    float d_next[SCALE_V ? CN : 1] = {};
+    if (SCALE_V && !vals)
+#pragma unroll
+        for (int i = 0; i < CN; ++i) d_next[i] = 1.0f;
+    auto fetch_cols = [&](int e0) {
+#pragma unroll
+        for (int i = 0; i < CN; ++i) {
+            const int idx = min(e0 + i * kWave + lane, e_end - 1);
+            c_next[i] = __builtin_nontemporal_load(colidx + idx);   // a stream: the caches are for rows of H
+            if (SCALE_V && vals) d_next[i] = vals[idx];
+        }
+    };
+    // row pointers (and dinv) of the first 64 rows of the coming sub-tile; further rows are read on demand
+    int m_v = 0, m_vn = 0;
+    float m_du = 1.0f;
+    auto fetch_rows = [&](int k0) {          // unconditional loads: the compiler then counts what is in flight exactly
+        const int k = min(k0 + lane, n - 1);
+        m_v = rowptr[k];
+        m_vn = rowptr[k + 1];
+        if (dinv) m_du = dinv[k];
+    };
+    auto row_ref = [&](int k, float du) { return RowRef{FAR ? (uint32_t)k : (uint32_t)k * kRowBytes, du}; };
+    auto store_row = [&](const RowRef &r, const float (&acc)[NV]) {
+        float out[NV];
+        if (relu) {
+            asm volatile("");                            // a branch of the whole wavefront, not a selection per value
+#pragma unroll
+            for (int q = 0; q < NV; ++q) out[q] = fmaxf(acc[q] * r.du, 0.0f);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) out[q] = acc[q] * r.du;
+        }
+        // written once, read by a later kernel
+        __builtin_nontemporal_store(Piece<BF16>::pack(out), reinterpret_cast<Raw *>(FAR ? z + (int64_t)r.at * kRowBytes + sub16 : z + (size_t)(r.at + sub16)));
+    };
+    auto to_carry = [&](int side, const float (&acc)[NV]) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) my_carry[side * F + sub * NV + q] = acc[q];
+    };
+
+    fetch_cols(e_begin);
+    // The row of e_begin: where it would be if rows were equally long, corrected by how far off that is, through the scalar
+    // cache (a search by all lanes takes a cache line per lane from the units that the gathers need: 0.15 of a sub-tile's
+    // time per round), then among the 64 rows around it.  k_cur: that row, or one up to 63 rows ahead of it.
+    int k_cur = 0;
+    if (e_begin > 0) {
+        int k = min((int)((float)e_begin * rows_per_entry), n - 1);
+        for (int round = 0; round < 3; ++round) {
+            const float off = (float)(e_begin - as_constant(rowptr)[uniform(k)]) * rows_per_entry;
+            k = max(0, min(k + (int)off, n - 1));
+            if (fabsf(off) < (float)kWave) break;
+        }
+        k_cur = uniform(max(k - kWave / 4, 0));
+    }
+    fetch_rows(k_cur);
+    if (!__ballot(m_v <= e_begin && m_vn > e_begin)) {
+        k_cur = max(wave_find_row(rowptr, n, e_begin, lane), 0);
+        fetch_rows(k_cur);
+    }
+
+    // the row that is open at the end of a sub-tile goes on in the lanes of group 0
     float run[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) run[q] = 0.0f;
     bool running = false;       // such a row exists
     bool began_here = false;    // ... and it began inside this range
-    int run_row = 0;
+    RowRef run_ref{0, 1.0f};
     int open_row = -1;
-    float *my_carry = carry + (int64_t)range * 2 * F;
 
-    // column indices (and their dinv) of the coming sub-tile: lane holds entries e + 32 g + sub CPL + i
-    int c_next[CPL];
-    float d_next[SCALE_V ? CPL : 1];
-    auto fetch_cols = [&](int e0) {
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            const int idx = e0 + g * kPer + sub * CPL + i;
-            c_next[i] = idx < e_end ? __builtin_nontemporal_load(colidx + idx) : 0;   // a stream: the caches are for rows of H
-        }
-        if (SCALE_V) {
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) {
-                const int idx = e0 + g * kPer + sub * CPL + i;
-                // an explicit value per stored entry (one coalesced stream) and / or dinv of the entry's column
-                d_next[i] = idx < e_end ? (vals ? vals[idx] : 1.0f) * (gather_dinv ? dinv[c_next[i]] : 1.0f) : 0.0f;
-            }
-        }
-    };
-    // row pointers (and dinv) of the first 64 rows of the coming sub-tile; further rows are read on demand
-    int m_v = 0;
-    float m_du = 1.0f;
-    auto fetch_rows = [&](int k0) {
-        const int k = k0 + lane;
-        m_v = k <= n ? rowptr[k] : 0x7fffffff;
-        m_du = (dinv && k < n) ? dinv[k] : 1.0f;
-    };
-    fetch_cols(e_begin);
-    fetch_rows(k_cur);
-    int k_win = k_cur, staged_last = kWave;   // the last staged window, for the rows beyond it
-    int e = e_begin;
-    while (e < e_end) {
-        // ---- stage rows k_cur, k_cur + 1, ... in LDS until one begins at or beyond the end of the sub-tile
-        const int e_lim = min(e + SUB, e_end);
-        int staged = 0, le_e = 0, le_stop = 0, lt_stop = 0;
-        bool complete = false;
-        {
-            int v = m_v;
-            float du = m_du;
-#pragma unroll 1
-            for (int round = 0; round < ROUNDS && !complete; ++round) {
-                const int t = lane + round * kWave;
-                if (round > 0) {
-                    const int k = k_cur + t;
-                    v = k <= n ? rowptr[k] : 0x7fffffff;
-                    du = (dinv && k < n) ? dinv[k] : 1.0f;
-                }
-                s_rp[t] = v;
-                s_du[t] = du;
-                le_e += __popcll(__ballot(v <= e));
-                le_stop += __popcll(__ballot(v <= e_lim));
-                lt_stop += __popcll(__ballot(v < e_lim));
-                staged += kWave;
-                complete = __ballot(v >= e_lim) != 0;
-            }
-        }
-        k_win = k_cur;
-        staged_last = staged;
-        const int t0 = max(le_e - 1, 0);                 // the staged row that holds entry e
-        __syncthreads();
-        // rows without entries give zero output (none exist when every row holds its diagonal)
-#pragma unroll 1
-        for (int t = lane; t + 1 < staged; t += kWave)
-            if (k_cur + t + 1 <= n && s_rp[t] == s_rp[t + 1]) zero_row<LPR, SLICES, BF16>(z, k_cur + t);
-        if (t0 > 0) {                                    // rows without entries were stepped over: restage from the row of e
-            k_cur += t0;
-            fetch_rows(k_cur);
-            __syncthreads();
-            continue;
-        }
-        int e_stop = e_lim;
-        if (!complete) {                                 // more rows begin here than fit (rows without entries): end early
-            e_stop = min(e_lim, s_rp[staged - 1]);
-            le_stop = lt_stop = 0;
-#pragma unroll 1
-            for (int t = lane; t - lane < staged; t += kWave) {
-                const int v = t < staged ? s_rp[t] : 0x7fffffff;
-                le_stop += __popcll(__ballot(v <= e_stop));
-                lt_stop += __popcll(__ballot(v < e_stop));
-            }
-        }
-        const int cnt = e_stop - e;
-        const int t_last = lt_stop - 1;                  // last staged row with entries in this sub-tile
-        const int k_next = k_cur + le_stop - 1;          // a row with rowptr <= e_stop
-
-        int cc[CPL];
-        float dd[SCALE_V ? CPL : 1];
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            cc[i] = c_next[i];
-            if (SCALE_V) dd[i] = d_next[i];
-        }
+    for (int e = e_begin; e < e_end;) {
+        const int e_stop = min(e + SUB, e_end), cnt = e_stop - e;
+        const bool final = ONE || e_stop == e_end;
+        // ---- the sub-tile's columns go to LDS, and the first gathers out
         if (lane <= G) s_heads[lane] = 0u;
-        // Every load issued so far has been used or is used next; saying so here, ahead of the prefetch, keeps
-        // the gathers below from being held up by waits for "possibly outstanding" column indices.
-        __builtin_amdgcn_s_waitcnt(kVmcntZero);
-        if (e_stop < e_end) {                            // fetched while this sub-tile is summed
+#pragma unroll
+        for (int i = 0; i < CN; ++i) {
+            const int p = i * kWave + lane, at = (p / kPer) * kStride + p % kPer;
+            s_off[at] = FAR ? (uint32_t)c_next[i] : (uint32_t)c_next[i] * kRowBytes;
+            if (SCALE_V) s_val[at] = gather_dinv ? d_next[i] * dinv[c_next[i]] : d_next[i];
+        }
+        wave_lds_sync();
+        const uint32_t *my_off = &s_off[g * kStride];
+        const float *my_val = &s_val[SCALE_V ? g * kStride : 0];
+        auto gather = [&](uint32_t off) {
+            if (FAR) return *reinterpret_cast<const Raw *>(h + (int64_t)off * kRowBytes + sub16);
+            return *reinterpret_cast<const Raw *>(h + (size_t)(off + sub16));
+        };
+        Raw buf[kBatch];
+        {
+            const uintx4 o0 = *reinterpret_cast<const uintx4 *>(my_off), o1 = *reinterpret_cast<const uintx4 *>(my_off + 4);
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) buf[k] = gather(k < 4 ? o0[k % 4] : o1[k % 4]);
+        }
+        // ---- its rows
+        int k_next = k_cur - 1, listed = 0;
+        for (int k = k_cur + lane;;) {
+            const bool row = k < n, has = m_vn > m_v;
+            const bool list = row && has && m_vn > e && m_v < e_stop;
+            const uint64_t mask = __ballot(list);
+            if (list) {
+                s_rows[min(listed + (int)__popcll(mask & ((1ull << lane) - 1)), SUB)] = row_ref(k, m_du);
+                if (m_v >= e) {
+                    const int p = m_v - e;
+                    atomicOr(&s_heads[p / kPer], 1u << (p % kPer));
+                    atomicOr(&s_heads[G], 1u << (p % kPer));
+                }
+            }
+            listed += __popcll(mask);
+            // no entries: zero output (those ahead of the first entry of all belong to the first range)
+            if (row && !has && (m_v > e || e == 0) && m_v <= e_stop) zero_row<LPR, SLICES>(z, k);
+            const uint64_t within = __ballot(row && m_v <= e_stop);
+            k_next += __popcll(within);                  // ends as the row of entry e_stop
+            if (~within) break;
+            k += kWave;
+            fetch_rows(k - lane);
+            __builtin_amdgcn_s_waitcnt(kVmcntZero);      // here, on the rare path, and not ahead of the next prefetch
+        }
+        if (cnt < SUB && lane == 0) {                    // behind the last entry: what is gathered there belongs to no row
+            atomicOr(&s_heads[cnt / kPer], 1u << (cnt % kPer));
+            atomicOr(&s_heads[G], 1u << (cnt % kPer));
+        }
+        wave_lds_sync();
+        if (!final) {                                    // fetched while this sub-tile is summed
             fetch_cols(e_stop);
             fetch_rows(k_next);
         }
-        __syncthreads();
-        // ---- row starts inside the sub-tile -> mask bits
-#pragma unroll 1
-        for (int t = lane; t < staged; t += kWave) {
-            const int v = s_rp[t];
-            if (t > 0 && v < e_stop) {
-                const int p = v - e;
-                atomicOr(&s_heads[p >> 5], 1u << (p & 31));
-            }
+
+        // ---- every lane group walks its entries
+        const unsigned w = s_heads[g], any = __builtin_amdgcn_readfirstlane(s_heads[G]) & ~1u;
+        const unsigned w_lane = lane < G ? s_heads[lane] : 0u;
+        const uint64_t headed = __ballot(w_lane != 0u), at_once = __ballot((w_lane & 1u) != 0u);   // groups with a row start; with one at their first entry
+        const bool starts = at_once & 1;                 // the sub-tile begins with a row
+        const int before = wave_scan_add(__popc(w_lane), lane) - __popc(w_lane);
+        const RowRef *next_ref = &s_rows[__shfl(before, g, kWave) + (int)(w & 1u) - (starts ? 1 : 0)];
+        RowRef ref = *next_ref;
+        if (running && starts && lane < LPR) {           // the row that was open ended with the last sub-tile
+            if (began_here) store_row(run_ref, run); else to_carry(0, run);
         }
-        if (lane == 0 && s_rp[0] == e) atomicOr(&s_heads[0], 1u);
-        __syncthreads();
+        const bool inherits = running && !starts && g == 0;
+        uint64_t closed = __ballot((w & 1u) || (inherits && began_here));   // lanes whose sum holds its row from the row's first entry on
+        const bool cut = !(closed & 1);                  // group 0 begins inside a row of an earlier range
+        float acc[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q] = inherits ? run[q] : 0.0f;
 
-        // ---- every lane group walks its 32 entries
-        const int p0 = g * kPer;
-        const int c1 = min(p0 + kPer, cnt);
-        if (p0 < c1) {
-            const unsigned w = s_heads[g];
-            int cur;                                     // staged row that holds entry p0: last one that begins at or before it
-            {
-                int lo = 0, hi = t_last + 1;
-                while (lo < hi) {
-                    const int mid = lo + ((hi - lo) >> 1);
-                    if (s_rp[mid] <= e + p0) lo = mid + 1; else hi = mid;
-                }
-                cur = lo - 1;
+        auto batch = [&](int b, auto more) {
+            uintx4 o[2];
+            floatx4 s[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (decltype(more)::value) o[i] = *reinterpret_cast<const uintx4 *>(my_off + (b + 1) * kBatch + i * 4);
+                if (SCALE_V) s[i] = *reinterpret_cast<const floatx4 *>(my_val + b * kBatch + i * 4);
             }
-            bool left_closed = (w & 1u) != 0;            // entry p0 begins its row
-            float acc[NV];
+            const unsigned wb = w >> (b * kBatch), anyb = any >> (b * kBatch);
 #pragma unroll
-            for (int q = 0; q < NV; ++q) acc[q] = 0.0f;
-
-            // a piece that is a whole row is finished and stored; a cut piece is parked for the step below
-            auto flush = [&](bool right_closed) {
-                if (left_closed && right_closed) {
-                    float out[NV];
-                    const float du = s_du[cur];
+            for (int k = 0; k < kBatch; ++k) {
+                if ((anyb >> k) & 1u) {                  // a row begins here in some group: those that end are put away
+                    asm volatile("");                    // (two decisions: the first is the wavefront's)
+                    const uint64_t begins = __ballot((wb >> k) & 1u);
+                    if (__builtin_amdgcn_inverse_ballot_w64(begins & closed)) store_row(ref, acc);
+                    if (begins & ~closed) {
+                        if (__builtin_amdgcn_inverse_ballot_w64(begins & ~closed)) {
 #pragma unroll
-                    for (int q = 0; q < NV; ++q) {
-                        out[q] = acc[q] * du;
-                        if (relu) out[q] = fmaxf(out[q], 0.0f);
-                    }
-                    Piece<BF16>::store(z + (int64_t)(k_cur + cur) * kRowBytes + sub * 16, out);
-                } else {
-                    float *dst = &s_part[g][left_closed ? 1 : 0][sub * NV];
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) dst[q] = acc[q];
-                }
-            };
-            // batch b covers entries 8 b .. 8 b + 7 of the group; ODD (the parity of b) makes the register
-            // slot q % CPL a compile-time constant while b itself stays a run-time loop counter
-            // FULL: all 32 entries of every group exist (any sub-tile but a range's last), so nothing about the
-            // gathers is conditional and each one is waited for by itself, in the order they were issued
-            auto batch = [&](int b, auto odd, auto full) {
-                constexpr int ODD = decltype(odd)::value;
-                constexpr bool FULL = decltype(full)::value;
-                constexpr int slot_odd = (ODD * kBatch) % CPL;
-                Raw buf[kBatch];
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const int q = b * kBatch + k;
-                    if (FULL || p0 + q < c1) {
-                        const int c = __shfl(cc[(slot_odd + k) % CPL], gbase + q / CPL, kWave);
-                        buf[k] = *reinterpret_cast<const Raw *>(h + (int64_t)c * kRowBytes + sub * 16);
-                    }
-                }
-                const unsigned wb = w >> (b * kBatch);
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const int q = b * kBatch + k;
-                    if (FULL || p0 + q < c1) {
-                        if (q > 0 && ((wb >> k) & 1u)) {
-                            flush(true);
-                            left_closed = true;
-                            do ++cur; while (s_rp[cur + 1] <= e + p0 + q);   // rows without entries are stepped over
-#pragma unroll
-                            for (int x = 0; x < NV; ++x) acc[x] = 0.0f;
+                            for (int q = 0; q < NV; ++q) s_left[g][sub * NV + q] = acc[q];
                         }
-                        const float s = SCALE_V ? __shfl(dd[(slot_odd + k) % CPL], gbase + q / CPL, kWave) : 1.0f;
-                        Piece<BF16>::fma(acc, s, buf[k]);
+                    }
+                    closed |= begins;
+                    if (__builtin_amdgcn_inverse_ballot_w64(begins)) {
+                        ref = *++next_ref;
+#pragma unroll
+                        for (int q = 0; q < NV; ++q) acc[q] = 0.0f;
                     }
                 }
-            };
-            if (cnt == SUB) {
-#pragma unroll 1
-                for (int b = 0; b < kPer / kBatch; b += 2) {
-                    batch(b, std::integral_constant<int, 0>{}, std::true_type{});
-                    batch(b + 1, std::integral_constant<int, 1>{}, std::true_type{});
-                }
-            } else {
-#pragma unroll 1
-                for (int b = 0; b < kPer / kBatch; b += 2) {
-                    batch(b, std::integral_constant<int, 0>{}, std::false_type{});
-                    batch(b + 1, std::integral_constant<int, 1>{}, std::false_type{});
-                }
+                Piece<BF16>::template add<SCALE_V>(acc, SCALE_V ? s[k / 4][k % 4] : 1.0f, buf[k]);
+                if (decltype(more)::value) buf[k] = gather(o[k / 4][k % 4]);
             }
-            // does the row of the last entry end with it?
-            flush(c1 == cnt ? s_rp[t_last + 1] == e_stop : (s_heads[g + 1] & 1u) != 0);
-        }
-        __syncthreads();
-
-        // ---- rows cut between lane groups or by the sub-tile: their pieces are added in entry order.
-        // Where a row's pieces lie follows from the row pointers alone.
-        auto pieces = [&](int t, float (&sum)[NV]) {
-            const int ps = s_rp[t] - e;
-            const int pe = min(s_rp[t + 1] - e, cnt);
-            const int ga = max(ps, 0) >> 5, gb = (pe - 1) >> 5;
-            int first = ga;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) sum[q] = 0.0f;
-            if (ps >= 0) {                               // begins here: its first piece is the last one of group ga
-#pragma unroll
-                for (int q = 0; q < NV; ++q) sum[q] = s_part[ga][1][sub * NV + q];
-                first = ga + 1;
-            }
-            for (int gg = first; gg <= gb; ++gg)
-#pragma unroll
-                for (int q = 0; q < NV; ++q) sum[q] += s_part[gg][0][sub * NV + q];
         };
-        for (int t = 1 + g; t < t_last; t += G) {        // rows strictly inside the sub-tile
-            const int ps = s_rp[t] - e, pe = s_rp[t + 1] - e;
-            if (pe > ps && (ps >> 5) != ((pe - 1) >> 5)) {
-                float sum[NV];
-                pieces(t, sum);
-                float out[NV];
+#pragma unroll 1
+        for (int b = 0; b + 1 < kPer / kBatch; ++b) batch(b, std::true_type{});
+        batch(kPer / kBatch - 1, std::false_type{});
+
+        // ---- rows cut between lane groups: the group where the row begins (group 0 for the one that is carried on) adds
+        // the others' sums up to their first row start, in entry order
+        if (g > 0 && w == 0u) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) {
-                    out[q] = sum[q] * s_du[t];
-                    if (relu) out[q] = fmaxf(out[q], 0.0f);
-                }
-                Piece<BF16>::store(z + (int64_t)(k_cur + t) * kRowBytes + sub * 16, out);
+            for (int q = 0; q < NV; ++q) s_left[g][sub * NV + q] = acc[q];
+        }
+        wave_lds_sync();
+        const int from = headed ? 63 - __builtin_clzll(headed) : 0;      // the group whose row is open at the end
+        const uint64_t behind = headed & ~((2ull << g) - 1);
+        const int next = behind ? __builtin_ctzll(behind) : G;           // the next group with a row start
+        const int last = behind && !((at_once >> next) & 1) ? next : next - 1;
+        const bool whole = __builtin_amdgcn_inverse_ballot_w64(closed);
+        if (g == 0 || w != 0u) {
+            for (int gg = g + 1; gg <= last; ++gg)
+#pragma unroll
+                for (int q = 0; q < NV; ++q) acc[q] += s_left[gg][sub * NV + q];
+            if (behind) {
+                if (whole) store_row(ref, acc); else to_carry(0, acc);   // (not whole: group 0 with the row of an earlier range)
+            } else if (final && cnt == SUB) {
+                const int row = FAR ? ref.at : ref.at / kRowBytes;
+                const bool ends = k_next > row || e_end == nnz;          // k_next: the row of the entry behind the range
+                if (whole && ends) store_row(ref, acc);
+                else to_carry(whole ? 1 : 0, acc);                       // goes on in the next range; or ends what earlier ranges began, or lies inside it
+                if (whole && !ends) open_row = row;
+            }
+            if (g == 0 && cut && w != 0u) {                              // the row of an earlier range ended inside group 0
+                float first[NV];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) first[q] = s_left[0][sub * NV + q];
+                to_carry(0, first);
             }
         }
-        if (lane < LPR) {                                // the first and the last row of the sub-tile
-            const bool first_starts = s_rp[0] == e, first_ends = s_rp[1] <= e_stop;
-            const bool first_whole_in_group = first_starts && first_ends && ((s_rp[1] - e - 1) >> 5) == 0;
-            if (!first_whole_in_group) {
-                float sum[NV];
-                pieces(0, sum);
-                if (first_starts) {                      // nothing is being carried: this row begins the carry
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) run[q] = sum[q];
-                    running = true;
-                    began_here = true;
-                    run_row = k_cur;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) run[q] += sum[q];
-                    if (!running) { running = true; began_here = false; run_row = k_cur; }
-                }
-                if (first_ends) {
-                    if (began_here) {
-                        finish_row<BF16, NV>(z, (int64_t)run_row, kRowBytes, lane, dinv, relu, run);
-                    } else {                             // end of the row inherited from the previous range
-#pragma unroll
-                        for (int q = 0; q < NV; ++q) my_carry[lane * NV + q] = run[q];
-                    }
-                    running = false;
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) run[q] = 0.0f;
-                }
-            }
-            if (t_last > 0) {
-                const bool last_ends = s_rp[t_last + 1] <= e_stop;
-                const int ps = s_rp[t_last] - e;
-                const bool last_whole_in_group = last_ends && (ps >> 5) == ((e_stop - e - 1) >> 5);
-                if (!last_whole_in_group) {
-                    float sum[NV];
-                    pieces(t_last, sum);
-                    if (last_ends) {
-                        float out[NV];
-#pragma unroll
-                        for (int q = 0; q < NV; ++q) {
-                            out[q] = sum[q] * s_du[t_last];
-                            if (relu) out[q] = fmaxf(out[q], 0.0f);
-                        }
-                        Piece<BF16>::store(z + (int64_t)(k_cur + t_last) * kRowBytes + lane * 16, out);
-                    } else {                             // goes on in the next sub-tile
-#pragma unroll
-                        for (int q = 0; q < NV; ++q) run[q] = sum[q];
-                        running = true;
-                        began_here = true;
-                        run_row = k_cur + t_last;
-                    }
-                }
-            }
+        if (final) {
+            open_row = __builtin_amdgcn_readlane(open_row, from * LPR);
+            break;
         }
+#pragma unroll
+        for (int q = 0; q < NV; ++q) run[q] = __shfl(acc[q], from * LPR + sub, kWave);
+        run_ref = RowRef{(uint32_t)__builtin_amdgcn_readlane((int)ref.at, from * LPR), __shfl(ref.du, from * LPR, kWave)};
+        began_here = (closed >> (from * LPR)) & 1;
+        running = true;
         k_cur = k_next;
         e = e_stop;
-        __syncthreads();
+        wave_lds_sync();
     }
-
-    if (lane < LPR) {
-        if (running) {
-            if (began_here) {                            // goes on in the next range
-#pragma unroll
-                for (int q = 0; q < NV; ++q) my_carry[F + lane * NV + q] = run[q];
-                open_row = run_row;
-            } else {                                     // the whole range lies inside one row
-#pragma unroll
-                for (int q = 0; q < NV; ++q) my_carry[lane * NV + q] = run[q];
-            }
-        }
-        if (lane == 0 && record) recs[range] = RangeRec{open_row, 0, 0, 0};
-    }
-    if (e_end == nnz)                                    // rows without entries beyond the last staged window
-        for (int k = k_win + staged_last - 1 + lane; k < n; k += kWave)
-            if (rowptr[k] == rowptr[k + 1]) zero_row<LPR, SLICES, BF16>(z, k);
+    if (lane == 0 && record) recs[range] = RangeRec{open_row, 0, 0, 0};
 }
 
-// Workgroups are dealt to the eight XCDs in turn, and each XCD has an L2 of its own.  Ranges are handed out in chunks of
-// kXcdChunk consecutive ones per XCD, so that rows which lie close together (and in a graph with locality gather the same
-// rows of H) meet in one L2, while every XCD still gets a share of every part of the matrix (parts differ in cost per entry
-// when row lengths are clustered).  With SLICES > 1 an XCD takes one slice of the columns of H only (see slices_of): each
-// range is then walked by SLICES wavefronts, on SLICES different XCDs.
-template <int LPR, int SLICES, bool BF16, bool SCALE_V>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4, 8))) void spmm_stream_kernel(int n, int relu, Batch batch) {
-    constexpr int kGroups = kXcds / SLICES;                             // XCDs per slice
-    const Item &it = batch.item[blockIdx.y];
-    const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds, slice = xcd % SLICES;
-    const int range = ((slot / kXcdChunk) * kGroups + xcd / SLICES) * kXcdChunk + slot % kXcdChunk;
+// Workgroups are dealt to the eight XCDs in turn, and each XCD has an L2 of its own, so what matters is which rows of H the
+// wavefronts of one XCD gather at the same time.  A launch's work is a line of units, an item's slice of columns each (see
+// slices_of), of `ranges` ranges, and every XCD takes an eighth of the line, or, where an XCD would get less than a unit,
+// kXcds / units of them deal the ranges of a unit among themselves in chunks of kXcdChunk (so that each gets a share of
+// every part of the matrix: parts differ in cost per entry when row lengths are clustered).  An XCD then has one frame of H (or one
+// slice of it) at a time to keep in its L2.
+struct Line { int first, units, ranges, per_xcd, sharing; };   // the first item of the launch; ranges of a unit; of an XCD; log2 of the XCDs that share a unit, or -1
+
+template <int LPR, int SLICES, bool BF16, bool SCALE_V, bool FAR, bool ONE>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(ONE || !SCALE_V ? 4 : 3, 8))) void spmm_stream_kernel(int n, int relu, Line line, Batch batch) {
+    const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
+    int unit, range;
+    if (line.sharing >= 0) {
+        unit = xcd >> line.sharing;
+        range = ((slot / kXcdChunk << line.sharing) + (xcd & ((1 << line.sharing) - 1))) * kXcdChunk + slot % kXcdChunk;
+    } else {
+        const int at = xcd * line.per_xcd + slot;
+        unit = at / line.ranges;
+        range = at - unit * line.ranges;
+    }
+    if (unit >= line.units) return;
+    const Item &it = batch.item[line.first + unit / SLICES];
     if (range >= it.n_ranges) return;
+    const int slice = unit % SLICES;
     constexpr int F = LPR * Piece<BF16>::kVals;                         // columns of a slice
-    spmm_stream<LPR, SLICES, BF16, SCALE_V>(range, n, it.nnz, it.range_len, it.n_ranges, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
+    spmm_stream<LPR, SLICES, BF16, SCALE_V, FAR, ONE>(range, n, it.nnz, it.range_len, as_global(it.rowptr), as_global(it.colidx), as_global(it.dinv),
                                             as_global(it.h) + slice * LPR * 16, as_global(it.z) + slice * LPR * 16, relu,
                                             as_global(it.recs), slice == 0, as_global(it.carry) + (int64_t)slice * it.n_ranges * 2 * F,
-                                            as_global(it.vals), it.gather_dinv != 0);
+                                            as_global(it.vals), it.gather_dinv != 0, it.rows_per_entry);
 }
 
 // Rows cut by range boundaries: the range where such a row begins owns it and adds the left carries of the following
@@ -584,29 +515,48 @@ size_t workspace_layout(int64_t nnz, int32_t f, Workspace *ws, void *base, int64
     return total;
 }
 
-// The aggregations of one launch pair; grid.x follows from the longest, the others leave early.
+// The aggregations of one launch pair; the line's units are as long as the longest, the others' wavefronts leave early.
 template <int LPR, int SLICES, bool BF16>
 int launch(int64_t n, int count, const Batch &b, bool scale_v, int relu, hipStream_t s) {
-    constexpr int G = 256 / LPR, kRound = kXcds / SLICES * kXcdChunk;   // ranges per round of chunks over the XCDs
+    constexpr int G = 256 / LPR;
     int ranges = 0;
     for (int k = 0; k < count; ++k) ranges = std::max(ranges, b.item[k].n_ranges);
-    const int grid = (ranges + kRound - 1) / kRound * kXcds * kXcdChunk;
-    if (scale_v)
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, SLICES, BF16, true>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
-    else
-        hipLaunchKernelGGL((spmm_stream_kernel<LPR, SLICES, BF16, false>), dim3(grid, count), dim3(kWave), 0, s, (int)n, relu, b);
-    DGNN_RETURN_IF_LAUNCH_FAILED();
+    bool one = true;
+    for (int k = 0; k < count; ++k) one = one && b.item[k].range_len == kWave / LPR * per_group(LPR);
+    auto stream_kernel = [&](auto far, auto single) {
+        return scale_v ? spmm_stream_kernel<LPR, SLICES, BF16, true, decltype(far)::value, decltype(single)::value>
+                       : spmm_stream_kernel<LPR, SLICES, BF16, false, decltype(far)::value, decltype(single)::value>;
+    };
+    const auto kernel = n * (LPR * SLICES * 16) > (int64_t(1) << 32) ? stream_kernel(std::true_type{}, std::false_type{})
+                        : one                                        ? stream_kernel(std::false_type{}, std::true_type{})
+                                                                     : stream_kernel(std::false_type{}, std::false_type{});
+    // a grid's threads are counted in 32 bits
+    const int most = (int)std::max<int64_t>(1, ((int64_t(1) << 31) / kWave) / ((int64_t)ranges * SLICES + kXcds * kXcdChunk));
+    for (int first = 0; first < count; first += most) {
+        const int units = std::min(count - first, most) * SLICES;
+        const int sharing = kXcds % units == 0 ? __builtin_ctz(kXcds / units) : -1, round = kXcdChunk << std::max(sharing, 0);
+        const int per_xcd = sharing >= 0 ? (ranges + round - 1) / round * kXcdChunk : (int)(((int64_t)units * ranges + kXcds - 1) / kXcds);
+        hipLaunchKernelGGL(kernel, dim3(kXcds * per_xcd), dim3(kWave), 0, s, (int)n, relu, Line{first, units, ranges, per_xcd, sharing}, b);
+        DGNN_RETURN_IF_LAUNCH_FAILED();
+    }
     hipLaunchKernelGGL((spmm_carry_kernel<LPR, SLICES, BF16>), dim3((ranges + G - 1) / G, count, SLICES), dim3(256), 0, s, relu, b);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
 
-// Into how many slices of columns an aggregation is cut, one group of XCDs per slice: an L2 then holds that slice of H only,
-// as if it were so much larger, and a lane group stays at 16 lanes.  Rows of 512 bytes in two slices of 256: uniform graph of
-// 32 K vertices 45 -> 36 us, R-MAT 2^20 1.10 -> 0.91 ms, uniform 2^20 (no reuse either way) 1.34 ms both.  Not for rows of 256
-// bytes: every entry's bookkeeping is done once per slice, which costs power-law graphs more (7 %) than the L2 gives back, and
-// below 128 bytes, the L2's line, nothing is saved at all (twice the time).
-int slices_of(int32_t f, dgnn_dtype dt) { return f * (dt == DGNN_F32 ? 4 : 2) > 256 ? 2 : 1; }
+// Into how many slices of columns an aggregation is cut, each with XCDs of its own: an L2 then holds that slice of H only, as if
+// it were so much larger.  Every entry's bookkeeping is done once per slice, and below 128 bytes, the L2's line, nothing is saved
+// (twice the time).  Slices of 128 bytes pay where H does not fit an L2 of 4 MB but a slice of it does for a good part; us per
+// aggregation, whole rows / slices (512-byte rows: slices of 256 / of 128), for several timesteps as the drivers batch them:
+//   256-byte rows   uniform graph, 16 entries per row: 25 K vertices 7.3 / 7.0, 50 K 23.3 / 16.5, 60 K 24.9 / 18.8, 100 K 59 / 50,
+//                   200 K equal, 1 M 664 / 690; R-MAT 2^16 18.5 / 20.1, 2^17 45 / 47, 2^20 361 / 373
+//   512-byte rows   uniform 50 K 40 / 30, 100 K 95 / 84, 300 K 309 / 301; R-MAT 2^16 43 / 48, 2^18 173 / 180
+// and rows of 512 bytes go in two slices of 256 everywhere else (uniform 32 K whole / two 45 / 36, R-MAT 2^20 1.10 / 0.91 ms).
+int slices_of(int64_t n, int32_t f, dgnn_dtype dt) {
+    const int row_bytes = f * (dt == DGNN_F32 ? 4 : 2);
+    const bool narrow = row_bytes >= 256 && n * 128 >= (int64_t(3) << 20) && n * 128 <= (int64_t(16) << 20);
+    return narrow ? row_bytes / 128 : row_bytes > 256 ? 2 : 1;
+}
 
 }  // namespace
 
@@ -621,14 +571,19 @@ extern "C" int dgnn_spmm_workspace(int64_t n, int64_t nnz, int32_t f, size_t *by
 namespace {
 
 // Entries per range of one call for this snapshot, width and storage type (max_ranges as in range_length).
-int range_length_of_call(int64_t nnz, int32_t f, dgnn_dtype dt, int64_t max_ranges = 0) {
-    const int lpr = (dt == DGNN_F32 ? f / 4 : f / 8) / slices_of(f, dt);
-    return range_length(nnz, (kWave / lpr) * kPer, max_ranges);
+int range_length_of_call(int64_t n, int64_t nnz, int32_t f, dgnn_dtype dt, int64_t max_ranges = 0) {
+    const int lpr = (dt == DGNN_F32 ? f / 4 : f / 8) / slices_of(n, f, dt);
+    return range_length(nnz, (kWave / lpr) * per_group(lpr), max_ranges);
 }
 
 int launch_width(int64_t n, int count, const Batch &b, bool scale_v, int32_t f, dgnn_dtype dt, int relu, hipStream_t s) {
     const bool bf = dt == DGNN_BF16;
-    if (slices_of(f, dt) == 2) return launch<16, 2, false>(n, count, b, scale_v, relu, s);      // fp32, 128 columns
+    switch (slices_of(n, f, dt)) {
+        case 4: return launch<8, 4, false>(n, count, b, scale_v, relu, s);                      // fp32, 128 columns
+        case 2: return f == 128 && !bf ? launch<16, 2, false>(n, count, b, scale_v, relu, s)
+                       : bf            ? launch<8, 2, true>(n, count, b, scale_v, relu, s) : launch<8, 2, false>(n, count, b, scale_v, relu, s);
+        default: break;
+    }
     switch (bf ? f / 8 : f / 4) {   // lanes per feature row, 16 bytes each
         case 2: return launch<2, 1, true>(n, count, b, scale_v, relu, s);
         case 4: return bf ? launch<4, 1, true>(n, count, b, scale_v, relu, s) : launch<4, 1, false>(n, count, b, scale_v, relu, s);
@@ -648,7 +603,7 @@ int spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *colidx, c
     if (!aligned16(h) || !aligned16(z) || !aligned16(ws)) return DGNN_ERR_ALIGN;
     if (h == z) return DGNN_ERR_ALIAS;
     // max_ranges > 0: the records of exactly this call, laid out for its own number of ranges
-    const int range_len = range_length_of_call(nnz, f, dt, max_ranges);
+    const int range_len = range_length_of_call(n, nnz, f, dt, max_ranges);
     if (range_len <= 0) return DGNN_ERR_CAPACITY;
     const int64_t ranges = (nnz + range_len - 1) / range_len;
     Workspace w;
@@ -656,7 +611,7 @@ int spmm(int64_t n, int64_t nnz, const int32_t *rowptr, const int32_t *colidx, c
     const bool scale_v = vals != nullptr || (dinv != nullptr && !(flags & DGNN_H_PRESCALED));
     Batch b;
     b.item[0] = Item{rowptr, colidx, dinv, vals, static_cast<const char *>(h), static_cast<char *>(z), w.recs, w.carry, (int32_t)nnz,
-                     range_len, (int32_t)ranges, dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0};
+                     range_len, (int32_t)ranges, dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0, (float)n / (float)nnz};
     return launch_width(n, 1, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
 }
 
@@ -675,7 +630,7 @@ extern "C" int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, 
     if (count <= 0 || nnz < 0 || !supported_width(f)) return DGNN_ERR_SHAPE;
     if (!fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // the shortest range any storage type uses at this width is one sub-tile; no call has more ranges than this
-    const int64_t shortest = kWave / (f / 4) * kPer;              // (slices make sub-tiles longer)
+    const int64_t shortest = kWave / (f / 4) * per_group(f / 4);  // (slices make sub-tiles longer)
     const int64_t ranges = std::min<int64_t>((nnz + shortest - 1) / shortest, std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange));
     *bytes = (size_t)count * workspace_layout(nnz, f, nullptr, nullptr, ranges + 1);
     return DGNN_OK;
@@ -691,7 +646,7 @@ extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *i
     const bool weighted = items[0].val != nullptr, normalised = items[0].dinv != nullptr;
     size_t needed = 0;
     auto ranges_of = [&](const dgnn_spmm_item &it, int &range_len) {
-        range_len = range_length_of_call(it.nnz, f, dt);
+        range_len = range_length_of_call(n, it.nnz, f, dt);
         return (it.nnz + range_len - 1) / range_len;
     };
     int range_len;
@@ -718,7 +673,7 @@ extern "C" int dgnn_spmm_batch(int64_t n, int32_t count, const dgnn_spmm_item *i
             Workspace w;
             base += workspace_layout(it.nnz, f, &w, base, ranges);
             b.item[k] = Item{it.rowptr, it.colidx, it.dinv, it.val, static_cast<const char *>(it.h), static_cast<char *>(it.z), w.recs, w.carry,
-                             (int32_t)it.nnz, range_len, (int32_t)ranges, it.dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0};
+                             (int32_t)it.nnz, range_len, (int32_t)ranges, it.dinv && !(flags & DGNN_H_PRESCALED) ? 1 : 0, (float)n / (float)it.nnz};
         }
         const int rc = launch_width(n, m, b, scale_v, f, dt, (flags & DGNN_RELU) ? 1 : 0, (hipStream_t)stream);
         if (rc != DGNN_OK) return rc;
@@ -773,7 +728,7 @@ extern "C" int dgnn_spmm_static(int64_t n, int64_t nnz, const int32_t *rowptr, c
     if (!fits_index(n + 1) || !fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // as many ranges as the array has room for records of: ranges grow longer where the usual ones would be too many
     const int64_t max_ranges = (int64_t)((kStaticScratchBytes - 512) / (sizeof(RangeRec) + 2 * (size_t)f * sizeof(float)));
-    if (range_length_of_call(nnz, f, dt, max_ranges) <= 0) return DGNN_ERR_CAPACITY;
+    if (range_length_of_call(n, nnz, f, dt, max_ranges) <= 0) return DGNN_ERR_CAPACITY;
     void *ptr = nullptr;
     const int rc = static_scratch(&ptr);
     if (rc != DGNN_OK) return rc;

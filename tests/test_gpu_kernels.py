@@ -6,6 +6,8 @@ import torch
 
 import oracle
 import paper_2109_07893_amd as dg
+from paper_2109_07893_amd import binding as B
+from paper_2109_07893_amd.batch import SpmmTable, pointers
 from dtdg_synth import WORKLOADS, DynamicGraph
 from helpers import assert_close, to_f64
 
@@ -407,6 +409,57 @@ def test_spmm_is_deterministic():
     h = torch.randn((n, 32), generator=torch.Generator().manual_seed(9))
     a, b = gpu_spmm(rp, ci, h, True), gpu_spmm(rp, ci, h, True)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("f,dtype", [(16, torch.bfloat16), (32, torch.float32), (64, torch.float32), (128, torch.bfloat16), (128, torch.float32)])
+@pytest.mark.parametrize("n", [3, 700, 24_600])
+def test_spmm_row_shapes_and_slices(n, f, dtype):
+    """Stretches of rows without entries longer than the 64 row pointers a wavefront looks at, runs of rows of one entry (a row
+    start at every entry), rows longer than a range, ends on edges of sub-tiles; 24 600 vertices: rows of 256 and 512 bytes in
+    slices of 128, and the first guess at a range's row misses.  The count handed over is an upper bound; several items at
+    once give the single call's result bit for bit, with values too."""
+    rng = np.random.default_rng(n + f)
+    lens = rng.choice([0, 1, 1, 2, 5, 16, 31], n)
+    lens[n // 5: n // 5 + min(200, n // 4)] = 0
+    lens[n // 2: n // 2 + min(700, n // 4)] = 1
+    lens[n // 3] = min(n, 2600)
+    lens[-1] = n % 2
+    lens = np.minimum(lens, n)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, l, replace=False)) for l in lens if l]).astype(np.int32)
+    val = rng.uniform(0.5, 2.0, ci.size).astype(np.float32)
+    h = torch.randn((n, f), generator=torch.Generator().manual_seed(n)).to(dtype)
+    bound = ci.size + 300
+    rp_d, ci_d, val_d = dev_i32(rp), dev_i32(np.concatenate([ci, np.zeros(300, np.int32)])), torch.tensor(np.concatenate([val, np.ones(300, np.float32)])).to(DEV)
+    h_d = h.to(DEV)
+    ws = torch.empty(dg.spmm_workspace(n, bound, f), dtype=torch.uint8, device=DEV)
+    ws_batch = torch.empty(B.spmm_batch_workspace(3, bound, f), dtype=torch.uint8, device=DEV)
+    for values in (None, val_d):
+        z = [torch.full((n, f), float("nan"), dtype=dtype, device=DEV) for _ in range(4)]
+        if values is None:
+            dg.spmm(rp_d, ci_d, bound, None, h_d, z[3], ws)
+        else:
+            dg.spmm_weighted(rp_d, ci_d, val_d, bound, h_d, z[3], ws)
+        table = SpmmTable(3)
+        for k, col in enumerate((rp_d.data_ptr(), ci_d.data_ptr(), 0, values.data_ptr() if values is not None else 0, h_d.data_ptr(), pointers(z[:3]), bound)):
+            table.column(k, col)
+        B.spmm_batch(n, 3, table.at(), f, dg.DGNN_F32 if dtype == torch.float32 else dg.DGNN_BF16, 0, ws_batch, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert all(torch.equal(z[3], k) for k in z[:3])
+        assert_close(to_f64(z[3]), oracle.spmm(rp, ci, to_f64(h), val=np.ones(ci.size) if values is None else val.astype(np.float64)), dtype, "row shapes")
+
+
+def test_spmm_beyond_32_bit_offsets():
+    """H and Z of more than 4 GB: rows of one entry copy a row of H each, exactly."""
+    n, f = (1 << 23) + 1000, 128
+    h = torch.arange(n, dtype=torch.float32, device=DEV)[:, None].expand(n, f).contiguous()
+    ci = ((torch.arange(n, dtype=torch.int64, device=DEV) * 5_000_011) % n).to(torch.int32)
+    rp = torch.arange(n + 1, dtype=torch.int32, device=DEV)
+    z = torch.full((n, f), float("nan"), device=DEV)
+    ws = torch.empty(dg.spmm_workspace(n, n, f), dtype=torch.uint8, device=DEV)
+    dg.spmm(rp, ci, n, None, h, z, ws)
+    torch.cuda.synchronize()
+    assert bool((z == ci.float()[:, None]).all())
 
 
 # ------------------------------------------------------------------------------- M-transform
