@@ -11,10 +11,13 @@ import torch
 
 from . import binding as B
 
-# Timesteps whose GCN operation is enqueued together: as many as keep the rows of H that the aggregations gather within this
-# many bytes (a quarter of the Infinity Cache).  Snapshots with larger frames fill the chip one at a time, and their H is
-# still in the cache when it is gathered.
-BATCH_BYTES = 64 << 20
+# Timesteps whose GCN operation is enqueued together: as many as keep the rows of H that the aggregations gather within this many
+# bytes.  An aggregation deals whole frames to the XCDs, each of which then gathers out of one frame at a time, so eight frames or
+# more are worth having, and every launch pair has a start and an end of its own; whether all of H stays in the Infinity Cache
+# (256 MB) matters less.  Whole passes in us for 64 / 256 / 512 / 1024 MB: two layers forward, 100 K vertices x 64 fp32, 2330 / 2108 /
+# 2056 / 2056; trained, 50 K, 1984 / 1676 / 1675 / 1675; 100 K x 128 bf16 forward 3379 / 2976 / 2947 / 2950; CD-GCN in bf16, 200 K x 64,
+# 944 / 860 / 858 / 859.
+BATCH_BYTES = 512 << 20
 
 # Stored entries up to which a block's snapshots are rebuilt as a series, and how many of them a step must make up for.  The
 # set-up takes 9 us per million entries; a step saves one rebuild's launches and the products and aggregations of its timestep

@@ -185,7 +185,7 @@ template <> struct Pack<true> {
     static __device__ __forceinline__ uintx4 pack(const float (&v)[8]) {
         uintx4 t;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = f32_to_bf16(v[2 * e]) | (f32_to_bf16(v[2 * e + 1]) << 16);
+        for (int e = 0; e < 4; ++e) t[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
         return t;
     }
 };

@@ -305,7 +305,7 @@ __device__ __forceinline__ void xw_bf16(const uint16_t *__restrict__ x, const ui
                                 if (relu) v[q] = fmaxf(v[q], 0.0f);
                             }
                             *reinterpret_cast<uint2 *>(h + row * FOUT + col) =
-                                make_uint2(f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16), f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16));
+                                make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
                         }
                     }
             }
@@ -396,8 +396,8 @@ __device__ __forceinline__ void xw_bf16_staged(const uint16_t *__restrict__ x, c
             for (int jj = 0; jj < JG; ++jj)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const uint32_t lo = f32_to_bf16(acc[jj][4 * g] * scale) | (f32_to_bf16(acc[jj][4 * g + 1] * scale) << 16);
-                    const uint32_t hi = f32_to_bf16(acc[jj][4 * g + 2] * scale) | (f32_to_bf16(acc[jj][4 * g + 3] * scale) << 16);
+                    const uint32_t lo = pack_bf16(acc[jj][4 * g] * scale, acc[jj][4 * g + 1] * scale);
+                    const uint32_t hi = pack_bf16(acc[jj][4 * g + 2] * scale, acc[jj][4 * g + 3] * scale);
                     *reinterpret_cast<uint2 *>(&tile_lds[i * LDT + ROFF + (j0 + jj) * 32 + 8 * g + 4 * hh]) = make_uint2(lo, hi);
                 }
             __builtin_amdgcn_sched_barrier(0);   // keep the column groups apart: their accumulators share registers
