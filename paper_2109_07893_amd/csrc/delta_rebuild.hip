@@ -23,7 +23,7 @@ using namespace dgnn;
 constexpr int kRowThreads = 256;
 constexpr int kRowsPerThread = 4;          // rowptr_kernel moves a thread's rows as one 16-byte access: keep at 4
 constexpr int kRowTile = kRowThreads * kRowsPerThread;
-constexpr int kHeavyList = 16 * kRowTile;    // list entries per row tile beyond which counting walks no more
+constexpr int kHeavyList = 8 * kRowTile;     // list entries per row tile beyond which counting walks no more (16: 21.2 instead of 19.4 us, see count_by_search)
 
 constexpr int kPerLane = 8;                  // old entries per lane and sub-tile of the merge
 constexpr int kSub = kWave * kPerLane;       // old entries per sub-tile, at most
@@ -97,20 +97,72 @@ __device__ __forceinline__ void wave_find_row_pair(const int32_t *__restrict__ a
     found_b = lo_b - 1;
 }
 
-// The same counts from lower bounds: thread t finds where each of its rows begins inside [lo, hi),
-// each search starting where the previous one ended.
-__device__ __forceinline__ void count_by_search(const int32_t *__restrict__ rows, int lo, int hi, int r0, int nr,
-                                                int *cnt, int tid) {
-    int from = lo;
-    int begin = 0;
+// The lists that change a snapshot: added entries, deleted entries and, in a weighted rebuild, value updates.
+constexpr int kLists = 3;
+
+// The same counts from lower bounds, for every list that `heavy` names: thread t finds where each of its rows begins inside
+// [lo, hi).  All searches of a thread advance in lock step, so the whole costs as many trips to memory as one search (one search
+// after the other, each starting where the last had ended, was what the kernel took: R-MAT, 2^19 vertices, 8.9 M entries,
+// 3 % churn with value updates 46.5 us, now 19.4).
+__device__ __forceinline__ void count_by_search(const int32_t *const (&rows)[kLists], const int (&lo)[kLists], const int (&hi)[kLists],
+                                                const bool (&heavy)[kLists], int r0, int nr, int (*cnt)[kRowTile], int tid) {
+    int pos[kLists][kRowsPerThread + 1], longest = 0;
+#pragma unroll
+    for (int l = 0; l < kLists; ++l) {
+        if (heavy[l]) longest = max(longest, hi[l] - lo[l]);
+#pragma unroll
+        for (int k = 0; k <= kRowsPerThread; ++k) pos[l][k] = lo[l];
+    }
+    auto key = [&](int k) { return r0 + min(tid * kRowsPerThread + k, nr); };
 #pragma unroll 1
-    for (int k = 0; k <= kRowsPerThread; ++k) {
-        const int t = tid * kRowsPerThread + k;
-        if (t > nr) break;
-        const int pos = lower_bound(rows, from, hi, r0 + t);     // first entry whose row is >= r0 + t
-        if (k > 0) cnt[t - 1] = pos - begin;
-        begin = pos;
-        from = pos;
+    for (int step = 1 << (31 - __clz(longest)); step > 0; step >>= 1) {
+        int v[kLists][kRowsPerThread + 1];
+#pragma unroll
+        for (int l = 0; l < kLists; ++l)
+            if (heavy[l])
+#pragma unroll
+                for (int k = 0; k <= kRowsPerThread; ++k) v[l][k] = rows[l][min(pos[l][k] + step, hi[l]) - 1];
+#pragma unroll
+        for (int l = 0; l < kLists; ++l)
+            if (heavy[l])
+#pragma unroll
+                for (int k = 0; k <= kRowsPerThread; ++k)
+                    if (pos[l][k] + step <= hi[l] && v[l][k] < key(k)) pos[l][k] += step;      // entries before pos have smaller rows
+    }
+#pragma unroll
+    for (int l = 0; l < kLists; ++l)
+        if (heavy[l])
+#pragma unroll
+            for (int k = 0; k < kRowsPerThread; ++k) cnt[l][tid * kRowsPerThread + k] = pos[l][k + 1] - pos[l][k];
+}
+
+// How many entries of each ascending list a[l][0 .. len[l]) lie below key[l]: 64-ary searches of the wavefront, in lock step.
+template <int LISTS>
+__device__ __forceinline__ void wave_count_below(const int32_t *const (&a)[LISTS], const int (&len)[LISTS], const int (&key)[LISTS], int lane, int (&below)[LISTS]) {
+    int hi[LISTS];
+    bool more = false;
+#pragma unroll
+    for (int l = 0; l < LISTS; ++l) {
+        below[l] = 0;
+        hi[l] = len[l];
+        more |= len[l] > 0;
+    }
+    while (more) {
+        int v[LISTS];
+#pragma unroll
+        for (int l = 0; l < LISTS; ++l) {
+            const int at = below[l] + lane * ((hi[l] - below[l] + kWave - 1) / kWave);
+            v[l] = at < hi[l] ? a[l][at] : key[l];
+        }
+        more = false;
+#pragma unroll
+        for (int l = 0; l < LISTS; ++l) {
+            const int step = (hi[l] - below[l] + kWave - 1) / kWave, m = __popcll(__ballot(v[l] < key[l]));
+            const int from = below[l];
+            below[l] = m ? from + (m - 1) * step + 1 : from;
+            hi[l] = m ? min(from + m * step, hi[l]) : from;
+            more |= hi[l] > below[l];
+        }
     }
 }
 
@@ -122,10 +174,9 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
     int32_t *__restrict__ rowptr_next, float *__restrict__ dinv,
     int range_len, int n_ranges, RangeStart *__restrict__ range_start,
     const int32_t *__restrict__ upd_row, int n_upd, int32_t *status) {
-    __shared__ int s_add[kRowTile];
-    __shared__ int s_del[kRowTile];
+    __shared__ int s_cnt[kLists][kRowTile];     // entries per row of the added, deleted and updated lists
     __shared__ int s_bound[6];
-    __shared__ int s_wsum[2][kRowThreads / kWave];
+    __shared__ int s_wsum[kLists][kRowThreads / kWave];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
@@ -158,32 +209,43 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
             if (wave < 2) s_bound[4 + wave] = found_upd + 1;
         }
     }
-    for (int i = tid; i < kRowTile; i += kRowThreads) { s_add[i] = 0; s_del[i] = 0; }
+    for (int i = tid; i < kRowTile; i += kRowThreads)
+#pragma unroll
+        for (int l = 0; l < kLists; ++l) s_cnt[l][i] = 0;
     __syncthreads();
-    const int a0 = s_bound[0], a1 = s_bound[1], d0 = s_bound[2], d1 = s_bound[3];
-    const int u0 = upd_row ? s_bound[4] : 0, u1 = upd_row ? s_bound[5] : 0;
     // A tile of hub rows can own a very long stretch of a list; walking it would leave the whole chip
     // waiting for this workgroup, so there the counts come from one lower bound per row instead.
-    if (a1 - a0 <= kHeavyList) count_runs(add_row, a0, a1, r0, nr, s_add, tid);
-    else count_by_search(add_row, a0, a1, r0, nr, s_add, tid);
-    if (d1 - d0 <= kHeavyList) count_runs(del_row, d0, d1, r0, nr, s_del, tid);
-    else count_by_search(del_row, d0, d1, r0, nr, s_del, tid);
+    const int32_t *const rows[kLists] = {add_row, del_row, upd_row};
+    const int lo[kLists] = {s_bound[0], s_bound[2], upd_row ? s_bound[4] : 0}, hi[kLists] = {s_bound[1], s_bound[3], upd_row ? s_bound[5] : 0};
+    bool heavy[kLists], any_heavy = false;
+#pragma unroll
+    for (int l = 0; l < kLists; ++l) {
+        heavy[l] = hi[l] - lo[l] > kHeavyList;
+        any_heavy |= heavy[l];
+        if (!heavy[l]) count_runs(rows[l], lo[l], hi[l], r0, nr, s_cnt[l], tid);
+    }
+    if (any_heavy) count_by_search(rows, lo, hi, heavy, r0, nr, s_cnt, tid);
     __syncthreads();
 
-    int ca[kRowsPerThread], cd[kRowsPerThread];
-    int sa = 0, sd = 0;
+    int ca[kRowsPerThread], cd[kRowsPerThread], cu[kRowsPerThread];
+    int sum[kLists] = {0, 0, 0}, inc[kLists];
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k) {
-        ca[k] = s_add[tid * kRowsPerThread + k];
-        cd[k] = s_del[tid * kRowsPerThread + k];
-        sa += ca[k];
-        sd += cd[k];
+        ca[k] = s_cnt[0][tid * kRowsPerThread + k];
+        cd[k] = s_cnt[1][tid * kRowsPerThread + k];
+        cu[k] = s_cnt[2][tid * kRowsPerThread + k];
+        sum[0] += ca[k];
+        sum[1] += cd[k];
+        sum[2] += cu[k];
     }
-    int ia = wave_scan_add(sa, lane), id = wave_scan_add(sd, lane);
-    if (lane == kWave - 1) { s_wsum[0][wave] = ia; s_wsum[1][wave] = id; }
+#pragma unroll
+    for (int l = 0; l < kLists; ++l) {
+        inc[l] = wave_scan_add(sum[l], lane);
+        if (lane == kWave - 1) s_wsum[l][wave] = inc[l];
+    }
     __syncthreads();
-    int oa = a0 + ia - sa, od = d0 + id - sd;      // exclusive offsets of this thread's first row
-    for (int w = 0; w < wave; ++w) { oa += s_wsum[0][w]; od += s_wsum[1][w]; }
+    int oa = lo[0] + inc[0] - sum[0], od = lo[1] + inc[1] - sum[1], ou = lo[2] + inc[2] - sum[2];      // exclusive offsets of this thread's first row
+    for (int w = 0; w < wave; ++w) { oa += s_wsum[0][w]; od += s_wsum[1][w]; ou += s_wsum[2][w]; }
 
     int rn[kRowsPerThread];
     float dv[kRowsPerThread];
@@ -196,17 +258,12 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
         if (r < r1) {
             // ranges of the merge that begin inside this row (few rows hold a multiple of the range length; a hub
             // row several): what the merge needs to know about the row, so that it starts without a search
-            int us = -1, ue = 0;
-            for (int g = max((p + range_len - 1) / range_len, 0); g < n_ranges && (int64_t)g * range_len < q; ++g) {
-                if (upd_row && us < 0) {      // where the row's value updates lie: two searches inside the tile's stretch
-                    us = lower_bound(upd_row, u0, u1, r);
-                    ue = lower_bound(upd_row, us, u1, r + 1);
-                }
-                range_start[g] = RangeStart{p, q, p + oa - od, q + oa + ca[k] - od - cd[k], oa, oa + ca[k], r, max(us, 0), ue, 0};
-            }
+            for (int g = max((p + range_len - 1) / range_len, 0); g < n_ranges && (int64_t)g * range_len < q; ++g)
+                range_start[g] = RangeStart{p, q, p + oa - od, q + oa + ca[k] - od - cd[k], oa, oa + ca[k], r, ou, ou + cu[k], 0};
         }
         oa += ca[k];
         od += cd[k];
+        ou += cu[k];
     }
     if (VEC && whole) {
         *reinterpret_cast<int4 *>(rowptr_next + r_own) = make_int4(rn[0], rn[1], rn[2], rn[3]);
@@ -304,21 +361,32 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
     };
     {
         const RangeStart st = range_start[blockIdx.x];                     // the row that holds entry e_begin
+        const int c_at = colidx_prev[e_begin], c_before = colidx_prev[max(e_begin - 1, 0)];
         const int rp = st.rp, rp1 = st.rp1, rn = st.rn, rn1 = st.rn1, as = st.as, ae = st.ae;
         const int ds = rp + as - rn, de = rp1 + ae - rn1;
         first_row = min(max(st.row, 0), n - 1);
         fetch_window(first_row);
         a_cur = as;
         d_cur = ds;
+        if (UPDATES) u_cur = st.us;
         if (rp < e_begin) {   // the range begins inside the row: skip what earlier ranges place
-            if (as >= 0 && as < ae && ae <= n_add) a_cur = lower_bound(add_col, as, ae, colidx_prev[e_begin - 1]);
-            if (ds >= 0 && ds < de && de <= n_del) d_cur = lower_bound(del_col, ds, de, colidx_prev[e_begin]);
+            // (all lists at once, 64 entries a trip: most ranges of a hub row start here)
+            constexpr int kFound = UPDATES ? 3 : 2;
+            const bool in_a = as >= 0 && as < ae && ae <= n_add, in_d = ds >= 0 && ds < de && de <= n_del;
+            const int32_t *list[kFound] = {add_col + (in_a ? as : 0), del_col + (in_d ? ds : 0)};
+            int len[kFound] = {in_a ? ae - as : 0, in_d ? de - ds : 0}, key[kFound] = {c_before, c_at}, below[kFound];
+            if constexpr (UPDATES) {
+                const bool in_u = st.us >= 0 && st.us < st.ue && st.ue <= n_upd;
+                list[2] = upd_col + (in_u ? st.us : 0);
+                len[2] = in_u ? st.ue - st.us : 0;
+                key[2] = c_at;
+            }
+            wave_count_below<kFound>(list, len, key, lane, below);
+            a_cur += below[0];
+            d_cur += below[1];
+            if constexpr (UPDATES) u_cur += below[2];
         }
-        if (UPDATES) {
-            u_cur = st.us;
-            if (rp < e_begin && st.us >= 0 && st.us < st.ue && st.ue <= n_upd) u_cur = lower_bound(upd_col, st.us, st.ue, colidx_prev[e_begin]);
-            u_cur = min(max(u_cur, 0), n_upd);
-        }
+        if (UPDATES) u_cur = min(max(u_cur, 0), n_upd);
         a_cur = min(max(a_cur, 0), n_add);
         d_cur = min(max(d_cur, 0), n_del);
         base = rn + (e_begin - rp) - (d_cur - ds) + (a_cur - as);

@@ -117,6 +117,30 @@ def test_weighted_rebuild_hub_rows_and_absent_updates():
         assert np.array_equal(got[2], f32(want[2])), merged
 
 
+@pytest.mark.parametrize("n,counts", [(700, (8193, 8192, 8193)), (1024, (9000, 0, 20000)), (1030, (100, 15000, 8192)), (2500, (20000, 12000, 30000))])
+def test_weighted_rebuild_of_tiles_that_own_long_list_stretches(n, counts):
+    """More than 8192 entries of some lists, and fewer of others, in one tile of 1024 rows, whose counts then come from searches;
+    hub rows in which many ranges of the merge begin."""
+    rng = np.random.default_rng(n)
+    hub = rng.choice(n, 3)
+    rows = np.concatenate([np.arange(n), rng.integers(0, n, 60 * n), np.repeat(hub, 600)])
+    cols = np.concatenate([np.arange(n), rng.integers(0, n, 60 * n), rng.integers(0, n, 1800)])
+    rp, ci = oracle.csr_from_edges(n, rows.astype(np.int32), cols.astype(np.int32))
+    val = f32(rng.uniform(0.1, 1.0, ci.size))
+    r_of = np.repeat(np.arange(n, dtype=np.int32), np.diff(rp))
+    off = rng.permutation(np.flatnonzero(r_of != ci))
+    n_add, n_del, n_upd = counts
+    gone, touched = np.sort(off[:n_del]), np.sort(off[n_del:n_del + n_upd])
+    free = np.setdiff1d(np.arange(n, dtype=np.int64)[:, None] * n + np.arange(n), r_of.astype(np.int64) * n + ci)
+    new = np.sort(rng.choice(free, n_add, replace=False))
+    add = ((new // n).astype(np.int32), (new % n).astype(np.int32), f32(rng.uniform(1, 2, n_add)))
+    dele, upd = (r_of[gone], ci[gone]), (r_of[touched], ci[touched], f32(rng.uniform(3, 4, n_upd)))
+    want = oracle.delta_apply_weighted(n, rp, ci, val, add=add, dele=dele, upd=upd)
+    got = gpu_rebuild_weighted(n, rp, ci, val, add, dele, upd, merged=True)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert np.array_equal(got[2], f32(want[2]))
+
+
 def test_weighted_rebuild_reports_an_unsorted_update_list():
     """Declared sorted, but not: the check says so, and nothing is written outside the result."""
     wl = WORKLOADS["c1"]
