@@ -15,8 +15,8 @@
 // dL/dh_{t-1}, which stays on chip for the next step, and dL/dY1 under the ReLU's mask; da leaves for the weight gradients,
 // which contract over vertices and timesteps and are one product afterwards.
 //
-// fp32 is bound by the fp32 matrix cores (and the cell's exponentials, which share their issue slots), bf16 by the cell and the
-// tile staging; what the series saves is the traffic and the launches of the state: h and c in, c out, dh and dc both ways.
+// fp32 is bound by the fp32 matrix cores (and the cell's exponentials, which share their issue slots), bf16 by the cell (and, up
+// to 64 columns of Y, the tile staging); what the series saves is the traffic and the launches of the state: h and c in, c out, dh and dc both ways.
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>
@@ -82,10 +82,18 @@ struct Weights {
     }
 };
 
-// acc[g] = transposed tile g of [Y | h] [W_x ; W_h] for the 32 vertices in `tile` (rows of LDT elements)
+// Where the lanes' rows of Y come straight from memory in operand layout (16 bytes of a row per lane) instead of through the tile
+// buffer, which then holds h or c only.  128 + 64 columns of bf16: W takes 100 KB of the LDS, whole tiles of [Y | h] leave room for four
+// wavefronts, one per SIMD, which multiply and then evaluate the cell with nothing beside it; without Y there are eight.  200 K
+// vertices, 6 steps: four wavefronts 315 us, eight 221.  With c kept for every step the buffer carries both states, and stays.
+template <int FY, int HID, bool BF16, bool KEEP_C> constexpr bool kDirectY = BF16 && FY == 128 && HID == 64 && !KEEP_C;
+
+// acc[g] = transposed tile g of [Y | h] [W_x ; W_h] for the 32 vertices in `tile` (rows of LDT elements).  In bf16 step s of the
+// contraction takes the 16 columns from 16 s on, the lane half h the second eight of them; with `y` the first FY / 16 steps'
+// operands are given, and the tile holds the columns behind them.
 template <int FY, int HID, bool BF16, int LDT>
 __device__ __forceinline__ void gate_tiles(const typename Store<BF16>::Elem *s_w, const typename Store<BF16>::Elem *tile, int i, int hh,
-                                           floatx16 (&acc)[4 * HID / 32]) {
+                                           floatx16 (&acc)[4 * HID / 32], const uintx4 *y = nullptr) {
     typedef Weights<FY, HID, BF16> W;
     constexpr int KH = W::K / 2;
 #pragma unroll
@@ -96,12 +104,14 @@ __device__ __forceinline__ void gate_tiles(const typename Store<BF16>::Elem *s_w
         constexpr int KS = KH / 8;
         bf16x8 a[KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) a[s] = *reinterpret_cast<const bf16x8 *>(&tile[i * LDT + hh * KH + s * 8]);
+        for (int s = 0; s < KS; ++s)
+            a[s] = y && s < FY / 16 ? __builtin_bit_cast(bf16x8, y[s < FY / 16 ? s : 0])
+                                    : *reinterpret_cast<const bf16x8 *>(&tile[i * LDT + 16 * s + 8 * hh - (y ? FY : 0)]);
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int g = 0; g < W::NT; ++g) {
-                const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(&s_w[(g * 32 + i) * W::kLd + hh * KH + s * 8]);
+                const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(&s_w[(g * 32 + i) * W::kLd + 16 * s + 8 * hh]);
                 acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, a[s], acc[g], 0, 0, 0);
             }
     } else {
@@ -134,9 +144,11 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     typedef typename S::Elem Elem;
     typedef Weights<FY, HID, BF16> W;
     constexpr int P = S::kPiece;
-    constexpr int LDT = W::K + S::kTilePad;
+    constexpr bool DIRECT = kDirectY<FY, HID, BF16, KEEP_C>;
+    constexpr int LDT = (DIRECT ? HID : W::K) + S::kTilePad;
+    constexpr int H_COL = DIRECT ? 0 : FY;             // where h lies in a row of the tile buffer
     constexpr int Y_PIECES = 32 * FY / P / kWave, S_PIECES = 32 * HID / P / kWave;     // 16-byte pieces per lane of a tile
-    static_assert(W::K >= 2 * HID, "the tile buffer also carries c beside h");
+    static_assert(DIRECT || W::K >= 2 * HID, "the tile buffer also carries c beside h");
     __shared__ __attribute__((aligned(16))) Elem s_w[W::kSize];
     __shared__ __attribute__((aligned(16))) float s_bias[W::G4];
     __shared__ __attribute__((aligned(16))) Elem s_tile[WAVES][32 * LDT];
@@ -158,6 +170,11 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     auto fetch_y = [&](int64_t tile, int t) {
 #pragma unroll
         for (int q = 0; q < Y_PIECES; ++q) {
+            if (DIRECT) {
+                const int64_t row = tile * 32 + i;
+                yv[q] = row < n ? *reinterpret_cast<const uintx4 *>(y + (t * n + row) * FY + 16 * q + 8 * hh) : zero;
+                continue;
+            }
             const int64_t piece = tile * (32 * FY / P) + q * kWave + lane;
             yv[q] = (tile < n_tiles && piece * P < n * FY) ? reinterpret_cast<const uintx4 *>(y + t * n * FY)[piece] : zero;
         }
@@ -191,28 +208,40 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     if (kStateAhead) fetch_state(first);
     for (int64_t tile = first; tile < n_tiles; tile += stride) {
         if (!kStateAhead) fetch_state(tile);
-        put(FY, hv);
+        if (!DIRECT) put(FY, hv);
         put(0, cv);
         wave_lds_sync();
         floatx4 cell[HID / 8];                          // c of this lane's state elements
 #pragma unroll
         for (int m = 0; m < HID / 8; ++m) cell[m] = S::load4(&tile_lds[i * LDT + 8 * m + 4 * hh]);
         wave_lds_sync();
+        if (DIRECT) {
+            put(0, hv);
+            wave_lds_sync();
+        }
 #pragma unroll 1
         for (int t = 0; t < T; ++t) {
-#pragma unroll
-            for (int q = 0; q < Y_PIECES; ++q) {
-                const int e = (q * kWave + lane) * P;
-                *reinterpret_cast<uintx4 *>(&tile_lds[(e / FY) * LDT + e % FY]) = yv[q];
-            }
-            if (t + 1 < T) fetch_y(tile, t + 1);
-            else {
-                fetch_y(tile + stride, 0);
-                if (kStateAhead) fetch_state(tile + stride);
-            }
-            wave_lds_sync();
+            auto fetch_next = [&]() {
+                if (t + 1 < T) fetch_y(tile, t + 1);
+                else {
+                    fetch_y(tile + stride, 0);
+                    if (kStateAhead) fetch_state(tile + stride);
+                }
+            };
             floatx16 acc[W::NT];
-            gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc);
+            if constexpr (DIRECT) {
+                gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc, yv);
+                fetch_next();                           // into the operands' registers, while the cell is evaluated
+            } else {
+#pragma unroll
+                for (int q = 0; q < Y_PIECES; ++q) {
+                    const int e = (q * kWave + lane) * P;
+                    *reinterpret_cast<uintx4 *>(&tile_lds[(e / FY) * LDT + e % FY]) = yv[q];
+                }
+                fetch_next();
+                wave_lds_sync();
+                gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc);
+            }
             wave_lds_sync();                            // every lane has its operands
 #pragma unroll
             for (int m = 0; m < HID / 8; ++m) {
@@ -227,12 +256,12 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
                     cell[m][r] = fast_sigmoid(af) * cell[m][r] + fast_sigmoid(ai) * fast_tanh(ag);
                     h_new[r] = fast_sigmoid(ao) * fast_tanh(cell[m][r]);
                 }
-                S::store4(&tile_lds[i * LDT + FY + k0], h_new);
+                S::store4(&tile_lds[i * LDT + H_COL + k0], h_new);
                 cell[m] = S::rounded(cell[m]);          // as a launch per step would hand it on: results do not depend on how many share one
                 if (KEEP_C) S::store4(&tile_lds[i * LDT + k0], cell[m]);
             }
             wave_lds_sync();
-            flush(FY, h + t * n * HID, tile);
+            flush(H_COL, h + t * n * HID, tile);
             if (KEEP_C) flush(0, c + t * n * HID, tile);
             wave_lds_sync();                            // Y's columns are written again
         }
@@ -604,15 +633,15 @@ bool backward_shape_ok(int32_t f_y, int32_t hidden, dgnn_dtype dt) {
     return f_y == 2 * hidden && (dt == DGNN_F32 ? hidden == 16 || hidden == 32 : dt == DGNN_BF16 && hidden == 32);
 }
 
-template <int FY, int HID, bool BF16, int WAVES>
+template <int FY, int HID, bool BF16, int WAVES, int KEEP_WAVES = WAVES>
 int launch_series(const void *y, const void *h0, const void *w_x, const void *w_h, const float *bias, const void *c0, void *c, void *h, int64_t n,
                   int T, bool keep_c, hipStream_t s) {
-    const int64_t n_tiles = (n + 31) / 32, needed = (n_tiles + WAVES - 1) / WAVES;
-    auto run = [&](auto kernel) {
-        const int64_t resident = resident_workgroups(kernel, WAVES * kWave, 256);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(needed, resident)), dim3(WAVES * kWave), 0, s, y, h0, w_x, w_h, bias, c0, c, h, n, n_tiles, T);
+    const int64_t n_tiles = (n + 31) / 32;
+    auto run = [&](auto kernel, int waves) {
+        const int64_t needed = (n_tiles + waves - 1) / waves, resident = resident_workgroups(kernel, waves * kWave, 256);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(needed, resident)), dim3(waves * kWave), 0, s, y, h0, w_x, w_h, bias, c0, c, h, n, n_tiles, T);
     };
-    if (keep_c) run(lstm_series_kernel<FY, HID, BF16, true, WAVES>); else run(lstm_series_kernel<FY, HID, BF16, false, WAVES>);
+    if (keep_c) run(lstm_series_kernel<FY, HID, BF16, true, KEEP_WAVES>, KEEP_WAVES); else run(lstm_series_kernel<FY, HID, BF16, false, WAVES>, WAVES);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
@@ -664,7 +693,7 @@ extern "C" int dgnn_lstm_series(const void *y, int32_t f_y, const void *h0, cons
     if (hidden == 32) return f_y == 32 ? launch_series<32, 32, true, 8>(y, h0, w_x, w_h, bias, c0, c, h, n, T, keep, s)
                                        : launch_series<64, 32, true, 8>(y, h0, w_x, w_h, bias, c0, c, h, n, T, keep, s);
     return f_y == 64 ? launch_series<64, 64, true, 8>(y, h0, w_x, w_h, bias, c0, c, h, n, T, keep, s)
-                     : launch_series<128, 64, true, 4>(y, h0, w_x, w_h, bias, c0, c, h, n, T, keep, s);
+                     : launch_series<128, 64, true, 8, 4>(y, h0, w_x, w_h, bias, c0, c, h, n, T, keep, s);
 }
 
 extern "C" int dgnn_lstm_step(const void *y, int32_t f_y, const void *h_prev, const void *w_x, const void *w_h,

@@ -432,6 +432,21 @@ def test_bf16_lstm_does_not_depend_on_the_steps_per_launch(f_y, hidden):
     assert torch.equal(h, out) and torch.equal(h_kept, out) and torch.equal(c, state)
 
 
+def test_bf16_lstm_of_more_vertices_than_wavefronts_hold():
+    """Wavefronts that walk several tiles of 32 vertices, a ragged last one among them: every vertex as in a call on its own slice."""
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    n, T, f_y, hidden = 3 * 65536 + 45, 3, 128, 64
+    y, h0, c0 = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((T, n, f_y), (n, hidden), (n, hidden)))
+    w_x, w_h = (torch.randn(k, 4 * hidden, generator=gen, device=DEV).mul_(k ** -0.5).to(torch.bfloat16) for k in (f_y, hidden))
+    c, h = torch.empty_like(c0), torch.empty(T, n, hidden, dtype=y.dtype, device=DEV)
+    dg.lstm_series(y, h0, w_x, w_h, None, c0, c, h)
+    for a in range(0, n, 50_000):
+        rows = slice(a, min(a + 50_000, n))
+        c_part, h_part = torch.empty_like(c0[rows]), torch.empty_like(h[:, rows])
+        dg.lstm_series(y[:, rows].contiguous(), h0[rows], w_x, w_h, None, c0[rows], c_part, h_part)
+        assert torch.equal(c[rows], c_part) and torch.equal(h[:, rows], h_part), a
+
+
 def test_bf16_cdgcn_layer_does_not_depend_on_the_steps_per_launch():
     from paper_2109_07893_amd.cdgcn import CdgcnLayer
     gen = torch.Generator().manual_seed(4)
