@@ -471,6 +471,14 @@ int dgnn_mproduct_backward_block(const void *g_y, void *g_z, int64_t T, int64_t 
                                  dgnn_dtype dt, void *stream);
 
 /*
+ * dgnn_mproduct_backward_block with the weights 1/min(w, t), followed by dgnn_relu_backward of every frame, in one pass and with
+ * the same results bit for bit: g_p[t][u][:] = row_scale[t][u] * (z[t][u][:] > 0 ? g_z[t][u][:] : 0).
+ *   z, g_p [T][n][f]            storage type dt; row_scale [T][n] fp32; g_p overlaps none of the inputs
+ */
+int dgnn_mproduct_relu_backward_block(const void *g_y, const void *z, const float *row_scale, void *g_p, int64_t T, int64_t n, int32_t f,
+                                      int32_t w, int64_t t0, const void *g_after, int64_t n_after, dgnn_dtype dt, void *stream);
+
+/*
  * Gradient through sigma = ReLU of Eqn (2): out[u][:] = row_scale[u] * (z[u][:] > 0 ? g[u][:] : 0).
  *   g, z, out [n][f]        storage type dt; z is the layer's OUTPUT (positive exactly where the
  *                           pre-activation was); out may be the same pointer as g

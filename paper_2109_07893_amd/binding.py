@@ -33,7 +33,7 @@ EXPORTS = (
     "dgnn_delta_rebuild_series_workspace", "dgnn_delta_rebuild_series", "dgnn_smooth_series_workspace", "dgnn_smooth_series", "dgnn_feature_transform_batch", "dgnn_spmm_batch_workspace", "dgnn_spmm_batch", "dgnn_weight_grad_batch",
     "dgnn_lstm_series", "dgnn_lstm_series_backward", "dgnn_lstm_weight_grad_workspace", "dgnn_lstm_weight_grad",
     "dgnn_evolve_weights", "dgnn_evolve_weights_backward_workspace", "dgnn_evolve_weights_backward",
-    "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
+    "dgnn_mproduct_backward", "dgnn_mproduct_block", "dgnn_mproduct_backward_block", "dgnn_mproduct_relu_backward_block", "dgnn_relu_backward", "dgnn_weight_grad_workspace", "dgnn_weight_grad", "dgnn_input_grad",
 )
 
 
@@ -148,6 +148,7 @@ def load_library():
     lib.dgnn_add.argtypes = [_vp, _vp, _vp, _i64, _i32, ctypes.c_int, _vp]
     lib.dgnn_lstm_step.argtypes = [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _i32, ctypes.c_int, _vp]
     lib.dgnn_mproduct_block.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, _i64, _vp, _i64, ctypes.c_int, _vp]
+    lib.dgnn_mproduct_relu_backward_block.argtypes = [_vp, _vp, _vp, _vp, _i64, _i64, _i32, _i32, _i64, _vp, _i64, ctypes.c_int, _vp]
     lib.dgnn_mproduct_backward_block.argtypes = [_vp, _vp, _i64, _i64, _i32, _i32, _vp, _i64, _vp, _i64, ctypes.c_int, _vp]
     lib.dgnn_relu_backward.argtypes = [_vp, _vp, _vp, _vp, _i64, _i32, ctypes.c_int, _vp]
     lib.dgnn_weight_grad_workspace.argtypes = [_i32, _i32, ctypes.POINTER(_sz)]
@@ -749,6 +750,25 @@ def mproduct_backward_block(g_y, g_z, w: int, t0: int, g_after: Optional[torch.T
     """Its adjoint for one block; g_after = upstream gradient of the (up to w-1) timesteps after the block."""
     _mproduct_block(load_library().dgnn_mproduct_backward_block, "dgnn_mproduct_backward_block", g_y, g_z, w, t0,
                     g_after, m_band)
+
+
+def mproduct_relu_backward_block(g_y, z, row_scale, g_p, w: int, t0: int, g_after: Optional[torch.Tensor] = None) -> None:
+    """mproduct_backward_block and then relu_backward of every frame (row_scale [T, n]) in one pass; z = the layer's output."""
+    dt = _dtype_code(g_y)
+    T, n, f = g_y.shape
+    if any(tuple(x.shape) != (T, n, f) or x.dtype != g_y.dtype for x in (z, g_p)):
+        raise ValueError("shape mismatch in mproduct_relu_backward_block")
+    _need(row_scale, torch.float32, "row_scale")
+    if row_scale.numel() != T * n:
+        raise ValueError("row_scale must have one entry per row and timestep")
+    n_after = 0
+    if g_after is not None and g_after.numel() > 0:
+        if g_after.dtype != g_y.dtype or tuple(g_after.shape[1:]) != (n, f):
+            raise ValueError("hand-over frames must have the block's frame shape and dtype")
+        n_after = g_after.shape[0]
+    _check(load_library().dgnn_mproduct_relu_backward_block(_ptr(g_y), _ptr(z), _ptr(row_scale), _ptr(g_p), T, n, f, w, t0,
+                                                            _ptr(g_after) if n_after else None, n_after, dt, _stream(g_y)),
+           "dgnn_mproduct_relu_backward_block")
 
 
 def relu_backward(g: torch.Tensor, z: torch.Tensor, out: torch.Tensor, row_scale: Optional[torch.Tensor] = None) -> None:

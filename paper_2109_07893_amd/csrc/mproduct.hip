@@ -33,6 +33,14 @@ struct Halo {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
+// What follows the adjoint where the frames came out of a ReLU and go into an aggregation: out = row_scale * (z > 0 ? G : 0).
+struct Through {
+    const char *z;               // [T] frames like the gradient's
+    const float *row_scale;      // [T][rows]
+    int64_t rows;
+    int row_shift;               // log2 of a row's 16-byte pieces
+};
+
 constexpr int kThreads = 256;
 
 template <bool BF16> struct Vec;
@@ -192,10 +200,14 @@ __global__ __launch_bounds__(kThreads) void mproduct_shift_kernel(const char *z,
 // fp32 and the shorter windows fit three wavefronts anyway.
 constexpr int uniform_waves_per_simd(int w, bool bf16, bool reverse) { return (bf16 && !reverse && w >= 12 && w <= 23) ? 3 : 1; }
 
-template <int W, bool BF16, bool REVERSE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(uniform_waves_per_simd(W, BF16, REVERSE))))
+// RELU (with REVERSE): the gradient passes the ReLU and takes its row scale on the way out (see Through), after the rounding
+// to the storage type that it would have had between two passes.  Saves a frame written and read per timestep; both passes / one in
+// us: 16 frames of 50 K x 64 fp32, window 8, 174 / 111; 12 frames of 60 K x 128 bf16, window 16, 202 / 137.
+template <int W, bool BF16, bool REVERSE, bool RELU = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RELU && W <= 24 ? 2 : uniform_waves_per_simd(W, BF16, REVERSE))))
 void mproduct_uniform_kernel(const char *z, char *y, int T, int64_t pieces,
-                                                                    int64_t frame_bytes, Halo halo) {
+                                                                    int64_t frame_bytes, Halo halo, Through through) {
+    static_assert(REVERSE || !RELU, "a gradient passes the ReLU");
     constexpr int NV = Vec<BF16>::kVals;
     constexpr int D = W % 4 == 0 ? 4 : (W % 2 == 0 ? 2 : 1);     // divides W, so a frame's queue slot is i % D = jj % D
     const int64_t piece = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -228,8 +240,20 @@ void mproduct_uniform_kernel(const char *z, char *y, int T, int64_t pieces,
 #pragma unroll
     for (int d = 0; d < D; ++d) ahead[d] = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(src + (int64_t)frame_of(min(d, T - 1)) * frame_bytes));
 
-    // one step i (0-based); `slot` holds the frame of step i - W, `queued` the frame of step i
-    auto step = [&](int i, uintx4 &slot, uintx4 &queued) {
+    // ... and of what the result has to pass, fetched as far ahead
+    uintx4 z_ahead[RELU ? D : 1];
+    float sc_ahead[RELU ? D : 1];
+    auto fetch_through = [&](int i, int d) {
+        const int64_t t = frame_of(min(i, T - 1));
+        z_ahead[d] = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(through.z + t * frame_bytes + piece * 16));
+        sc_ahead[d] = through.row_scale[t * through.rows + (piece >> through.row_shift)];
+    };
+    if constexpr (RELU)
+#pragma unroll
+        for (int d = 0; d < D; ++d) fetch_through(d, d);
+
+    // one step i (0-based); `slot` holds the frame of step i - W, `queued` the frame of step i, d its place in the queues
+    auto step = [&](int i, uintx4 &slot, uintx4 &queued, int d) {
         const int t = frame_of(i);
         const uintx4 cur = queued;
         queued = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(src + (int64_t)frame_of(min(i + D, T - 1)) * frame_bytes));   // before the store: y may be z
@@ -250,6 +274,19 @@ void mproduct_uniform_kernel(const char *z, char *y, int T, int64_t pieces,
                 out[e] = sum[e] * scale;
             }
         }
+        if constexpr (RELU) {
+            const uintx4 zv = z_ahead[d];
+            const float sc = sc_ahead[d];
+            fetch_through(i + D, d);
+            float z_val[NV];
+            Vec<BF16>::unpack(z_val, zv);
+#pragma unroll
+            for (int e = 0; e < NV; ++e) {
+                const float g = BF16 ? bf16_to_f32(f32_to_bf16(out[e])) : out[e];
+                // (a bf16 by its bits, as the pass on its own has it: positive and not a zero)
+                out[e] = (BF16 ? __float_as_int(z_val[e]) > 0 : z_val[e] > 0.0f) ? g * sc : 0.0f;
+            }
+        }
         Vec<BF16>::store(dst + (int64_t)t * frame_bytes, out);
     };
     int tb = 0;
@@ -257,7 +294,7 @@ void mproduct_uniform_kernel(const char *z, char *y, int T, int64_t pieces,
 #pragma unroll
         for (int e = 0; e < NV; ++e) fresh[e] = 0.0f;
 #pragma unroll
-        for (int jj = 0; jj < W; ++jj) step(tb + jj, ring[jj], ahead[jj % D]);
+        for (int jj = 0; jj < W; ++jj) step(tb + jj, ring[jj], ahead[jj % D], jj % D);
         // A whole round has gone by: the W frames it brought in are exactly the window now, and `fresh` is their sum
         // formed on its own.  It replaces the running sum, so that rounding residue of large values, and anything
         // that is not a number, stop travelling along here instead of staying in the sum for the rest of the series.
@@ -266,29 +303,29 @@ void mproduct_uniform_kernel(const char *z, char *y, int T, int64_t pieces,
     }
 #pragma unroll
     for (int jj = 0; jj < W; ++jj)
-        if (tb + jj < T) step(tb + jj, ring[jj], ahead[jj % D]);
+        if (tb + jj < T) step(tb + jj, ring[jj], ahead[jj % D], jj % D);
 }
 
-template <int W, bool REVERSE>
-int launch_uniform(const void *z, void *y, int64_t T, int64_t n, int32_t f, dgnn_dtype dt, Halo halo, hipStream_t s) {
+template <int W, bool REVERSE, bool RELU>
+int launch_uniform(const void *z, void *y, int64_t T, int64_t n, int32_t f, dgnn_dtype dt, Halo halo, const Through &through, hipStream_t s) {
     const int64_t frame_bytes = n * f * (dt == DGNN_F32 ? 4 : 2);
     const int64_t pieces = frame_bytes / 16;
     const unsigned blocks = (unsigned)((pieces + kThreads - 1) / kThreads);
     if (dt == DGNN_F32)
-        hipLaunchKernelGGL((mproduct_uniform_kernel<W, false, REVERSE>), dim3(blocks), dim3(kThreads), 0, s,
-                           static_cast<const char *>(z), static_cast<char *>(y), (int)T, pieces, frame_bytes, halo);
+        hipLaunchKernelGGL((mproduct_uniform_kernel<W, false, REVERSE, RELU>), dim3(blocks), dim3(kThreads), 0, s,
+                           static_cast<const char *>(z), static_cast<char *>(y), (int)T, pieces, frame_bytes, halo, through);
     else
-        hipLaunchKernelGGL((mproduct_uniform_kernel<W, true, REVERSE>), dim3(blocks), dim3(kThreads), 0, s,
-                           static_cast<const char *>(z), static_cast<char *>(y), (int)T, pieces, frame_bytes, halo);
+        hipLaunchKernelGGL((mproduct_uniform_kernel<W, true, REVERSE, RELU>), dim3(blocks), dim3(kThreads), 0, s,
+                           static_cast<const char *>(z), static_cast<char *>(y), (int)T, pieces, frame_bytes, halo, through);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
 
-template <int W, bool REVERSE>
+template <int W, bool REVERSE, bool RELU>
 int dispatch_uniform(int w, const void *z, void *y, int64_t T, int64_t n, int32_t f, dgnn_dtype dt, Halo halo,
-                     hipStream_t s) {
-    if (w == W) return launch_uniform<W, REVERSE>(z, y, T, n, f, dt, halo, s);
-    if constexpr (W > 1) return dispatch_uniform<W - 1, REVERSE>(w, z, y, T, n, f, dt, halo, s);
+                     const Through &through, hipStream_t s) {
+    if (w == W) return launch_uniform<W, REVERSE, RELU>(z, y, T, n, f, dt, halo, through, s);
+    if constexpr (W > 1) return dispatch_uniform<W - 1, REVERSE, RELU>(w, z, y, T, n, f, dt, halo, through, s);
     return DGNN_ERR_SHAPE;
 }
 
@@ -324,9 +361,9 @@ int launch_shift(const void *z, void *y, int64_t T, int64_t n, int32_t f, int32_
     return DGNN_OK;
 }
 
-template <bool REVERSE>
+template <bool REVERSE, bool RELU = false>
 int mproduct(const void *z, void *y, int64_t T, int64_t n, int32_t f, int32_t w, const float *m_band, int64_t t0,
-             const void *halo_frames, int64_t n_halo, dgnn_dtype dt, void *stream) {
+             const void *halo_frames, int64_t n_halo, dgnn_dtype dt, void *stream, const Through &through = Through{}) {
     if (!z || !y) return DGNN_ERR_NULL;
     if (T <= 0 || n <= 0 || w <= 0 || t0 < 0 || n_halo < 0 || !supported_width(f)) return DGNN_ERR_SHAPE;
     if (dt != DGNN_F32 && dt != DGNN_BF16) return DGNN_ERR_SHAPE;
@@ -351,7 +388,8 @@ int mproduct(const void *z, void *y, int64_t T, int64_t n, int32_t f, int32_t w,
     const int32_t wk = m_band ? w : (int32_t)eff;
     const Halo halo{static_cast<const char *>(halo_frames), (int)n_halo, (int)t0};
     hipStream_t s = (hipStream_t)stream;
-    if (!m_band) return dispatch_uniform<32, REVERSE>((int)eff, z, y, T, n, f, dt, halo, s);
+    if (!m_band) return dispatch_uniform<32, REVERSE, RELU>((int)eff, z, y, T, n, f, dt, halo, through, s);
+    if constexpr (RELU) return DGNN_ERR_SHAPE;
     if (eff <= 4) return launch<4, REVERSE>(z, y, T, n, f, wk, m_band, dt, halo, s);
     if (eff <= 8) return launch<8, REVERSE>(z, y, T, n, f, wk, m_band, dt, halo, s);
     if (eff <= 16) return launch<16, REVERSE>(z, y, T, n, f, wk, m_band, dt, halo, s);
@@ -381,4 +419,18 @@ extern "C" int dgnn_mproduct_backward_block(const void *g_y, void *g_z, int64_t 
                                             const float *m_band, int64_t t0, const void *g_after, int64_t n_after,
                                             dgnn_dtype dt, void *stream) {
     return mproduct<true>(g_y, g_z, T, n, f, w, m_band, t0, g_after, n_after, dt, stream);
+}
+
+extern "C" int dgnn_mproduct_relu_backward_block(const void *g_y, const void *z, const float *row_scale, void *g_p, int64_t T, int64_t n, int32_t f,
+                                                 int32_t w, int64_t t0, const void *g_after, int64_t n_after, dgnn_dtype dt, void *stream) {
+    if (!z || !row_scale) return DGNN_ERR_NULL;
+    if (!supported_width(f) || (dt != DGNN_F32 && dt != DGNN_BF16) || T <= 0 || n <= 0) return DGNN_ERR_SHAPE;
+    if (!fits_index(n) || !fits_i32(T)) return DGNN_ERR_OVERFLOW;
+    if (!aligned16(z)) return DGNN_ERR_ALIGN;
+    const int row_bytes = f * (dt == DGNN_F32 ? 4 : 2);
+    const int64_t bytes = T * n * row_bytes;
+    const char *a = static_cast<const char *>(z), *b = static_cast<const char *>(g_p);
+    if (g_p == g_y || (a < b + bytes && b < a + bytes)) return DGNN_ERR_ALIAS;
+    const Through through{a, row_scale, n, __builtin_ctz(row_bytes / 16)};
+    return mproduct<true, true>(g_y, g_p, T, n, f, w, nullptr, t0, g_after, n_after, dt, stream, through);
 }

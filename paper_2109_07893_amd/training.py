@@ -6,8 +6,9 @@ the reverse direction).  Like pipeline.py this owns buffers and the order of lib
                    first layer    P = A~_t X,  Z = relu(P W)                     both kept (fp32)
                    other layers   H = Z_below W,  Z = relu(A~_t H)               Z kept
                then Y = Z x_1 M
-    backward   G = G_Y x_1 M^T (dgnn_mproduct_backward), then per timestep, last layer to first:
-                   other layers   G_P = dinv * (Z > 0 ? G : 0)                   dgnn_relu_backward
+    backward   G = G_Y x_1 M^T (dgnn_mproduct_backward_block), then per timestep, last layer to first:
+                   other layers   G_P = dinv * (Z > 0 ? G : 0)                   dgnn_relu_backward; for the top layer together with
+                                                                                 G (dgnn_mproduct_relu_backward_block)
                                   G_H = A~_t^T G_P                               dgnn_spmm on the transposed snapshot
                                   dW += Z_below^T G_H,  G = G_H W^T              dgnn_weight_grad, dgnn_input_grad
                    first layer    dW += P^T (Z > 0 ? G : 0)                      dgnn_weight_grad_batch
@@ -133,11 +134,13 @@ class GcnStack:
                 a.column(a.H, h)
                 self.spmm.append(spmm_table(snapshot, h, z[layer]))
             self.transform.append(a)
-        self.spmm_t = None
+        self.spmm_t = self.spmm_top = None
         if aggregated > 0:
             rp_t, ci_t, val_t = transposed if transposed is not None else (rowptr, colidx, vals)
             arrays = (pointers(rp_t), pointers(ci_t), snapshot[2], pointers(val_t) if val_t is not None else 0)
             self.spmm_t = spmm_table(arrays, pointers([self.gp[t % m] for t in range(T)]), h)
+            # the top layer's, where its G_P is formed with the M-transform's adjoint; the frames are named going back
+            self.spmm_top = spmm_table(arrays, 0, h) if blk.window else None
             self.input = TransformTable(T)                  # with one weight per timestep: G_H W_t^T
             self.input.column(TransformTable.X, h)
         self.wgrad = WeightGradTable(T)
@@ -145,7 +148,7 @@ class GcnStack:
     def bind(self, blk: BlockInputs, nnz) -> None:
         """The frames, weights and entry counts of the coming pass."""
         T = blk.T
-        for b in self.spmm + ([self.spmm_t] if self.spmm_t is not None else []):
+        for b in self.spmm + [b for b in (self.spmm_t, self.spmm_top) if b is not None]:
             b.refresh(b.NNZ, nnz[:T], T)
         x = self.x.addresses(blk.x[:T])
         if self.p0 is None:
@@ -195,8 +198,14 @@ class GcnStack:
                                   self.z[layer, t + j].data_ptr() if masked else 0, dw_t[t + j][layer].data_ptr())
                 B.weight_grad_batch(k, a.at(), n, f, f, False, dt, self.ws_wgrad, stream)
 
-    def backward(self, blk: BlockInputs, t: int, k: int, g_top: torch.Tensor, dinv: torch.Tensor, dw, dw_t, accumulate: bool, stream) -> None:
-        """Gradients of timesteps t .. t + k - 1; g_top [k, n, f] = dL/dZ of the last layer, dinv [k, n]."""
+    def masks_ahead(self, per_step: bool, timed: bool) -> bool:
+        """Whether the M-transform's adjoint forms the top layer's G_P: that layer's gradient goes through an aggregation, the
+        normalisations of all timesteps are there, and no timer wants the two stages apart."""
+        return self.spmm_top is not None and per_step and not timed
+
+    def backward(self, blk: BlockInputs, t: int, k: int, g_top: torch.Tensor, dinv: torch.Tensor, dw, dw_t, accumulate: bool, stream,
+                 masked: bool = False) -> None:
+        """Gradients of timesteps t .. t + k - 1; g_top [k, n, f] = dL/dZ of the last layer (masked: its G_P), dinv [k, n]."""
         n, f, dt = self.n, self.f, self.dt
         flat = (k * n, f)
         g = g_top
@@ -204,10 +213,15 @@ class GcnStack:
             if layer == 0 and self.p0 is not None:
                 self._weight_grad(blk, t, k, 0, self.p0[t:t + k], g, True, dw, dw_t, accumulate, stream)
                 return
-            with self.stage("relu_backward"):
-                B.relu_backward(g.view(flat), self.z[layer, t:t + k].view(flat), self.gp[:k].view(flat), row_scale=dinv.view(-1))
+            table = self.spmm_t
+            if masked and layer == self.L - 1:
+                table = self.spmm_top
+                table.column(table.H, pointers(g), slice(t, t + k))
+            else:
+                with self.stage("relu_backward"):
+                    B.relu_backward(g.view(flat), self.z[layer, t:t + k].view(flat), self.gp[:k].view(flat), row_scale=dinv.view(-1))
             with self.stage("spmm_weighted_transposed" if self.weighted else "spmm_transposed"):
-                B.spmm_batch(n, k, self.spmm_t.at(t), f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
+                B.spmm_batch(n, k, table.at(t), f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
             if layer > 0:
                 self._weight_grad(blk, t, k, layer, self.z[layer - 1, t:t + k], self.h, False, dw, dw_t, accumulate, stream)
             else:                                  # the frames of X are tensors of their own, added up from the last one on
@@ -358,6 +372,7 @@ class BlockTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
+        masked = not overwrite and stack.masks_ahead(self.a.per_step, self.timer is not None)
         if blk.window:
             if overwrite:
                 g_top = g_y
@@ -366,7 +381,10 @@ class BlockTrainer:
                     self.g = torch.empty((self.T_max,) + tuple(g_y.shape[1:]), dtype=g_y.dtype, device=g_y.device)
                 g_top = self.g[:T]
             with self._stage("mproduct_backward"):
-                B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
+                if masked:
+                    B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1, :T], self.a.dinv_all[:T], g_top, blk.window, self.t0, g_after=g_after)
+                else:
+                    B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
         else:
             g_top = g_y
         self.g_top = g_top
@@ -376,7 +394,7 @@ class BlockTrainer:
             k = min(m, T - t)
             slot = self.a.slot_of(t + 1)
             stack.backward(blk, t, k, g_top[t:t + k], self.a.dinv_all[slot:slot + k] if self.a.per_step else self.a.dinv_all[slot:slot + 1],
-                           self.dw, self.dw_t, accumulate or t != last, stream)
+                           self.dw, self.dw_t, accumulate or t != last, stream, masked)
             if stack.needs_transposed and t >= 2 and not self.keep_snapshots:   # A_{t-1} from A_t: the lists exchanged (A_1 was kept)
                 for chain, lists, _ in self._chains():
                     self._rebuild(chain, lists[t - 1], blk.nnz[t], t + 1, t, reverse=True)
@@ -709,11 +727,15 @@ class SmoothedTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
+        masked = stack.masks_ahead(True, self.timer is not None)
         if blk.window:
             if self.g is None:
                 self.g = torch.empty_like(g_y)
             with self._stage("mproduct_backward"):
-                B.mproduct_backward_block(g_y, self.g, blk.window, 0)
+                if masked:
+                    B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1], self.dinv_s, self.g, blk.window, 0)
+                else:
+                    B.mproduct_backward_block(g_y, self.g, blk.window, 0)
             g_top = self.g
         else:
             g_top = g_y
@@ -721,4 +743,4 @@ class SmoothedTrainer:
         last = (T - 1) // m * m
         for t in range(last, -1, -m):
             k = min(m, T - t)
-            stack.backward(blk, t, k, g_top[t:t + k], self.dinv_s[t:t + k], self.dw, self.dw_t, t != last, stream)
+            stack.backward(blk, t, k, g_top[t:t + k], self.dinv_s[t:t + k], self.dw, self.dw_t, t != last, stream, masked)

@@ -182,6 +182,16 @@ def test_backward_argument_errors(lib):
     f = lib.dgnn_mproduct_backward_block
     assert f(FAKE, FAKE, 8, 10, 16, 3, None, 0, FAKE + (1 << 20), 3, 0, None) == -2
     assert f(FAKE, FAKE + (1 << 20), 8, 10, 16, 3, None, 0, FAKE + (1 << 20), 2, 0, None) == -5   # output over the hand-over
+    f = lib.dgnn_mproduct_relu_backward_block
+    far = [FAKE + (k << 20) for k in range(5)]
+    assert f(far[0], None, far[2], far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -1
+    assert f(far[0], far[1], None, far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -1
+    assert f(far[0], far[1], far[2], far[3], 8, 10, 48, 3, 0, None, 0, 0, None) == -2
+    assert f(far[0], far[1], far[2], far[3], 8, 10, 16, 33, 40, None, 0, 0, None) == -2           # the window is too long
+    assert f(far[0], far[1] + 4, far[2], far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -7
+    assert f(far[0], far[1], far[2], far[0], 8, 10, 16, 3, 0, None, 0, 0, None) == -5             # not in place
+    assert f(far[0], far[3] + 16, far[2], far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -5
+    assert f(far[0], far[1], far[2], far[3], 8, 10, 16, 3, 0, far[3], 2, 0, None) == -5
 
 
 def test_weighted_argument_errors(lib):

@@ -214,3 +214,20 @@ def test_mproduct_block_argument_checks():
         dg.mproduct_block(z, torch.empty_like(z), 3, 3, z_before=z[:1])
     with pytest.raises(dg.DgnnError):      # more gradient frames than the window reaches
         dg.mproduct_backward_block(z, torch.empty_like(z), 3, 0, g_after=torch.zeros((3, 10, 16), device=DEV))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("w,T,t0,after,n,f", [(1, 3, 0, 0, 1, 16), (3, 1, 0, 0, 77, 32), (3, 7, 2, 2, 333, 64), (8, 20, 0, 0, 130, 128),
+                                              (16, 12, 12, 12, 201, 128), (16, 33, 5, 15, 65, 16), (23, 40, 3, 4, 50, 32), (32, 70, 0, 31, 33, 64)])
+def test_mproduct_adjoint_that_masks_on_the_way_out(dtype, w, T, t0, after, n, f):
+    """Bit for bit the adjoint followed by the ReLU's mask and the row scale; zeros and negative zeros do not pass."""
+    g, z = (torch.randn((k, n, f), device=DEV).to(dtype) for k in (T + after, T))
+    z[:, ::3] = 0.0
+    z[:, 1::7] = -0.0
+    dinv = torch.rand((T, n), device=DEV) + 0.1
+    g_z, want, got = torch.empty_like(z), torch.empty_like(z), torch.full_like(z, float("nan"))
+    tail = g[T:] if after else None
+    dg.mproduct_backward_block(g[:T], g_z, w, t0, g_after=tail)
+    dg.relu_backward(g_z.view(-1, f), z.view(-1, f), want.view(-1, f), row_scale=dinv.view(-1))
+    dg.binding.mproduct_relu_backward_block(g[:T], z, dinv, got, w, t0, g_after=tail)
+    assert torch.equal(got, want)
