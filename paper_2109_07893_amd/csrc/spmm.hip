@@ -215,6 +215,8 @@ __device__ __forceinline__ void spmm_stream(
     fetch_rows(k_cur);
     if (!__ballot(m_v <= e_begin && m_vn > e_begin)) {
         k_cur = max(wave_find_row(rowptr, n, e_begin, lane), 0);
+        if (range == 0)                      // rows without entries that the walk, which begins at k_cur, does not come to
+            for (int k = lane; k < k_cur; k += kWave) zero_row<LPR, SLICES>(z, k);
         fetch_rows(k_cur);
     }
 
@@ -266,7 +268,7 @@ __device__ __forceinline__ void spmm_stream(
                 }
             }
             listed += __popcll(mask);
-            // no entries: zero output (those ahead of the first entry of all belong to the first range)
+            // no entries: zero output (those ahead of the first entry of all belong to the first range, see above for more than 64)
             if (row && !has && (m_v > e || e == 0) && m_v <= e_stop) zero_row<LPR, SLICES>(z, k);
             const uint64_t within = __ballot(row && m_v <= e_stop);
             k_next += __popcll(within);                  // ends as the row of entry e_stop

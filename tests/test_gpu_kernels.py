@@ -449,6 +449,41 @@ def test_spmm_row_shapes_and_slices(n, f, dtype):
         assert_close(to_f64(z[3]), oracle.spmm(rp, ci, to_f64(h), val=np.ones(ci.size) if values is None else val.astype(np.float64)), dtype, "row shapes")
 
 
+@pytest.mark.parametrize("f,dtype", [(16, torch.bfloat16), (32, torch.float32), (64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("lead", [63, 64, 65, 1000])
+@pytest.mark.parametrize("n", [1400, 24_600])
+def test_spmm_leading_rows_without_entries(n, lead, f, dtype):
+    """As many rows without entries before the first stored one as a wavefront looks at in one go, one fewer and more: zeros there,
+    whichever call is made, and with one range (1400 vertices) as with many."""
+    rng = np.random.default_rng(lead + f)
+    lens = rng.integers(1, 9, n)
+    lens[:lead] = 0
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, l, replace=False)) for l in lens if l]).astype(np.int32)
+    val = rng.uniform(0.5, 2.0, ci.size).astype(np.float32)
+    h = torch.randn((n, f), generator=torch.Generator().manual_seed(n)).to(dtype)
+    rp_d, ci_d, val_d, h_d = dev_i32(rp), dev_i32(ci), torch.as_tensor(val).to(DEV), h.to(DEV)
+    ws = torch.empty(dg.spmm_workspace(n, ci.size, f), dtype=torch.uint8, device=DEV)
+    ws_batch = torch.empty(B.spmm_batch_workspace(2, ci.size, f), dtype=torch.uint8, device=DEV)
+    table = SpmmTable(2)
+    for values in (None, val_d):
+        z = torch.full((4, n, f), float("nan"), dtype=dtype, device=DEV)
+        if values is None:
+            dg.spmm(rp_d, ci_d, ci.size, None, h_d, z[0], ws)
+            dg.spmm_static(rp_d, ci_d, ci.size, None, h_d, z[1])
+        else:
+            dg.spmm_weighted(rp_d, ci_d, val_d, ci.size, h_d, z[0], ws)
+            z[1].zero_()
+        for k, col in enumerate((rp_d.data_ptr(), ci_d.data_ptr(), 0, 0 if values is None else values.data_ptr(), h_d.data_ptr(), pointers(z[2:]), ci.size)):
+            table.column(k, col)
+        B.spmm_batch(n, 2, table.at(), f, dg.DGNN_F32 if dtype == torch.float32 else dg.DGNN_BF16, 0, ws_batch, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert bool((z[:, :lead] == 0).all())
+        want = oracle.spmm(rp, ci, to_f64(h), val=np.ones(ci.size) if values is None else val.astype(np.float64))
+        for k in (0, 2, 3) if values is not None else range(4):
+            assert_close(to_f64(z[k]), want, dtype, "leading rows without entries")
+
+
 def test_spmm_beyond_32_bit_offsets():
     """H and Z of more than 4 GB: rows of one entry copy a row of H each, exactly."""
     n, f = (1 << 23) + 1000, 128
