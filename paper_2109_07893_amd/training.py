@@ -198,10 +198,10 @@ class GcnStack:
                                   self.z[layer, t + j].data_ptr() if masked else 0, dw_t[t + j][layer].data_ptr())
                 B.weight_grad_batch(k, a.at(), n, f, f, False, dt, self.ws_wgrad, stream)
 
-    def masks_ahead(self, per_step: bool, timed: bool) -> bool:
-        """Whether the M-transform's adjoint forms the top layer's G_P: that layer's gradient goes through an aggregation, the
-        normalisations of all timesteps are there, and no timer wants the two stages apart."""
-        return self.spmm_top is not None and per_step and not timed
+    def masks_ahead(self, blk: BlockInputs, per_step: bool, timed: bool) -> bool:
+        """Whether the M-transform's adjoint forms the top layer's G_P: the block of this pass has one, that layer's gradient goes
+        through an aggregation, the normalisations of all timesteps are there, and no timer wants the two stages apart."""
+        return bool(blk.window) and self.spmm_top is not None and per_step and not timed
 
     def backward(self, blk: BlockInputs, t: int, k: int, g_top: torch.Tensor, dinv: torch.Tensor, dw, dw_t, accumulate: bool, stream,
                  masked: bool = False) -> None:
@@ -372,7 +372,7 @@ class BlockTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
-        masked = not overwrite and stack.masks_ahead(self.a.per_step, self.timer is not None)
+        masked = not overwrite and stack.masks_ahead(blk, self.a.per_step, self.timer is not None)
         if blk.window:
             if overwrite:
                 g_top = g_y
@@ -727,7 +727,7 @@ class SmoothedTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
-        masked = stack.masks_ahead(True, self.timer is not None)
+        masked = stack.masks_ahead(blk, True, self.timer is not None)
         if blk.window:
             if self.g is None:
                 self.g = torch.empty_like(g_y)

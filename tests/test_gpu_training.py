@@ -116,6 +116,38 @@ def test_training_step_repeats_bit_for_bit():
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("case", ["undirected_2layers_window", "directed_2layers_window", "bf16_window"])
+def test_trainer_bound_to_a_block_without_a_window(case):
+    """A trainer built for a block with an M-transform takes one without: the gradients of a trainer built for that one."""
+    wl = CASES[case]
+    blk = make_block(wl, DEV, gen_device="cpu")
+    plain = replace(blk, window=0)
+    g_y = torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV)
+    tr, want = make_trainer(wl, blk), make_trainer(wl, plain)
+    tr.forward()
+    tr.backward(g_y)
+    again = {} if tr.at is None else dict(transposed_first=(tr.at.rowptr[0].clone(), tr.at.colidx[0].clone()), transposed_deltas=tr.t_deltas)
+    tr.rebind(plain, **again)
+    for t in (tr, want):
+        t.forward()
+        t.backward(g_y)
+    assert all(torch.equal(a, b) for a, b in zip(tr.dw, want.dw))
+
+
+def test_smoothed_trainer_whose_block_has_no_window_any_more():
+    from paper_2109_07893_amd.training import make_smoothed_trainer
+    wl = CASES["directed_2layers_window"]
+    blk = make_block(wl, DEV, gen_device="cpu")
+    plain = replace(blk, window=0)
+    g_y = torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV)
+    tr, want = make_smoothed_trainer(wl, blk, 3), make_smoothed_trainer(wl, plain, 3)
+    tr.blk = plain
+    for t in (tr, want):
+        t.forward()
+        t.backward(g_y)
+    assert all(torch.equal(a, b) for a, b in zip(tr.dw, want.dw))
+
+
 @pytest.mark.parametrize("case,bsize", [("undirected_2layers_window", 3), ("directed_2layers_window", 2),
                                         ("directed_2layers_window", 4), ("undirected_1layer_window", 1),
                                         ("directed_1layer", 2), ("bf16_window", 4)])
