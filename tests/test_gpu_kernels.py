@@ -451,13 +451,13 @@ def test_spmm_row_shapes_and_slices(n, f, dtype):
 
 @pytest.mark.parametrize("f,dtype", [(16, torch.bfloat16), (32, torch.float32), (64, torch.float32), (128, torch.float32)])
 @pytest.mark.parametrize("lead", [63, 64, 65, 1000])
-@pytest.mark.parametrize("n", [1400, 24_600])
-def test_spmm_leading_rows_without_entries(n, lead, f, dtype):
-    """As many rows without entries before the first stored one as a wavefront looks at in one go, one fewer and more: zeros there,
-    whichever call is made, and with one range (1400 vertices) as with many."""
+@pytest.mark.parametrize("n", [2400, 24_600])
+def test_spmm_leading_and_trailing_rows_without_entries(n, lead, f, dtype):
+    """As many rows without entries before the first stored one, and behind the last, as a wavefront looks at in one go, one fewer
+    and more: zeros there, whichever call is made, and with few ranges (2400 vertices) as with many."""
     rng = np.random.default_rng(lead + f)
     lens = rng.integers(1, 9, n)
-    lens[:lead] = 0
+    lens[:lead] = lens[-lead:] = 0
     rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     ci = np.concatenate([np.sort(rng.choice(n, l, replace=False)) for l in lens if l]).astype(np.int32)
     val = rng.uniform(0.5, 2.0, ci.size).astype(np.float32)
@@ -478,10 +478,10 @@ def test_spmm_leading_rows_without_entries(n, lead, f, dtype):
             table.column(k, col)
         B.spmm_batch(n, 2, table.at(), f, dg.DGNN_F32 if dtype == torch.float32 else dg.DGNN_BF16, 0, ws_batch, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
-        assert bool((z[:, :lead] == 0).all())
+        assert bool((z[:, :lead] == 0).all()) and bool((z[:, -lead:] == 0).all())
         want = oracle.spmm(rp, ci, to_f64(h), val=np.ones(ci.size) if values is None else val.astype(np.float64))
         for k in (0, 2, 3) if values is not None else range(4):
-            assert_close(to_f64(z[k]), want, dtype, "leading rows without entries")
+            assert_close(to_f64(z[k]), want, dtype, "leading and trailing rows without entries")
 
 
 def test_spmm_beyond_32_bit_offsets():
