@@ -429,8 +429,9 @@ extern "C" int dgnn_mproduct_relu_backward_block(const void *g_y, const void *z,
     if (!aligned16(z)) return DGNN_ERR_ALIGN;
     const int row_bytes = f * (dt == DGNN_F32 ? 4 : 2);
     const int64_t bytes = T * n * row_bytes;
-    const char *a = static_cast<const char *>(z), *b = static_cast<const char *>(g_p);
+    const char *a = static_cast<const char *>(z), *b = static_cast<const char *>(g_p), *c = reinterpret_cast<const char *>(row_scale);
     if (g_p == g_y || (a < b + bytes && b < a + bytes)) return DGNN_ERR_ALIAS;
+    if (c < b + bytes && b < c + T * n * (int64_t)sizeof(float)) return DGNN_ERR_ALIAS;      // read ahead of what is written
     const Through through{a, row_scale, n, __builtin_ctz(row_bytes / 16)};
     return mproduct<true, true>(g_y, g_p, T, n, f, w, nullptr, t0, g_after, n_after, dt, stream, through);
 }

@@ -192,6 +192,8 @@ def test_backward_argument_errors(lib):
     assert f(far[0], far[1], far[2], far[0], 8, 10, 16, 3, 0, None, 0, 0, None) == -5             # not in place
     assert f(far[0], far[3] + 16, far[2], far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -5
     assert f(far[0], far[1], far[2], far[3], 8, 10, 16, 3, 0, far[3], 2, 0, None) == -5
+    for overlap in (0, 5120 - 4, -316):                                              # row_scale over g_p's first, over its last, from before it
+        assert f(far[0], far[1], far[3] + overlap, far[3], 8, 10, 16, 3, 0, None, 0, 0, None) == -5
 
 
 def test_weighted_argument_errors(lib):
