@@ -727,7 +727,7 @@ class SmoothedTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
-        masked = stack.masks_ahead(blk, True, self.timer is not None)
+        masked = g_y.shape[0] == T and stack.masks_ahead(blk, True, self.timer is not None)       # (frames behind the block count in the window)
         if blk.window:
             if self.g is None:
                 self.g = torch.empty_like(g_y)

@@ -148,6 +148,21 @@ def test_smoothed_trainer_whose_block_has_no_window_any_more():
     assert all(torch.equal(a, b) for a, b in zip(tr.dw, want.dw))
 
 
+def test_smoothed_trainer_takes_gradients_of_timesteps_behind_its_block():
+    """More frames than the block has: the window carries the later ones' gradient back into the block."""
+    from paper_2109_07893_amd.training import make_smoothed_trainer
+    wl = CASES["directed_2layers_window"]
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.randn((wl.T + 2, wl.n, wl.f), generator=torch.Generator().manual_seed(2)).to(DEV)
+    g_z = torch.empty_like(g_y)
+    dg.mproduct_backward_block(g_y, g_z, wl.window, 0)
+    tr, want = make_smoothed_trainer(wl, blk, 3), make_smoothed_trainer(wl, replace(blk, window=0), 3)
+    for t, g in ((tr, g_y), (want, g_z[:wl.T])):
+        t.forward()
+        t.backward(g)
+    assert all(torch.equal(a, b) for a, b in zip(tr.dw, want.dw))
+
+
 @pytest.mark.parametrize("case,bsize", [("undirected_2layers_window", 3), ("directed_2layers_window", 2),
                                         ("directed_2layers_window", 4), ("undirected_1layer_window", 1),
                                         ("directed_1layer", 2), ("bf16_window", 4)])
