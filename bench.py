@@ -95,19 +95,21 @@ def algorithmic_bytes(blk, stage, t=None):
     raise KeyError(stage)
 
 
-def training_bytes(blk, stack, forwards):
+def training_bytes(blk, stack, forwards, per_step):
     """Bytes the method itself must move per stage of a training step, all calls together (a call may take several timesteps).
-    forwards: timesteps that go forward in a step (those of a block that is rerun count twice)."""
+    forwards: timesteps that go forward in a step (those of a block that is rerun count twice); per_step: the trainer holds every
+    timestep's normalisation."""
     s, n, f, T, L = blk.x[0].element_size(), blk.n, blk.f, blk.T, blk.layers
     frame, dense = s * n * f, 2 * s * n * f + s * f * f
     kept = stack.p0 is not None                         # A~ X: the first layer needs no aggregation going back
     back = L - 1 if kept else L
+    masked = 1 if stack.masks_ahead(blk, per_step) else 0             # layers whose ReLU the M-transform's adjoint takes along
     gather = sum(algorithmic_bytes(blk, "spmm", t) for t in range(1, T + 1)) / T
     return {"feature_transform": forwards * (L * dense + (2 * frame + 4 * n if stack.prescale else 0)),     # X scaled by dinv beforehand
             "spmm": forwards * L * gather, "spmm_transposed": T * back * gather,
-            "relu_backward": T * back * (3 * frame + 4 * n),          # gradient in, activation in, masked gradient out
+            "relu_backward": T * (back - masked) * (3 * frame + 4 * n),          # gradient in, activation in, masked gradient out
             "weight_grad": T * (L * dense + (frame if kept else 0)),  # ... the activation is read here where the mask is taken on the way
-            "input_grad": T * (L - 1) * dense, "mproduct": forwards * 2 * frame, "mproduct_backward": T * 2 * frame}
+            "input_grad": T * (L - 1) * dense, "mproduct": forwards * 2 * frame, "mproduct_backward": T * 2 * frame, "mproduct_relu_backward": T * (3 * frame + 4 * n)}
 
 
 STAGE_SOURCES = {"spmm": ("spmm.hip", "common.hpp"), "delta_rebuild": ("delta_rebuild.hip", "common.hpp"),
@@ -647,7 +649,7 @@ def training_step(args, wl, blk, dev):
     torch.cuda.synchronize()
     stages = {}
     forwards = blk.T if n_blocks == 1 else sum(e - a for a, e in ck.bounds + ck.bounds[:-1])      # the last block is not rerun
-    needed = training_bytes(blk, timed.stack, forwards)
+    needed = training_bytes(blk, timed.stack, forwards, timed.a.per_step)
     for name, (calls, total_ms) in timed.timer.totals().items():
         byts = needed.get(name, 0) / calls
         entry = {"calls_per_step": calls, "avg_ms": round(total_ms / calls, 4), "ms_per_step": round(total_ms, 4)}

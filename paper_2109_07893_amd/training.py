@@ -198,10 +198,10 @@ class GcnStack:
                                   self.z[layer, t + j].data_ptr() if masked else 0, dw_t[t + j][layer].data_ptr())
                 B.weight_grad_batch(k, a.at(), n, f, f, False, dt, self.ws_wgrad, stream)
 
-    def masks_ahead(self, blk: BlockInputs, per_step: bool, timed: bool) -> bool:
+    def masks_ahead(self, blk: BlockInputs, per_step: bool) -> bool:
         """Whether the M-transform's adjoint forms the top layer's G_P: the block of this pass has one, that layer's gradient goes
-        through an aggregation, the normalisations of all timesteps are there, and no timer wants the two stages apart."""
-        return bool(blk.window) and self.spmm_top is not None and per_step and not timed
+        through an aggregation, and the normalisations of all timesteps are there."""
+        return bool(blk.window) and self.spmm_top is not None and per_step
 
     def backward(self, blk: BlockInputs, t: int, k: int, g_top: torch.Tensor, dinv: torch.Tensor, dw, dw_t, accumulate: bool, stream,
                  masked: bool = False) -> None:
@@ -278,7 +278,9 @@ class BlockTrainer:
         self.stack = GcnStack(blk, cap, *arrays, transposed=back, want_dx=want_dx, stage=_stage_of(self), together=None if self.series else 1)
         self.z, self.dx = self.stack.z, self.stack.dx                     # activations of the block
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
-        self.g = self.g_top = None                                        # dL/dZ of the last layer, if g_y must be kept; wherever it is
+        # dL/dZ of the last layer, if g_y must be kept, and wherever it is; where a pass masks ahead (GcnStack.masks_ahead) it is not
+        # formed on its own, and G_P is what there is
+        self.g = self.g_top = self.g_p = None
         self.dw = [torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)]
         # with one weight per timestep (Section "EvolveGCN") every timestep has a gradient of its own
         self.dw_t = ([[torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)] for _ in range(T)]
@@ -372,8 +374,14 @@ class BlockTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
-        masked = not overwrite and stack.masks_ahead(blk, self.a.per_step, self.timer is not None)
-        if blk.window:
+        masked = not overwrite and stack.masks_ahead(blk, self.a.per_step)
+        if masked:
+            if self.g_p is None:
+                self.g_p = torch.empty((self.T_max,) + tuple(g_y.shape[1:]), dtype=g_y.dtype, device=g_y.device)
+            g_top = self.g_p[:T]
+            with self._stage("mproduct_relu_backward"):
+                B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1, :T], self.a.dinv_all[:T], g_top, blk.window, self.t0, g_after=g_after)
+        elif blk.window:
             if overwrite:
                 g_top = g_y
             else:
@@ -381,13 +389,10 @@ class BlockTrainer:
                     self.g = torch.empty((self.T_max,) + tuple(g_y.shape[1:]), dtype=g_y.dtype, device=g_y.device)
                 g_top = self.g[:T]
             with self._stage("mproduct_backward"):
-                if masked:
-                    B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1, :T], self.a.dinv_all[:T], g_top, blk.window, self.t0, g_after=g_after)
-                else:
-                    B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
+                B.mproduct_backward_block(g_y, g_top, blk.window, self.t0, g_after=g_after)
         else:
             g_top = g_y
-        self.g_top = g_top
+        self.g_top = None if masked else g_top
         m = stack.steps_back(self.dw_t, T)
         last = (T - 1) // m * m
         for t in range(last, -1, -m):
@@ -637,7 +642,7 @@ class SmoothedTrainer:
         self.stack = GcnStack(blk, max(self.cap_s, blk.nnz[0]), arrays[0], arrays[1], self.dinv_s, vals=arrays[2], transposed=back, stage=_stage_of(self))
         self.z = self.stack.z
         self.y = torch.empty((T, n, f), dtype=dt, device=dev) if blk.window else None
-        self.g = None
+        self.g = self.g_p = None                           # dL/dZ of the last layer, or G_P where a pass masks ahead
         self.dw = [torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)]
         # with one weight per timestep (Section "EvolveGCN") every timestep has a gradient of its own
         self.dw_t = ([[torch.zeros((f, f), dtype=torch.float32, device=dev) for _ in range(L)] for _ in range(T)]
@@ -727,15 +732,18 @@ class SmoothedTrainer:
         T = blk.T
         g_y = upstream_frames(g_y, T, blk.n, blk.f, self.z.dtype, blk.window)
         stream = torch.cuda.current_stream(self.dev).cuda_stream
-        masked = g_y.shape[0] == T and stack.masks_ahead(blk, True, self.timer is not None)       # (frames behind the block count in the window)
-        if blk.window:
+        masked = g_y.shape[0] == T and stack.masks_ahead(blk, True)       # (frames behind the block count in the window)
+        if masked:
+            if self.g_p is None:
+                self.g_p = torch.empty_like(g_y)
+            with self._stage("mproduct_relu_backward"):
+                B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1], self.dinv_s, self.g_p, blk.window, 0)
+            g_top = self.g_p
+        elif blk.window:
             if self.g is None:
                 self.g = torch.empty_like(g_y)
             with self._stage("mproduct_backward"):
-                if masked:
-                    B.mproduct_relu_backward_block(g_y, self.z[blk.layers - 1], self.dinv_s, self.g, blk.window, 0)
-                else:
-                    B.mproduct_backward_block(g_y, self.g, blk.window, 0)
+                B.mproduct_backward_block(g_y, self.g, blk.window, 0)
             g_top = self.g
         else:
             g_top = g_y

@@ -163,6 +163,40 @@ def test_smoothed_trainer_takes_gradients_of_timesteps_behind_its_block():
     assert all(torch.equal(a, b) for a, b in zip(tr.dw, want.dw))
 
 
+@pytest.mark.parametrize("smoothed", [False, True])
+def test_a_timer_changes_neither_the_stages_nor_what_they_leave(smoothed):
+    """A timed step runs the calls of an untimed one, and dL/dZ of the top layer is not found where G_P was formed; a gradient that
+    overwrites its frames is dL/dZ in them, with and without."""
+    from paper_2109_07893_amd.training import make_smoothed_trainer
+    from paper_2109_07893_amd.pipeline import StageTimer
+    wl = CASES["directed_2layers_window"]
+    blk = make_block(wl, DEV, gen_device="cpu")
+    g_y = torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV)
+    tr = make_smoothed_trainer(wl, blk, 3) if smoothed else make_trainer(wl, blk)
+    g_z = torch.empty_like(g_y)
+    dg.mproduct_backward_block(g_y, g_z, wl.window, 0)
+    for timer in (None, StageTimer(DEV)):
+        tr.timer = timer
+        tr.forward()
+        tr.backward(g_y)
+        dw, g_p = [d.clone() for d in tr.dw], tr.g_p.clone()
+        assert tr.g is None
+        for t in range(wl.T):
+            want = torch.empty_like(g_p[t])
+            dg.relu_backward(g_z[t], tr.z[-1, t], want, row_scale=tr.dinv_s[t] if smoothed else tr.a.dinv[tr.a.slot_of(t + 1)])
+            assert torch.equal(g_p[t], want)
+        if timer is None:
+            first = dw
+        assert all(torch.equal(a, b) for a, b in zip(dw, first))
+        if not smoothed:
+            assert tr.g_top is None
+            own = g_y.clone()
+            tr.backward(own, overwrite=True)
+            assert tr.g_top is own and torch.equal(own, g_z) and all(torch.equal(a, b) for a, b in zip(tr.dw, first))
+    torch.cuda.synchronize()
+    assert "mproduct_relu_backward" in tr.timer.totals()
+
+
 @pytest.mark.parametrize("case,bsize", [("undirected_2layers_window", 3), ("directed_2layers_window", 2),
                                         ("directed_2layers_window", 4), ("undirected_1layer_window", 1),
                                         ("directed_1layer", 2), ("bf16_window", 4)])
