@@ -167,9 +167,21 @@ class TransformTable(Table):
 class SpmmTable(Table):
     """dgnn_spmm_item: rowptr, colidx, dinv, val, h, z, nnz."""
     ROWPTR, COLIDX, DINV, VAL, H, Z, NNZ = range(7)
+    LAUNCH = 32                                      # aggregations that the library enqueues together
 
     def __init__(self, rows: int):
         super().__init__(rows, 7)
+
+    @staticmethod
+    def workspace(together: int, cap: int, f: int) -> int:
+        """Bytes of scratch for run(): it follows the entries, not the frames (2048 vertices, 4 M entries, 128 columns: 1 MB a frame,
+        34 MB an aggregation), so no more than one launch has it at a time."""
+        return B.spmm_batch_workspace(min(together, SpmmTable.LAUNCH), cap, f)
+
+    def run(self, n: int, row: int, count: int, f: int, dt: int, flags: int, ws: torch.Tensor, stream) -> None:
+        """The aggregations of rows row .. row + count - 1, a launch's worth after the other on the same scratch."""
+        for k in range(0, count, self.LAUNCH):
+            B.spmm_batch(n, min(self.LAUNCH, count - k), self.at(row + k), f, dt, flags, ws, stream)
 
 
 class WeightGradTable(Table):

@@ -73,7 +73,7 @@ class CdgcnLayer(BlockRunner):
             scaled.column(scaled.SCALE, dinv)
             scaled.column(scaled.H, xs)
             b.column(b.H, xs)
-        self.ws_batch = torch.empty(B.spmm_batch_workspace(self.together, self.cap, blk.f), dtype=torch.uint8, device=self.dev)
+        self.ws_batch = torch.empty(SpmmTable.workspace(self.together, self.cap, blk.f), dtype=torch.uint8, device=self.dev)
         return scaled, b
 
     def _overrides(self, name: str) -> bool:
@@ -108,7 +108,7 @@ class CdgcnLayer(BlockRunner):
             with self._stage("row_scale"):
                 B.feature_transform_batch(k, scaled.at(t), n, f, f, 0, dt, stream)
         with self._stage("spmm"):
-            B.spmm_batch(n, k, b.at(t), f, dt, B.DGNN_H_PRESCALED if self.prescale else 0, self.ws_batch, stream)
+            b.run(n, t, k, f, dt, B.DGNN_H_PRESCALED if self.prescale else 0, self.ws_batch, stream)
         if self._overrides("form_y"):
             self.y0, self.y = y0[0], y[0]
             self.form_y()

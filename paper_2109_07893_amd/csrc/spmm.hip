@@ -638,7 +638,8 @@ extern "C" int dgnn_spmm_batch_workspace(int32_t count, int64_t nnz, int32_t f, 
     if (count <= 0 || nnz < 0 || !supported_width(f)) return DGNN_ERR_SHAPE;
     if (!fits_index(nnz)) return DGNN_ERR_OVERFLOW;
     // the shortest range any storage type uses at this width is one sub-tile; no call has more ranges than this
-    const int64_t shortest = kWave / (f / 4) * per_group(f / 4);  // (slices make sub-tiles longer)
+    const int lanes = std::min(f / 4, 16);                        // per row, at most: fp32 rows of 128 columns are always cut (see slices_of)
+    const int64_t shortest = kWave / lanes * per_group(lanes);    // (slices make sub-tiles longer)
     const int64_t ranges = std::min<int64_t>((nnz + shortest - 1) / shortest, std::max<int64_t>(kTargetWaves + 1, (nnz + kMaxRange - 1) / kMaxRange));
     *bytes = (size_t)count * workspace_layout(nnz, f, nullptr, nullptr, ranges + 1);
     return DGNN_OK;

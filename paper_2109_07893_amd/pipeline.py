@@ -274,7 +274,7 @@ class BlockRunner:
             tb.transform.append(a)
             tb.spmm.append(b)
         tb.series.prepare(blk.deltas[:T - 1], blk.nnz[0], dev)
-        tb.ws = torch.empty(B.spmm_batch_workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
+        tb.ws = torch.empty(SpmmTable.workspace(m, self.cap, f), dtype=torch.uint8, device=dev)
         return tb
 
     def _bind_frames(self, tb) -> None:
@@ -311,7 +311,7 @@ class BlockRunner:
             k = min(m, T - t)
             for layer in range(blk.layers):
                 B.feature_transform_batch(k, tb.transform[layer].at(t), n, f, f, 0, dt, stream)
-                B.spmm_batch(n, k, tb.spmm[layer].at(t), f, dt, B.DGNN_RELU | B.DGNN_H_PRESCALED, tb.ws, stream)
+                tb.spmm[layer].run(n, t, k, f, dt, B.DGNN_RELU | B.DGNN_H_PRESCALED, tb.ws, stream)
 
     def _run_overlapped(self, first: int, validate: bool, on_snapshot, pinned: bool, prefetch_next: bool) -> None:
         """The same pass on two streams: the rebuild of A_t, whatever a subclass does to A_t (snapshot_ready) and the

@@ -99,7 +99,7 @@ class GcnStack:
         self.gp = torch.empty((m, n, f), dtype=dt, device=dev) if aggregated > 0 else None
         self.g_mid = torch.empty((m, n, f), dtype=dt, device=dev) if L > 1 else None
         self.dx = torch.empty((T, n, f), dtype=dt, device=dev) if want_dx else None
-        self.ws_spmm = torch.empty(B.spmm_batch_workspace(m, cap, f), dtype=torch.uint8, device=dev)
+        self.ws_spmm = torch.empty(SpmmTable.workspace(m, cap, f), dtype=torch.uint8, device=dev)
         self.ws_wgrad = torch.empty(B.weight_grad_workspace(f, f), dtype=torch.uint8, device=dev)
         self.x, self.w = Frames((n, f), dt, "x"), [Frames((f, f), dt, "w") for _ in range(L)]
 
@@ -174,7 +174,7 @@ class GcnStack:
                     B.feature_transform_batch(k, self.transform[layer].at(t), n, f, f, 0, dt, stream)
             flags = (0 if first else B.DGNN_RELU) | (0 if first and not self.prescale else B.DGNN_H_PRESCALED)
             with self.stage("spmm_weighted" if self.weighted else "spmm"):
-                B.spmm_batch(n, k, self.spmm[layer].at(t), f, dt, flags, self.ws_spmm, stream)
+                self.spmm[layer].run(n, t, k, f, dt, flags, self.ws_spmm, stream)
             if first:
                 with self.stage("feature_transform"):
                     B.feature_transform_batch(k, self.transform[0].at(t), n, f, f, B.DGNN_RELU, dt, stream)
@@ -221,7 +221,7 @@ class GcnStack:
                 with self.stage("relu_backward"):
                     B.relu_backward(g.view(flat), self.z[layer, t:t + k].view(flat), self.gp[:k].view(flat), row_scale=dinv.view(-1))
             with self.stage("spmm_weighted_transposed" if self.weighted else "spmm_transposed"):
-                B.spmm_batch(n, k, table.at(t), f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
+                table.run(n, t, k, f, dt, B.DGNN_H_PRESCALED, self.ws_spmm, stream)
             if layer > 0:
                 self._weight_grad(blk, t, k, layer, self.z[layer - 1, t:t + k], self.h, False, dw, dw_t, accumulate, stream)
             else:                                  # the frames of X are tensors of their own, added up from the last one on

@@ -443,6 +443,25 @@ def test_batched_aggregations_are_checked_before_the_first_of_them(lib):
     assert call(10, 33, items(), 32, 0, 0, FAKE, 33 * one - 1, None) == -3
 
 
+def test_scratch_of_many_dense_snapshots_on_few_vertices(lib):
+    """Aggregations enqueued together: frames of 1 MB would let 512 of 4 M entries share a batch, whose scratch is that of 32."""
+    import torch
+    from paper_2109_07893_amd.batch import BATCH_BYTES, SpmmTable, steps_together
+    from paper_2109_07893_amd.pipeline import BlockInputs
+    from paper_2109_07893_amd.training import GcnStack
+    n, f, entries = 2048, 128, 2048 * 2048
+    assert steps_together(n * f * 4, 10_000) == BATCH_BYTES // (n * f * 4) == 512
+    size = ctypes.c_size_t(0)
+    for count in (1, 31, 32, 33, 512):
+        assert lib.dgnn_spmm_batch_workspace(min(count, 32), entries, f, ctypes.byref(size)) == 0
+        assert SpmmTable.workspace(count, entries, f) == size.value <= 32 * 35e6
+    blk = BlockInputs(n=16, T=40, f=128, layers=1, window=0, rowptr1=torch.zeros(17, dtype=torch.int32), colidx1=torch.zeros(1, dtype=torch.int32),
+                      deltas=[], x=[torch.zeros(16, 128)] * 40, w=[torch.zeros(128, 128)], nnz=[16] * 40)
+    arrays = [[torch.zeros(17, dtype=torch.int32)] * 40 for _ in range(3)]
+    stack = GcnStack(blk, 100_000, *arrays)
+    assert stack.together == 40 and stack.ws_spmm.numel() == SpmmTable.workspace(32, 100_000, 128)
+
+
 def test_a_series_needs_steps_enough_for_its_set_up(lib):
     """Blocks of one step are rebuilt as a series up to half the entries of longer ones."""
     import torch
