@@ -121,13 +121,13 @@ __device__ __forceinline__ void count_by_search(const int32_t *const (&rows)[kLi
         for (int l = 0; l < kLists; ++l)
             if (heavy[l])
 #pragma unroll
-                for (int k = 0; k <= kRowsPerThread; ++k) v[l][k] = rows[l][min(pos[l][k] + step, hi[l]) - 1];
+                for (int k = 0; k <= kRowsPerThread; ++k) v[l][k] = rows[l][pos[l][k] + min(step, hi[l] - pos[l][k]) - 1];   // (a sum with step itself may pass 2^31)
 #pragma unroll
         for (int l = 0; l < kLists; ++l)
             if (heavy[l])
 #pragma unroll
                 for (int k = 0; k <= kRowsPerThread; ++k)
-                    if (pos[l][k] + step <= hi[l] && v[l][k] < key(k)) pos[l][k] += step;      // entries before pos have smaller rows
+                    if (step <= hi[l] - pos[l][k] && v[l][k] < key(k)) pos[l][k] += step;      // entries before pos have smaller rows
     }
 #pragma unroll
     for (int l = 0; l < kLists; ++l)

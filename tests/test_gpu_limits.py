@@ -92,3 +92,29 @@ def test_rebuild_at_the_int32_limit():
         want = sorted((old - set(dc[dr == r].tolist())) | set(ac[ar == r].tolist()))
         got = cin[int(rpn[r]):int(rpn[r + 1])].cpu().numpy().tolist()
         assert got == want, r
+
+
+@pytest.mark.timeout(600)
+def test_rebuild_that_deletes_all_of_a_full_matrix():
+    """A deleted list just under 2^31 entries whose last row tile owns millions of them: the counts come from searches whose steps
+    lead beyond 2^31 there.  What is left is the diagonal."""
+    n = 46_340
+    nnz, n_del = n * n, n * (n - 1)
+    assert nnz <= (1 << 31) - 65537 and n_del + (1 << 22) > 1 << 31
+    rowptr = (torch.arange(n + 1, dtype=torch.int64, device=DEV) * n).to(torch.int32)
+    colidx = torch.arange(n, dtype=torch.int32, device=DEV).repeat(n)
+    d_row, d_col = (torch.empty(n_del, dtype=torch.int32, device=DEV) for _ in range(2))
+    c = torch.arange(n - 1, dtype=torch.int32, device=DEV)[None, :]
+    for r0 in range(0, n, 1024):
+        r = torch.arange(r0, min(r0 + 1024, n), dtype=torch.int32, device=DEV)[:, None]
+        d_row.view(n, n - 1)[r0:r0 + 1024] = r
+        d_col.view(n, n - 1)[r0:r0 + 1024] = c + (c >= r).to(torch.int32)
+    none = torch.empty(0, dtype=torch.int32, device=DEV)
+    rpn = torch.full((n + 1,), -7, dtype=torch.int32, device=DEV)
+    cin = torch.full((n,), -7, dtype=torch.int32, device=DEV)
+    dinv = torch.empty(n, device=DEV)
+    ws = torch.empty(dg.delta_rebuild_workspace(n, nnz, 0, n_del), dtype=torch.uint8, device=DEV)
+    assert dg.delta_rebuild(rowptr, colidx, nnz, none, none, 0, d_row, d_col, n_del, rpn, cin, dinv, ws) == n
+    torch.cuda.synchronize()
+    want = torch.arange(n + 1, dtype=torch.int32, device=DEV)
+    assert torch.equal(rpn, want) and torch.equal(cin, want[:n]) and bool((dinv == 1).all())
