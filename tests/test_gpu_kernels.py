@@ -497,6 +497,37 @@ def test_spmm_beyond_32_bit_offsets():
     assert bool((z == ci.float()[:, None]).all())
 
 
+@pytest.mark.parametrize("n,f,dtype", [((1 << 23) + 1000, 128, torch.float32), ((1 << 27) + 1000, 16, torch.bfloat16)])
+@pytest.mark.parametrize("factors", ["none", "dinv", "values"])
+def test_spmm_beyond_32_bit_offsets_with_factors(n, f, dtype, factors):
+    """H and Z of more than 4 GB: rows of one entry and, at both ends and in the middle, rows over several ranges; small whole
+    numbers and powers of two, so that every sum is exact and a result is rounded once, to its storage type."""
+    gen = torch.Generator(device=DEV).manual_seed(f)
+    ints = (torch.arange(n, dtype=torch.int32, device=DEV) % 61 - 20).to(torch.float32)
+    h = ints.to(dtype)[:, None].expand(n, f).contiguous()
+    lens = torch.ones(n, dtype=torch.int64, device=DEV)
+    lens[[0, n // 2, n - 1]] = 5000
+    rp = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    rp[1:] = lens.cumsum(0)
+    nnz = n + 3 * 4999
+    ci = torch.randint(0, n, (nnz,), generator=gen, dtype=torch.int32, device=DEV)
+    entry = ints[ci]
+    val = torch.randint(0, 3, (nnz,), generator=gen, device=DEV).float().exp2() if factors == "values" else None
+    total = torch.zeros(nnz + 1, dtype=torch.float64, device=DEV)
+    total[1:] = (entry if val is None else entry * val).double().cumsum(0)
+    want = (total[rp[1:]] - total[rp[:-1]]) * (0.25 if factors == "dinv" else 1.0)
+    del total, entry
+    z = torch.full((n, f), float("nan"), dtype=dtype, device=DEV)
+    ws = torch.empty(dg.spmm_workspace(n, nnz, f), dtype=torch.uint8, device=DEV)
+    rp = rp.to(torch.int32)
+    if val is not None:
+        dg.spmm_weighted(rp, ci, val, nnz, h, z, ws)
+    else:
+        dg.spmm(rp, ci, nnz, torch.full((n,), 0.5, device=DEV) if factors == "dinv" else None, h, z, ws)
+    torch.cuda.synchronize()
+    assert bool((z == want.to(dtype)[:, None]).all())
+
+
 # ------------------------------------------------------------------------------- M-transform
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("T,w", [(8, 3), (32, 8), (40, 16), (5, 1), (6, 9), (70, 32), (3, 2), (1, 4)])
