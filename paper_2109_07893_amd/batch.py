@@ -14,16 +14,22 @@ from . import binding as B
 # Timesteps whose GCN operation is enqueued together: as many as keep the rows of H that the aggregations gather within this many
 # bytes.  An aggregation deals whole frames to the XCDs, each of which then gathers out of one frame at a time, so eight frames or
 # more are worth having, and every launch pair has a start and an end of its own; whether all of H stays in the Infinity Cache
-# (256 MB) matters less.  Whole passes in us for 64 / 256 / 512 / 1024 MB: two layers forward, 100 K vertices x 64 fp32, 2330 / 2108 /
-# 2056 / 2056; trained, 50 K, 1984 / 1676 / 1675 / 1675; 100 K x 128 bf16 forward 3379 / 2976 / 2947 / 2950; CD-GCN in bf16, 200 K x 64,
-# 944 / 860 / 858 / 859.
+# (256 MB) matters less.  Whole passes in us for 64 / 256 / 512 / 1024 MB, uniform graphs: two layers forward, 100 K vertices x 64 fp32,
+# 2330 / 2118 / 2062 / 2064; trained, 50 K, 1984 / 1676 / 1675 / 1675; 100 K x 128 bf16 forward 3379 / 2976 / 2947 / 2950; CD-GCN in bf16,
+# 200 K x 64, 944 / 860 / 858 / 859; R-MAT: two layers forward, 2^16 x 64 fp32, 1242 / 1119 / 1113 / 1113, 2^17 2494 / 2227 / 2218 / 2212;
+# trained, 2^16, 2519 / 2250 / 2249 / 2241; 2^17 x 128 bf16 forward 2572 / 2332 / 2307 / 2284; CD-GCN in bf16, 2^17 x 64, 1073 / 1050 / 1043 /
+# 1054.  The price is memory: a driver holds up to four buffers of a batch's frames (H, the masked gradient, and with several layers
+# a layer's output and its gradient), 2 GB at most, beside the scratch of 32 aggregations (SpmmTable.workspace).
 BATCH_BYTES = 512 << 20
 
 # Stored entries up to which a block's snapshots are rebuilt as a series, and how many of them a step must make up for.  The
 # set-up takes 9 us per million entries; a step saves one rebuild's launches and the products and aggregations of its timestep
-# a launch of their own, less the more entries there are.  Whole passes (32 columns, uniform graph), series / step by step in us:
-# one step 1.4 M entries 90 / 101, 2.0 M 123 / 124, 2.8 M 163 / 159, 4.0 M 224 / 212; two steps 2.8 M 221 / 244, 4.0 M 324 / 325;
-# nine steps 4.0 M 964 / 1123.  Above 2^22 the chip is full with one timestep (17 M, per step: 15 steps 48 / 54 us, 3 steps 85 / 62).
+# a launch of their own, less the more entries there are.  Whole passes (32 columns), series / step by step in us: uniform graph, one
+# step 1.4 M entries 79 / 88, 2.0 M 115 / 110, 2.8 M 162 / 149, 4.0 M 228 / 210; two steps 2.8 M 220 / 231, 4.0 M 316 / 326; nine steps
+# 4.0 M 915 / 1085; R-MAT, one step 1.4 M 73 / 85, 2.0 M 102 / 106, 2.7 M 115 / 116, 3.9 M 171 / 162; two steps 3.9 M 229 / 255; nine 662 / 894.
+# Above 2^22 the chip is full with one timestep, and what a long series still gains gets less (15 steps, uniform 5.6 M 2134 / 2416, 8 M
+# 3079 / 3382, 17 M 6749 / 7010), a short one loses (3 steps of 17 M 1834 / 1799): such blocks keep the step-by-step order, and its
+# three slots instead of a snapshot per timestep.
 SERIES_ENTRIES = 1 << 22
 SERIES_ENTRIES_PER_STEP = 1 << 21
 
@@ -35,9 +41,14 @@ SERIES_BYTES = 16 << 30
 # Vertices up to which the aggregation of X gathers dinv with the rows instead of finding them scaled by a pass of their own.
 # The pass costs per byte of X and a launch, the gather per entry, and far more once the factors (4 bytes per vertex, 1 MB here)
 # leave an L2 of 4 MB to the rows no more.  Uniform graphs, timesteps together as batch.py has them, gather / pass in us per
-# aggregation: 128-byte rows, 16 entries per row 2^14 vertices 5.7 / 6.0, 2^16 19.1 / 18.6, 2^18 94 / 94, 2^19 216 / 201; 4 entries
-# per row 2^16 9.3 / 11.3, 2^18 40 / 47, 2^19 84 / 95; 512-byte rows, 16 entries 2^16 75 / 84, 2^18 361 / 369, 2^19 794 / 751.
-# (64-byte rows cross at 2^15 already, 2^18 82 / 75: a tenth, for which the rule takes no width.)
+# aggregation, 16 entries per row:
+#                  2^14          2^15          2^16          2^17          2^18          2^19          2^20 vertices
+#   64-byte rows   2.9 / 2.4     6.1 / 5.0    13.0 / 9.8    28.7 / 25.0   87.3 / 75.7    194 / 171     466 / 355
+#   128            3.7 / 3.5     7.5 / 6.5    15.6 / 14.9   35.7 / 37.8   96.0 / 99.6    213 / 202     490 / 400
+#   256            5.9 / 6.2    14.2 / 12.2   31.9 / 29.7   73.3 / 78.8    185 / 199     400 / 387     863 / 765
+#   512           11.2 / 11.6   29.9 / 25.4   65.1 / 61.3    146 / 160     358 / 383     793 / 766    1722 / 1509
+# and 4 entries per row, 128-byte rows, 2^14 1.5 / 2.2, 2^16 6.4 / 8.1, 2^18 30.5 / 38.5, 2^19 69.7 / 79.7, 2^20 168 / 171.  Rows of 64 bytes and
+# graphs of 2^15 - 2^16 with many entries per row are the exceptions, for which the rule takes neither a width nor a degree.
 GATHERED_DINV_ROWS = 1 << 18
 
 

@@ -8,8 +8,9 @@
 // per cache line touched), so lines other than those of H count.  It is split by ENTRIES, not by rows, and every wavefront is
 // an independent stream:
 //   - a wavefront owns a contiguous range of stored entries and walks it in sub-tiles (up to 65536 sub-tiles: one per wavefront,
-//     which then needs 64 registers only).  The row that holds the range's first entry is found once, mostly by two scalar
-//     loads and one look at 64 row pointers; afterwards rows simply follow on;
+//     which then takes 64 registers in fp32, 73 with factors, 81 - 88 in bf16, where one that walks on takes 94 - 154).  The row that
+//     holds the range's first entry is found once, mostly by two scalar loads and one look at 64 row pointers; afterwards rows
+//     simply follow on;
 //   - the sub-tile's columns go to LDS as byte offsets, a lane group reads four of them at once; the rows with entries are listed
 //     in LDS, their starts become a bit mask (one 32-bit word per lane group);
 //   - every lane group takes 32 consecutive entries, keeps eight gathers in flight, each replaced as it is used, and where
@@ -23,8 +24,9 @@
 // short rows share a wavefront, and every sum has a fixed order: no floating-point atomics,
 // results repeat bit for bit.
 // Against the form with a search per lane group, a branch per entry and workgroup barriers, us per aggregation: uniform 50 K
-// vertices x 64 fp32 25.9 -> 17.0 (with slices of columns, see slices_of), 100 K 59.5 -> 50, R-MAT 2^18 x 32 fp32 with values 71 -> 52,
-// 2^23 (misses) 2250 both.
+// vertices x 64 fp32 25.1 -> 16.2 (with slices of columns, see slices_of), 100 K 55.5 -> 47.5, R-MAT 2^16 x 64 20.7 -> 18.8, 2^19 x 32 with
+// values 131 -> 99.  Where misses bound it, R-MAT 2^23: x 32 fp32 2292 / 2286, bf16 2161 / 2156; with values fp32 2326 -> 2360 (1 - 2 %
+// more, 2^24 too; neither nontemporal loads of the values nor a later prefetch gave it back), bf16 x 16 2344 -> 2083.
 #include <algorithm>
 #include <type_traits>
 
@@ -52,7 +54,8 @@ constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: all vector memory loa
 // and with it whose left carries are its pieces, follows from the row pointers.
 struct RangeRec { int32_t open_row, pad0, pad1, pad2; };
 
-// One aggregation of a launch; blockIdx.y says which (a launch may take the aggregations of several timesteps).
+// One aggregation of a launch, which may take those of several timesteps: the first kernel finds it by its place in the launch's
+// line of units (see Line), the second by blockIdx.y.
 struct Item {
     const int32_t *rowptr, *colidx;
     const float *dinv, *vals;
@@ -403,6 +406,8 @@ __device__ __forceinline__ void spmm_stream(
 // slice of it) at a time to keep in its L2.
 struct Line { int first, units, ranges, per_xcd, sharing; };   // the first item of the launch; ranges of a unit; of an XCD; log2 of the XCDs that share a unit, or -1
 
+// Four wavefronts per SIMD, but three where factors and several sub-tiles meet, which in bf16 and in rows of four lanes takes 133 - 158
+// registers: four would spill up to 20 of them (R-MAT 2^23 x 32 bf16 with values 2280 -> 2440 us; 2^20 x 64 224 -> 236).
 template <int LPR, int SLICES, bool BF16, bool SCALE_V, bool FAR, bool ONE>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(ONE || !SCALE_V ? 4 : 3, 8))) void spmm_stream_kernel(int n, int relu, Line line, Batch batch) {
     const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
@@ -554,12 +559,21 @@ int launch(int64_t n, int count, const Batch &b, bool scale_v, int relu, hipStre
 
 // Into how many slices of columns an aggregation is cut, each with XCDs of its own: an L2 then holds that slice of H only, as if
 // it were so much larger.  Every entry's bookkeeping is done once per slice, and below 128 bytes, the L2's line, nothing is saved
-// (twice the time).  Slices of 128 bytes pay where H does not fit an L2 of 4 MB but a slice of it does for a good part; us per
-// aggregation, whole rows / slices (512-byte rows: slices of 256 / of 128), for several timesteps as the drivers batch them:
-//   256-byte rows   uniform graph, 16 entries per row: 25 K vertices 7.3 / 7.0, 50 K 23.3 / 16.5, 60 K 24.9 / 18.8, 100 K 59 / 50,
-//                   200 K equal, 1 M 664 / 690; R-MAT 2^16 18.5 / 20.1, 2^17 45 / 47, 2^20 361 / 373
-//   512-byte rows   uniform 50 K 40 / 30, 100 K 95 / 84, 300 K 309 / 301; R-MAT 2^16 43 / 48, 2^18 173 / 180
-// and rows of 512 bytes go in two slices of 256 everywhere else (uniform 32 K whole / two 45 / 36, R-MAT 2^20 1.10 / 0.91 ms).
+// (twice the time).  Slices of 128 bytes pay where H does not fit an L2 of 4 MB but a slice of it does for a good part.  us per
+// aggregation of eight together, 17 entries per row, without / with slices of 128 bytes:
+//                     64 columns fp32    128 columns bf16    128 columns fp32 (without: two slices of 256 bytes)
+//   uniform   25 K      8.3 /  8.0         9.2 /  8.8          15.8 / 14.4
+//             33 K     12.5 / 10.1        13.3 / 11.0          24.3 / 19.7
+//             50 K     23.2 / 16.1        24.1 / 17.3          46.3 / 32.3
+//            100 K     56.7 / 47.7        58.8 / 48.8           113 / 97
+//            131 K     78.5 / 68.8        80.6 / 70.3           154 / 139
+//   R-MAT    2^15       9.0 /  9.9        10.4 / 10.8          16.7 / 18.1
+//            2^16      17.6 / 18.8        19.7 / 20.3          40.6 / 42.1
+//            2^17      42.3 / 43.5        47.3 / 46.7          89.5 / 92.1
+// (uniform 200 K equal, 1 M 664 / 690; R-MAT 2^20 361 / 373.)  On a power-law graph the rows that most entries name lie in the L2s anyway,
+// and the slices cost 2 - 10 %; a uniform one gains up to 30 %.  The launch knows n and the entry count only, not how rows
+// are named, so the line follows the larger of the two.  Rows of 512 bytes go in two slices of 256 everywhere else (uniform 32 K whole /
+// two 45 / 36, R-MAT 2^20 1.10 / 0.91 ms).
 int slices_of(int64_t n, int32_t f, dgnn_dtype dt) {
     const int row_bytes = f * (dt == DGNN_F32 ? 4 : 2);
     const bool narrow = row_bytes >= 256 && n * 128 >= (int64_t(3) << 20) && n * 128 <= (int64_t(16) << 20);
