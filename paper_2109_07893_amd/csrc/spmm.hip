@@ -24,9 +24,12 @@
 // short rows share a wavefront, and every sum has a fixed order: no floating-point atomics,
 // results repeat bit for bit.
 // Against the form with a search per lane group, a branch per entry and workgroup barriers, us per aggregation: uniform 50 K
-// vertices x 64 fp32 25.1 -> 16.2 (with slices of columns, see slices_of), 100 K 55.5 -> 47.5, R-MAT 2^16 x 64 20.7 -> 18.8, 2^19 x 32 with
-// values 131 -> 99.  Where misses bound it, R-MAT 2^23: x 32 fp32 2292 / 2286, bf16 2161 / 2156; with values fp32 2326 -> 2360 (1 - 2 %
-// more, 2^24 too; neither nontemporal loads of the values nor a later prefetch gave it back), bf16 x 16 2344 -> 2083.
+// vertices x 64 fp32 25.1 -> 16.2 (with slices of columns, see slices_of), 100 K 55.5 -> 47.5, R-MAT 2^16 x 64 20.7 -> 18.8, 2^18 x 128 bf16
+// 125 -> 97, 2^19 x 32 with values 131 -> 99.  Where misses bound it, more wavefronts wait for the same fabric: R-MAT 2^23 x 32 2292 / 2286, but
+// with values 2326 -> 2360, and uniform graphs of 135 K - 2 M vertices with rows of 256 and 512 bytes take 2 - 5 % longer (200 K x 64 126.7 ->
+// 129.3, 500 K 246 -> 256, x 128 491 -> 516, 2 M 986 -> 1005): the same bytes pass the L2s, a request is away for 1130 cycles
+// instead of 1040.  Eight wavefronts per CU instead of up to 32 give that back (500 K 248) and take more from power-law graphs, whose hot
+// rows come from the L2s (2^18 x 64 92 -> 107); nothing that a call is given tells the two apart.
 #include <algorithm>
 #include <type_traits>
 
