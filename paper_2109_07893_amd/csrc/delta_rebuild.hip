@@ -665,8 +665,9 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
 }
 
 // Surviving entries whose value changes, for an update list in no particular order: one thread per listed entry
-// finds it in its (new) row and overwrites the value.  Entries that are not there are skipped.
-__global__ __launch_bounds__(256) void update_values_kernel(int n, const int32_t *__restrict__ rowptr,
+// finds it in its (new) row and overwrites the value.  Entries that are not there are skipped.  cap: entries that the arrays hold;
+// row pointers that came out of lists which break the preconditions can point anywhere.
+__global__ __launch_bounds__(256) void update_values_kernel(int n, const int32_t *__restrict__ rowptr, int cap,
                                                             const int32_t *__restrict__ colidx,
                                                             const int32_t *__restrict__ upd_row,
                                                             const int32_t *__restrict__ upd_col,
@@ -676,7 +677,7 @@ __global__ __launch_bounds__(256) void update_values_kernel(int n, const int32_t
     if (j >= n_upd) return;
     const int r = upd_row[j], c = upd_col[j];
     if ((unsigned)r >= (unsigned)n) return;
-    const int lo = rowptr[r], hi = rowptr[r + 1];
+    const int lo = max(rowptr[r], 0), hi = min(rowptr[r + 1], cap);
     const int p = lower_bound(colidx, lo, hi, c);
     if (p < hi && colidx[p] == c) val[p] = upd_val[j];
 }
@@ -950,7 +951,7 @@ extern "C" int dgnn_delta_rebuild_weighted(int64_t n,
                            rowptr_next, colidx_next, cap_next, nnz_next, nullptr, &vals, ws, ws_bytes, flags, d_status, stream);
     if (rc != DGNN_OK || n_upd == 0 || folded) return rc;
     hipLaunchKernelGGL(update_values_kernel, dim3((unsigned)((n_upd + 255) / 256)), dim3(256), 0, (hipStream_t)stream, (int)n,
-                       rowptr_next, colidx_next, upd_row, upd_col, upd_val, (int)n_upd, val_next);
+                       rowptr_next, (int)std::min<int64_t>(cap_next, 2147483647LL), colidx_next, upd_row, upd_col, upd_val, (int)n_upd, val_next);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }

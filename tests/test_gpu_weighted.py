@@ -156,6 +156,35 @@ def test_weighted_rebuild_reports_an_unsorted_update_list():
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])      # the structure does not depend on the updates
 
 
+@pytest.mark.parametrize("merged", [False, True])
+def test_weighted_rebuild_of_long_lists_in_reverse_order(merged):
+    """More than 8192 entries in a tile of 1024 rows, added, deleted and updated ones from the last to the first: reported, and nothing
+    is written outside the arrays, whose row pointers point anywhere then."""
+    n, m = 1500, 20_000
+    rng = np.random.default_rng(3)
+    rows, cols = np.divmod(np.sort(rng.choice(n * n, 40 * n, replace=False)), n)
+    rp, ci = oracle.csr_from_edges(n, np.concatenate([rows, np.arange(n)]).astype(np.int32), np.concatenate([cols, np.arange(n)]).astype(np.int32))
+    r_of = np.repeat(np.arange(n, dtype=np.int32), np.diff(rp))
+    off = np.flatnonzero(r_of != ci)
+    gone, touched = np.sort(rng.choice(off, m, replace=False))[::-1], np.sort(rng.choice(off, m, replace=False))[::-1]
+    free = np.setdiff1d(np.arange(n * n), r_of.astype(np.int64) * n + ci)
+    new = np.sort(rng.choice(free, m, replace=False))[::-1]
+    one = torch.ones(m, device=DEV)
+    guard = 4096
+    arrays = [torch.full((ci.size + guard,), -7, dtype=dt, device=DEV) for dt in (torch.int32, torch.float32)]
+    cin, vn = (a[:ci.size] for a in arrays)
+    rpn = torch.full((n + 1 + guard,), -7, dtype=torch.int32, device=DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(dg.delta_rebuild_workspace(n, ci.size, m, m), dtype=torch.uint8, device=DEV)
+    dg.delta_rebuild_weighted(dev(rp, torch.int32), dev(ci, torch.int32), torch.ones(ci.size, device=DEV), ci.size,
+                              (dev(new // n, torch.int32), dev(new % n, torch.int32), one), (dev(r_of[gone], torch.int32), dev(ci[gone], torch.int32)),
+                              (dev(r_of[touched], torch.int32), dev(ci[touched], torch.int32), one), rpn[:n + 1], cin, vn, ws,
+                              flags=dg.DGNN_VALIDATE | (dg.DGNN_UPDATES_SORTED if merged else 0), d_status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 2
+    assert all(bool((a[ci.size:] == -7).all()) for a in arrays) and bool((rpn[n + 1:] == -7).all())
+
+
 def test_weighted_rebuild_edge_cases():
     n = 6
     base = [(u, u) for u in range(n)] + [(0, 1), (0, 5), (1, 0), (2, 3), (2, 4), (2, 5), (5, 0), (5, 4)]
