@@ -509,7 +509,8 @@ typedef struct {
 
 /*
  * dgnn_weight_grad for `count` gradients over n rows each (one weight per timestep, or one item over the rows of several
- * timesteps).  With z = the layer's output the gradient passes its ReLU on the way in: with x = A~ X and g = dL/dZ this is
+ * timesteps).  Items that follow each other with the same dw are summed into it, in this order: one weight whose timesteps lie
+ * in tensors of their own.  With z = the layer's output the gradient passes its ReLU on the way in: with x = A~ X and g = dL/dZ this is
  * the gradient of W for a layer evaluated as Z = sigma((A~ X) W), X^T A~^T G_P = (A~ X)^T G_P: no aggregation going back.
  * Workspace as dgnn_weight_grad.
  */

@@ -61,18 +61,23 @@ struct Split {
 };
 
 // MASKED: G is taken where Z > 0 only (the gradient through the ReLU, which then needs no pass of its own).
+// The gradient is the sum over `items` items from the first one on, n rows each, whose steps are one line: worker `me` takes steps
+// me, me + workers, ... of it.
 template <int FIN, int FOUT, bool BF16, bool MASKED>
-__device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *__restrict__ gv, const void *__restrict__ zv, int64_t n,
-                                      int64_t n_steps, float *__restrict__ partial) {
+__device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items, int64_t n, int64_t n_steps, float *__restrict__ partial) {
     using S = Split<FIN, FOUT>;
     typedef typename std::conditional<BF16, uint16_t, float>::type Elem;
     typedef typename std::conditional<BF16, uint32_t, float>::type Raw;
-    const Elem *x = static_cast<const Elem *>(xv);
-    const Elem *g = static_cast<const Elem *>(gv);
-    const Elem *z = static_cast<const Elem *>(zv);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int i = lane & 31, hh = lane >> 5;
     const int group = wave % S::GROUPS, rs = wave / S::GROUPS;
+    const Elem *x, *g, *z;
+    int item = 0;
+    auto open_item = [&] {
+        x = static_cast<const Elem *>(as_global(first[item].x));
+        g = static_cast<const Elem *>(as_global(first[item].g));
+        z = static_cast<const Elem *>(as_global(first[item].z));
+    };
     const int it0 = (group / S::GJ) * S::TI, jt0 = (group % S::GJ) * S::TJ;
     const int64_t workers = (int64_t)gridDim.x * S::RS;
     const int64_t me = (int64_t)blockIdx.x * S::RS + rs;
@@ -104,12 +109,23 @@ __device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *_
             }
         }
     };
-    if (me < n_steps) fetch(me);
-    for (int64_t step = me; step < n_steps; step += workers) {
+    // the step fetched last: its number within its item
+    int64_t at = me, left = me < n_steps * items ? (n_steps * items - me + workers - 1) / workers : 0;    // steps of this worker
+    auto advance = [&] {
+        bool turned = false;
+        for (; at >= n_steps; at -= n_steps, turned = true) item = uniform(item + 1);
+        if (turned) open_item();
+    };
+    open_item();
+    if (left > 0) {
+        advance();
+        fetch(at);
+    }
+    for (; left > 0; --left) {
         Raw xa[S::TI][8], gb[S::TJ][8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const bool row_ok = row_of(step, e) < n;
+            const bool row_ok = row_of(at, e) < n;
 #pragma unroll
             for (int ti = 0; ti < S::TI; ++ti) xa[ti][e] = (row_ok && (it0 + ti) * 32 + i < FIN) ? xa_next[ti][e] : Raw(0);
 #pragma unroll
@@ -120,7 +136,11 @@ __device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *_
                 gb[tj][e] = ok ? gb_next[tj][e] : Raw(0);
             }
         }
-        fetch(std::min(step + workers, n_steps - 1));      // the next step's rows travel while this one is multiplied
+        if (left > 1) {
+            at += workers;
+            advance();
+        }
+        fetch(at);                                          // the next step's rows travel while this one is multiplied
         __builtin_amdgcn_sched_barrier(0);                  // ... so the loads must stay ahead of the multiplications
         if constexpr (BF16) {
             bf16x8 a[S::TI], b[S::TJ];
@@ -191,38 +211,41 @@ __device__ __forceinline__ void wgrad(const void *__restrict__ xv, const void *_
             }
 }
 
+// `items` items of every gradient of the launch
 template <int FIN, int FOUT, bool BF16, bool MASKED>
-__global__ __launch_bounds__(kWavesPerBlock *kWave) void wgrad_kernel(Batch batch, int64_t n, int64_t n_steps, float *__restrict__ partial) {
-    const Item &it = batch.item[blockIdx.y];
-    wgrad<FIN, FOUT, BF16, MASKED>(as_global(it.x), as_global(it.g), as_global(it.z), n, n_steps,
-                                   partial + (int64_t)blockIdx.y * gridDim.x * FIN * FOUT);
+__global__ __launch_bounds__(kWavesPerBlock *kWave) void wgrad_kernel(Batch batch, int items, int64_t n, int64_t n_steps, float *__restrict__ partial) {
+    wgrad<FIN, FOUT, BF16, MASKED>(&batch.item[blockIdx.y * items], items, n, n_steps, partial + (int64_t)blockIdx.y * gridDim.x * FIN * FOUT);
 }
 
 // dw[e] = (accumulate ? dw[e] : 0) + sum over the workers' partial results: sixteen wavefronts take a slice of
 // the workers each (in worker order), then the sixteen slice sums are added in slice order: a fixed order.
+// `items` of them in a row have one dw; apart: each with partial results of its own, added to dw one after the other.
 constexpr int kReduceSlices = 16;
-__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, const float *__restrict__ partial, int workers,
+__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, int items, int apart, const float *__restrict__ partial, int workers,
                                                                             int elems, int accumulate) {
-    float *__restrict__ dw = as_global(batch.item[blockIdx.y].dw);
+    float *__restrict__ dw = as_global(batch.item[blockIdx.y * items].dw);
     partial += (int64_t)blockIdx.y * workers * elems;
     __shared__ float s_sum[kReduceSlices][kWave];
     const int lane = threadIdx.x & (kWave - 1), slice = threadIdx.x / kWave;
     const int e = blockIdx.x * kWave + lane;
     const int per = (workers + kReduceSlices - 1) / kReduceSlices;
     const int p0 = slice * per, p1 = min(p0 + per, workers);
-    float sum = 0.0f;
-    if (e < elems) {
+    float out = accumulate && e < elems ? dw[e] : 0.0f;
+    for (int k = 0; k < (apart ? items : 1); ++k, partial += (int64_t)workers * elems) {
+        float sum = 0.0f;
+        if (e < elems) {
 #pragma unroll 8
-        for (int p = p0; p < p1; ++p) sum += partial[(int64_t)p * elems + e];
-    }
-    s_sum[slice][lane] = sum;
-    __syncthreads();
-    if (slice == 0 && e < elems) {
+            for (int p = p0; p < p1; ++p) sum += partial[(int64_t)p * elems + e];
+        }
+        if (k) __syncthreads();
+        s_sum[slice][lane] = sum;
+        __syncthreads();
         float total = s_sum[0][lane];
 #pragma unroll
-        for (int k = 1; k < kReduceSlices; ++k) total += s_sum[k][lane];
-        dw[e] = accumulate ? dw[e] + total : total;
+        for (int s = 1; s < kReduceSlices; ++s) total += s_sum[s][lane];
+        out = accumulate || k ? out + total : total;
     }
+    if (slice == 0 && e < elems) dw[e] = out;
 }
 
 // out = (Z > 0 ? G : 0) * row_scale[row]; one 16-byte piece per lane.
@@ -253,41 +276,49 @@ __global__ __launch_bounds__(kThreads) void relu_backward_kernel(const uintx4 *_
     __builtin_nontemporal_store(o, out + p);
 }
 
+// `count` gradients, each the sum over `items` items (count = 1 where items > 1)
 template <int FIN, int FOUT, bool BF16, bool MASKED>
-int launch_wgrad(int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
+int launch_wgrad(int count, int items, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     using S = Split<FIN, FOUT>;
     const int64_t n_steps = (n + kStepRows - 1) / kStepRows;
-    const int64_t needed = (n_steps + S::RS - 1) / S::RS;
-    // the items of a launch share the workspace (one partial result per workgroup) and the device
+    auto workgroups = [](int64_t steps) { return (steps + S::RS - 1) / S::RS; };
+    // the gradients of a launch share the workspace (one partial result per workgroup) and the device
     const int64_t most = std::min<int64_t>(resident_workgroups(wgrad_kernel<FIN, FOUT, BF16, MASKED>, kWavesPerBlock * kWave, 256), kMaxBlocks);
-    const int64_t blocks = std::min<int64_t>(needed, std::max<int64_t>(1, most / count));
-    hipLaunchKernelGGL((wgrad_kernel<FIN, FOUT, BF16, MASKED>), dim3((unsigned)blocks, (unsigned)count), dim3(kWavesPerBlock * kWave), 0, s, b, n, n_steps, partial);
+    // Items of one sum: with partial results of their own where the workspace has room for all of them, which is then bit for bit
+    // a call per item; otherwise their steps are one line and a workgroup leaves one result for all of them.  On large items the
+    // results would be as many bytes as the items are (60 K x 128 bf16: 31 MB of rows, 17 MB of results; a checkpointed step over 24
+    // such timesteps, twelve of them to a line instead of a launch pair each, 2497 -> 2297 us).
+    const int64_t alone = std::min<int64_t>(workgroups(n_steps), most);
+    const int apart = items > 1 && alone * items <= kMaxBlocks;
+    const int64_t blocks = apart ? alone : std::min<int64_t>(workgroups(n_steps * items), std::max<int64_t>(1, most / count));
+    hipLaunchKernelGGL((wgrad_kernel<FIN, FOUT, BF16, MASKED>), dim3((unsigned)blocks, (unsigned)(apart ? items : count)), dim3(kWavesPerBlock * kWave), 0, s, b,
+                       apart ? 1 : items, n, n_steps, partial);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     constexpr int elems = FIN * FOUT;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((elems + kWave - 1) / kWave, (unsigned)count), dim3(kReduceSlices * kWave), 0, s, b, partial,
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((elems + kWave - 1) / kWave, (unsigned)count), dim3(kReduceSlices * kWave), 0, s, b, items, apart, partial,
                        (int)blocks, elems, accumulate);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
 
 template <int FIN, bool BF16, bool MASKED>
-int wgrad_out(int32_t f_out, int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
+int wgrad_out(int32_t f_out, int count, int items, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     switch (f_out) {
-        case 16: return launch_wgrad<FIN, 16, BF16, MASKED>(count, b, n, accumulate, partial, s);
-        case 32: return launch_wgrad<FIN, 32, BF16, MASKED>(count, b, n, accumulate, partial, s);
-        case 64: return launch_wgrad<FIN, 64, BF16, MASKED>(count, b, n, accumulate, partial, s);
-        case 128: return launch_wgrad<FIN, 128, BF16, MASKED>(count, b, n, accumulate, partial, s);
+        case 16: return launch_wgrad<FIN, 16, BF16, MASKED>(count, items, b, n, accumulate, partial, s);
+        case 32: return launch_wgrad<FIN, 32, BF16, MASKED>(count, items, b, n, accumulate, partial, s);
+        case 64: return launch_wgrad<FIN, 64, BF16, MASKED>(count, items, b, n, accumulate, partial, s);
+        case 128: return launch_wgrad<FIN, 128, BF16, MASKED>(count, items, b, n, accumulate, partial, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
 
 template <bool BF16, bool MASKED>
-int wgrad_in(int32_t f_in, int32_t f_out, int count, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
+int wgrad_in(int32_t f_in, int32_t f_out, int count, int items, const Batch &b, int64_t n, int accumulate, float *partial, hipStream_t s) {
     switch (f_in) {
-        case 16: return wgrad_out<16, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
-        case 32: return wgrad_out<32, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
-        case 64: return wgrad_out<64, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
-        case 128: return wgrad_out<128, BF16, MASKED>(f_out, count, b, n, accumulate, partial, s);
+        case 16: return wgrad_out<16, BF16, MASKED>(f_out, count, items, b, n, accumulate, partial, s);
+        case 32: return wgrad_out<32, BF16, MASKED>(f_out, count, items, b, n, accumulate, partial, s);
+        case 64: return wgrad_out<64, BF16, MASKED>(f_out, count, items, b, n, accumulate, partial, s);
+        case 128: return wgrad_out<128, BF16, MASKED>(f_out, count, items, b, n, accumulate, partial, s);
         default: return DGNN_ERR_SHAPE;
     }
 }
@@ -321,14 +352,20 @@ extern "C" int dgnn_weight_grad_batch(int32_t count, const dgnn_weight_grad_item
     if (ws_bytes < need) return DGNN_ERR_CAPACITY;
     hipStream_t s = (hipStream_t)stream;
     float *partial = static_cast<float *>(ws);
-    for (int done = 0; done < count; done += kMaxBatch) {
-        const int m = std::min(count - done, kMaxBatch);
+    for (int done = 0; done < count;) {
+        // items that follow each other with one dw are one sum; gradients of their own go together up to the next such run
+        auto same = [&](int k) { return k + 1 < count && items[k].dw == items[k + 1].dw; };
+        const bool sum = same(done), goes_on = done > 0 && items[done - 1].dw == items[done].dw;     // (a run longer than a launch)
+        int m = 1;
+        while ((sum || !goes_on) && m < kMaxBatch && done + m < count && (sum ? same(done + m - 1) : !same(done + m))) ++m;
         Batch b;
         for (int k = 0; k < m; ++k) b.item[k] = Item{items[done + k].x, items[done + k].g, items[done + k].z, items[done + k].dw};
-        const int acc = accumulate ? 1 : 0;
-        const int rc = dt == DGNN_BF16 ? (masked ? wgrad_in<true, true>(f_in, f_out, m, b, n, acc, partial, s) : wgrad_in<true, false>(f_in, f_out, m, b, n, acc, partial, s))
-                                       : (masked ? wgrad_in<false, true>(f_in, f_out, m, b, n, acc, partial, s) : wgrad_in<false, false>(f_in, f_out, m, b, n, acc, partial, s));
+        const int gradients = sum ? 1 : m, each = sum ? m : 1;
+        const int acc = accumulate || goes_on ? 1 : 0;
+        const int rc = dt == DGNN_BF16 ? (masked ? wgrad_in<true, true>(f_in, f_out, gradients, each, b, n, acc, partial, s) : wgrad_in<true, false>(f_in, f_out, gradients, each, b, n, acc, partial, s))
+                                       : (masked ? wgrad_in<false, true>(f_in, f_out, gradients, each, b, n, acc, partial, s) : wgrad_in<false, false>(f_in, f_out, gradients, each, b, n, acc, partial, s));
         if (rc != DGNN_OK) return rc;
+        done += m;
     }
     return DGNN_OK;
 }

@@ -231,3 +231,30 @@ def test_mproduct_adjoint_that_masks_on_the_way_out(dtype, w, T, t0, after, n, f
     dg.relu_backward(g_z.view(-1, f), z.view(-1, f), want.view(-1, f), row_scale=dinv.view(-1))
     dg.binding.mproduct_relu_backward_block(g[:T], z, dinv, got, w, t0, g_after=tail)
     assert torch.equal(got, want)
+
+
+# runs of items with one dw: apart (partial results of their own), as one line of steps, longer than a launch, with others around
+@pytest.mark.parametrize("dtype,f_in,f_out", [(torch.float32, 32, 64), (torch.bfloat16, 128, 128)])
+@pytest.mark.parametrize("into,n", [((0, 0, 0), 1), ((0, 0, 0, 0, 0), 333), ((0,) * 33 + (1, 2, 2), 17), ((0, 1, 1, 2), 333), ((0, 0, 0, 0, 0), 20_003)])
+def test_weight_grad_of_items_with_one_dw(dtype, f_in, f_out, into, n):
+    """Items that follow each other with the same dw are summed into it: where their partial results all fit, bit for bit as a
+    call per item."""
+    from paper_2109_07893_amd import binding as B
+    from paper_2109_07893_amd.batch import WeightGradTable, pointers
+    m = len(into)
+    x, g = randn((m, n, f_in), n + m, dtype).to(DEV), randn((m, n, f_out), n + m + 1, dtype).to(DEV)
+    ws = torch.empty(dg.weight_grad_workspace(f_in, f_out), dtype=torch.uint8, device=DEV)
+    start = torch.randn((max(into) + 1, f_in, f_out), device=DEV)
+    table = WeightGradTable(m)
+    for accumulate in (False, True):
+        dw, want, single = start.clone(), start.double() * accumulate, start.clone()
+        for k, column in ((table.X, pointers(list(x))), (table.G, pointers(list(g))), (table.DW, [dw[k].data_ptr() for k in into])):
+            table.column(k, column)
+        B.weight_grad_batch(m, table.at(), n, f_in, f_out, accumulate, B._dtype_code(x), ws, torch.cuda.current_stream().cuda_stream)
+        for j, k in enumerate(into):
+            want[k] += x[j].double().t() @ g[j].double()
+            dg.weight_grad(x[j], g[j], single[k], ws, accumulate=accumulate or (j > 0 and into[j - 1] == k))
+        torch.cuda.synchronize()
+        assert_close(to_f64(dw), want.cpu().numpy(), torch.float32, f"{into} n={n}")
+        if n < 1000:
+            assert torch.equal(dw, single)
