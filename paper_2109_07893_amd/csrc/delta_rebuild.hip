@@ -279,15 +279,29 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
     if (r1 == n && tid == 0) rowptr_next[n] = rowptr_prev[n] + n_add - n_del;
 }
 
-// First position in the ascending LDS array a[lo, hi) whose value is >= key (STRICT = false) or > key.
-template <bool STRICT>
-__device__ __forceinline__ int lds_bound(const int *a, int lo, int hi, int key) {
-    while (lo < hi) {
-        const int mid = lo + ((hi - lo) >> 1);
-        const bool left = STRICT ? a[mid] <= key : a[mid] < key;
-        if (left) lo = mid + 1; else hi = mid;
-    }
-    return lo;
+// For K stretches [pos, hi) of an ascending LDS array at once (hi >= pos): moves pos to the first element >= key.  Element p of the
+// array is a[p + 1]; a[0] is only read.  All searches advance in lock step, five trips to the LDS where no stretch of the
+// wavefront is longer than 31 elements.
+template <int K>
+__device__ __forceinline__ void lds_bound(const int *a, int (&pos)[K], const int (&hi)[K], const int (&key)[K]) {
+    auto round = [&](int step) {
+        int to[K], v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            to[k] = min(pos[k] + step, hi[k]);
+            v[k] = a[to[k]];                     // the element before it; where nothing is left, the move is none
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) pos[k] = v[k] < key[k] ? to[k] : pos[k];
+    };
+    bool far = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) far |= hi[k] - pos[k] > 31;
+    if (__ballot(far))
+#pragma unroll 1
+        for (int step = kSub; step >= 32; step >>= 1) round(step);
+#pragma unroll
+    for (int step = 16; step > 0; step >>= 1) round(step);
 }
 
 // One wavefront streams a contiguous range of old entries in sub-tiles of kSub entries.
@@ -308,6 +322,10 @@ __device__ __forceinline__ int lds_bound(const int *a, int lo, int hi, int key) 
 //     at the start of the range and simply advances by what each sub-tile wrote.
 // Lane l owns entries l, l + 64, ... of the sub-tile, so loads and stores coalesce; the column
 // indices of the next sub-tile are fetched while this one is placed.
+// What bounds it is the instructions beside these two streams, so the accesses go through buffer descriptors: no branch and no
+// 64-bit address per access, and what lies outside is 0 or dropped; the loads in flight can then be counted, so that a sub-tile waits
+// for its own and not for the last one's stores.  us per call against a branch per access and a search per list: R-MAT 2^18 x 16 entries
+// 18.4 -> 14.7, 2^20 49 -> 38, 2^23 290 -> 269 (4.1 TB/s), 2^19 with values and updates 80 -> 70.
 // VALUES: every stored entry carries a value, which travels with its column index (same position); added
 // entries bring theirs.  UPDATES (with VALUES): a third list, sorted like the other two, names surviving entries
 // that get a new value; it is consumed through a cursor of its own, each entry finds its old entry in the staged
@@ -321,16 +339,17 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
     int32_t *__restrict__ colidx_next, int cap_next,
     const float *__restrict__ val_prev, const float *__restrict__ add_val, float *__restrict__ val_next,
     const int32_t *__restrict__ upd_row, const int32_t *__restrict__ upd_col, const float *__restrict__ upd_val, int n_upd) {
-    constexpr int kWindow = 2 * kWave + 1;  // row pointers fetched ahead for every sub-tile; more are fetched when rows are short
+    constexpr int kWindow = 2 * kWave;      // row pointers fetched ahead for every sub-tile; more are fetched when rows are short
     constexpr int kMaxWindow = kSub + kWave;
-    __shared__ int s_col[kSub];
-    __shared__ int s_mark[kSub + kWave];    // bit 0: deleted; bit 1: new value in s_newval; bits 2..: added entries that go right before this slot
+    constexpr unsigned kDropped = 0x80000000u;   // an offset that no buffer here reaches
+    __shared__ int s_col[1 + kSub];              // from s_col[1] on
+    __shared__ __align__(16) int s_mark[kSub + kWave];   // bit 0: deleted; bit 1: new value in s_newval; bits 2..: added entries that go right before this slot
     // Until the prefix sums are taken: s_rows[k] = rowptr_prev[first_row + k], the rows that meet the sub-tile.
-    // From then on: s_start[p] = outputs (kept + added) that precede slot p's block.
-    __shared__ int s_shared[kMaxWindow];
+    // From then on: s_start[p] / 4 = outputs (kept + added) that precede slot p's block; its low bits are the mark's of entry p - 1.
+    __shared__ __align__(16) int s_shared[kMaxWindow + 4];
     __shared__ float s_newval[UPDATES ? kSub : 1];
     int *const s_rows = s_shared;
-    int *const s_start = s_shared;
+    int *const s_start = s_shared + 3;           // (16-byte alignment from s_start[1] on)
     static_assert(kMaxWindow >= kWindow + kWave, "the window must be able to grow");
 
     const int lane = threadIdx.x;
@@ -338,33 +357,38 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
     const int e_end = (int)min((int64_t)e_begin + range_len, (int64_t)nnz_prev);
     constexpr int kNone = 0x7fffffff;    // a pointer "beyond everything"
 
+    // the range's column indices and values
+    const __amdgpu_buffer_rsrc_t col_in = buffer_of(colidx_prev + e_begin, e_end - e_begin);
+    const __amdgpu_buffer_rsrc_t val_in = buffer_of(VALUES ? val_prev + e_begin : nullptr, VALUES ? e_end - e_begin : 0);
+    auto word = [](__amdgpu_buffer_rsrc_t from, int at) { return (int)__builtin_amdgcn_raw_buffer_load_b32(from, at * 4, 0, 0); };
     int c_next[kPerLane];
     float v_next[VALUES ? kPerLane : 1];
+    auto fetch_entries = [&](int e) {
 #pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-        const int i = e_begin + lane + j * kWave;
-        c_next[j] = i < e_end ? colidx_prev[i] : 0;
-        if (VALUES) v_next[j] = i < e_end ? val_prev[i] : 0.0f;
-    }
+        for (int j = 0; j < kPerLane; ++j) {
+            c_next[j] = word(col_in, e - e_begin + lane + j * kWave);
+            if (VALUES) v_next[j] = __int_as_float(word(val_in, e - e_begin + lane + j * kWave));
+        }
+    };
+    fetch_entries(e_begin);
 
     // ---- start of the range: its row, the list cursors, the first output position
     int a_cur, d_cur;   // first added / deleted entry not yet placed
     int u_cur = 0;      // first value update not yet looked at
     int base;           // output position of the next entry to be written
     int first_row;      // the row that holds the sub-tile's first entry
-    // the pointers of rows first_row + lane, first_row + 64 + lane and (lane 0) first_row + 128, for the next sub-tile
-    int w0 = kNone, w1 = kNone, w2 = kNone;
+    // the pointers of rows first_row + lane and first_row + 64 + lane, for the next sub-tile (behind the last row: the number of entries)
+    int w0, w1;
     auto fetch_window = [&](int row) {
-        w0 = row + lane <= n ? rowptr_prev[row + lane] : kNone;
-        w1 = row + kWave + lane <= n ? rowptr_prev[row + kWave + lane] : kNone;
-        w2 = (lane == 0 && row + 2 * kWave <= n) ? rowptr_prev[row + 2 * kWave] : kNone;
+        w0 = rowptr_prev[row + min(lane, n - row)];
+        w1 = rowptr_prev[row + min(kWave + lane, n - row)];
     };
     {
         const RangeStart st = range_start[blockIdx.x];                     // the row that holds entry e_begin
         const int c_at = colidx_prev[e_begin], c_before = colidx_prev[max(e_begin - 1, 0)];
         const int rp = st.rp, rp1 = st.rp1, rn = st.rn, rn1 = st.rn1, as = st.as, ae = st.ae;
         const int ds = rp + as - rn, de = rp1 + ae - rn1;
-        first_row = min(max(st.row, 0), n - 1);
+        first_row = uniform(min(max(st.row, 0), n - 1));
         fetch_window(first_row);
         a_cur = as;
         d_cur = ds;
@@ -386,45 +410,37 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
             d_cur += below[1];
             if constexpr (UPDATES) u_cur += below[2];
         }
-        if (UPDATES) u_cur = min(max(u_cur, 0), n_upd);
-        a_cur = min(max(a_cur, 0), n_add);
-        d_cur = min(max(d_cur, 0), n_del);
-        base = rn + (e_begin - rp) - (d_cur - ds) + (a_cur - as);
+        if (UPDATES) u_cur = uniform(min(max(u_cur, 0), n_upd));
+        a_cur = uniform(min(max(a_cur, 0), n_add));
+        d_cur = uniform(min(max(d_cur, 0), n_del));
+        base = uniform(rn + (e_begin - rp) - (d_cur - ds) + (a_cur - as));
     }
-    // The 64 list entries at each cursor (row, column) are held in registers ahead of use.  A sub-tile consumes only
-    // some of them: the rest slide down to lane 0 and only the freed lanes load, without anyone waiting for those
-    // loads before the next sub-tile needs them.  An entry that does not exist has row kNone.
+    // The 64 list entries at each cursor (row, column) are fetched ahead of use, for every sub-tile anew: it consumes only some of
+    // them, but the others are in the caches, and sliding them down costs more.  An entry that does not exist reads as 0.
     constexpr int kVmcntZero = 0x0F70;   // s_waitcnt operand: every vector memory load has returned, other counters untouched
-    int pa_row = kNone, pa_col = 0, pd_row = kNone, pd_col = 0;
-    auto load_entry = [&](const int32_t *__restrict__ rows, const int32_t *__restrict__ cols, int len, int j, bool want, int &r, int &c) {
-        if (want && j < len) {
-            r = rows[j];
-            c = cols[j];
-        }
+    auto at_cursor = [&](const void *list, int len, int cur) {
+        const bool some = cur < len;
+        return word(buffer_of(some ? (const int32_t *)list + cur : nullptr, some ? min(len - cur, kWave) : 0), lane);
     };
-    // registers hold the entries from (cur - got) on; afterwards from cur on
-    auto slide = [&](const int32_t *__restrict__ rows, const int32_t *__restrict__ cols, int len, int cur, int got, int &r, int &c) {
-        const int src = lane + got;
-        const int r2 = __shfl(r, src & (kWave - 1), kWave);
-        const int c2 = __shfl(c, src & (kWave - 1), kWave);
-        const bool fresh = src >= kWave;
-        c = c2;
-        r = fresh ? kNone : r2;
-        load_entry(rows, cols, len, cur + lane, fresh, r, c);
+    int pa_row, pa_col, pd_row, pd_col, pu_row = 0, pu_col = 0;
+    float pa_val = 0.0f, pu_val = 0.0f;
+    auto load_added = [&] {
+        pa_row = at_cursor(add_row, n_add, a_cur);
+        pa_col = at_cursor(add_col, n_add, a_cur);
+        if (VALUES) pa_val = __int_as_float(at_cursor(add_val, n_add, a_cur));
     };
-    load_entry(add_row, add_col, n_add, a_cur + lane, true, pa_row, pa_col);
-    load_entry(del_row, del_col, n_del, d_cur + lane, true, pd_row, pd_col);
-    // ... and the same for the value updates, each with its value
-    int pu_row = kNone, pu_col = 0;
-    float pu_val = 0.0f;
-    auto load_update = [&](int j, bool want) {
-        if (want && j < n_upd) {
-            pu_row = upd_row[j];
-            pu_col = upd_col[j];
-            pu_val = upd_val[j];
-        }
+    auto load_deleted = [&] {
+        pd_row = at_cursor(del_row, n_del, d_cur);
+        pd_col = at_cursor(del_col, n_del, d_cur);
     };
-    if (UPDATES) load_update(u_cur + lane, true);
+    auto load_updates = [&] {
+        pu_row = at_cursor(upd_row, n_upd, u_cur);
+        pu_col = at_cursor(upd_col, n_upd, u_cur);
+        pu_val = __int_as_float(at_cursor(upd_val, n_upd, u_cur));
+    };
+    load_added();
+    load_deleted();
+    if (UPDATES) load_updates();
 
     for (int e = e_begin; e < e_end; e += kSub) {
         const int e_stop = min(e + kSub, e_end);
@@ -435,40 +451,35 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         for (int j = 0; j < kPerLane; ++j) {
             c_[j] = c_next[j];
             if (VALUES) v_[j] = v_next[j];
-            s_col[lane + j * kWave] = c_[j];
+            s_col[1 + lane + j * kWave] = c_[j];
             s_mark[lane + j * kWave] = 0;
         }
         s_mark[kSub + lane] = 0;
+        if (cnt < kSub) {                            // behind the last entry nothing is kept
+            wave_lds_sync();
+            for (int p = cnt + lane; p < kSub; p += kWave) s_mark[p] = 1;
+        }
         // ---- the rows that meet the sub-tile: their pointers go to LDS; `below` counts the staged pointers that are
         // <= e_stop, so the row that holds entry e_stop (the next sub-tile's first) is first_row + below - 1
         s_rows[lane] = w0;
         s_rows[kWave + lane] = w1;
-        if (lane == 0) s_rows[2 * kWave] = w2;
         int n_win = kWindow;
-        int last = __shfl(w2, 0, kWave);
-        int below = __popcll(__ballot(w0 <= e_stop)) + __popcll(__ballot(w1 <= e_stop)) + (last <= e_stop ? 1 : 0);
+        int last = __builtin_amdgcn_readlane(w1, kWave - 1);
+        int below = __popcll(__ballot(w0 <= e_stop)) + __popcll(__ballot(w1 <= e_stop));
 #pragma unroll 1
         while (last < e_stop && n_win + kWave <= kMaxWindow) {      // short rows: the sub-tile reaches beyond the window
-            const int idx = first_row + n_win + lane;
-            const int v = idx <= n ? rowptr_prev[idx] : kNone;
+            const int v = rowptr_prev[first_row + min(n_win + lane, n - first_row)];
             s_rows[n_win + lane] = v;
             below += __popcll(__ballot(v <= e_stop));
-            last = __shfl(v, kWave - 1, kWave);
+            last = __builtin_amdgcn_readlane(v, kWave - 1);
             n_win += kWave;
         }
         const int row0 = first_row;                  // the window staged now starts here
         first_row = min(first_row + max(below, 1) - 1, n - 1);
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {      // fetched while this sub-tile is placed
-            const int i = e_stop + lane + j * kWave;
-            c_next[j] = i < e_end ? colidx_prev[i] : 0;
-            if (VALUES) v_next[j] = i < e_end ? val_prev[i] : 0.0f;
-        }
-        if (e_stop < e_end) fetch_window(first_row);
-        // the values of the (at most 64) added entries placed first in this sub-tile, fetched ahead of their use
-        float av_first = 0.0f;
-        if (VALUES && n_add > 0) av_first = add_val[min(a_cur + lane, n_add - 1)];
-        __syncthreads();
+        // fetched while this sub-tile is placed; behind the range's last one too, so that the loads in flight can be counted
+        fetch_entries(e_stop);
+        fetch_window(first_row);
+        wave_lds_sync();
 
         // where a list entry's row lies in A_prev, from the staged pointers: rows outside the window do not meet the sub-tile
         auto extent = [&](int row, int &lo, int &hi) {
@@ -479,145 +490,146 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
                 hi = s_rows[k + 1];
             }
         };
-        // ---- deleted entries: mark the old entry dead.  The first 64 are in registers already; a sub-tile
-        // with more than that is rare and pays for its loads on the spot.
-        auto strike = [&](int j) {
-            bool owned = false;
-            int r_lo, r_hi;
-            extent(pd_row, r_lo, r_hi);
-            if (j < n_del && r_lo < e_stop && r_hi > e) {      // its row has entries in this sub-tile
-                const int lo = max(r_lo - e, 0), hi = min(r_hi - e, cnt);
-                const int p = lds_bound<false>(s_col, lo, hi, pd_col);
-                owned = p < hi && s_col[p] == pd_col;
-                if (owned) atomicOr(&s_mark[p], 1);
-            }
+        // the stretch of the sub-tile in which the entry of a row is looked for, if the row has entries here
+        auto stretch = [&](bool exists, int row, int &r_lo, int &r_hi, int &lo, int &hi) {
+            extent(row, r_lo, r_hi);
+            const bool here = exists && r_lo < e_stop && r_hi > e;
+            lo = here ? max(r_lo - e, 0) : 0;
+            hi = here ? min(r_hi - e, cnt) : 0;
+            return here;
+        };
+        // ---- of the first 64 entries of every list, which are in registers: where they belong.  A sub-tile with more than that
+        // of one list is rare and pays for its loads on the spot.
+        constexpr int kSearches = UPDATES ? 3 : 2;
+        int r_lo[kSearches], r_hi[kSearches], at[kSearches], hi[kSearches], key[kSearches];
+        bool here[kSearches];
+        const int a_tile = a_cur;
+        here[0] = stretch(d_cur + lane < n_del, pd_row, r_lo[0], r_hi[0], at[0], hi[0]);
+        here[1] = stretch(a_cur + lane < n_add, pa_row, r_lo[1], r_hi[1], at[1], hi[1]);
+        key[0] = pd_col;
+        key[1] = pa_col + 1;                         // behind an equal one
+        if constexpr (UPDATES) {
+            here[2] = stretch(u_cur + lane < n_upd, pu_row, r_lo[2], r_hi[2], at[2], hi[2]);
+            key[2] = pu_col;
+        }
+        lds_bound<kSearches>(s_col, at, hi, key);
+
+        // ---- deleted entries: mark the old entry dead
+        auto strike = [&](bool here, int p, int hi) {
+            const bool owned = here && p < hi && s_col[1 + p] == pd_col;
+            if (owned) atomicOr(&s_mark[p], 1);
             return __popcll(__ballot(owned));
         };
-        int d_got = strike(d_cur + lane);
+        auto search_one = [&](int lo, int hi, int key) {
+            int p[1] = {lo}, h[1] = {hi}, k[1] = {key};
+            lds_bound<1>(s_col, p, h, k);
+            return p[0];
+        };
+        int d_got = strike(here[0], at[0], hi[0]);
 #pragma unroll 1
         while (d_got == kWave) {
             d_cur += kWave;
-            pd_row = kNone;
-            load_entry(del_row, del_col, n_del, d_cur + lane, true, pd_row, pd_col);
+            load_deleted();
             __builtin_amdgcn_s_waitcnt(kVmcntZero);
-            d_got = strike(d_cur + lane);
+            int r0, r1, lo, h;
+            const bool in = stretch(d_cur + lane < n_del, pd_row, r0, r1, lo, h);
+            d_got = strike(in, search_one(lo, h, pd_col), h);
         }
         d_cur += d_got;
         // ---- value updates: leave the new value at the old entry.  An entry is done with once its place in A_prev's
         // order lies before the end of this sub-tile, whether something is stored there or not.
-        if (UPDATES) {
-            auto touch = [&](int j) {
-                bool done = false;
-                int r_lo, r_hi;
-                extent(pu_row, r_lo, r_hi);
-                if (j < n_upd && pu_row < row0) done = true;      // a row before the sub-tile's first: nothing left to find
-                else if (j < n_upd && r_lo < e_stop) {
-                    const int lo = max(r_lo - e, 0), hi = min(r_hi - e, cnt);
-                    const int p = lo < hi ? lds_bound<false>(s_col, lo, hi, pu_col) : hi;
-                    if (p < hi) {
-                        done = true;
-                        if (s_col[p] == pu_col) {
-                            s_newval[p] = pu_val;
-                            atomicOr(&s_mark[p], 2);
-                        }
-                    } else {
-                        done = r_hi <= e_stop;        // beyond the sub-tile's part of an unfinished row: later
+        if constexpr (UPDATES) {
+            auto touch = [&](bool here, int r_lo, int r_hi, int p, int hi) {
+                const bool exists = u_cur + lane < n_upd;
+                bool done = exists && pu_row < row0;              // a row before the sub-tile's first: nothing left to find
+                if (here && p < hi) {
+                    done = true;
+                    if (s_col[1 + p] == pu_col) {
+                        s_newval[p] = pu_val;
+                        atomicOr(&s_mark[p], 2);
                     }
+                } else if (exists && r_lo < e_stop) {
+                    done |= r_hi <= e_stop;                       // beyond the sub-tile's part of an unfinished row: later
                 }
                 return __popcll(__ballot(done));
             };
-            int u_got = touch(u_cur + lane);
+            int u_got = touch(here[2], r_lo[2], r_hi[2], at[2], hi[2]);
 #pragma unroll 1
             while (u_got == kWave) {
                 u_cur += kWave;
-                pu_row = kNone;
-                load_update(u_cur + lane, true);
+                load_updates();
                 __builtin_amdgcn_s_waitcnt(kVmcntZero);
-                u_got = touch(u_cur + lane);
+                int r0, r1, lo, h;
+                const bool in = stretch(u_cur + lane < n_upd, pu_row, r0, r1, lo, h);
+                u_got = touch(in, r0, r1, search_one(lo, h, pu_col), h);
             }
             u_cur += u_got;
-            const int src = lane + u_got;       // the entries at the new cursor, for the next sub-tile
-            const int r2 = __shfl(pu_row, src & (kWave - 1), kWave);
-            const int c2 = __shfl(pu_col, src & (kWave - 1), kWave);
-            const float v2 = __shfl(pu_val, src & (kWave - 1), kWave);
-            const bool fresh = src >= kWave;
-            pu_col = c2;
-            pu_val = v2;
-            pu_row = fresh ? kNone : r2;
-            load_update(u_cur + lane, fresh);
         }
         // ---- added entries: count at the slot (old entry they precede; a row's end if none)
-        const int a_tile = a_cur;
-        auto slot = [&](int j, int &q) {
-            bool owned = false;
-            int r_lo, r_hi;
-            extent(pa_row, r_lo, r_hi);
-            q = -2 - lane;
-            if (j < n_add && r_lo < e_stop && r_hi > e) {
-                const int lo = max(r_lo - e, 0), hi = min(r_hi - e, cnt);
-                q = lds_bound<true>(s_col, lo, hi, pa_col);
-                owned = q < hi || r_hi <= e_stop;         // beyond the sub-tile's part of an unfinished row: later
-                if (owned) atomicAdd(&s_mark[q], 4);
-            }
-            if (!owned) q = -2 - lane;
+        auto slot = [&](bool here, int r_hi, int &q, int hi) {
+            const bool owned = here && (q < hi || r_hi <= e_stop);        // beyond the sub-tile's part of an unfinished row: later
+            if (owned) atomicAdd(&s_mark[q], 4); else q = -2 - lane;
             return __popcll(__ballot(owned));
         };
-        int q_first;                              // slot and column of the first 64, kept for the write below
+        int q_first = at[1];                      // slot, column and value of the first 64, kept for the write below
         const int c_first = pa_col;
-        int a_got = slot(a_cur + lane, q_first);
+        const float av_first = pa_val;
+        int a_got = slot(here[1], r_hi[1], q_first, hi[1]);
 #pragma unroll 1
         while (a_got == kWave) {
             a_cur += kWave;
-            pa_row = kNone;
-            load_entry(add_row, add_col, n_add, a_cur + lane, true, pa_row, pa_col);
+            load_added();
             __builtin_amdgcn_s_waitcnt(kVmcntZero);
-            int q_unused;
-            a_got = slot(a_cur + lane, q_unused);
+            int r0, r1, lo, h;
+            const bool in = stretch(a_cur + lane < n_add, pa_row, r0, r1, lo, h);
+            int q = search_one(lo, h, pa_col + 1);
+            a_got = slot(in, r1, q, h);
         }
         a_cur += a_got;
         // the list entries at the new cursors, for the next sub-tile
-        slide(del_row, del_col, n_del, d_cur, d_got, pd_row, pd_col);
-        slide(add_row, add_col, n_add, a_cur, a_got, pa_row, pa_col);
-        __syncthreads();
+        load_added();
+        load_deleted();
+        if (UPDATES) load_updates();
+        wave_lds_sync();
 
         // ---- prefix sums: s_start[p] = kept entries before p + added entries of slots before p (the staged row
         // pointers are not needed any more; their place is taken)
         int written;
         {
-            int mk[kPerLane];
-            int alive = 0, ins = 0;
+            int mk[kPerLane], sum = 0;
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j) {
-                const int p = lane * kPerLane + j;
-                mk[j] = s_mark[p];
-                alive += (p < cnt && !(mk[j] & 1)) ? 1 : 0;
-                ins += mk[j] >> 2;
+                mk[j] = s_mark[lane * kPerLane + j];
+                sum += (mk[j] >> 2) + (~mk[j] & 1);
             }
-            const int inc_alive = wave_scan_add(alive, lane), inc_ins = wave_scan_add(ins, lane);
-            int run = (inc_alive - alive) + (inc_ins - ins);
+            const int inc = wave_scan_add(sum, lane);
+            int run = inc - sum;
+            if (lane == 0) s_start[0] = 0;
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j) {
-                const int p = lane * kPerLane + j;
-                s_start[p] = run;
-                run += ((p < cnt && !(mk[j] & 1)) ? 1 : 0) + (mk[j] >> 2);
+                run += (mk[j] >> 2) + (~mk[j] & 1);
+                s_start[lane * kPerLane + j + 1] = (run << 2) | (mk[j] & 3);
             }
-            if (lane == kWave - 1) s_start[kSub] = run;   // slot "after the last entry" of a full sub-tile
-            written = __shfl(run, kWave - 1, kWave) + (s_mark[kSub] >> 2);
+            written = uniform(__builtin_amdgcn_readlane(inc, kWave - 1) + (s_mark[kSub] >> 2));
         }
-        __syncthreads();
+        wave_lds_sync();
 
+        // the entries from one before `base` on: a kept entry's place is one before what precedes the next slot
+        const int room = (unsigned)base < (unsigned)cap_next ? min(cap_next - base, (1 << 29) - 2) + 1 : 0;
+        const __amdgpu_buffer_rsrc_t col_out = buffer_of(colidx_next + (int64_t)base - 1, room);
+        const __amdgpu_buffer_rsrc_t val_out = buffer_of(VALUES ? val_next + (int64_t)base - 1 : nullptr, VALUES ? room : 0);
+        auto put = [&](unsigned offset, int c, float v) {
+            __builtin_amdgcn_raw_buffer_store_b32(c, col_out, offset, 0, 0);
+            if (VALUES) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), val_out, offset, 0, 0);
+        };
         // ---- old entries
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
             const int p = lane + j * kWave;
-            if (p < cnt) {
-                const int mk = s_mark[p];
-                const unsigned pos = (unsigned)(base + s_start[p] + (mk >> 2));
-                if (!(mk & 1) && pos < (unsigned)cap_next) {
-                    colidx_next[pos] = c_[j];
-                    if (VALUES) val_next[pos] = (UPDATES && (mk & 2)) ? s_newval[p] : v_[j];
-                }
-            }
+            const unsigned s = (unsigned)s_start[p + 1];
+            float v = VALUES ? v_[j] : 0.0f;
+            if (UPDATES) v = (s & 2u) ? s_newval[p] : v;
+            put((s & ~3u) | (s << 31), c_[j], v);              // the deleted ones are dropped
         }
         // ---- added entries: their slot, then the rank among the adds of the same slot (they are consecutive).
         // The first 64 kept their slot and column from the search above; more than 64 per sub-tile are rare.
@@ -630,13 +642,7 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
             const int run_start = 63 - __clzll(upto);
             int rank = lane - run_start;
             if (run_start == 0 && !(true_heads & 1ull)) rank += rank_carry;   // run continues from the previous 64
-            if (j < a_cur) {
-                const unsigned pos = (unsigned)(base + s_start[q] + rank);
-                if (pos < (unsigned)cap_next) {
-                    colidx_next[pos] = c;
-                    if (VALUES) val_next[pos] = v;
-                }
-            }
+            put(j < a_cur ? ((unsigned)s_start[max(q, 0)] & ~3u) + 4u * (unsigned)(rank + 1) : kDropped, c, v);
             q_carry = __shfl(q, kWave - 1, kWave);
             rank_carry = __shfl(rank, kWave - 1, kWave) + 1;
         };
@@ -646,21 +652,24 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
             // these search again; the extent of an entry's row comes from the row pointers themselves, two loads that
             // depend on the entry's, which a sub-tile this full can afford
             const int j = j0 + lane;
-            int q = -2 - lane, c = 0;
+            int lo = 0, h = 0, c = 0;
             float v = 0.0f;
+            bool there = false;
             if (j < a_cur) {
                 const int r = add_row[j];
                 c = add_col[j];
                 if (VALUES) v = add_val[j];
                 if ((unsigned)r < (unsigned)n) {
-                    const int hi = min(rowptr_prev[r + 1] - e, cnt), lo = min(max(rowptr_prev[r] - e, 0), max(hi, 0));
-                    q = lds_bound<true>(s_col, lo, hi, c);
+                    there = true;
+                    h = max(min(rowptr_prev[r + 1] - e, cnt), 0);
+                    lo = min(max(rowptr_prev[r] - e, 0), h);
                 }
             }
-            place(j, q, c, v);
+            const int q = search_one(lo, h, c + 1);
+            place(j, there ? q : -2 - lane, c, v);
         }
         base += written;
-        __syncthreads();           // LDS is rewritten by the next sub-tile
+        wave_lds_sync();           // LDS is rewritten by the next sub-tile
     }
 }
 
