@@ -15,8 +15,10 @@
 // dL/dh_{t-1}, which stays on chip for the next step, and dL/dY1 under the ReLU's mask; da leaves for the weight gradients,
 // which contract over vertices and timesteps and are one product afterwards.
 //
-// fp32 is bound by the fp32 matrix cores (and the cell's exponentials, which share their issue slots), bf16 by the cell (and, up
-// to 64 columns of Y, the tile staging); what the series saves is the traffic and the launches of the state: h and c in, c out, dh and dc both ways.
+// fp32 products are formed on the bf16 matrix cores (below): 262 144 vertices, 4 steps, 64 + 32 columns, forward 292 -> 200 us, back
+// 503 -> 405, against the fp32 matrix instruction, which alone takes 164 and 328 of these.  What is left in fp32 is the cell
+// (exponentials) and the vector instructions of the parts, at two wavefronts per SIMD, and the traffic: 0.8 and 1.3 GB.  bf16 is
+// bound by the cell (and, up to 64 columns of Y, the tile staging); what the series saves is the traffic and the launches of the state: h and c in, c out, dh and dc both ways.
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>
@@ -45,6 +47,7 @@ template <> struct Store<false> {
     static __device__ __forceinline__ floatx4 load4(const float *p) { return *reinterpret_cast<const floatx4 *>(p); }
     static __device__ __forceinline__ void store4(float *p, floatx4 v) { *reinterpret_cast<floatx4 *>(p) = v; }
     static __device__ __forceinline__ floatx4 rounded(floatx4 v) { return v; }
+    static __device__ __forceinline__ float product(float v) { return -v; }          // of what the products below leave
 };
 template <> struct Store<true> {
     typedef uint16_t Elem;
@@ -57,28 +60,116 @@ template <> struct Store<true> {
     static __device__ __forceinline__ void store4(uint16_t *p, floatx4 v) {
         *reinterpret_cast<uint2 *>(p) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
     }
+    static __device__ __forceinline__ float product(float v) { return v; }
     static __device__ __forceinline__ floatx4 rounded(floatx4 v) {
         const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
         return floatx4{__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
     }
 };
 
-// [W_x ; W_h] in LDS.  fp32: row k of W is kLd floats, the values of one column-in-tile of all tiles side by side, so that one
-// LDS read brings a k-step's operand for every gate tile; rows are padded so that the adjoint, which reads the same column of
-// 32 rows, finds them in different banks.  bf16: W^T with k contiguous.
+// ---- fp32 products on the bf16 matrix cores.  An fp32 number is the sum of three bf16 numbers, each the rounded rest of the
+// ones before it (8 + 8 + 8 bits), and of the nine products of two such sums the six largest are formed, 2.6 times as fast as the fp32 matrix
+// instruction forms the one; what is left out is below 2^-25 of the product, less than the rounding of one of the sums' additions.
+// Numbers beyond kSplitMost, whose first part would be infinite, and infinities, whose rest would not be a number, send the
+// wavefront's step to the fp32 instruction.
+constexpr int kParts = 3;
+constexpr uint32_t kSplitMost = 0x7f7f7fffu;           // the largest fp32 that rounds to a finite bf16
+
+// Whether all numbers noted can be split: the largest pattern of either sign (half an instruction each per number).
+struct Largest {
+    int above = 0;
+    uint32_t below = 0;
+    __device__ __forceinline__ void note(uint32_t bits) {
+        above = max(above, (int)bits);
+        below = max(below, bits);
+    }
+    __device__ __forceinline__ bool odd() const { return above > (int)kSplitMost || below > (kSplitMost | 0x80000000u); }
+};
+
+__device__ __forceinline__ void split(const float (&v)[8], bf16x8 (&part)[kParts]) {
+    float rest[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) rest[e] = v[e];
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) {
+        uintx4 p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            p[e] = pack_bf16(rest[2 * e], rest[2 * e + 1]);
+            if (k + 1 < kParts) {
+                rest[2 * e] -= __uint_as_float(p[e] << 16);
+                rest[2 * e + 1] -= __uint_as_float(p[e] & 0xffff0000u);
+            }
+        }
+        part[k] = __builtin_bit_cast(bf16x8, p);
+    }
+}
+
+// Two passes over the contraction: first the five smaller products of every step, then the largest, (part of a, part of b) in turn.
+// The matrix cores cut what they add towards minus infinity, a few thousandths of the last place per instruction, and sums over all
+// vertices see that.  With the smaller products ahead it counts for a sixth of the instructions, and from the middle of the second pass on
+// the sum is carried with the other sign, so that the cuts of its two halves meet (the bias gradient of 40 K vertices and four steps,
+// error against 64 bits: 2.3e-7 with the fp32 instruction, 4.9e-7 with all products step by step, 2.8e-7 with them in two passes).
+// The result has the other sign.
+constexpr int kSmaller = 5;
+constexpr int kTermA[kSmaller] = {2, 0, 1, 1, 0}, kTermB[kSmaller] = {0, 2, 1, 0, 1};
+
+template <int N>
+__device__ __forceinline__ void smaller_products(floatx16 (&acc)[N], const bf16x8 (&a)[N][kParts], const bf16x8 (&b)[kParts]) {
+#pragma unroll
+    for (int k = 0; k < kSmaller; ++k)
+#pragma unroll
+        for (int g = 0; g < N; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][kTermA[k]], b[kTermB[k]], acc[g], 0, 0, 0);
+}
+
+// The operand of the second pass' step s of `steps`.
+__device__ __forceinline__ bf16x8 first_part(const float (&v)[8], int s, int steps) {
+    const uint32_t sign = s < steps / 2 ? 0u : 0x80008000u;
+    return __builtin_bit_cast(bf16x8, uintx4{pack_bf16(v[0], v[1]) ^ sign, pack_bf16(v[2], v[3]) ^ sign, pack_bf16(v[4], v[5]) ^ sign, pack_bf16(v[6], v[7]) ^ sign});
+}
+template <int N>
+__device__ __forceinline__ void turn_sign(floatx16 (&acc)[N]) {
+#pragma unroll
+    for (int g = 0; g < N; ++g)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[g][v] = -acc[g][v];
+}
+
+// [W_x ; W_h] transposed in LDS, k contiguous: in bf16 as it is, in fp32 its three parts one after the other.
 template <int FY, int HID, bool BF16>
 struct Weights {
     static constexpr int G4 = 4 * HID, NT = G4 / 32, K = FY + HID;
-    static constexpr int kLd = BF16 ? K + 8 : G4 + NT;
-    static constexpr int kSize = BF16 ? G4 * kLd : K * kLd;
+    static constexpr int kLd = K + 8, kImage = G4 * kLd, kSize = BF16 ? kImage : kParts * kImage;
     typedef typename Store<BF16>::Elem Elem;
-    static __device__ __forceinline__ void stage(Elem *s_w, const Elem *__restrict__ w_x, const Elem *__restrict__ w_h, int tid, int threads) {
+    // whether this thread has met a number that cannot be split
+    static __device__ __forceinline__ bool stage(uint16_t *s_w, const Elem *__restrict__ w_x, const Elem *__restrict__ w_h, int tid, int threads) {
+        bool odd = false;
         for (int idx = tid; idx < K * G4; idx += threads) {
             const int k = idx / G4, col = idx % G4;
             const Elem v = k < FY ? w_x[idx] : w_h[idx - FY * G4];
-            if (BF16) s_w[col * kLd + k] = v;
-            else s_w[k * kLd + (col % 32) * NT + col / 32] = v;
+            if constexpr (BF16) {
+                s_w[col * kLd + k] = v;
+            } else {
+                const uint32_t bits = __float_as_uint(v) & 0x7fffffffu;
+                const bool whole = bits >= 0x7f800000u;            // an infinity, or no number: the first part is all of it
+                odd |= bits > kSplitMost;
+                float rest = v;
+#pragma unroll
+                for (int part = 0; part < kParts; ++part) {
+                    const uint32_t p = bits > kSplitMost && !whole ? __float_as_uint(rest) >> 16 : f32_to_bf16(rest);
+                    s_w[part * kImage + col * kLd + k] = (uint16_t)p;
+                    rest = whole ? 0.0f : rest - __uint_as_float(p << 16);
+                }
+            }
         }
+        return odd;
+    }
+    // fp32: element [k][col], put together again
+    static __device__ __forceinline__ float at(const uint16_t *s_w, int k, int col) {
+        float v = 0.0f;
+#pragma unroll
+        for (int part = kParts - 1; part >= 0; --part) v += bf16_to_f32(s_w[part * kImage + col * kLd + k]);
+        return v;
     }
 };
 
@@ -91,47 +182,107 @@ template <int FY, int HID, bool BF16, bool KEEP_C> constexpr bool kDirectY = BF1
 // acc[g] = transposed tile g of [Y | h] [W_x ; W_h] for the 32 vertices in `tile` (rows of LDT elements).  In bf16 step s of the
 // contraction takes the 16 columns from 16 s on, the lane half h the second eight of them; with `y` the first FY / 16 steps'
 // operands are given, and the tile holds the columns behind them.
-template <int FY, int HID, bool BF16, int LDT>
-__device__ __forceinline__ void gate_tiles(const typename Store<BF16>::Elem *s_w, const typename Store<BF16>::Elem *tile, int i, int hh,
-                                           floatx16 (&acc)[4 * HID / 32], const uintx4 *y = nullptr) {
-    typedef Weights<FY, HID, BF16> W;
-    constexpr int KH = W::K / 2;
+template <int FY, int HID, int LDT>
+__device__ __forceinline__ void gate_tiles(const uint16_t *s_w, const uint16_t *tile, int i, int hh, floatx16 (&acc)[4 * HID / 32], const uintx4 *y = nullptr) {
+    typedef Weights<FY, HID, true> W;
+    constexpr int KS = W::K / 16;
 #pragma unroll
     for (int g = 0; g < W::NT; ++g)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[g][v] = 0.0f;
-    if constexpr (BF16) {
-        constexpr int KS = KH / 8;
-        bf16x8 a[KS];
+    bf16x8 a[KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
-            a[s] = y && s < FY / 16 ? __builtin_bit_cast(bf16x8, y[s < FY / 16 ? s : 0])
-                                    : *reinterpret_cast<const bf16x8 *>(&tile[i * LDT + 16 * s + 8 * hh - (y ? FY : 0)]);
+    for (int s = 0; s < KS; ++s)
+        a[s] = y && s < FY / 16 ? __builtin_bit_cast(bf16x8, y[s < FY / 16 ? s : 0])
+                                : *reinterpret_cast<const bf16x8 *>(&tile[i * LDT + 16 * s + 8 * hh - (y ? FY : 0)]);
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int g = 0; g < W::NT; ++g) {
-                const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(&s_w[(g * 32 + i) * W::kLd + 16 * s + 8 * hh]);
-                acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, a[s], acc[g], 0, 0, 0);
-            }
-    } else {
-        floatx4 a[KH / 4];
-#pragma unroll
-        for (int q = 0; q < KH / 4; ++q) a[q] = *reinterpret_cast<const floatx4 *>(&tile[i * LDT + hh * KH + q * 4]);
-#pragma unroll
-        for (int s = 0; s < KH; ++s) {
-            float wv[W::NT];
-#pragma unroll
-            for (int g = 0; g < W::NT; ++g) wv[g] = s_w[(hh * KH + s) * W::kLd + i * W::NT + g];      // consecutive: one read
-#pragma unroll
-            for (int g = 0; g < W::NT; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[g], a[s / 4][s % 4], acc[g], 0, 0, 0);
+        for (int g = 0; g < W::NT; ++g) {
+            const bf16x8 wv = *reinterpret_cast<const bf16x8 *>(&s_w[(g * 32 + i) * W::kLd + 16 * s + 8 * hh]);
+            acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, a[s], acc[g], 0, 0, 0);
         }
+}
+
+// Eight fp32 columns of a row of the tile buffer, from 16 s + 8 h on: a lane's operand of step s.
+__device__ __forceinline__ void operand(const float *row, int s, int hh, float (&v)[8]) {
+    const floatx4 lo = *reinterpret_cast<const floatx4 *>(&row[16 * s + 8 * hh]), hi = *reinterpret_cast<const floatx4 *>(&row[16 * s + 8 * hh + 4]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = lo[e];
+        v[4 + e] = hi[e];
     }
+}
+
+// The same in fp32, with the other sign: Y's columns lie in the tile buffer, those of h in the lanes (step by step, as operands).
+// odd: some number is not to be split.
+template <int FY, int HID, int LDT>
+__device__ __forceinline__ void gate_tiles_f32(const uint16_t *s_w, const float *tile, const float (&h)[HID / 16][8], bool odd, int i, int hh,
+                                               floatx16 (&acc)[4 * HID / 32]) {
+    typedef Weights<FY, HID, false> W;
+#pragma unroll
+    for (int g = 0; g < W::NT; ++g)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[g][v] = 0.0f;
+    if (!odd) {
+        auto weights = [&](int s, int g, int part) { return *reinterpret_cast<const bf16x8 *>(&s_w[part * W::kImage + (g * 32 + i) * W::kLd + 16 * s + 8 * hh]); };
+#pragma unroll
+        for (int s = 0; s < W::K / 16; ++s) {
+            float v[8];
+            if (s < FY / 16) operand(&tile[i * LDT], s, hh, v);
+            bf16x8 a[W::NT][kParts], b[kParts];
+#pragma unroll
+            for (int g = 0; g < W::NT; ++g)
+#pragma unroll
+                for (int part = 0; part < kParts; ++part) a[g][part] = weights(s, g, part);
+            split(s < FY / 16 ? v : h[s < FY / 16 ? 0 : s - FY / 16], b);
+            smaller_products(acc, a, b);
+            __builtin_amdgcn_sched_barrier(0);           // the operands of all steps at once would not fit the registers
+        }
+#pragma unroll
+        for (int s = 0; s < W::K / 16; ++s) {
+            float v[8];
+            if (s < FY / 16) operand(&tile[i * LDT], s, hh, v);
+            const bf16x8 b = first_part(s < FY / 16 ? v : h[s < FY / 16 ? 0 : s - FY / 16], s, W::K / 16);
+            if (s == W::K / 16 / 2) turn_sign(acc);
+#pragma unroll
+            for (int g = 0; g < W::NT; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(weights(s, g, 0), b, acc[g], 0, 0, 0);
+        }
+    } else {
+        auto product = [&](int k, float v) {             // rare: few registers rather than few trips
+#pragma unroll
+            for (int g = 0; g < W::NT; ++g) acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(W::at(s_w, k, g * 32 + i), v, acc[g], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll 1
+        for (int k = 0; k < FY / 2; ++k) {
+            const int at = 16 * (k / 8) + 8 * hh + k % 8;
+            product(at, tile[i * LDT + at]);
+        }
+#pragma unroll
+        for (int s = 0; s < HID / 16; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) product(FY + 16 * s + 8 * hh + e, h[s][e]);
+        turn_sign(acc);
+    }
+}
+
+__device__ __forceinline__ uint2 read_transposed(const uint16_t *p) {
+    typedef short shortx4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) shortx4 LdsShortx4;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsShortx4 *)p));
 }
 
 // register of gate g, state elements 8 m + 4 h + r: tile and first of four registers
 template <int HID> constexpr int gate_tile(int g, int m) { return (g * HID + 8 * m) / 32; }
 template <int HID> constexpr int gate_reg(int g, int m) { return 4 * (((g * HID + 8 * m) % 32) / 8); }
+
+// The rows of the 32 vertices of a tile in one of a step's tensors, `bytes` each, behind a buffer descriptor: what lies behind the last
+// vertex is 0 or dropped, without a mask or an address per access.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const void *step, int64_t tile, int64_t n, int bytes) {
+    const int rows = (int)max((int64_t)0, min((int64_t)32, n - tile * 32));
+    return buffer_of(static_cast<const char *>(step) + tile * 32 * bytes, rows * bytes / 4);
+}
 
 // h_1 .. h_T from h_0, c_0; KEEP_C: c_t of every step is kept (c [T][n][HID]), else c is the state after the last step
 // (and may be c_0's array: a wavefront reads its vertices before it writes them).
@@ -144,48 +295,69 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     typedef typename S::Elem Elem;
     typedef Weights<FY, HID, BF16> W;
     constexpr int P = S::kPiece;
+    // The widest step is the faster with an address and a mask per piece, all others behind buffer descriptors (bf16, 200 K vertices, 6 steps,
+    // 128 + 64 columns with c kept 285 / 309 us, without 252 / 255; 64 + 64 198.9 / 196.3)
+    constexpr bool BY_ADDRESS = BF16 && FY == 128;
     constexpr bool DIRECT = kDirectY<FY, HID, BF16, KEEP_C>;
-    constexpr int LDT = (DIRECT ? HID : W::K) + S::kTilePad;
-    constexpr int H_COL = DIRECT ? 0 : FY;             // where h lies in a row of the tile buffer
+    // the tile buffer: [Y | h], or h alone where Y's operands come straight from memory; in fp32, where W's parts take 80 KB, the lanes
+    // hold h's operands while the buffer holds Y, and it carries h (and c beside it) between the steps
+    constexpr int LDT = (!BF16 ? (KEEP_C ? 2 * HID : FY) : DIRECT ? HID : W::K) + S::kTilePad;
+    constexpr int H_COL = !BF16 ? (KEEP_C ? HID : 0) : DIRECT ? 0 : FY;
     constexpr int Y_PIECES = 32 * FY / P / kWave, S_PIECES = 32 * HID / P / kWave;     // 16-byte pieces per lane of a tile
-    static_assert(DIRECT || W::K >= 2 * HID, "the tile buffer also carries c beside h");
-    __shared__ __attribute__((aligned(16))) Elem s_w[W::kSize];
+    static_assert(DIRECT || LDT >= H_COL + HID, "the tile buffer also carries c beside h");
+    static_assert(BF16 || LDT >= FY, "... and Y");
+    __shared__ __attribute__((aligned(16))) uint16_t s_w[W::kSize];
     __shared__ __attribute__((aligned(16))) float s_bias[W::G4];
     __shared__ __attribute__((aligned(16))) Elem s_tile[WAVES][32 * LDT];
     const Elem *y = static_cast<const Elem *>(yv_), *h0 = static_cast<const Elem *>(h0_), *c0 = static_cast<const Elem *>(c0_);
     Elem *c = static_cast<Elem *>(c_), *h = static_cast<Elem *>(h_);
 
     const int tid = threadIdx.x;
-    W::stage(s_w, static_cast<const Elem *>(wx_), static_cast<const Elem *>(wh_), tid, WAVES * kWave);
+    bool odd_w = W::stage(s_w, static_cast<const Elem *>(wx_), static_cast<const Elem *>(wh_), tid, WAVES * kWave);
     for (int idx = tid; idx < W::G4; idx += WAVES * kWave) s_bias[idx] = bias ? bias[idx] : 0.0f;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lane = tid & (kWave - 1), wave = BY_ADDRESS ? tid / kWave : uniform(tid / kWave);
     const int i = lane & 31, hh = lane >> 5;
     Elem *tile_lds = s_tile[wave];
     const int64_t stride = (int64_t)gridDim.x * WAVES;
     const int64_t first = (int64_t)blockIdx.x * WAVES + wave;
-    __syncthreads();                                   // W is in LDS; from here on every wavefront is on its own
+    if (BF16) __syncthreads(); else odd_w = __syncthreads_or(odd_w);      // W is in LDS; from here on every wavefront is on its own
+    constexpr int Y_BYTES = FY * sizeof(Elem), S_BYTES = HID * sizeof(Elem);
     const uintx4 zero = {0u, 0u, 0u, 0u};
     // the rows of the next step (or of the next tile, with its state) travel while this one is multiplied
     uintx4 yv[Y_PIECES], hv[S_PIECES], cv[S_PIECES];
     auto fetch_y = [&](int64_t tile, int t) {
+        if constexpr (DIRECT) {
+            const int64_t row = tile * 32 + i;
 #pragma unroll
-        for (int q = 0; q < Y_PIECES; ++q) {
-            if (DIRECT) {
-                const int64_t row = tile * 32 + i;
-                yv[q] = row < n ? *reinterpret_cast<const uintx4 *>(y + (t * n + row) * FY + 16 * q + 8 * hh) : zero;
-                continue;
+            for (int q = 0; q < Y_PIECES; ++q) yv[q] = row < n ? *reinterpret_cast<const uintx4 *>(y + (t * n + row) * FY + 16 * q + 8 * hh) : zero;
+        } else if constexpr (BY_ADDRESS) {
+#pragma unroll
+            for (int q = 0; q < Y_PIECES; ++q) {
+                const int64_t piece = tile * (32 * FY / P) + q * kWave + lane;
+                yv[q] = (tile < n_tiles && piece * P < n * FY) ? reinterpret_cast<const uintx4 *>(y + t * n * FY)[piece] : zero;
             }
-            const int64_t piece = tile * (32 * FY / P) + q * kWave + lane;
-            yv[q] = (tile < n_tiles && piece * P < n * FY) ? reinterpret_cast<const uintx4 *>(y + t * n * FY)[piece] : zero;
+        } else {
+            const __amdgpu_buffer_rsrc_t rows = tile_rows(y + t * n * FY, tile, n, Y_BYTES);
+#pragma unroll
+            for (int q = 0; q < Y_PIECES; ++q) yv[q] = __builtin_amdgcn_raw_buffer_load_b128(rows, (q * kWave + lane) * 16, 0, 0);
         }
     };
     auto fetch_state = [&](int64_t tile) {
+        if constexpr (BY_ADDRESS) {
 #pragma unroll
-        for (int q = 0; q < S_PIECES; ++q) {
-            const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
-            const bool ok = tile < n_tiles && piece * P < n * HID;
-            hv[q] = ok ? reinterpret_cast<const uintx4 *>(h0)[piece] : zero;
-            cv[q] = ok ? reinterpret_cast<const uintx4 *>(c0)[piece] : zero;
+            for (int q = 0; q < S_PIECES; ++q) {
+                const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
+                const bool ok = tile < n_tiles && piece * P < n * HID;
+                hv[q] = ok ? reinterpret_cast<const uintx4 *>(h0)[piece] : zero;
+                cv[q] = ok ? reinterpret_cast<const uintx4 *>(c0)[piece] : zero;
+            }
+        } else {
+            const __amdgpu_buffer_rsrc_t of_h = tile_rows(h0, tile, n, S_BYTES), of_c = tile_rows(c0, tile, n, S_BYTES);
+#pragma unroll
+            for (int q = 0; q < S_PIECES; ++q) {
+                hv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_h, (q * kWave + lane) * 16, 0, 0);
+                cv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_c, (q * kWave + lane) * 16, 0, 0);
+            }
         }
     };
     auto put = [&](int col, const uintx4 (&v)[S_PIECES]) {           // a tile of HID columns: registers -> LDS
@@ -196,11 +368,20 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
         }
     };
     auto flush = [&](int col, Elem *dst, int64_t tile) {             // ... LDS -> memory, whole lines
+        if constexpr (BY_ADDRESS) {
+#pragma unroll
+            for (int q = 0; q < S_PIECES; ++q) {
+                const int e = (q * kWave + lane) * P;
+                const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
+                if (piece * P < n * HID) reinterpret_cast<uintx4 *>(dst)[piece] = *reinterpret_cast<const uintx4 *>(&tile_lds[(e / HID) * LDT + col + e % HID]);
+            }
+            return;
+        }
+        const __amdgpu_buffer_rsrc_t rows = tile_rows(dst, tile, n, S_BYTES);
 #pragma unroll
         for (int q = 0; q < S_PIECES; ++q) {
             const int e = (q * kWave + lane) * P;
-            const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
-            if (piece * P < n * HID) reinterpret_cast<uintx4 *>(dst)[piece] = *reinterpret_cast<const uintx4 *>(&tile_lds[(e / HID) * LDT + col + e % HID]);
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const uintx4 *>(&tile_lds[(e / HID) * LDT + col + e % HID]), rows, e * (int)sizeof(Elem), 0, 0);
         }
     };
     constexpr bool kStateAhead = !(BF16 && HID == 64);     // the widest step has no registers left for it
@@ -208,15 +389,15 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     if (kStateAhead) fetch_state(first);
     for (int64_t tile = first; tile < n_tiles; tile += stride) {
         if (!kStateAhead) fetch_state(tile);
-        if (!DIRECT) put(FY, hv);
+        if (BF16 && !DIRECT) put(FY, hv);
         put(0, cv);
         wave_lds_sync();
         floatx4 cell[HID / 8];                          // c of this lane's state elements
 #pragma unroll
         for (int m = 0; m < HID / 8; ++m) cell[m] = S::load4(&tile_lds[i * LDT + 8 * m + 4 * hh]);
         wave_lds_sync();
-        if (DIRECT) {
-            put(0, hv);
+        if (DIRECT || !BF16) {
+            put(H_COL, hv);
             wave_lds_sync();
         }
 #pragma unroll 1
@@ -230,8 +411,28 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
             };
             floatx16 acc[W::NT];
             if constexpr (DIRECT) {
-                gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc, yv);
+                gate_tiles<FY, HID, LDT>(s_w, tile_lds, i, hh, acc, yv);
                 fetch_next();                           // into the operands' registers, while the cell is evaluated
+            } else if constexpr (!BF16) {
+                float hop[HID / 16][8];
+                Largest top;
+#pragma unroll
+                for (int q = 0; q < HID / 16; ++q) {
+                    operand(&tile_lds[i * LDT + H_COL], q, hh, hop[q]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) top.note(__float_as_uint(hop[q][e]));
+                }
+                wave_lds_sync();
+#pragma unroll
+                for (int q = 0; q < Y_PIECES; ++q) {
+                    const int e = (q * kWave + lane) * P;
+                    *reinterpret_cast<uintx4 *>(&tile_lds[(e / FY) * LDT + e % FY]) = yv[q];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) top.note(yv[q][k]);
+                }
+                fetch_next();
+                wave_lds_sync();
+                gate_tiles_f32<FY, HID, LDT>(s_w, tile_lds, hop, odd_w || __ballot(top.odd()), i, hh, acc);
             } else {
 #pragma unroll
                 for (int q = 0; q < Y_PIECES; ++q) {
@@ -240,7 +441,7 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
                 }
                 fetch_next();
                 wave_lds_sync();
-                gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc);
+                gate_tiles<FY, HID, LDT>(s_w, tile_lds, i, hh, acc);
             }
             wave_lds_sync();                            // every lane has its operands
 #pragma unroll
@@ -249,10 +450,10 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
                 floatx4 h_new;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float ai = acc[gate_tile<HID>(0, m)][gate_reg<HID>(0, m) + r] + s_bias[k0 + r];
-                    const float af = acc[gate_tile<HID>(1, m)][gate_reg<HID>(1, m) + r] + s_bias[HID + k0 + r];
-                    const float ag = acc[gate_tile<HID>(2, m)][gate_reg<HID>(2, m) + r] + s_bias[2 * HID + k0 + r];
-                    const float ao = acc[gate_tile<HID>(3, m)][gate_reg<HID>(3, m) + r] + s_bias[3 * HID + k0 + r];
+                    const float ai = S::product(acc[gate_tile<HID>(0, m)][gate_reg<HID>(0, m) + r]) + s_bias[k0 + r];
+                    const float af = S::product(acc[gate_tile<HID>(1, m)][gate_reg<HID>(1, m) + r]) + s_bias[HID + k0 + r];
+                    const float ag = S::product(acc[gate_tile<HID>(2, m)][gate_reg<HID>(2, m) + r]) + s_bias[2 * HID + k0 + r];
+                    const float ao = S::product(acc[gate_tile<HID>(3, m)][gate_reg<HID>(3, m) + r]) + s_bias[3 * HID + k0 + r];
                     cell[m][r] = fast_sigmoid(af) * cell[m][r] + fast_sigmoid(ai) * fast_tanh(ag);
                     h_new[r] = fast_sigmoid(ao) * fast_tanh(cell[m][r]);
                 }
@@ -286,12 +487,13 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
     typedef typename S::Elem Elem;
     typedef Weights<FY, HID, BF16> W;
     constexpr int P = S::kPiece, NT = W::NT, G4 = W::G4;
-    constexpr int LDT = (W::K > 2 * HID ? W::K : 2 * HID) + S::kTilePad;
+    constexpr int LDT = (BF16 ? W::K : FY > 2 * HID ? FY : 2 * HID) + S::kTilePad;     // fp32: h's operands are held by the lanes, as going forward
+    static_assert(W::K >= 2 * HID, "c and the incoming gradient, halves of da");
     constexpr int Y_PIECES = 32 * FY / P / kWave, S_PIECES = 32 * HID / P / kWave, HALF_PIECES = 2 * S_PIECES;
     constexpr int ROWS = 2 * HID, N2 = ROWS / 32;               // rows of [W_x ; W_h] that da meets: those of Y1, then W_h
     constexpr int LDR = G4 + 8;                                 // bf16: these rows once more, columns contiguous
     static_assert(FY >= HID && ROWS % 32 == 0, "whole tiles of output columns");
-    __shared__ __attribute__((aligned(16))) Elem s_w[W::kSize];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w[W::kSize];
     __shared__ __attribute__((aligned(16))) Elem s_wr[BF16 ? ROWS * LDR : 1];
     __shared__ __attribute__((aligned(16))) float s_bias[G4];
     __shared__ __attribute__((aligned(16))) Elem s_tile[WAVES][32 * LDT];
@@ -300,34 +502,36 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
     Elem *da = static_cast<Elem *>(da_), *dy1 = static_cast<Elem *>(dy1_);
 
     const int tid = threadIdx.x;
-    W::stage(s_w, static_cast<const Elem *>(wx_), static_cast<const Elem *>(wh_), tid, WAVES * kWave);
+    bool odd_w = W::stage(s_w, static_cast<const Elem *>(wx_), static_cast<const Elem *>(wh_), tid, WAVES * kWave);
     if (BF16)
         for (int idx = tid; idx < ROWS * G4; idx += WAVES * kWave) {
             const int k = FY - HID + idx / G4;
             s_wr[(idx / G4) * LDR + idx % G4] = k < FY ? static_cast<const Elem *>(wx_)[k * G4 + idx % G4] : static_cast<const Elem *>(wh_)[(k - FY) * G4 + idx % G4];
         }
     for (int idx = tid; idx < G4; idx += WAVES * kWave) s_bias[idx] = bias ? bias[idx] : 0.0f;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lane = tid & (kWave - 1), wave = uniform(tid / kWave);
     const int i = lane & 31, hh = lane >> 5;
     Elem *tile_lds = s_tile[wave];
     const int64_t stride = (int64_t)gridDim.x * WAVES;
-    __syncthreads();
-    const uintx4 zero = {0u, 0u, 0u, 0u};
+    if (BF16) __syncthreads(); else odd_w = __syncthreads_or(odd_w);
+    // fp32: rows of W from its transposed parts, by the LDS's transposing read: four lanes name 16 elements of a column's image, 16
+    // lanes the four columns of a read, and lane k of them gets element k of each
+    const int from = (4 * hh + (lane & 15) / 4) * W::kLd + FY - HID + (lane & 16) + (lane & 3) * 4;
+    constexpr int Y_BYTES = FY * sizeof(Elem), S_BYTES = HID * sizeof(Elem);
     uintx4 yv[Y_PIECES], hv[S_PIECES], cv[S_PIECES], gv[S_PIECES];
     auto fetch = [&](int64_t tile, int t) {
+        const __amdgpu_buffer_rsrc_t of_y = tile_rows(y + t * n * FY, tile, n, Y_BYTES), of_h = tile_rows(t > 0 ? h + (t - 1) * n * HID : h0, tile, n, S_BYTES);
 #pragma unroll
-        for (int q = 0; q < Y_PIECES; ++q) {
-            const int64_t piece = tile * (32 * FY / P) + q * kWave + lane;
-            yv[q] = (tile < n_tiles && piece * P < n * FY) ? reinterpret_cast<const uintx4 *>(y + t * n * FY)[piece] : zero;
-        }
-        const Elem *hp = t > 0 ? h + (t - 1) * n * HID : h0, *cp = t > 0 ? c + (t - 1) * n * HID : c0;
+        for (int q = 0; q < Y_PIECES; ++q) yv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_y, (q * kWave + lane) * 16, 0, 0);
+#pragma unroll
+        for (int q = 0; q < S_PIECES; ++q) hv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_h, (q * kWave + lane) * 16, 0, 0);
+    };
+    auto fetch_rest = [&](int64_t tile, int t) {        // what the cell takes, behind the gates
+        const __amdgpu_buffer_rsrc_t of_c = tile_rows(t > 0 ? c + (t - 1) * n * HID : c0, tile, n, S_BYTES), of_g = tile_rows(gh + t * n * HID, tile, n, S_BYTES);
 #pragma unroll
         for (int q = 0; q < S_PIECES; ++q) {
-            const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
-            const bool ok = tile < n_tiles && piece * P < n * HID;
-            hv[q] = ok ? reinterpret_cast<const uintx4 *>(hp)[piece] : zero;
-            cv[q] = ok ? reinterpret_cast<const uintx4 *>(cp)[piece] : zero;
-            gv[q] = ok ? reinterpret_cast<const uintx4 *>(gh + t * n * HID)[piece] : zero;
+            cv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_c, (q * kWave + lane) * 16, 0, 0);
+            gv[q] = __builtin_amdgcn_raw_buffer_load_b128(of_g, (q * kWave + lane) * 16, 0, 0);
         }
     };
     auto put = [&](int col, const uintx4 (&v)[S_PIECES]) {
@@ -353,15 +557,32 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
 #pragma unroll 1
         for (int t = T - 1; t >= 0; --t) {
             // ---- [Y | h_{t-1}] and the gates
+            float hop[HID / 16][8];
+            Largest top;
+            if (!BF16) {
+                put(0, hv);
+                wave_lds_sync();
+#pragma unroll
+                for (int q = 0; q < HID / 16; ++q) {
+                    operand(reinterpret_cast<const float *>(&tile_lds[i * LDT]), q, hh, hop[q]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) top.note(__float_as_uint(hop[q][e]));
+                }
+                wave_lds_sync();
+            }
 #pragma unroll
             for (int q = 0; q < Y_PIECES; ++q) {
                 const int e = (q * kWave + lane) * P;
                 *reinterpret_cast<uintx4 *>(&tile_lds[(e / FY) * LDT + e % FY]) = yv[q];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) top.note(yv[q][k]);
             }
-            put(FY, hv);
+            if (BF16) put(FY, hv);
+            fetch_rest(tile, t);
             wave_lds_sync();
             floatx16 acc[NT];
-            gate_tiles<FY, HID, BF16, LDT>(s_w, tile_lds, i, hh, acc);
+            if constexpr (BF16) gate_tiles<FY, HID, LDT>(s_w, tile_lds, i, hh, acc);
+            else gate_tiles_f32<FY, HID, LDT>(s_w, tile_lds, hop, odd_w || __ballot(top.odd()), i, hh, acc);
             uint32_t through = 0;                       // where Y1 > 0 among the columns this lane will form
 #pragma unroll
             for (int m = 0; m < HID / 8; ++m) {
@@ -383,10 +604,10 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     constexpr int kI = 0, kF = 1, kG = 2, kO = 3;
-                    const float gi = fast_sigmoid(acc[gate_tile<HID>(kI, m)][gate_reg<HID>(kI, m) + r] + s_bias[k0 + r]);
-                    const float gf = fast_sigmoid(acc[gate_tile<HID>(kF, m)][gate_reg<HID>(kF, m) + r] + s_bias[HID + k0 + r]);
-                    const float gg = fast_tanh(acc[gate_tile<HID>(kG, m)][gate_reg<HID>(kG, m) + r] + s_bias[2 * HID + k0 + r]);
-                    const float go = fast_sigmoid(acc[gate_tile<HID>(kO, m)][gate_reg<HID>(kO, m) + r] + s_bias[3 * HID + k0 + r]);
+                    const float gi = fast_sigmoid(S::product(acc[gate_tile<HID>(kI, m)][gate_reg<HID>(kI, m) + r]) + s_bias[k0 + r]);
+                    const float gf = fast_sigmoid(S::product(acc[gate_tile<HID>(kF, m)][gate_reg<HID>(kF, m) + r]) + s_bias[HID + k0 + r]);
+                    const float gg = fast_tanh(S::product(acc[gate_tile<HID>(kG, m)][gate_reg<HID>(kG, m) + r]) + s_bias[2 * HID + k0 + r]);
+                    const float go = fast_sigmoid(S::product(acc[gate_tile<HID>(kO, m)][gate_reg<HID>(kO, m) + r]) + s_bias[3 * HID + k0 + r]);
                     const float tc = fast_tanh(gf * c_old[r] + gi * gg);
                     const float d_h = g_h[r] + dh[m][r];
                     const float d = d_h * go * (1.0f - tc * tc) + dc[m][r];
@@ -396,6 +617,7 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
                     acc[gate_tile<HID>(kO, m)][gate_reg<HID>(kO, m) + r] = d_h * tc * go * (1.0f - go);
                     dc[m][r] = d * gf;
                 }
+                if (!BF16) __builtin_amdgcn_sched_barrier(0);            // a few elements at a time: registers
             }
             // ---- [dY1 | dh_{t-1}]^T = W da^T
             floatx16 out[N2];
@@ -420,17 +642,65 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
                         }
                     }
             } else {
+                Largest most;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {          // column 8 (q / 4) + 4 h + q % 4 of every tile
-                    float wv[N2][NT];
+                for (int g = 0; g < NT; ++g)
 #pragma unroll
-                    for (int j = 0; j < N2; ++j)
+                    for (int v = 0; v < 16; ++v) most.note(__float_as_uint(acc[g][v]));
+                const bool odd = odd_w || __ballot(most.odd());
+                auto columns = [&](int g, int p, float (&v)[8]) {          // the same as above
 #pragma unroll
-                        for (int g = 0; g < NT; ++g) wv[j][g] = s_w[(FY - HID + j * 32 + i) * W::kLd + (8 * (q / 4) + 4 * hh + q % 4) * NT + g];
+                    for (int e = 0; e < 8; ++e) v[e] = acc[g][8 * p + e];
+                };
+                auto rows_of_w = [&](int g, int p, int j, int part) {
+                    const uint16_t *src = &s_w[from + part * W::kImage + (32 * g + 16 * p) * W::kLd + 32 * j];
+                    const uint2 lo = read_transposed(src), hi = read_transposed(src + 8 * W::kLd);
+                    return __builtin_bit_cast(bf16x8, uintx4{lo.x, lo.y, hi.x, hi.y});
+                };
+                if (!odd) {
 #pragma unroll
                     for (int g = 0; g < NT; ++g)
 #pragma unroll
-                        for (int j = 0; j < N2; ++j) out[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j][g], acc[g][q], out[j], 0, 0, 0);
+                        for (int p = 0; p < 2; ++p) {
+                            float v[8];
+                            columns(g, p, v);
+                            bf16x8 a[N2][kParts], b[kParts];
+#pragma unroll
+                            for (int j = 0; j < N2; ++j)
+#pragma unroll
+                                for (int part = 0; part < kParts; ++part) a[j][part] = rows_of_w(g, p, j, part);
+                            split(v, b);
+                            smaller_products(out, a, b);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                    for (int g = 0; g < NT; ++g)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) {
+                            float v[8];
+                            columns(g, p, v);
+                            const bf16x8 b = first_part(v, 2 * g + p, 2 * NT);
+                            if (g == NT / 2 && p == 0) turn_sign(out);
+#pragma unroll
+                            for (int j = 0; j < N2; ++j) out[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows_of_w(g, p, j, 0), b, out[j], 0, 0, 0);
+                        }
+                } else {
+#pragma unroll
+                    for (int g = 0; g < NT; ++g)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) {
+                            float v[8];
+                            columns(g, p, v);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+#pragma unroll
+                                for (int j = 0; j < N2; ++j)
+                                    out[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(W::at(s_w, FY - HID + j * 32 + i, 32 * g + 16 * p + 4 * hh + e % 4 + 8 * (e / 4)),
+                                                                                  v[e], out[j], 0, 0, 0);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                        }
+                    turn_sign(out);
                 }
             }
             // ---- da leaves in two halves of two gates each (a whole tile of it does not fit the buffer)
@@ -446,12 +716,13 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
                         S::store4(&tile_lds[i * LDT + g * HID + 8 * m + 4 * hh], floatx4{src[q], src[q + 1], src[q + 2], src[q + 3]});
                     }
                 wave_lds_sync();
+                const __amdgpu_buffer_rsrc_t rows = tile_rows(da + t * n * G4, tile, n, G4 * (int)sizeof(Elem));
 #pragma unroll
                 for (int q = 0; q < HALF_PIECES; ++q) {
                     const int e = (q * kWave + lane) * P;
                     const int r = e / (2 * HID), col = e % (2 * HID);
-                    const int64_t row = tile * 32 + r;
-                    if (row < n) *reinterpret_cast<uintx4 *>(&da[(t * n + row) * G4 + half * 2 * HID + col]) = *reinterpret_cast<const uintx4 *>(&tile_lds[r * LDT + col]);
+                    __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const uintx4 *>(&tile_lds[r * LDT + col]), rows,
+                                                           (r * G4 + half * 2 * HID + col) * (int)sizeof(Elem), 0, 0);
                 }
             }
             wave_lds_sync();
@@ -461,8 +732,8 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
                 floatx4 v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v[r] = (through >> (4 * m + r)) & 1u ? out[(8 * m) / 32][4 * (((8 * m) % 32) / 8) + r] : 0.0f;
-                    dh[m][r] = out[(HID + 8 * m) / 32][4 * (((HID + 8 * m) % 32) / 8) + r];
+                    v[r] = (through >> (4 * m + r)) & 1u ? S::product(out[(8 * m) / 32][4 * (((8 * m) % 32) / 8) + r]) : 0.0f;
+                    dh[m][r] = S::product(out[(HID + 8 * m) / 32][4 * (((HID + 8 * m) % 32) / 8) + r]);
                 }
                 S::store4(&tile_lds[i * LDT + 8 * m + 4 * hh], v);
             }
@@ -470,11 +741,11 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_backward_kernel(
             if (t > 0) fetch(tile, t - 1);
             else fetch(tile + stride, T - 1);
             wave_lds_sync();
+            const __amdgpu_buffer_rsrc_t of_dy1 = tile_rows(dy1 + t * n * HID, tile, n, S_BYTES);
 #pragma unroll
             for (int q = 0; q < S_PIECES; ++q) {
                 const int e = (q * kWave + lane) * P;
-                const int64_t piece = tile * (32 * HID / P) + q * kWave + lane;
-                if (piece * P < n * HID) reinterpret_cast<uintx4 *>(dy1 + t * n * HID)[piece] = *reinterpret_cast<const uintx4 *>(&tile_lds[(e / HID) * LDT + e % HID]);
+                __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const uintx4 *>(&tile_lds[(e / HID) * LDT + e % HID]), of_dy1, e * (int)sizeof(Elem), 0, 0);
             }
             wave_lds_sync();
         }

@@ -479,3 +479,49 @@ def test_parameter_gradients_of_the_lstm_at_the_edges_of_its_steps(dtype, hidden
         # fp32 sums of exact products (bf16) or once-rounded ones: an error of 2^-24 per term and addition of the magnitudes
         bound = (min(rows, 4096) + 2) * 2.0 ** -24 * (np.abs(left).T @ np.abs(g)) + 1e-30
         assert np.all(np.abs(to_f64(got).reshape(bound.shape) - left.T @ g) <= bound)
+
+
+# fp32 numbers that are no sum of three bf16 numbers: infinite, or so large that the first of the three would be; at the edge of a tile
+@pytest.mark.parametrize("hidden,f_y", [(32, 64), (16, 16)])
+@pytest.mark.parametrize("where", ["y", "h0", "w"])
+def test_fp32_lstm_with_numbers_that_cannot_be_split(hidden, f_y, where):
+    n, T, odd = 70, 2, (0, 33, 69)
+    y, h0, c0 = randn((T, n, f_y), 7), randn((n, hidden), 8), randn((n, hidden), 9)
+    w_x, w_h = randn((f_y, 4 * hidden), 10) / f_y ** 0.5, randn((hidden, 4 * hidden), 11) / hidden ** 0.5
+    if where == "w":                                # met by zeros only, which an infinite part would make no numbers of
+        y[:, :, 3] = 0.0
+        w_x[3, 5] = 3.4e38
+    else:
+        for row, value in zip(odd, (float("inf"), -float("inf"), -3.4e38)):
+            (y[0] if where == "y" else h0)[row, 2] = value
+    h, c = torch.empty((T, n, hidden), device=DEV), torch.empty((T, n, hidden), device=DEV)
+    dev = [t.to(DEV) for t in (y, h0, w_x, w_h, c0)]
+    dg.lstm_series(dev[0], dev[1], dev[2], dev[3], None, dev[4], c, h)
+    hw, cw = h0.double(), c0.double()
+    for t in range(T):
+        i, f, g, o = (y[t].double() @ w_x.double() + hw @ w_h.double()).split(hidden, 1)
+        cw = torch.sigmoid(f) * cw + torch.sigmoid(i) * torch.tanh(g)
+        hw = torch.sigmoid(o) * torch.tanh(cw)
+        assert_close(to_f64(h[t]), hw.numpy(), torch.float32, f"h_{t + 1}")
+        assert_close(to_f64(c[t]), cw.numpy(), torch.float32, f"c_{t + 1}")
+
+
+def test_fp32_lstm_backward_with_an_infinite_gradient():
+    """The row that receives it sends no number on; the 31 others of its tile are as without it."""
+    n, hidden, f_y, row = 40, 32, 64, 5
+    y, h0, c0, g_h = (randn(s, 20 + k).to(DEV) for k, s in enumerate(((1, n, f_y), (n, hidden), (n, hidden), (1, n, hidden))))
+    w_x, w_h = (randn((f_y, 4 * hidden), 30) / f_y ** 0.5).to(DEV), (randn((hidden, 4 * hidden), 31) / hidden ** 0.5).to(DEV)
+    h, c = torch.empty((1, n, hidden), device=DEV), torch.empty((1, n, hidden), device=DEV)
+    dg.lstm_series(y, h0, w_x, w_h, None, c0, c, h)
+    out = []
+    for infinite in (False, True):
+        g = g_h.clone()
+        if infinite:
+            g[0, row, 3] = float("inf")
+        da, dy1, dh, dc = (torch.empty(s, device=DEV) for s in ((1, n, 4 * hidden), (1, n, hidden), (n, hidden), (n, hidden)))
+        dg.lstm_series_backward(y, h0, h, w_x, w_h, None, c0, c, g, da, dy1, dh, dc, carried=False)
+        out.append([to_f64(t).reshape(n, -1) for t in (da, dy1, dh, dc)])
+    others = np.arange(n) != row
+    for name, want, got in zip(("da", "dY1", "dh", "dc"), *out):
+        assert_close(got[others], want[others], torch.float32, name)
+        assert not np.isfinite(got[row]).all() and np.isfinite(got[others]).all(), name
