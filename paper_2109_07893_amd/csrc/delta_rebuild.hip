@@ -27,13 +27,13 @@ constexpr int kHeavyList = 8 * kRowTile;     // list entries per row tile beyond
 
 constexpr int kPerLane = 8;                  // old entries per lane and sub-tile of the merge
 constexpr int kSub = kWave * kPerLane;       // old entries per sub-tile, at most
-constexpr int kMaxRange = kSub * 16;         // old entries streamed by one wavefront, at most
-constexpr int kTargetWaves = 16384;          // ranges shrink on small inputs so that about this many wavefronts exist
+constexpr int kWavesAtOnce = 4096;           // see merge_range_length
+constexpr int kLongestShare = kSub * 9;
+constexpr int kLongRange = kSub * 13;
 
 // The row in which a range of the merge begins: its extent in A_prev (rp, rp1) and in A_next (rn, rn1), and the stretch
-// of the added list that belongs to it (as, ae); the deleted list's stretch follows from these.  us, ue: the row's
-// stretch of the sorted value-update list of a weighted rebuild (0, 0 without one).
-struct RangeStart { int rp, rp1, rn, rn1, as, ae, row, us, ue, pad; };
+// of the added list that belongs to it (as, ae); the deleted list's stretch follows from these.
+struct RangeStart { int rp, rp1, rn, rn1, as, ae, row, pad; };
 
 __device__ __forceinline__ void report(int32_t *status, int code) {
     if (!status) return;
@@ -73,37 +73,13 @@ __device__ __forceinline__ void count_runs(const int32_t *__restrict__ rows, int
     }
 }
 
-// wave_find_row for two lists at once: the two searches advance in lock step, so their loads travel together.
-// A list of length 0 (its pointer may be null) is not read and gives -1.
-__device__ __forceinline__ void wave_find_row_pair(const int32_t *__restrict__ a, int na, int key_a, const int32_t *__restrict__ b,
-                                                   int nb, int key_b, int lane, int &found_a, int &found_b) {
-    int lo_a = 0, hi_a = na, lo_b = 0, hi_b = nb;
-    while (hi_a > lo_a || hi_b > lo_b) {
-        const int step_a = (hi_a - lo_a + kWave - 1) / kWave, step_b = (hi_b - lo_b + kWave - 1) / kWave;
-        const int idx_a = lo_a + lane * step_a, idx_b = lo_b + lane * step_b;
-        const bool in_a = hi_a > lo_a && idx_a < hi_a, in_b = hi_b > lo_b && idx_b < hi_b;
-        const int v_a = in_a ? a[idx_a] : 0, v_b = in_b ? b[idx_b] : 0;
-        const int m_a = __popcll(__ballot(in_a && v_a <= key_a)), m_b = __popcll(__ballot(in_b && v_b <= key_b));
-        if (hi_a > lo_a) {
-            if (m_a == 0) hi_a = lo_a;
-            else { const int nlo = lo_a + (m_a - 1) * step_a + 1; hi_a = min(lo_a + m_a * step_a, hi_a); lo_a = nlo; }
-        }
-        if (hi_b > lo_b) {
-            if (m_b == 0) hi_b = lo_b;
-            else { const int nlo = lo_b + (m_b - 1) * step_b + 1; hi_b = min(lo_b + m_b * step_b, hi_b); lo_b = nlo; }
-        }
-    }
-    found_a = lo_a - 1;
-    found_b = lo_b - 1;
-}
-
-// The lists that change a snapshot: added entries, deleted entries and, in a weighted rebuild, value updates.
-constexpr int kLists = 3;
+// The lists that change a snapshot's rows: added entries and deleted ones.
+constexpr int kLists = 2;
 
 // The same counts from lower bounds, for every list that `heavy` names: thread t finds where each of its rows begins inside
 // [lo, hi).  All searches of a thread advance in lock step, so the whole costs as many trips to memory as one search (one search
 // after the other, each starting where the last had ended, was what the kernel took: R-MAT, 2^19 vertices, 8.9 M entries,
-// 3 % churn with value updates 46.5 us, now 19.4).
+// 3 % churn with value updates 46.5 us, then 19.4).
 __device__ __forceinline__ void count_by_search(const int32_t *const (&rows)[kLists], const int (&lo)[kLists], const int (&hi)[kLists],
                                                 const bool (&heavy)[kLists], int r0, int nr, int (*cnt)[kRowTile], int tid) {
     int pos[kLists][kRowsPerThread + 1], longest = 0;
@@ -172,10 +148,9 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
     int n, const int32_t *__restrict__ rowptr_prev,
     const int32_t *__restrict__ add_row, int n_add, const int32_t *__restrict__ del_row, int n_del,
     int32_t *__restrict__ rowptr_next, float *__restrict__ dinv,
-    int range_len, int n_ranges, RangeStart *__restrict__ range_start,
-    const int32_t *__restrict__ upd_row, int n_upd, int32_t *status) {
-    __shared__ int s_cnt[kLists][kRowTile];     // entries per row of the added, deleted and updated lists
-    __shared__ int s_bound[6];
+    int range_len, int n_ranges, RangeStart *__restrict__ range_start, int32_t *status) {
+    __shared__ int s_cnt[kLists][kRowTile];     // entries per row of the added and deleted lists
+    __shared__ int s_bound[4];
     __shared__ int s_wsum[kLists][kRowThreads / kWave];
 
     const int tid = threadIdx.x;
@@ -197,17 +172,9 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
 #pragma unroll
         for (int k = 0; k <= kRowsPerThread; ++k) rp[k] = r_own + k <= n ? rowptr_prev[r_own + k] : 0;
     }
-    {   // how many list entries have a row below r0 / below r1: one 64-ary search per wavefront and list; the
-        // wavefronts that search the added list take the value-update list of a weighted rebuild along
-        const int32_t *list = wave < 2 ? add_row : del_row;
-        const int len = wave < 2 ? n_add : n_del;
-        const int key = ((wave & 1) ? r1 : r0) - 1;
-        int found, found_upd;
-        wave_find_row_pair(list, len, key, upd_row, (wave < 2 && upd_row) ? n_upd : 0, key, lane, found, found_upd);
-        if (lane == 0) {
-            s_bound[wave] = found + 1;
-            if (wave < 2) s_bound[4 + wave] = found_upd + 1;
-        }
+    {   // how many list entries have a row below r0 / below r1: one 64-ary search per wavefront and list
+        const int found = wave_find_row(wave < 2 ? add_row : del_row, wave < 2 ? n_add : n_del, ((wave & 1) ? r1 : r0) - 1, lane);
+        if (lane == 0) s_bound[wave] = found + 1;
     }
     for (int i = tid; i < kRowTile; i += kRowThreads)
 #pragma unroll
@@ -215,8 +182,8 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
     __syncthreads();
     // A tile of hub rows can own a very long stretch of a list; walking it would leave the whole chip
     // waiting for this workgroup, so there the counts come from one lower bound per row instead.
-    const int32_t *const rows[kLists] = {add_row, del_row, upd_row};
-    const int lo[kLists] = {s_bound[0], s_bound[2], upd_row ? s_bound[4] : 0}, hi[kLists] = {s_bound[1], s_bound[3], upd_row ? s_bound[5] : 0};
+    const int32_t *const rows[kLists] = {add_row, del_row};
+    const int lo[kLists] = {s_bound[0], s_bound[2]}, hi[kLists] = {s_bound[1], s_bound[3]};
     bool heavy[kLists], any_heavy = false;
 #pragma unroll
     for (int l = 0; l < kLists; ++l) {
@@ -227,16 +194,14 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
     if (any_heavy) count_by_search(rows, lo, hi, heavy, r0, nr, s_cnt, tid);
     __syncthreads();
 
-    int ca[kRowsPerThread], cd[kRowsPerThread], cu[kRowsPerThread];
-    int sum[kLists] = {0, 0, 0}, inc[kLists];
+    int ca[kRowsPerThread], cd[kRowsPerThread];
+    int sum[kLists] = {0, 0}, inc[kLists];
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k) {
         ca[k] = s_cnt[0][tid * kRowsPerThread + k];
         cd[k] = s_cnt[1][tid * kRowsPerThread + k];
-        cu[k] = s_cnt[2][tid * kRowsPerThread + k];
         sum[0] += ca[k];
         sum[1] += cd[k];
-        sum[2] += cu[k];
     }
 #pragma unroll
     for (int l = 0; l < kLists; ++l) {
@@ -244,8 +209,8 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
         if (lane == kWave - 1) s_wsum[l][wave] = inc[l];
     }
     __syncthreads();
-    int oa = lo[0] + inc[0] - sum[0], od = lo[1] + inc[1] - sum[1], ou = lo[2] + inc[2] - sum[2];      // exclusive offsets of this thread's first row
-    for (int w = 0; w < wave; ++w) { oa += s_wsum[0][w]; od += s_wsum[1][w]; ou += s_wsum[2][w]; }
+    int oa = lo[0] + inc[0] - sum[0], od = lo[1] + inc[1] - sum[1];      // exclusive offsets of this thread's first row
+    for (int w = 0; w < wave; ++w) { oa += s_wsum[0][w]; od += s_wsum[1][w]; }
 
     int rn[kRowsPerThread];
     float dv[kRowsPerThread];
@@ -259,11 +224,10 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
             // ranges of the merge that begin inside this row (few rows hold a multiple of the range length; a hub
             // row several): what the merge needs to know about the row, so that it starts without a search
             for (int g = max((p + range_len - 1) / range_len, 0); g < n_ranges && (int64_t)g * range_len < q; ++g)
-                range_start[g] = RangeStart{p, q, p + oa - od, q + oa + ca[k] - od - cd[k], oa, oa + ca[k], r, ou, ou + cu[k], 0};
+                range_start[g] = RangeStart{p, q, p + oa - od, q + oa + ca[k] - od - cd[k], oa, oa + ca[k], r, 0};
         }
         oa += ca[k];
         od += cd[k];
-        ou += cu[k];
     }
     if (VEC && whole) {
         *reinterpret_cast<int4 *>(rowptr_next + r_own) = make_int4(rn[0], rn[1], rn[2], rn[3]);
@@ -277,6 +241,21 @@ __global__ __launch_bounds__(kRowThreads) void rowptr_kernel(
             }
     }
     if (r1 == n && tid == 0) rowptr_next[n] = rowptr_prev[n] + n_add - n_del;
+}
+
+// How many entries of a list sorted by (row, column) come before (row, col): a 64-ary search of the wavefront.
+__device__ __forceinline__ int wave_count_before(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols, int len, int row, int col, int lane) {
+    int lo = 0, hi = len;
+    while (hi > lo) {
+        const int step = (hi - lo + kWave - 1) / kWave, at = lo + lane * step;
+        const bool in = at < hi;
+        const int r = in ? rows[at] : 0, c = in ? cols[at] : 0;
+        const int m = __popcll(__ballot(in && (r < row || (r == row && c < col))));
+        if (m == 0) break;                       // the first one does not: lo come before
+        hi = min(lo + m * step, hi);
+        lo += (m - 1) * step + 1;
+    }
+    return lo;
 }
 
 // For K stretches [pos, hi) of an ascending LDS array at once (hi >= pos): moves pos to the first element >= key.  Element p of the
@@ -330,7 +309,10 @@ __device__ __forceinline__ void lds_bound(const int *a, int (&pos)[K], const int
 // entries bring theirs.  UPDATES (with VALUES): a third list, sorted like the other two, names surviving entries
 // that get a new value; it is consumed through a cursor of its own, each entry finds its old entry in the staged
 // columns as a deleted entry does and leaves the new value there.  An entry that names nothing stored is passed over.
-template <bool VALUES, bool UPDATES>
+// The list may be long: AHEAD batches of 64 of its entries are fetched ahead, eight where a sub-tile takes more than two or three
+// (a smoothed series changes nearly every value in its first steps: R-MAT 2^19, 8.5 M entries, 8.3 M updates, a whole rebuild 92 -> 76 us, with
+// the place of a range's first update found here, where it is wanted once, and not per row in rowptr_kernel).
+template <bool VALUES, int AHEAD>
 __global__ __launch_bounds__(kWave) void merge_kernel(
     int n, const int32_t *__restrict__ rowptr_prev, const int32_t *__restrict__ colidx_prev, int nnz_prev, int range_len,
     const int32_t *__restrict__ add_row, const int32_t *__restrict__ add_col, int n_add,
@@ -339,6 +321,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
     int32_t *__restrict__ colidx_next, int cap_next,
     const float *__restrict__ val_prev, const float *__restrict__ add_val, float *__restrict__ val_next,
     const int32_t *__restrict__ upd_row, const int32_t *__restrict__ upd_col, const float *__restrict__ upd_val, int n_upd) {
+    constexpr bool UPDATES = AHEAD > 0;
+    constexpr int kBatches = UPDATES ? AHEAD : 1;
     constexpr int kWindow = 2 * kWave;      // row pointers fetched ahead for every sub-tile; more are fetched when rows are short
     constexpr int kMaxWindow = kSub + kWave;
     constexpr unsigned kDropped = 0x80000000u;   // an offset that no buffer here reaches
@@ -392,25 +376,16 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         fetch_window(first_row);
         a_cur = as;
         d_cur = ds;
-        if (UPDATES) u_cur = st.us;
         if (rp < e_begin) {   // the range begins inside the row: skip what earlier ranges place
-            // (all lists at once, 64 entries a trip: most ranges of a hub row start here)
-            constexpr int kFound = UPDATES ? 3 : 2;
+            // (both lists at once, 64 entries a trip: most ranges of a hub row start here)
             const bool in_a = as >= 0 && as < ae && ae <= n_add, in_d = ds >= 0 && ds < de && de <= n_del;
-            const int32_t *list[kFound] = {add_col + (in_a ? as : 0), del_col + (in_d ? ds : 0)};
-            int len[kFound] = {in_a ? ae - as : 0, in_d ? de - ds : 0}, key[kFound] = {c_before, c_at}, below[kFound];
-            if constexpr (UPDATES) {
-                const bool in_u = st.us >= 0 && st.us < st.ue && st.ue <= n_upd;
-                list[2] = upd_col + (in_u ? st.us : 0);
-                len[2] = in_u ? st.ue - st.us : 0;
-                key[2] = c_at;
-            }
-            wave_count_below<kFound>(list, len, key, lane, below);
+            const int32_t *list[2] = {add_col + (in_a ? as : 0), del_col + (in_d ? ds : 0)};
+            int len[2] = {in_a ? ae - as : 0, in_d ? de - ds : 0}, key[2] = {c_before, c_at}, below[2];
+            wave_count_below<2>(list, len, key, lane, below);
             a_cur += below[0];
             d_cur += below[1];
-            if constexpr (UPDATES) u_cur += below[2];
         }
-        if (UPDATES) u_cur = uniform(min(max(u_cur, 0), n_upd));
+        if (UPDATES) u_cur = uniform(wave_count_before(upd_row, upd_col, n_upd, st.row, rp < e_begin ? c_at : 0, lane));
         a_cur = uniform(min(max(a_cur, 0), n_add));
         d_cur = uniform(min(max(d_cur, 0), n_del));
         base = uniform(rn + (e_begin - rp) - (d_cur - ds) + (a_cur - as));
@@ -422,8 +397,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         const bool some = cur < len;
         return word(buffer_of(some ? (const int32_t *)list + cur : nullptr, some ? min(len - cur, kWave) : 0), lane);
     };
-    int pa_row, pa_col, pd_row, pd_col, pu_row = 0, pu_col = 0;
-    float pa_val = 0.0f, pu_val = 0.0f;
+    int pa_row, pa_col, pd_row, pd_col, pu_row[kBatches], pu_col[kBatches];
+    float pa_val = 0.0f, pu_val[kBatches];
     auto load_added = [&] {
         pa_row = at_cursor(add_row, n_add, a_cur);
         pa_col = at_cursor(add_col, n_add, a_cur);
@@ -433,10 +408,15 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         pd_row = at_cursor(del_row, n_del, d_cur);
         pd_col = at_cursor(del_col, n_del, d_cur);
     };
+    auto load_batch = [&](int b) {
+        const int from = u_cur + min(b * kWave, n_upd - u_cur);
+        pu_row[b] = at_cursor(upd_row, n_upd, from);
+        pu_col[b] = at_cursor(upd_col, n_upd, from);
+        pu_val[b] = __int_as_float(at_cursor(upd_val, n_upd, from));
+    };
     auto load_updates = [&] {
-        pu_row = at_cursor(upd_row, n_upd, u_cur);
-        pu_col = at_cursor(upd_col, n_upd, u_cur);
-        pu_val = __int_as_float(at_cursor(upd_val, n_upd, u_cur));
+#pragma unroll
+        for (int b = 0; b < kBatches; ++b) load_batch(b);
     };
     load_added();
     load_deleted();
@@ -509,8 +489,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         key[0] = pd_col;
         key[1] = pa_col + 1;                         // behind an equal one
         if constexpr (UPDATES) {
-            here[2] = stretch(u_cur + lane < n_upd, pu_row, r_lo[2], r_hi[2], at[2], hi[2]);
-            key[2] = pu_col;
+            here[2] = stretch(u_cur + lane < n_upd, pu_row[0], r_lo[2], r_hi[2], at[2], hi[2]);
+            key[2] = pu_col[0];
         }
         lds_bound<kSearches>(s_col, at, hi, key);
 
@@ -539,13 +519,13 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
         // ---- value updates: leave the new value at the old entry.  An entry is done with once its place in A_prev's
         // order lies before the end of this sub-tile, whether something is stored there or not.
         if constexpr (UPDATES) {
-            auto touch = [&](bool here, int r_lo, int r_hi, int p, int hi) {
+            auto touch = [&](int b, bool here, int r_lo, int r_hi, int p, int hi) {
                 const bool exists = u_cur + lane < n_upd;
-                bool done = exists && pu_row < row0;              // a row before the sub-tile's first: nothing left to find
+                bool done = exists && pu_row[b] < row0;           // a row before the sub-tile's first: nothing left to find
                 if (here && p < hi) {
                     done = true;
-                    if (s_col[1 + p] == pu_col) {
-                        s_newval[p] = pu_val;
+                    if (s_col[1 + p] == pu_col[b]) {
+                        s_newval[p] = pu_val[b];
                         atomicOr(&s_mark[p], 2);
                     }
                 } else if (exists && r_lo < e_stop) {
@@ -553,15 +533,25 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
                 }
                 return __popcll(__ballot(done));
             };
-            int u_got = touch(here[2], r_lo[2], r_hi[2], at[2], hi[2]);
+            auto find_and_touch = [&](int b) {
+                int r0, r1, lo, h;
+                const bool in = stretch(u_cur + lane < n_upd, pu_row[b], r0, r1, lo, h);
+                return touch(b, in, r0, r1, search_one(lo, h, pu_col[b]), h);
+            };
+            int u_got = touch(0, here[2], r_lo[2], r_hi[2], at[2], hi[2]);
+#pragma unroll
+            for (int b = 1; b < kBatches; ++b)
+                if (u_got == kWave) {
+                    u_cur += kWave;
+                    u_got = find_and_touch(b);
+                }
+                else break;
 #pragma unroll 1
             while (u_got == kWave) {
                 u_cur += kWave;
-                load_updates();
+                load_batch(0);
                 __builtin_amdgcn_s_waitcnt(kVmcntZero);
-                int r0, r1, lo, h;
-                const bool in = stretch(u_cur + lane < n_upd, pu_row, r0, r1, lo, h);
-                u_got = touch(in, r0, r1, search_one(lo, h, pu_col), h);
+                u_got = find_and_touch(0);
             }
             u_cur += u_got;
         }
@@ -827,15 +817,20 @@ extern "C" int dgnn_delta_h2d(const int32_t *h_add_row, const int32_t *h_add_col
 
 namespace {
 
-// Entries per wavefront of the merge: a multiple of the sub-tile, at most kMaxRange, smaller when the input is small.
+// Entries per wavefront of the merge, a multiple of the sub-tile: where all of them fit the device at once, one such generation, so that
+// no range pays for its start a second time, beyond that shorter ones, which end together.  us per rebuild with 16384 wavefronts or ranges of
+// 8192, and with these: R-MAT 2^18, 4.2 M entries 21.4 / 19.1, 2^20, 17 M 44.3 / 41.1, 2^23, 140 M 344 / 341
+// (of 4096 333, but their records would not fit the workspace that callers were told to bring).
 int64_t merge_range_length(int64_t nnz_prev) {
-    int64_t range_len = (nnz_prev + kTargetWaves - 1) / kTargetWaves;
-    range_len = (range_len + kSub - 1) / kSub * kSub;
-    return std::min<int64_t>(std::max<int64_t>(range_len, kSub), kMaxRange);
+    const int64_t share = ((nnz_prev + kWavesAtOnce - 1) / kWavesAtOnce + kSub - 1) / kSub * kSub;
+    return share <= kLongestShare ? std::max<int64_t>(share, kSub) : kLongRange;
 }
-// No call with at most nnz_prev entries has more ranges than this (a smaller snapshot gets shorter ranges, never more
-// than kTargetWaves + 1 of them), so a workspace sized for the largest snapshot of a block serves every step.
-int64_t max_ranges(int64_t nnz_prev) { return std::max<int64_t>(kTargetWaves + 1, (nnz_prev + kMaxRange - 1) / kMaxRange) + 1; }
+// The workspace holds a record per range of any snapshot of at most nnz_prev entries, so that one sized for the largest snapshot of a
+// block serves every step: 40 bytes per 8192 entries, never less than 16386 times, as callers are told.
+constexpr int64_t kRoomEntries = 8192, kRoomBytes = 40, kLeastRoom = 16385;
+int64_t workspace_records(int64_t nnz_prev) { return std::max<int64_t>(kLeastRoom, (nnz_prev + kRoomEntries - 1) / kRoomEntries) + 1; }
+static_assert(kLeastRoom * kRoomBytes >= (kWavesAtOnce + 1) * (int64_t)sizeof(RangeStart) && kRoomBytes * kLongRange >= (int64_t)sizeof(RangeStart) * kRoomEntries,
+              "records of short and of long snapshots fit");
 
 }  // namespace
 
@@ -843,7 +838,7 @@ extern "C" int dgnn_delta_rebuild_workspace(int64_t n, int64_t nnz_prev, int64_t
     if (!bytes) return DGNN_ERR_NULL;
     if (n <= 0 || nnz_prev < 0 || n_add < 0 || n_del < 0) return DGNN_ERR_SHAPE;
     if (!fits_index(n + 1) || !fits_index(nnz_prev + n_add)) return DGNN_ERR_OVERFLOW;
-    *bytes = round_up((size_t)max_ranges(nnz_prev) * sizeof(RangeStart), 256);   // the row every range of the merge begins in
+    *bytes = round_up((size_t)workspace_records(nnz_prev) * kRoomBytes, 256);   // the row every range of the merge begins in
     return DGNN_OK;
 }
 
@@ -890,15 +885,14 @@ int rebuild(int64_t n, const int32_t *rowptr_prev, const int32_t *colidx_prev, i
     const int cap = (int)min(cap_next, (int64_t)2147483647LL);
     const int64_t range_len = merge_range_length(nnz_prev);
     const int n_ranges = (int)((nnz_prev + range_len - 1) / range_len);
-    const int32_t *upd_row = n_upd > 0 ? vals->upd_row : nullptr;
 
     const dim3 row_grid((unsigned)((n + kRowTile - 1) / kRowTile));
     if (aligned16(rowptr_prev) && aligned16(rowptr_next) && aligned16(dinv_next))
         hipLaunchKernelGGL(rowptr_kernel<true>, row_grid, dim3(kRowThreads), 0, s, (int)n, rowptr_prev, add_row, (int)n_add, del_row,
-                           (int)n_del, rowptr_next, dinv_next, (int)range_len, n_ranges, range_start, upd_row, (int)n_upd, d_status);
+                           (int)n_del, rowptr_next, dinv_next, (int)range_len, n_ranges, range_start, d_status);
     else
         hipLaunchKernelGGL(rowptr_kernel<false>, row_grid, dim3(kRowThreads), 0, s, (int)n, rowptr_prev, add_row, (int)n_add, del_row,
-                           (int)n_del, rowptr_next, dinv_next, (int)range_len, n_ranges, range_start, upd_row, (int)n_upd, d_status);
+                           (int)n_del, rowptr_next, dinv_next, (int)range_len, n_ranges, range_start, d_status);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     if ((flags & DGNN_VALIDATE) && d_status) {
         int64_t work = n_add + n_del + n;
@@ -914,15 +908,15 @@ int rebuild(int64_t n, const int32_t *rowptr_prev, const int32_t *colidx_prev, i
     }
     const dim3 grid((unsigned)n_ranges);
     if (vals && n_upd > 0)
-        hipLaunchKernelGGL((merge_kernel<true, true>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
-                           (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
+        hipLaunchKernelGGL((n_upd > nnz_prev / 4 ? merge_kernel<true, 8> : merge_kernel<true, 1>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev,
+                           (int)nnz_prev, (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, vals->upd_row, vals->upd_col, vals->upd_val, (int)n_upd);
     else if (vals)
-        hipLaunchKernelGGL((merge_kernel<true, false>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
+        hipLaunchKernelGGL((merge_kernel<true, 0>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
                            (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, nullptr, nullptr, nullptr, 0);
     else
-        hipLaunchKernelGGL((merge_kernel<false, false>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
+        hipLaunchKernelGGL((merge_kernel<false, 0>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
                            (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
     DGNN_RETURN_IF_LAUNCH_FAILED();

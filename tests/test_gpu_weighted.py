@@ -141,6 +141,32 @@ def test_weighted_rebuild_of_tiles_that_own_long_list_stretches(n, counts):
     assert np.array_equal(got[2], f32(want[2]))
 
 
+# updates per stored entry: one batch ahead (a quarter), eight (more), every entry, and several that name nothing per stored one
+@pytest.mark.parametrize("share,absent", [(0.25, 0), (0.26, 0), (1.0, 0), (1.0, 4)])
+@pytest.mark.parametrize("n", [40, 3000])
+def test_weighted_rebuild_with_long_update_lists(n, share, absent):
+    """3000 rows of 20: ranges of one sub-tile of 512 entries; sub-tiles with up to 512 updates of theirs and 2500 in all."""
+    rng = np.random.default_rng(n + absent)
+    rows = np.concatenate([np.arange(n), rng.integers(0, n, 19 * n)])
+    rp, ci = oracle.csr_from_edges(n, rows.astype(np.int32), np.concatenate([np.arange(n), rng.integers(0, n, 19 * n)]).astype(np.int32))
+    val = f32(rng.uniform(0.1, 1.0, ci.size))
+    r_of = np.repeat(np.arange(n, dtype=np.int32), np.diff(rp))
+    key = r_of.astype(np.int64) * n + ci
+    off = rng.permutation(np.flatnonzero(r_of != ci))
+    gone = np.sort(off[:ci.size // 50])
+    kept = rng.permutation(np.setdiff1d(np.arange(ci.size), gone))[:int(share * ci.size)]
+    free = np.setdiff1d(np.arange(n * n), key)
+    new = np.sort(rng.choice(free, min(ci.size // 50, free.size), replace=False))
+    nothing = rng.choice(np.setdiff1d(free, new), min(absent * ci.size, free.size - new.size), replace=False) if absent else np.zeros(0, np.int64)
+    upd = np.sort(np.concatenate([key[kept], nothing]))
+    add = ((new // n).astype(np.int32), (new % n).astype(np.int32), f32(rng.uniform(1, 2, new.size)))
+    dele, change = (r_of[gone], ci[gone]), ((upd // n).astype(np.int32), (upd % n).astype(np.int32), f32(rng.uniform(3, 4, upd.size)))
+    want = oracle.delta_apply_weighted(n, rp, ci, val, add=add, dele=dele, upd=change)
+    got = gpu_rebuild_weighted(n, rp, ci, val, add, dele, change, merged=True)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert np.array_equal(got[2], f32(want[2]))
+
+
 def test_weighted_rebuild_reports_an_unsorted_update_list():
     """Declared sorted, but not: the check says so, and nothing is written outside the result."""
     wl = WORKLOADS["c1"]
