@@ -329,9 +329,9 @@ class BlockTrainer:
         return out
 
     # ------------------------------------------------------------------ forward, keeping activations
-    def forward(self, after=None) -> torch.Tensor:
+    def forward(self, after=None, mix: bool = True) -> torch.Tensor:
         """`after`: the snapshot behind the block is wanted too, [(lists, rowptr, colidx)] for A and, where a transposed
-        chain is kept, for A^T."""
+        chain is kept, for A^T.  Without `mix` the pass ends with the top layer's frames, which is all that backward() takes."""
         blk, stack = self.blk, self.stack
         stream = torch.cuda.current_stream(self.dev).cuda_stream
         if self.series:
@@ -361,7 +361,7 @@ class BlockTrainer:
                     B.delta_rebuild(chain.rowptr[slot], chain.colidx[slot], blk.nnz[-1], ar, ac, int(ar.numel()), dr, dc, int(dr.numel()),
                                     rowptr, colidx, None, self.ws_rebuild)
         top = self.z[blk.layers - 1, : blk.T]
-        if blk.window:
+        if blk.window and mix:
             with self._stage("mproduct"):
                 B.mproduct_block(top, self.y[: blk.T], blk.window, self.t0, z_before=self.z_before)
             return self.y[: blk.T]
@@ -571,7 +571,8 @@ class CheckpointedTrainer:
             a, e = self.bounds[b]
             if self.resident != b:                      # the last block's activations are still there from the forward pass
                 self._bind(b)
-                tr.forward()                                                # the rerun
+                # the rerun: of the M-transform's frames nothing goes back (24 x 60 K x 128 bf16 in blocks of 12: 68 us of 2300)
+                tr.forward(mix=False)
             self.resident = None
             after = g_y[e:min(e + w1, s.T)] if (w1 and e < s.T) else None
             tr.backward(g_y[a:e], g_after=after, accumulate=b != last)
