@@ -269,6 +269,9 @@ class CdgcnTrainer(CdgcnLayer):
 
     def forward(self) -> torch.Tensor:
         blk, m = self.blk, self.together
+        # Where Y of all timesteps is kept, one LSTM over them, whose state then stays on chip between the steps (2^18 vertices, 64 + 32
+        # columns fp32, four timesteps: a launch each 1341 us a training step, one for all 1247)
+        whole = self.keep and self.lstm_fused
         self._bind()
         if self.series:
             self.rebuild_all()
@@ -281,7 +284,10 @@ class CdgcnTrainer(CdgcnLayer):
                     self._rebuild_transposed(j, j + 1, blk.nnz[j - 1], reverse=False)
             y0, y = self._activations(t, k)
             self.gcn_steps(t, k, y0, y)
-            self.lstm_steps(t, k, y, self.c_all[t], self.c_all[t + 1:t + 1 + k])
+            if not whole:
+                self.lstm_steps(t, k, y, self.c_all[t], self.c_all[t + 1:t + 1 + k])
+        if whole:
+            self.lstm_steps(0, blk.T, self._activations(0, blk.T)[1], self.c_all[0], self.c_all[1:1 + blk.T])
         return self.h_all
 
     def _rebuild_transposed(self, src_t: int, dst_t: int, nnz_src: int, reverse: bool) -> None:
