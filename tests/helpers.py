@@ -12,15 +12,17 @@ def assert_close(got, expect, dtype, what="", stores=1):
     """|g - o| <= rtol |o| + rtol rms(o), rtol = 1e-4 for fp32 storage, 2e-2 for bf16 storage.
     (Purely relative error is meaningless next to the zeros ReLU produces.)  The bound is the one for a
     result that was rounded to its storage type once; a bf16 result that has passed through `stores`
-    consecutive bf16 tensors carries that many independent roundings and gets sqrt(stores) times the bound."""
+    consecutive bf16 tensors carries that many independent roundings and gets sqrt(stores) times the bound.
+    What is no number fits only where none is expected, an infinity only where that one is."""
     got = np.asarray(got, dtype=np.float64)
     expect = np.asarray(expect, dtype=np.float64)
     assert got.shape == expect.shape, (what, got.shape, expect.shape)
     rtol = RTOL[dtype] * (float(stores) ** 0.5 if dtype == torch.bfloat16 else 1.0)
     rms = float(np.sqrt(np.mean(expect ** 2))) if expect.size else 0.0
-    err = np.abs(got - expect)
+    with np.errstate(invalid="ignore"):
+        err = np.where((got == expect) | (np.isnan(got) & np.isnan(expect)), 0.0, np.abs(got - expect))
     bound = rtol * np.abs(expect) + rtol * rms
-    bad = err > bound
+    bad = ~(err <= bound)
     assert not bad.any(), f"{what}: {int(bad.sum())} of {bad.size} outside tolerance, max err {err.max():.3e}, rms {rms:.3e}"
 
 
