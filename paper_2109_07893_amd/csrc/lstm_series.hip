@@ -70,12 +70,14 @@ template <> struct Store<true> {
 // ---- fp32 products on the bf16 matrix cores.  An fp32 number is the sum of three bf16 numbers, each the rounded rest of the
 // ones before it (8 + 8 + 8 bits), and of the nine products of two such sums the six largest are formed, 2.6 times as fast as the fp32 matrix
 // instruction forms the one; what is left out is below 2^-25 of the product, less than the rounding of one of the sums' additions.
-// Numbers beyond kSplitMost, whose first part would be infinite, and infinities, whose rest would not be a number, send the
-// wavefront's step to the fp32 instruction.
+// From kSplitBelow on a wavefront's step takes the fp32 instruction: there a smaller product could pass fp32 ahead of the largest, with the
+// other sign, and the sum would be no number where the product is infinite.  Below, the at most 128 products of a sum, 2^120 each, stay
+// in fp32 whatever their order.
 constexpr int kParts = 3;
-constexpr uint32_t kSplitMost = 0x7f7f7fffu;           // the largest fp32 that rounds to a finite bf16
+constexpr uint32_t kSplitBelow = 0x5d800000u;          // 2^60
+constexpr uint32_t kRoundsFinite = 0x7f7f7fffu;        // the largest fp32 that rounds to a finite bf16
 
-// Whether all numbers noted can be split: the largest pattern of either sign (half an instruction each per number).
+// Whether all numbers noted are to be split: the largest pattern of either sign (half an instruction each per number).
 struct Largest {
     int above = 0;
     uint32_t below = 0;
@@ -83,7 +85,7 @@ struct Largest {
         above = max(above, (int)bits);
         below = max(below, bits);
     }
-    __device__ __forceinline__ bool odd() const { return above > (int)kSplitMost || below > (kSplitMost | 0x80000000u); }
+    __device__ __forceinline__ bool odd() const { return above >= (int)kSplitBelow || below >= (kSplitBelow | 0x80000000u); }
 };
 
 __device__ __forceinline__ void split(const float (&v)[8], bf16x8 (&part)[kParts]) {
@@ -141,7 +143,7 @@ struct Weights {
     static constexpr int G4 = 4 * HID, NT = G4 / 32, K = FY + HID;
     static constexpr int kLd = K + 8, kImage = G4 * kLd, kSize = BF16 ? kImage : kParts * kImage;
     typedef typename Store<BF16>::Elem Elem;
-    // whether this thread has met a number that cannot be split
+    // whether this thread has met a number that is not to be split (its parts are put together again: at())
     static __device__ __forceinline__ bool stage(uint16_t *s_w, const Elem *__restrict__ w_x, const Elem *__restrict__ w_h, int tid, int threads) {
         bool odd = false;
         for (int idx = tid; idx < K * G4; idx += threads) {
@@ -152,11 +154,11 @@ struct Weights {
             } else {
                 const uint32_t bits = __float_as_uint(v) & 0x7fffffffu;
                 const bool whole = bits >= 0x7f800000u;            // an infinity, or no number: the first part is all of it
-                odd |= bits > kSplitMost;
+                odd |= bits >= kSplitBelow;
                 float rest = v;
 #pragma unroll
                 for (int part = 0; part < kParts; ++part) {
-                    const uint32_t p = bits > kSplitMost && !whole ? __float_as_uint(rest) >> 16 : f32_to_bf16(rest);
+                    const uint32_t p = bits > kRoundsFinite && !whole ? __float_as_uint(rest) >> 16 : f32_to_bf16(rest);
                     s_w[part * kImage + col * kLd + k] = (uint16_t)p;
                     rest = whole ? 0.0f : rest - __uint_as_float(p << 16);
                 }

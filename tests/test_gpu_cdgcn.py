@@ -506,6 +506,66 @@ def test_fp32_lstm_with_numbers_that_cannot_be_split(hidden, f_y, where):
         assert_close(to_f64(c[t]), cw.numpy(), torch.float32, f"c_{t + 1}")
 
 
+# numbers that could be split, but not their products: 1e22 x 1e22 passes the largest fp32 (and 3e38 x 1e3 does), as 2^60 x 2^60 does not
+@pytest.mark.parametrize("left,right", [(1e22, 1e22), (1e22, -1e22), (3e38, 1003.0), (2.0 ** 60, 2.0 ** 60), (1.15e18, -1.15e18)])
+@pytest.mark.parametrize("hidden", [32, 16])
+def test_fp32_lstm_with_products_beyond_fp32(hidden, left, right):
+    """The gate whose pre-activation passes fp32 saturates, going forward and back, as 64-bit arithmetic has it; both rows of gradients of
+    the one vertex and the 31 others of its tile stay numbers."""
+    n, T, f_y, row = 70, 2, 2 * hidden, 33
+    y, h0, c0, g_h = (randn(s, 40 + k) for k, s in enumerate(((T, n, f_y), (n, hidden), (n, hidden), (T, n, hidden))))
+    w_x, w_h = randn((f_y, 4 * hidden), 50) / f_y ** 0.5, randn((hidden, 4 * hidden), 51) / hidden ** 0.5
+    y[:, :, 3] = 0.0                                # ... met by zeros elsewhere
+    y[0, row, 3] = left
+    w_x[3] = right * torch.sign(randn((4 * hidden,), 52))
+    dev = [t.to(DEV) for t in (y, h0, w_x, w_h, c0, g_h)]
+    h, c = torch.empty((T, n, hidden), device=DEV), torch.empty((T, n, hidden), device=DEV)
+    dg.lstm_series(dev[0], dev[1], dev[2], dev[3], None, dev[4], c, h)
+    da, dy1, dh, dc = (torch.empty(s, device=DEV) for s in ((T, n, 4 * hidden), (T, n, hidden), (n, hidden), (n, hidden)))
+    dg.lstm_series_backward(dev[0], dev[1], h, dev[2], dev[3], None, dev[4], c, dev[5], da, dy1, dh, dc, carried=False)
+    gates = [(y[t].double() @ w_x.double()).requires_grad_() for t in range(T)]
+    hw, cw, frames = h0.double().requires_grad_(), c0.double().requires_grad_(), []
+    first = hw, cw
+    for t in range(T):
+        i, f, g, o = (gates[t] + hw @ w_h.double()).split(hidden, 1)
+        cw = torch.sigmoid(f) * cw + torch.sigmoid(i) * torch.tanh(g)
+        hw = torch.sigmoid(o) * torch.tanh(cw)
+        frames.append((hw, cw))
+    sum((hw * g_h[t].double()).sum() for t, (hw, _) in enumerate(frames)).backward()
+    for t, (hw, cw) in enumerate(frames):
+        assert_close(to_f64(h[t]), hw.detach().numpy(), torch.float32, f"h_{t + 1}")
+        assert_close(to_f64(c[t]), cw.detach().numpy(), torch.float32, f"c_{t + 1}")
+        d_gates = gates[t].grad
+        assert_close(to_f64(da[t]), d_gates.numpy(), torch.float32, f"da_{t + 1}")
+        want = torch.where(y[t, :, hidden:] > 0, (d_gates @ w_x.double().t())[:, hidden:], 0.0)
+        assert_close(to_f64(dy1[t]), want.numpy(), torch.float32, f"dY1_{t + 1}")
+    assert_close(to_f64(dh), first[0].grad.numpy(), torch.float32, "dh_0")
+    assert_close(to_f64(dc), first[1].grad.numpy(), torch.float32, "dc_0")
+
+
+def test_fp32_lstm_adjoint_with_products_beyond_fp32():
+    """A gradient and a weight whose product passes fp32: infinite where it is, of the sign that it has, and a number elsewhere."""
+    n, hidden, f_y, row = 40, 32, 64, 5
+    y, h0, c0, g_h = (randn(s, 60 + k) for k, s in enumerate(((1, n, f_y), (n, hidden), (n, hidden), (1, n, hidden))))
+    y, c0 = y.abs(), c0.abs() + 1.0
+    w_x, w_h = randn((f_y, 4 * hidden), 70) / f_y ** 0.5, randn((hidden, 4 * hidden), 71) / hidden ** 0.5
+    g_h[0, row], g_h[0, row, 3] = 0.0, 1e24
+    w_x[hidden + 7], y[0, :, hidden + 7] = 0.0, 1e-30     # the gates hardly see it ...
+    w_x[hidden + 7, 3 * hidden + 3] = -1e22               # ... but the output gate's gradient of element 3 meets it going back
+    dev = [t.to(DEV) for t in (y, h0, w_x, w_h, c0, g_h)]
+    h, c = torch.empty((1, n, hidden), device=DEV), torch.empty((1, n, hidden), device=DEV)
+    dg.lstm_series(dev[0], dev[1], dev[2], dev[3], None, dev[4], c, h)
+    da, dy1, dh, dc = (torch.empty(s, device=DEV) for s in ((1, n, 4 * hidden), (1, n, hidden), (n, hidden), (n, hidden)))
+    dg.lstm_series_backward(dev[0], dev[1], h, dev[2], dev[3], None, dev[4], c, dev[5], da, dy1, dh, dc, carried=False)
+    want = (to_f64(da[0]).reshape(n, -1) @ w_x.double().numpy().T)[:, hidden:]
+    got = to_f64(dy1[0]).reshape(n, -1)
+    beyond = np.abs(want) > 3.4028235e38
+    assert beyond[row, 7] and beyond.sum() == 1
+    assert got[row, 7] == np.copysign(np.inf, want[row, 7])
+    assert_close(got[~beyond], want[~beyond], torch.float32, "dY1")
+    assert np.isfinite(to_f64(dh)).all()
+
+
 def test_fp32_lstm_backward_with_an_infinite_gradient():
     """The row that receives it sends no number on; the 31 others of its tile are as without it."""
     n, hidden, f_y, row = 40, 32, 64, 5
