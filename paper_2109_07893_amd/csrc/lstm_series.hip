@@ -791,23 +791,22 @@ __global__ __launch_bounds__(kGradWaves *kWave) void lstm_wgrad_kernel(const voi
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[ti][v] = 0.0f;
     auto row_in_step = [&](int e) { return BF16 ? 8 * hh + e : 2 * e + hh; };
+    auto add_to_bias = [&](auto g) { bsum += ((g(0) + g(1)) + (g(2) + g(3))) + ((g(4) + g(5)) + (g(6) + g(7))); };     // a chain of an eighth of the rows
     auto multiply = [&](const Raw (&xa)[NI][8], const Raw (&gb)[8]) {
         if constexpr (BF16) {
             const uintx4 pb = {gb[0] | (gb[1] << 16), gb[2] | (gb[3] << 16), gb[4] | (gb[5] << 16), gb[6] | (gb[7] << 16)};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bsum += bf16_to_f32(gb[e]);
+            add_to_bias([&](int e) { return bf16_to_f32(gb[e]); });
 #pragma unroll
             for (int ti = 0; ti < NI; ++ti) {
                 const uintx4 pa = {xa[ti][0] | (xa[ti][1] << 16), xa[ti][2] | (xa[ti][3] << 16), xa[ti][4] | (xa[ti][5] << 16), xa[ti][6] | (xa[ti][7] << 16)};
                 acc[ti] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pa), __builtin_bit_cast(bf16x8, pb), acc[ti], 0, 0, 0);
             }
         } else {
+            add_to_bias([&](int e) { return gb[e]; });
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                bsum += gb[e];
+            for (int e = 0; e < 8; ++e)
 #pragma unroll
                 for (int ti = 0; ti < NI; ++ti) acc[ti] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[ti][e], gb[e], acc[ti], 0, 0, 0);
-            }
         }
     };
     // Steps whose 16 rows are all there and take their states from one tensor: the bases are uniform (scalar), a lane's offsets
@@ -871,17 +870,20 @@ __global__ __launch_bounds__(kGradWaves *kWave) void lstm_wgrad_kernel(const voi
     if (hh == 0) mine[K * G4 + tj * 32 + i] = bsum;
 }
 
-// The partial results in worker order: sixteen wavefronts take a slice of the workers each, then the slices are added in order.
+// The partial results in worker order: sixteen wavefronts take a slice of the workers each, then the slices are added in order.  In 64
+// bits and rounded once: added in fp32 they were most of the error of a sum over all vertices (40 K vertices, 4 steps, 64 + 32
+// columns fp32, against 64 bits: db 6.5e-8 -> 3.0e-8, dW_x 6.9e-8 -> 3.2e-8, dW_h 9.4e-8 -> 7.0e-8, of which h's own error is 6.1e-8), in the
+// same time (2^18 vertices, both kernels 301 / 295 us: what bounds it is the partial results' way from memory).
 constexpr int kReduceSlices = 16;
 __global__ __launch_bounds__(kReduceSlices *kWave) void lstm_wgrad_reduce_kernel(const float *__restrict__ partial, int workers, int x_elems, int h_elems,
                                                                                 int b_elems, float *__restrict__ dw_x, float *__restrict__ dw_h,
                                                                                 float *__restrict__ db, int accumulate) {
-    __shared__ float s_sum[kReduceSlices][kWave];
+    __shared__ double s_sum[kReduceSlices][kWave];
     const int lane = threadIdx.x & (kWave - 1), slice = threadIdx.x / kWave;
     const int elems = x_elems + h_elems + b_elems, e = blockIdx.x * kWave + lane;
     const int per = (workers + kReduceSlices - 1) / kReduceSlices;
     const int p0 = slice * per, p1 = min(p0 + per, workers);
-    float sum = 0.0f;
+    double sum = 0.0;
     if (e < elems) {
 #pragma unroll 8
         for (int p = p0; p < p1; ++p) sum += partial[(int64_t)p * elems + e];
@@ -889,11 +891,11 @@ __global__ __launch_bounds__(kReduceSlices *kWave) void lstm_wgrad_reduce_kernel
     s_sum[slice][lane] = sum;
     __syncthreads();
     if (slice == 0 && e < elems) {
-        float total = s_sum[0][lane];
+        double total = s_sum[0][lane];
 #pragma unroll
         for (int k = 1; k < kReduceSlices; ++k) total += s_sum[k][lane];
         float *dst = e < x_elems ? dw_x + e : e < x_elems + h_elems ? dw_h + (e - x_elems) : db + (e - x_elems - h_elems);
-        *dst = accumulate ? *dst + total : total;
+        *dst = (float)(accumulate ? *dst + total : total);
     }
 }
 

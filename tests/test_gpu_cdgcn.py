@@ -481,6 +481,23 @@ def test_parameter_gradients_of_the_lstm_at_the_edges_of_its_steps(dtype, hidden
         assert np.all(np.abs(to_f64(got).reshape(bound.shape) - left.T @ g) <= bound)
 
 
+@pytest.mark.parametrize("n,hidden,dtype", [(40_000, 32, torch.float32), (40_000, 16, torch.float32), (40_000, 32, torch.bfloat16), (1000, 32, torch.float32)])
+def test_parameter_gradients_of_the_lstm_are_rounded_once(n, hidden, dtype):
+    """Sums over all vertices with a direction of their own, as upstream gradients have it: what the result's own rounding leaves (2^-24
+    of numbers spread over a power of two: 2.5e-8 in the 2-norm) and the chains of the wavefronts, whose errors meet as 512 of them are
+    added (at most 20 rounds of chains of eight here: their share is below 2e-8)."""
+    T, f_y = 4, 2 * hidden
+    sign = torch.sign(randn((1, 4 * hidden), 81)).to(DEV)
+    y, h0, h = (randn(s, 82 + k, dtype).to(DEV).abs() for k, s in enumerate([(T, n, f_y), (n, hidden), (T, n, hidden)]))
+    da = (randn((T, n, 4 * hidden), 85).to(DEV) * 0.5 + sign).to(dtype)
+    dw_x, dw_h, db = (torch.empty(s, device=DEV) for s in ((f_y, 4 * hidden), (hidden, 4 * hidden), (4 * hidden,)))
+    ws = torch.empty(dg.binding.lstm_weight_grad_workspace(f_y, hidden), dtype=torch.uint8, device=DEV)
+    dg.lstm_weight_grad(y, h0, h, da, dw_x, dw_h, db, ws)
+    g, before = da.double().view(T * n, -1), torch.cat([h0[None], h[:-1]]).double().view(T * n, -1)
+    for got, want in ((dw_x, y.double().view(T * n, -1).t() @ g), (dw_h, before.t() @ g), (db, g.sum(0))):
+        assert float((got - want).norm() / want.norm()) <= 4.5e-8
+
+
 # fp32 numbers that are no sum of three bf16 numbers: infinite, or so large that the first of the three would be; at the edge of a tile
 @pytest.mark.parametrize("hidden,f_y", [(32, 64), (16, 16)])
 @pytest.mark.parametrize("where", ["y", "h0", "w"])
