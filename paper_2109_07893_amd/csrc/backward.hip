@@ -63,7 +63,7 @@ struct Split {
 // MASKED: G is taken where Z > 0 only (the gradient through the ReLU, which then needs no pass of its own).
 // The gradient is the sum over `items` items from the first one on, n rows each, whose steps are one line: worker `me` takes steps
 // me, me + workers, ... of it.  LINE: there are several; the worker then adds up its steps of each item on their own, as a call per
-// item does (one sum over all of its steps: 12 x 60 K x 128 bf16 1.4e-7 -> 2.4e-7 away from 64 bits).
+// item does (one sum over all of its steps: 12 x 60 K x 128 bf16 1.4e-7 -> 2.4e-7 away from 64 bits while partial results met in fp32).
 template <int FIN, int FOUT, bool BF16, bool MASKED, bool LINE>
 __device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items, int64_t n, int64_t n_steps, float *__restrict__ partial) {
     using S = Split<FIN, FOUT>;
@@ -251,21 +251,24 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave) void wgrad_kernel(Batch batc
 }
 
 // dw[e] = (accumulate ? dw[e] : 0) + sum over the workers' partial results: sixteen wavefronts take a slice of
-// the workers each (in worker order), then the sixteen slice sums are added in slice order: a fixed order.
+// the workers each (in worker order), then the sixteen slice sums are added in slice order: a fixed order.  In 64 bits and rounded
+// once per item: a line of items has one such sum where calls have one each, whose roundings average out, and with fp32 additions it
+// was the further off on positive numbers (12 x 60 K x 128 bf16: 6.2e-8 from 64 bits in calls, 6.6e-8 as a line; now 5.8e-8 and
+// 3.2e-8; 6 x 200 K 4.7e-8 and 6.0e-8, now 3.6e-8 and 1.9e-8), in the same time (116 / 115 us).
 // `items` of them in a row have one dw; apart: each with partial results of its own, added to dw one after the other.
 constexpr int kReduceSlices = 16;
 __global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, int items, int apart, const float *__restrict__ partial, int workers,
                                                                             int elems, int accumulate) {
     float *__restrict__ dw = as_global(batch.item[blockIdx.y * items].dw);
     partial += (int64_t)blockIdx.y * workers * elems;
-    __shared__ float s_sum[kReduceSlices][kWave];
+    __shared__ double s_sum[kReduceSlices][kWave];
     const int lane = threadIdx.x & (kWave - 1), slice = threadIdx.x / kWave;
     const int e = blockIdx.x * kWave + lane;
     const int per = (workers + kReduceSlices - 1) / kReduceSlices;
     const int p0 = slice * per, p1 = min(p0 + per, workers);
     float out = accumulate && e < elems ? dw[e] : 0.0f;
     for (int k = 0; k < (apart ? items : 1); ++k, partial += (int64_t)workers * elems) {
-        float sum = 0.0f;
+        double sum = 0.0;
         if (e < elems) {
 #pragma unroll 8
             for (int p = p0; p < p1; ++p) sum += partial[(int64_t)p * elems + e];
@@ -273,10 +276,10 @@ __global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batc
         if (k) __syncthreads();
         s_sum[slice][lane] = sum;
         __syncthreads();
-        float total = s_sum[0][lane];
+        double total = s_sum[0][lane];
 #pragma unroll
         for (int s = 1; s < kReduceSlices; ++s) total += s_sum[s][lane];
-        out = accumulate || k ? out + total : total;
+        out = (float)(accumulate || k ? out + total : total);
     }
     if (slice == 0 && e < elems) dw[e] = out;
 }

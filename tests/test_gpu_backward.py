@@ -258,3 +258,21 @@ def test_weight_grad_of_items_with_one_dw(dtype, f_in, f_out, into, n):
         assert_close(to_f64(dw), want.cpu().numpy(), torch.float32, f"{into} n={n}")
         if n < 1000:
             assert torch.equal(dw, single)
+
+
+@pytest.mark.parametrize("k,n,f,dtype", [(12, 60_013, 128, torch.bfloat16), (16, 20_003, 64, torch.bfloat16), (4, 1_000_000, 16, torch.float32)])
+def test_weight_grad_of_many_positive_items_with_one_dw(k, n, f, dtype):
+    """Sums of one sign, in which nothing averages out: the result's own rounding (2.5e-8 in the 2-norm), and as much for the chains of
+    the workgroups' sums; partial results added in fp32 left 5.7e-8 to 6.6e-8 here."""
+    from paper_2109_07893_amd import binding as B
+    from paper_2109_07893_amd.batch import WeightGradTable, pointers
+    x = torch.stack([randn((n, f), 90 + j).to(DEV).abs().to(dtype) for j in range(k)])
+    g = torch.stack([(randn((n, f), 190 + j).to(DEV) * 0.5 + 1.0).to(dtype) for j in range(k)])
+    ws = torch.empty(dg.weight_grad_workspace(f, f), dtype=torch.uint8, device=DEV)
+    dw = torch.empty((f, f), device=DEV)
+    table = WeightGradTable(k)
+    for column, values in ((table.X, pointers(list(x))), (table.G, pointers(list(g))), (table.DW, [dw.data_ptr()] * k)):
+        table.column(column, values)
+    B.weight_grad_batch(k, table.at(), n, f, f, False, B._dtype_code(x), ws, torch.cuda.current_stream().cuda_stream)
+    want = sum(x[j].double().t() @ g[j].double() for j in range(k))
+    assert float((dw - want).norm() / want.norm()) <= 4e-8
