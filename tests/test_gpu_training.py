@@ -271,6 +271,24 @@ def test_one_weight_per_timestep():
             assert_close(to_f64(tr.dw_t[t][layer]), dw, torch.float32, f"dW_t t={t + 1} layer {layer}")
 
 
+@pytest.mark.parametrize("n,f,dtype,want_dx", [(20_003, 64, "bf16", False), (30_001, 64, "f32", True)])
+def test_weight_gradients_of_every_timestep_over_all_of_the_device(n, f, dtype, want_dx):
+    """One weight per timestep and X in frames of its own: the gradients of the first layer are calls of their own, whose sums over the
+    vertices are spread over the whole device (side by side in one launch they would be eight times as long)."""
+    wl = replace(WORKLOADS["c2"].scaled(n, T=8), layers=1, f=f, dtype=dtype, window=0, name="evolving")
+    blk = make_block(wl, DEV, gen_device="cpu")
+    blk.w_t = [[glorot_weight(wl, 0, t=t).to(DEV)] for t in range(1, wl.T + 1)]
+    tr = make_trainer(wl, blk, want_dx=want_dx)
+    assert tr.stack.p0 is None and tr.stack.together >= wl.T
+    tr.forward()
+    tr.backward(torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV))
+    ws = torch.empty(dg.weight_grad_workspace(f, f), dtype=torch.uint8, device=DEV)
+    for t in range(wl.T):
+        want = torch.empty((f, f), device=DEV)
+        dg.weight_grad(blk.x[t], tr.stack.h[t], want, ws)
+        assert torch.equal(tr.dw_t[t][0], want), t
+
+
 def test_gradient_descent_on_the_weights_reduces_a_loss():
     """End to end: the weight gradients drive plain gradient descent on L = 1/2 |Y - Y*|^2, where Y* comes from a
     hidden weight pair; the loss layer (Y - Y*) is the caller's, everything below it is the library's."""
