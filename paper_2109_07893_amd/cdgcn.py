@@ -270,8 +270,9 @@ class CdgcnTrainer(CdgcnLayer):
     def forward(self) -> torch.Tensor:
         blk, m = self.blk, self.together
         # Where Y of all timesteps is kept, one LSTM over them, whose state then stays on chip between the steps (2^18 vertices, 64 + 32
-        # columns fp32, four timesteps: a launch each 1341 us a training step, one for all 1247)
-        whole = self.keep and self.lstm_fused
+        # columns fp32, four timesteps: a launch each 1341 us a training step, one for all 1247).  A subclass that has a part of a
+        # timestep's work in its own hands meets the states of the timesteps before, and is asked for them in turn.
+        whole = self.keep and self.lstm_fused and not any(map(self._overrides, ("gcn_steps", "form_y", "lstm_steps")))
         self._bind()
         if self.series:
             self.rebuild_all()

@@ -667,6 +667,38 @@ def test_cdgcn_subclasses_are_asked_for_every_timestep(fused):
     assert not SlotsOfItsOwn(blk).series and BlockRunner(blk).series
 
 
+@pytest.mark.parametrize("hook", ["lstm_steps", "gcn_steps"])
+def test_cdgcn_trainers_that_override_a_batch_of_steps_are_asked_in_turn(hook, monkeypatch):
+    """Kept Y or not: the LSTM of a batch of timesteps right behind its GCN operations, before the next batch's."""
+    from paper_2109_07893_amd import batch
+    from paper_2109_07893_amd.cdgcn import CdgcnTrainer
+    n, T = 1003, 7
+    monkeypatch.setattr(batch, "BATCH_BYTES", 3 * n * 32 * 4)
+    wl = replace(graph("er", n, 6, T, 0.05, 0.05), f=32, dtype="f32", layers=1, window=0)
+    blk = make_block(wl, DEV, gen_device="cpu")
+    weights = [torch.randn(s, device=DEV) * 0.2 for s in ((32, 32), (64, 128), (32, 128))]
+    seen = []
+
+    class Hooked(CdgcnTrainer):
+        pass
+
+    def asked(self, t, k, *rest):
+        # h of the timesteps before is there
+        seen.append((t, k, t == 0 or bool((self.h_all[t - 1] == want[t - 1]).all())))
+        return getattr(CdgcnTrainer, hook)(self, t, k, *rest)
+    for keep in (True, False):
+        plain = CdgcnTrainer(blk, *weights, None, 32, keep_activations=keep)
+        plain.load_first()
+        want = plain.forward().clone()
+        setattr(Hooked, hook, asked)
+        tr = Hooked(blk, *weights, None, 32, keep_activations=keep)
+        tr.h_all.fill_(float("nan"))
+        tr.load_first()
+        seen.clear()
+        assert tr.together == 3 and torch.equal(tr.forward(), want)
+        assert seen == [(0, 3, True), (3, 3, True), (6, 1, True)], keep
+
+
 @pytest.mark.parametrize("dtype,f", [("f32", 32), ("f32", 16), ("bf16", 32)])
 @pytest.mark.parametrize("n,T", [(1000, 5), (30_001, 7)])
 def test_cdgcn_trainer_recomputes_what_it_was_not_asked_to_keep(dtype, f, n, T, monkeypatch):
