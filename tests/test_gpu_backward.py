@@ -276,3 +276,29 @@ def test_weight_grad_of_many_positive_items_with_one_dw(k, n, f, dtype):
     B.weight_grad_batch(k, table.at(), n, f, f, False, B._dtype_code(x), ws, torch.cuda.current_stream().cuda_stream)
     want = sum(x[j].double().t() @ g[j].double() for j in range(k))
     assert float((dw - want).norm() / want.norm()) <= 4e-8
+
+
+@pytest.mark.parametrize("dtype,f_in,f_out", [(torch.float32, 32, 64), (torch.bfloat16, 128, 128)])
+@pytest.mark.parametrize("into,n", [((0, 0, 0), 1), ((0, 0, 1, 2, 2), 333), ((0,) * 33 + (1,), 17), ((0, 0, 0, 0, 0), 20_003)])
+def test_masked_weight_grad_of_items_with_one_dw(dtype, f_in, f_out, into, n):
+    """Under a mask too, bit for bit a call per item."""
+    from paper_2109_07893_amd import binding as B
+    from paper_2109_07893_amd.batch import WeightGradTable, pointers
+    m, stream = len(into), torch.cuda.current_stream().cuda_stream
+    x, g, z = randn((m, n, f_in), n + m, dtype).to(DEV), randn((m, n, f_out), n + m + 1, dtype).to(DEV), randn((m, n, f_out), n + m + 2, dtype).to(DEV)
+    z[:, ::3, ::2], z[:, 1::3, ::5] = 0.0, -0.0
+    ws = torch.empty(dg.weight_grad_workspace(f_in, f_out), dtype=torch.uint8, device=DEV)
+    start = torch.randn((max(into) + 1, f_in, f_out), device=DEV)
+    table, one = WeightGradTable(m), WeightGradTable(1)
+    for accumulate in (False, True):
+        dw, want, single = start.clone(), start.double() * accumulate, start.clone()
+        for k, column in ((table.X, pointers(list(x))), (table.G, pointers(list(g))), (table.Z, pointers(list(z))), (table.DW, [dw[k].data_ptr() for k in into])):
+            table.column(k, column)
+        B.weight_grad_batch(m, table.at(), n, f_in, f_out, accumulate, B._dtype_code(x), ws, stream)
+        for j, k in enumerate(into):
+            one.words[0] = (x[j].data_ptr(), g[j].data_ptr(), z[j].data_ptr(), single[k].data_ptr())
+            B.weight_grad_batch(1, one.at(), n, f_in, f_out, accumulate or (j > 0 and into[j - 1] == k), B._dtype_code(x), ws, stream)
+            want[k] += x[j].double().t() @ torch.where(z[j] > 0, g[j], torch.zeros_like(g[j])).double()
+        torch.cuda.synchronize()
+        assert torch.equal(dw, single)
+        assert_close(to_f64(dw), want.cpu().numpy(), torch.float32, f"{into} n={n}")

@@ -167,6 +167,38 @@ def test_weighted_rebuild_with_long_update_lists(n, share, absent):
     assert np.array_equal(got[2], f32(want[2]))
 
 
+# ranges of two or three sub-tiles: a batch used up in part, updates left over for the rest of a row, marks and values written again;
+# an update for a fifth of the entries (one batch ahead), for more than a quarter (eight), for all, and as many that name nothing
+@pytest.mark.parametrize("share,absent", [(0.2, 0), (0.3, 0), (1.0, 0), (1.0, 1)])
+@pytest.mark.parametrize("n,deg", [(200_003, 12), (300_007, 15)])
+def test_weighted_rebuild_of_ranges_of_several_sub_tiles(n, deg, share, absent):
+    rng = np.random.default_rng(n)
+    hubs = np.repeat(rng.choice(n, 6, replace=False), [150_000, 70_000, 5000, 2000, 1100, 513])
+    rows = np.concatenate([np.arange(n), rng.integers(0, n, deg * n), hubs]).astype(np.int32)
+    cols = np.concatenate([np.arange(n), rng.integers(0, n, deg * n + hubs.size)]).astype(np.int32)
+    rp, ci = oracle.csr_from_edges(n, rows, cols)
+    assert ci.size > 4096 * 512
+    r_of = np.repeat(np.arange(n, dtype=np.int32), np.diff(rp))
+    key = r_of.astype(np.int64) * n + ci
+    val = f32(rng.uniform(0.1, 1.0, ci.size))
+    off = np.flatnonzero(r_of != ci)
+    gone = np.sort(rng.choice(off, ci.size // 50, replace=False))
+    pairs = np.unique(np.concatenate([rng.integers(0, n, (1 + absent) * ci.size), hubs[:100_000]]).astype(np.int64) * n + rng.integers(0, n, (1 + absent) * ci.size + 100_000))
+    free = rng.permutation(pairs[key[np.minimum(np.searchsorted(key, pairs), key.size - 1)] != pairs])      # pairs that are not stored
+    new, nothing = np.sort(free[:ci.size // 40]), free[ci.size // 40:][:absent * ci.size]
+    stays = np.ones(ci.size, bool)
+    stays[gone] = False
+    touched = np.flatnonzero(stays if share == 1.0 else stays & (rng.random(ci.size) < share))
+    named = np.sort(np.concatenate([key[touched], nothing]))
+    assert (named.size > ci.size // 4) == (share > 0.25)
+    add = ((new // n).astype(np.int32), (new % n).astype(np.int32), f32(rng.uniform(1, 2, new.size)))
+    dele, upd = (r_of[gone], ci[gone]), ((named // n).astype(np.int32), (named % n).astype(np.int32), f32(rng.uniform(3, 4, named.size)))
+    want = oracle.delta_apply_weighted(n, rp, ci, val, add=add, dele=dele, upd=upd)
+    got = gpu_rebuild_weighted(n, rp, ci, val, add, dele, upd, merged=True)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert np.array_equal(got[2], f32(want[2]))
+
+
 def test_weighted_rebuild_reports_an_unsorted_update_list():
     """Declared sorted, but not: the check says so, and nothing is written outside the result."""
     wl = WORKLOADS["c1"]
