@@ -30,6 +30,7 @@ constexpr int kSub = kWave * kPerLane;       // old entries per sub-tile, at mos
 constexpr int kWavesAtOnce = 4096;           // see merge_range_length
 constexpr int kLongestShare = kSub * 9;
 constexpr int kLongRange = kSub * 13;
+constexpr int kBufferReach = (1 << 29) - 2;  // words behind a place that a store through a buffer descriptor can name (31 bits of bytes)
 
 // The row in which a range of the merge begins: its extent in A_prev (rp, rp1) and in A_next (rn, rn1), and the stretch
 // of the added list that belongs to it (as, ae); the deleted list's stretch follows from these.
@@ -312,7 +313,9 @@ __device__ __forceinline__ void lds_bound(const int *a, int (&pos)[K], const int
 // The list may be long: AHEAD batches of 64 of its entries are fetched ahead, eight where a sub-tile takes more than two or three
 // (a smoothed series changes nearly every value in its first steps: R-MAT 2^19, 8.5 M entries, 8.3 M updates, a whole rebuild 92 -> 76 us, with
 // the place of a range's first update found here, where it is wanted once, and not per row in rowptr_kernel).
-template <bool VALUES, int AHEAD>
+// FAR: a sub-tile may leave more entries than a buffer's offsets reach (kBufferReach): positions are kept whole, and the stores
+// find their addresses themselves.
+template <bool VALUES, int AHEAD, bool FAR>
 __global__ __launch_bounds__(kWave) void merge_kernel(
     int n, const int32_t *__restrict__ rowptr_prev, const int32_t *__restrict__ colidx_prev, int nnz_prev, int range_len,
     const int32_t *__restrict__ add_row, const int32_t *__restrict__ add_col, int n_add,
@@ -329,7 +332,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
     __shared__ int s_col[1 + kSub];              // from s_col[1] on
     __shared__ __align__(16) int s_mark[kSub + kWave];   // bit 0: deleted; bit 1: new value in s_newval; bits 2..: added entries that go right before this slot
     // Until the prefix sums are taken: s_rows[k] = rowptr_prev[first_row + k], the rows that meet the sub-tile.
-    // From then on: s_start[p] / 4 = outputs (kept + added) that precede slot p's block; its low bits are the mark's of entry p - 1.
+    // From then on: s_start[p] / 4 = outputs (kept + added) that precede slot p's block; its low bits are the mark's of entry p - 1 (FAR:
+    // the outputs, and the marks stay where they are).
     __shared__ __align__(16) int s_shared[kMaxWindow + 4];
     __shared__ float s_newval[UPDATES ? kSub : 1];
     int *const s_rows = s_shared;
@@ -598,28 +602,36 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j) {
                 run += (mk[j] >> 2) + (~mk[j] & 1);
-                s_start[lane * kPerLane + j + 1] = (run << 2) | (mk[j] & 3);
+                s_start[lane * kPerLane + j + 1] = FAR ? run : (run << 2) | (mk[j] & 3);
             }
             written = uniform(__builtin_amdgcn_readlane(inc, kWave - 1) + (s_mark[kSub] >> 2));
         }
         wave_lds_sync();
 
         // the entries from one before `base` on: a kept entry's place is one before what precedes the next slot
-        const int room = (unsigned)base < (unsigned)cap_next ? min(cap_next - base, (1 << 29) - 2) + 1 : 0;
+        const int room = (unsigned)base < (unsigned)cap_next ? min(cap_next - base, kBufferReach) + 1 : 0;
         const __amdgpu_buffer_rsrc_t col_out = buffer_of(colidx_next + (int64_t)base - 1, room);
         const __amdgpu_buffer_rsrc_t val_out = buffer_of(VALUES ? val_next + (int64_t)base - 1 : nullptr, VALUES ? room : 0);
         auto put = [&](unsigned offset, int c, float v) {
             __builtin_amdgcn_raw_buffer_store_b32(c, col_out, offset, 0, 0);
             if (VALUES) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), val_out, offset, 0, 0);
         };
+        auto put_far = [&](bool kept, int place, int c, float v) {       // place: from 1 on, as above
+            const unsigned pos = (unsigned)base + (unsigned)place - 1u;
+            if (kept && pos < (unsigned)cap_next) {
+                colidx_next[pos] = c;
+                if (VALUES) val_next[pos] = v;
+            }
+        };
         // ---- old entries
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
             const int p = lane + j * kWave;
-            const unsigned s = (unsigned)s_start[p + 1];
+            const unsigned s = (unsigned)s_start[p + 1], mark = FAR ? (unsigned)s_mark[p] : s;
             float v = VALUES ? v_[j] : 0.0f;
-            if (UPDATES) v = (s & 2u) ? s_newval[p] : v;
-            put((s & ~3u) | (s << 31), c_[j], v);              // the deleted ones are dropped
+            if (UPDATES) v = (mark & 2u) ? s_newval[p] : v;
+            if (FAR) put_far(!(mark & 1u), (int)s, c_[j], v);
+            else put((s & ~3u) | (s << 31), c_[j], v);         // the deleted ones are dropped
         }
         // ---- added entries: their slot, then the rank among the adds of the same slot (they are consecutive).
         // The first 64 kept their slot and column from the search above; more than 64 per sub-tile are rare.
@@ -632,7 +644,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(
             const int run_start = 63 - __clzll(upto);
             int rank = lane - run_start;
             if (run_start == 0 && !(true_heads & 1ull)) rank += rank_carry;   // run continues from the previous 64
-            put(j < a_cur ? ((unsigned)s_start[max(q, 0)] & ~3u) + 4u * (unsigned)(rank + 1) : kDropped, c, v);
+            if (FAR) put_far(j < a_cur, s_start[max(q, 0)] + rank + 1, c, v);
+            else put(j < a_cur ? ((unsigned)s_start[max(q, 0)] & ~3u) + 4u * (unsigned)(rank + 1) : kDropped, c, v);
             q_carry = __shfl(q, kWave - 1, kWave);
             rank_carry = __shfl(rank, kWave - 1, kWave) + 1;
         };
@@ -907,16 +920,19 @@ int rebuild(int64_t n, const int32_t *rowptr_prev, const int32_t *colidx_prev, i
         }
     }
     const dim3 grid((unsigned)n_ranges);
+    // (a sub-tile leaves no more than its own entries and all that is added)
+    const bool far = n_add > kBufferReach - kSub;
     if (vals && n_upd > 0)
-        hipLaunchKernelGGL((n_upd > nnz_prev / 4 ? merge_kernel<true, 8> : merge_kernel<true, 1>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev,
+        hipLaunchKernelGGL((far ? merge_kernel<true, 1, true> : n_upd > nnz_prev / 4 ? merge_kernel<true, 8, false> : merge_kernel<true, 1, false>), grid,
+                           dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev,
                            (int)nnz_prev, (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, vals->upd_row, vals->upd_col, vals->upd_val, (int)n_upd);
     else if (vals)
-        hipLaunchKernelGGL((merge_kernel<true, 0>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
+        hipLaunchKernelGGL((far ? merge_kernel<true, 0, true> : merge_kernel<true, 0, false>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
                            (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, nullptr, nullptr, nullptr, 0);
     else
-        hipLaunchKernelGGL((merge_kernel<false, 0>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
+        hipLaunchKernelGGL((far ? merge_kernel<false, 0, true> : merge_kernel<false, 0, false>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
                            (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
     DGNN_RETURN_IF_LAUNCH_FAILED();

@@ -118,3 +118,77 @@ def test_rebuild_that_deletes_all_of_a_full_matrix():
     torch.cuda.synchronize()
     want = torch.arange(n + 1, dtype=torch.int32, device=DEV)
     assert torch.equal(rpn, want) and torch.equal(cin, want[:n]) and bool((dinv == 1).all())
+
+
+@pytest.mark.timeout(600)
+def test_rebuild_of_a_sub_tile_that_leaves_more_than_2_29_entries():
+    """512 rows of one entry each that are full afterwards, all of them placed by one wavefront: more words than 31 bits of bytes
+    reach from the first."""
+    rows, n = 512, (1 << 20) + 1024
+    assert rows * n > 1 << 29
+    cols = torch.arange(n, dtype=torch.int32, device=DEV)
+    add_row = torch.arange(rows, dtype=torch.int32, device=DEV).repeat_interleave(n - 1)
+    add_col = torch.empty(rows * (n - 1), dtype=torch.int32, device=DEV)
+    for r in range(rows):
+        add_col[r * (n - 1):(r + 1) * (n - 1)] = cols[:-1] + (cols[:-1] >= r)
+    n_add, none = add_row.numel(), torch.empty(0, dtype=torch.int32, device=DEV)
+    rpn = torch.full((n + 1,), -7, dtype=torch.int32, device=DEV)
+    cin = torch.full((n + n_add,), -7, dtype=torch.int32, device=DEV)
+    ws = torch.empty(dg.delta_rebuild_workspace(n, n, n_add, 0), dtype=torch.uint8, device=DEV)
+    rp = torch.arange(n + 1, dtype=torch.int32, device=DEV)
+    assert dg.delta_rebuild(rp, cols, n, add_row, add_col, n_add, none, none, 0, rpn, cin, torch.empty(n, device=DEV), ws) == n + n_add
+    torch.cuda.synchronize()
+    assert torch.equal(rpn[:rows + 1], rp[:rows + 1] * n) and torch.equal(rpn[rows:], rp[rows:] + rows * (n - 1))
+    assert torch.equal(cin[rows * n:], cols[rows:])
+    for r in range(0, rows, 64):
+        assert torch.equal(cin[r * n:(r + 64) * n].view(64, n), cols.expand(64, n)), r
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("weighted", [False, True])
+def test_rebuild_that_adds_more_than_2_29_entries(weighted):
+    """... spread over all rows: deleted entries, added ones and, with values, an update for every diagonal entry.  Row r has r, for even r
+    also r + 1, and receives 520 columns that are r + 1000 modulo 2000."""
+    n, each = 1 << 20, 520
+    n_add = n * each
+    assert n_add > (1 << 29) and 2000 * each <= n
+    r = torch.arange(n, dtype=torch.int32, device=DEV)
+    even = (r % 2 == 0).to(torch.int32)
+    rp = torch.cat([torch.zeros_like(r[:1]), torch.cumsum(1 + even, 0, dtype=torch.int32)])
+    nnz = int(rp[-1])
+    pairs = torch.stack([r, r + 1], 1).view(-1)
+    ci = pairs[torch.stack([torch.ones_like(even), even], 1).view(-1).bool()]
+    d_row = r[::4].contiguous()
+    d_col = d_row + 1
+    add_row, add_col = r.repeat_interleave(each), torch.empty(n_add, dtype=torch.int32, device=DEV)
+    step = torch.arange(each, dtype=torch.int32, device=DEV)[None, :] * 2000
+    chunk = 1 << 15
+    for a in range(0, n, chunk):
+        add_col.view(n, each)[a:a + chunk] = step + ((r[a:a + chunk] + 1000) % 2000)[:, None]
+    cap = nnz + n_add - d_row.numel()
+    rpn, cin = torch.full((n + 1,), -7, dtype=torch.int32, device=DEV), torch.full((cap,), -7, dtype=torch.int32, device=DEV)
+    ws = torch.empty(dg.delta_rebuild_workspace(n, nnz, n_add, d_row.numel()), dtype=torch.uint8, device=DEV)
+
+    def value(row, col):                                # of an entry that is stored or added
+        return ((row * 31 + col * 7) % 1021).to(torch.float32)
+    if weighted:
+        val, add_val, vn = value(r.repeat_interleave(1 + even), ci), value(add_row, add_col), torch.full((cap,), float("nan"), device=DEV)
+        got = dg.delta_rebuild_weighted(rp, ci, val, nnz, (add_row, add_col, add_val), (d_row, d_col), (r, r, value(r, r) + 2000.0), rpn, cin, vn, ws,
+                                        flags=dg.DGNN_UPDATES_SORTED)
+        del add_val
+    else:
+        got = dg.delta_rebuild(rp, ci, nnz, add_row, add_col, n_add, d_row, d_col, d_row.numel(), rpn, cin, torch.empty(n, device=DEV), ws)
+    torch.cuda.synchronize()
+    assert got == cap
+    long = (r % 4 == 2).to(torch.int32)                 # r + 1 is kept
+    assert torch.equal(rpn[1:], torch.cumsum(each + 1 + long, 0, dtype=torch.int32)) and int(rpn[0]) == 0
+    beyond = torch.full((chunk, 1), 1 << 30, dtype=torch.int32, device=DEV)
+    for a in range(0, n, chunk):
+        rows = r[a:a + chunk, None]
+        want = torch.cat([add_col.view(n, each)[a:a + chunk], rows, torch.where(long[a:a + chunk, None] > 0, rows + 1, beyond)], 1).sort(1).values
+        there = want < (1 << 30)
+        lo, hi = int(rpn[a]), int(rpn[min(a + chunk, n)])
+        assert torch.equal(cin[lo:hi], want[there]), a
+        if weighted:
+            v = value(rows, want) + 2000.0 * (want == rows)
+            assert torch.equal(vn[lo:hi], v[there]), a
