@@ -28,8 +28,8 @@ constexpr int kHeavyList = 8 * kRowTile;     // list entries per row tile beyond
 constexpr int kPerLane = 8;                  // old entries per lane and sub-tile of the merge
 constexpr int kSub = kWave * kPerLane;       // old entries per sub-tile, at most
 constexpr int kWavesAtOnce = 4096;           // see merge_range_length
-constexpr int kLongestShare = kSub * 9;
-constexpr int kLongRange = kSub * 13;
+constexpr int kLongestShare = kSub * 13;     // ... entries
+constexpr unsigned kLdsOfTwelve = 12800, kMergeLds = 6676, kMergeLdsUpdates = 8736;      // bytes: a twelfth of a CU's, and what the merge declares
 constexpr int kBufferReach = (1 << 29) - 2;  // words behind a place that a store through a buffer descriptor can name (31 bits of bytes)
 
 // The row in which a range of the merge begins: its extent in A_prev (rp, rp1) and in A_next (rn, rn1), and the stretch
@@ -304,15 +304,16 @@ __device__ __forceinline__ void lds_bound(const int *a, int (&pos)[K], const int
 // indices of the next sub-tile are fetched while this one is placed.
 // What bounds it is the instructions beside these two streams, so the accesses go through buffer descriptors: no branch and no
 // 64-bit address per access, and what lies outside is 0 or dropped; the loads in flight can then be counted, so that a sub-tile waits
-// for its own and not for the last one's stores.  us per call against a branch per access and a search per list: R-MAT 2^18 x 16 entries
-// 18.4 -> 14.7, 2^20 49 -> 38, 2^23 290 -> 269 (4.1 TB/s), 2^19 with values and updates 80 -> 70.
+// for its own and not for the last one's stores.  us per rebuild, this form and its ranges against a branch per access, a search per list and
+// 16384 ranges or ranges of 8192: R-MAT, 4.2 M entries 24.7 -> 18.8, 17 M 54.2 -> 41.2, 140 M 350 -> 333 (the merge alone 249: 4.5 TB/s);
+// with values and updates for nearly all 8.5 M entries 101 -> 77, for a tenth of 9 M 59 -> 48.
 // VALUES: every stored entry carries a value, which travels with its column index (same position); added
 // entries bring theirs.  UPDATES (with VALUES): a third list, sorted like the other two, names surviving entries
 // that get a new value; it is consumed through a cursor of its own, each entry finds its old entry in the staged
 // columns as a deleted entry does and leaves the new value there.  An entry that names nothing stored is passed over.
-// The list may be long: AHEAD batches of 64 of its entries are fetched ahead, eight where a sub-tile takes more than two or three
-// (a smoothed series changes nearly every value in its first steps: R-MAT 2^19, 8.5 M entries, 8.3 M updates, a whole rebuild 92 -> 76 us, with
-// the place of a range's first update found here, where it is wanted once, and not per row in rowptr_kernel).
+// The list may be long: AHEAD batches of 64 of its entries are fetched ahead, eight where most entries have an update, as in the first steps of a
+// smoothed series (figures in rebuild()); the place of a range's first update is found here, where it is wanted once, and not per row in
+// rowptr_kernel.
 // FAR: a sub-tile may leave more entries than a buffer's offsets reach (kBufferReach): positions are kept whole, and the stores
 // find their addresses themselves.
 template <bool VALUES, int AHEAD, bool FAR>
@@ -830,20 +831,28 @@ extern "C" int dgnn_delta_h2d(const int32_t *h_add_row, const int32_t *h_add_col
 
 namespace {
 
-// Entries per wavefront of the merge, a multiple of the sub-tile: where all of them fit the device at once, one such generation, so that
-// no range pays for its start a second time, beyond that shorter ones, which end together.  us per rebuild with 16384 wavefronts or ranges of
-// 8192, and with these: R-MAT 2^18, 4.2 M entries 21.4 / 19.1, 2^20, 17 M 44.3 / 41.1, 2^23, 140 M 344 / 341
-// (of 4096 333, but their records would not fit the workspace that callers were told to bring).
-int64_t merge_range_length(int64_t nnz_prev) {
-    const int64_t share = ((nnz_prev + kWavesAtOnce - 1) / kWavesAtOnce + kSub - 1) / kSub * kSub;
-    return share <= kLongestShare ? std::max<int64_t>(share, kSub) : kLongRange;
-}
 // The workspace holds a record per range of any snapshot of at most nnz_prev entries, so that one sized for the largest snapshot of a
 // block serves every step: 40 bytes per 8192 entries, never less than 16386 times, as callers are told.
 constexpr int64_t kRoomEntries = 8192, kRoomBytes = 40, kLeastRoom = 16385;
 int64_t workspace_records(int64_t nnz_prev) { return std::max<int64_t>(kLeastRoom, (nnz_prev + kRoomEntries - 1) / kRoomEntries) + 1; }
-static_assert(kLeastRoom * kRoomBytes >= (kWavesAtOnce + 1) * (int64_t)sizeof(RangeStart) && kRoomBytes * kLongRange >= (int64_t)sizeof(RangeStart) * kRoomEntries,
-              "records of short and of long snapshots fit");
+static_assert(kLeastRoom * kRoomBytes >= kWavesAtOnce * (int64_t)sizeof(RangeStart), "records of one generation fit");
+
+// Entries per wavefront of the merge, a multiple of the sub-tile.  Up to 27 M stored entries all wavefronts are one generation that the
+// device holds at once (16 on a CU, as registers and LDS allow every variant), so that no range pays for its start a second time.  Beyond, ranges are
+// as short as their records fit the workspace, so that wavefronts end together; with updates, whose place a range has to search for, no shorter than
+// eight sub-tiles, nine where the updates are many.  A generation of eight sub-tiles, 16 KB of entries, is slower than its neighbours and takes
+// nine (uniform, with values: 14.5 M entries, 7 / 8 / 9 sub-tiles 59.3 / 65.2 / 59.3; 16 M 8 / 9 75.2 / 69.6).  us per rebuild, uniform graphs, by
+// sub-tiles to a range (* one generation): without values 14 M 4: 36.3, 7*: 33.9, 13: 38.4;
+// 22 M 4: 49.6, 11*: 48.0; 27 M 4: 59.4, 13*: 56.7; 31 M 3: 78.1, 9: 82.0, 13: 82.3, 15*: 81.2; 56 M 6: 131.4, 13: 133.8; R-MAT 40 M 4: 93.9, 13: 105.8;
+// with values 31 M 3: 126, 13: 138; 56 M 6: 225, 13: 236; with an update for 3 entries of 10, 30 M 4: 187, 9: 171, 13: 193, 15*: 169; 56 M 9: 306, 13: 324.
+bool few_updates(int64_t nnz_prev, int64_t n_upd) { return n_upd <= nnz_prev / 5; }
+int64_t merge_range_length(int64_t nnz_prev, int64_t n_upd) {
+    auto dealt = [&](int64_t ranges) { return ((nnz_prev + ranges - 1) / ranges + kSub - 1) / kSub * kSub; };
+    const int64_t generation = dealt(kWavesAtOnce);
+    if (generation <= kLongestShare) return generation == 8 * kSub ? 9 * kSub : generation;
+    const int64_t least = dealt(workspace_records(nnz_prev) * kRoomBytes / (int64_t)sizeof(RangeStart));
+    return n_upd > 0 ? std::max<int64_t>(least, (few_updates(nnz_prev, n_upd) ? 8 : 9) * kSub) : least;
+}
 
 }  // namespace
 
@@ -896,7 +905,7 @@ int rebuild(int64_t n, const int32_t *rowptr_prev, const int32_t *colidx_prev, i
     char *wsb = static_cast<char *>(ws);
     RangeStart *range_start = reinterpret_cast<RangeStart *>(wsb);
     const int cap = (int)min(cap_next, (int64_t)2147483647LL);
-    const int64_t range_len = merge_range_length(nnz_prev);
+    const int64_t range_len = merge_range_length(nnz_prev, n_upd);
     const int n_ranges = (int)((nnz_prev + range_len - 1) / range_len);
 
     const dim3 row_grid((unsigned)((n + kRowTile - 1) / kRowTile));
@@ -922,13 +931,20 @@ int rebuild(int64_t n, const int32_t *rowptr_prev, const int32_t *colidx_prev, i
     const dim3 grid((unsigned)n_ranges);
     // (a sub-tile leaves no more than its own entries and all that is added)
     const bool far = n_add > kBufferReach - kSub;
+    // Many generations with values: twelve wavefronts on a CU instead of 16 or 20, by LDS that nobody uses.  With more of them at work the
+    // lists' lines, of which a sub-tile takes a part, are gone from the L2 when the next one comes for the rest: R-MAT, 69 M entries, without
+    // updates 306 / 292 us (all that fit / twelve), one for 50 entries 324 / 313, for 10 342 / 328, 280 M 1180 / 1120, 1250 / 1202, 1323 / 1274.
+    // Where updates are many it is their chain of batches that counts: one for 3 of 10 entries, 44 M 246 / 267, 69 M 382 / 406.
+    const unsigned lds = n_ranges > kWavesAtOnce && few_updates(nnz_prev, n_upd) ? kLdsOfTwelve : 0;
+    // Eight batches ahead from three updates for five entries on: fewer of them are fetched in vain (us with one / eight: 8.5 M entries, for 3 of
+    // 10 entries 49.5 / 61.2, 5 of 10 56.1 / 64.7, 7 of 10 63.8 / 67.1, all 77.5 / 70.9; 17 M 99 / 117, 117 / 123, 132 / 125, 166 / 140).
     if (vals && n_upd > 0)
-        hipLaunchKernelGGL((far ? merge_kernel<true, 1, true> : n_upd > nnz_prev / 4 ? merge_kernel<true, 8, false> : merge_kernel<true, 1, false>), grid,
-                           dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev,
+        hipLaunchKernelGGL((far ? merge_kernel<true, 1, true> : n_upd > nnz_prev * 3 / 5 ? merge_kernel<true, 8, false> : merge_kernel<true, 1, false>), grid,
+                           dim3(kWave), lds ? lds - kMergeLdsUpdates : 0, s, (int)n, rowptr_prev, colidx_prev,
                            (int)nnz_prev, (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, vals->upd_row, vals->upd_col, vals->upd_val, (int)n_upd);
     else if (vals)
-        hipLaunchKernelGGL((far ? merge_kernel<true, 0, true> : merge_kernel<true, 0, false>), grid, dim3(kWave), 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
+        hipLaunchKernelGGL((far ? merge_kernel<true, 0, true> : merge_kernel<true, 0, false>), grid, dim3(kWave), lds ? lds - kMergeLds : 0, s, (int)n, rowptr_prev, colidx_prev, (int)nnz_prev,
                            (int)range_len, add_row, add_col, (int)n_add, del_row, del_col, (int)n_del, range_start, colidx_next, cap,
                            vals->prev, vals->add, vals->next, nullptr, nullptr, nullptr, 0);
     else

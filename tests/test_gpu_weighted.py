@@ -199,6 +199,48 @@ def test_weighted_rebuild_of_ranges_of_several_sub_tiles(n, deg, share, absent):
     assert np.array_equal(got[2], f32(want[2]))
 
 
+@pytest.mark.parametrize("share", [0.1, 0.4, 0.9])
+def test_weighted_rebuild_of_more_ranges_than_run_at_once(share):
+    """28 M stored entries: several generations of ranges, few of them at once where updates are few.  The merge that consumes the updates
+    against the one that leaves them to a kernel of their own, and that one's structure against the rebuild without values; updates for
+    deleted entries and for pairs that are not stored among them."""
+    n, deg = 2_000_003, 13
+    gen = torch.Generator(device=DEV).manual_seed(int(10 * share))
+    def draw(k):
+        return torch.randint(0, n * n, (k,), generator=gen, device=DEV)
+    def rows_cols(keys):
+        return torch.div(keys, n, rounding_mode="floor").to(torch.int32), (keys % n).to(torch.int32)
+    diag = torch.arange(n, device=DEV) * (n + 1)
+    hub = 77_777 * n + torch.randint(0, n, (300_000,), generator=gen, device=DEV)
+    key = torch.unique(torch.cat([diag, draw(deg * n), hub]))
+    assert key.numel() > 13 * 512 * 4096
+    row, col = rows_cols(key)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int32, device=DEV), torch.cumsum(torch.bincount(row.long(), minlength=n), 0).to(torch.int32)])
+    val = torch.rand(key.numel(), generator=gen, device=DEV)
+    gone = key[(torch.rand(key.numel(), generator=gen, device=DEV) < 0.02) & (row != col)]
+    fresh = torch.unique(draw(key.numel() // 20))
+    fresh = fresh[key[torch.searchsorted(key, fresh).clamp_(max=key.numel() - 1)] != fresh]
+    new, nothing = fresh[::2], fresh[1::2]
+    named = torch.unique(torch.cat([key[torch.rand(key.numel(), generator=gen, device=DEV) < share], nothing]))
+    assert (named.numel() > key.numel() // 5) == (share > 0.2) and (named.numel() > key.numel() * 3 // 5) == (share > 0.6)
+    add = rows_cols(new) + (torch.rand(new.numel(), generator=gen, device=DEV) + 1,)
+    dele, upd = rows_cols(gone), rows_cols(named) + (torch.rand(named.numel(), generator=gen, device=DEV) + 3,)
+    cap = key.numel() + new.numel() - gone.numel()
+    ws = torch.empty(dg.delta_rebuild_workspace(n, key.numel(), new.numel(), gone.numel()), dtype=torch.uint8, device=DEV)
+    out = []
+    for flags in (dg.DGNN_UPDATES_SORTED, 0):
+        rpn, cin, vn = torch.empty_like(rp), torch.full((cap,), -7, dtype=torch.int32, device=DEV), torch.full((cap,), float("nan"), device=DEV)
+        assert dg.delta_rebuild_weighted(rp, col, val, key.numel(), add, dele, upd, rpn, cin, vn, ws, flags=flags) == cap
+        out.append((rpn, cin, vn))
+    rpn, cin = torch.empty_like(rp), torch.full((cap,), -7, dtype=torch.int32, device=DEV)
+    dg.delta_rebuild(rp, col, key.numel(), *add[:2], new.numel(), *dele, gone.numel(), rpn, cin, None, ws)
+    want = torch.cat([key[~torch.isin(key, gone)], new]).sort().values
+    assert torch.equal(rows_cols(want)[1], cin)
+    for r, c, v in out:
+        assert torch.equal(r, rpn) and torch.equal(c, cin) and not bool(v.isnan().any())
+    assert torch.equal(out[0][2], out[1][2])
+
+
 def test_weighted_rebuild_reports_an_unsorted_update_list():
     """Declared sorted, but not: the check says so, and nothing is written outside the result."""
     wl = WORKLOADS["c1"]
