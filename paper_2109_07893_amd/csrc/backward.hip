@@ -72,7 +72,9 @@ __device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items,
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int i = lane & 31, hh = lane >> 5;
     const int group = wave % S::GROUPS, rs = wave / S::GROUPS;
-    const Elem *x, *g, *z;
+    const Elem *x = static_cast<const Elem *>(as_global(first->x));
+    const Elem *g = static_cast<const Elem *>(as_global(first->g));
+    const Elem *z = static_cast<const Elem *>(as_global(first->z));
     int item = 0;
     auto open_item = [&] {
         x = static_cast<const Elem *>(as_global(first[item].x));
@@ -132,24 +134,12 @@ __device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items,
             }
         }
     };
-    // the step fetched last: its number within its item
-    int64_t at = me, left = me < n_steps * items ? (n_steps * items - me + workers - 1) / workers : 0;    // steps of this worker
-    auto advance = [&] {
-        bool turned = false;
-        for (; at >= n_steps; at -= n_steps, turned = true) item = uniform(item + 1);
-        if (turned) open_item();
-        return turned;
-    };
-    open_item();
-    if (left > 0) {
-        advance();
-        fetch(at);
-    }
-    for (; left > 0; --left) {
+    // What was fetched, the rows of `step`, is multiplied while fetch_next() is under way.
+    auto take = [&](int64_t step, auto fetch_next) {
         Raw xa[S::TI][8], gb[S::TJ][8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const bool row_ok = row_of(at, e) < n;
+            const bool row_ok = row_of(step, e) < n;
 #pragma unroll
             for (int ti = 0; ti < S::TI; ++ti) xa[ti][e] = (row_ok && (it0 + ti) * 32 + i < FIN) ? xa_next[ti][e] : Raw(0);
 #pragma unroll
@@ -160,13 +150,8 @@ __device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items,
                 gb[tj][e] = ok ? gb_next[tj][e] : Raw(0);
             }
         }
-        bool turned = false;
-        if (left > 1) {
-            at += workers;
-            turned = advance();
-        }
-        fetch(at);                                          // the next step's rows travel while this one is multiplied
-        __builtin_amdgcn_sched_barrier(0);                  // ... so the loads must stay ahead of the multiplications
+        fetch_next();
+        __builtin_amdgcn_sched_barrier(0);                  // the loads must stay ahead of the multiplications
         if constexpr (BF16) {
             bf16x8 a[S::TI], b[S::TJ];
 #pragma unroll
@@ -195,14 +180,42 @@ __device__ __forceinline__ void wgrad(const Item *__restrict__ first, int items,
                     for (int tj = 0; tj < S::TJ; ++tj)
                         acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[ti][e], gb[tj][e], acc[ti][tj], 0, 0, 0);
         }
-        if (LINE && turned) close_item();
-    }
-    if constexpr (LINE) {
-        close_item();
+    };
+    // One item: without the line's bookkeeping beside every step (720 K x 128 bf16: 105 / 87 us), but in fp32 under a mask the compiler makes
+    // more of the counted loop (60 K x 128, twelve gradients 345 / 380; of 16 columns 165 / 150).
+    if constexpr (!LINE && (BF16 || !MASKED || FIN == 16)) {
+        if (me < n_steps) fetch(me);
+        for (int64_t step = me; step < n_steps; step += workers) take(step, [&] { fetch(std::min(step + workers, n_steps - 1)); });
+    } else {
+        int64_t at = me, left = me < n_steps * items ? (n_steps * items - me + workers - 1) / workers : 0;    // step within the item; this worker's
+        auto advance = [&] {
+            bool turned = false;
+            for (; at >= n_steps; at -= n_steps, turned = true) item = uniform(item + 1);
+            if (turned) open_item();
+            return turned;
+        };
+        if (left > 0) {
+            advance();
+            fetch(at);
+        }
+        for (; left > 0; --left) {
+            bool turned = false;
+            take(at, [&] {
+                if (left > 1) {
+                    at += workers;
+                    turned = advance();
+                }
+                fetch(at);
+            });
+            if (turned) close_item();
+        }
+        if constexpr (LINE) {
+            close_item();
 #pragma unroll
-        for (int ti = 0; ti < S::TI; ++ti)
+            for (int ti = 0; ti < S::TI; ++ti)
 #pragma unroll
-            for (int tj = 0; tj < S::TJ; ++tj) acc[ti][tj] = behind[ti][tj];
+                for (int tj = 0; tj < S::TJ; ++tj) acc[ti][tj] = behind[ti][tj];
+        }
     }
 
     // ---- the workgroup's workers: the upper half hands its sums to the lower half until one is left
@@ -257,8 +270,9 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave) void wgrad_kernel(Batch batc
 // 3.2e-8; 6 x 200 K 4.7e-8 and 6.0e-8, now 3.6e-8 and 1.9e-8), in the same time (116 / 115 us).
 // `items` of them in a row have one dw; apart: each with partial results of its own, added to dw one after the other.
 constexpr int kReduceSlices = 16;
-__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, int items, int apart, const float *__restrict__ partial, int workers,
-                                                                            int elems, int accumulate) {
+template <bool APART>
+__global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batch batch, int items, const float *__restrict__ partial, int workers, int elems,
+                                                                            int accumulate) {
     float *__restrict__ dw = as_global(batch.item[blockIdx.y * items].dw);
     partial += (int64_t)blockIdx.y * workers * elems;
     __shared__ double s_sum[kReduceSlices][kWave];
@@ -266,22 +280,31 @@ __global__ __launch_bounds__(kReduceSlices *kWave) void wgrad_reduce_kernel(Batc
     const int e = blockIdx.x * kWave + lane;
     const int per = (workers + kReduceSlices - 1) / kReduceSlices;
     const int p0 = slice * per, p1 = min(p0 + per, workers);
-    float out = accumulate && e < elems ? dw[e] : 0.0f;
-    for (int k = 0; k < (apart ? items : 1); ++k, partial += (int64_t)workers * elems) {
+    auto sum_of = [&](const float *__restrict__ from) {
         double sum = 0.0;
         if (e < elems) {
 #pragma unroll 8
-            for (int p = p0; p < p1; ++p) sum += partial[(int64_t)p * elems + e];
+            for (int p = p0; p < p1; ++p) sum += from[(int64_t)p * elems + e];
         }
-        if (k) __syncthreads();
         s_sum[slice][lane] = sum;
         __syncthreads();
         double total = s_sum[0][lane];
 #pragma unroll
         for (int s = 1; s < kReduceSlices; ++s) total += s_sum[s][lane];
-        out = (float)(accumulate || k ? out + total : total);
+        return total;
+    };
+    if constexpr (!APART) {
+        const double total = sum_of(partial);
+        if (slice == 0 && e < elems) dw[e] = (float)(accumulate ? dw[e] + total : total);
+    } else {
+        float out = accumulate && e < elems ? dw[e] : 0.0f;
+        for (int k = 0; k < items; ++k) {
+            if (k) __syncthreads();
+            const double total = sum_of(partial + (int64_t)k * workers * elems);
+            out = (float)(accumulate || k ? out + total : total);
+        }
+        if (slice == 0 && e < elems) dw[e] = out;
     }
-    if (slice == 0 && e < elems) dw[e] = out;
 }
 
 // out = (Z > 0 ? G : 0) * row_scale[row]; one 16-byte piece per lane.
@@ -333,8 +356,8 @@ int launch_wgrad(int count, int items, const Batch &b, int64_t n, int accumulate
                        dim3((unsigned)blocks, (unsigned)(apart ? items : count)), dim3(kWavesPerBlock * kWave), 0, s, b, apart ? 1 : items, n, n_steps, partial);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     constexpr int elems = FIN * FOUT;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((elems + kWave - 1) / kWave, (unsigned)count), dim3(kReduceSlices * kWave), 0, s, b, items, apart, partial,
-                       (int)blocks, elems, accumulate);
+    hipLaunchKernelGGL((apart ? wgrad_reduce_kernel<true> : wgrad_reduce_kernel<false>), dim3((elems + kWave - 1) / kWave, (unsigned)count),
+                       dim3(kReduceSlices * kWave), 0, s, b, items, partial, (int)blocks, elems, accumulate);
     DGNN_RETURN_IF_LAUNCH_FAILED();
     return DGNN_OK;
 }
