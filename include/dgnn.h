@@ -96,9 +96,9 @@ int dgnn_delta_h2d(const int32_t *h_add_row, const int32_t *h_add_col, int64_t n
                    int32_t *d_add_row, int32_t *d_add_col, int32_t *d_del_row, int32_t *d_del_col,
                    void *stream);
 
-/* Workspace size of dgnn_delta_rebuild and dgnn_delta_rebuild_weighted in bytes (HOST out-parameter): 40 per range of
- * 8192 stored entries (never fewer than 16386 ranges), rounded up; it grows with nnz_prev only, so the size queried
- * for the largest snapshot of a block serves every step. */
+/* Workspace size of dgnn_delta_rebuild and dgnn_delta_rebuild_weighted in bytes (HOST out-parameter):
+ * 40 * (max(16385, ceil(nnz_prev / 8192)) + 1), rounded up to 256; it grows with nnz_prev only, so the size queried for the
+ * largest snapshot of a block serves every step. */
 int dgnn_delta_rebuild_workspace(int64_t n, int64_t nnz_prev, int64_t n_add, int64_t n_del, size_t *bytes);
 
 /*
@@ -496,7 +496,8 @@ int dgnn_weight_grad_workspace(int32_t f_in, int32_t f_out, size_t *bytes);
  *   dw [f_in][f_out]            fp32 whatever dt is; with accumulate != 0 the result is added to it (the sum
  *                               over the timesteps of a block that share one W)
  *   ws, ws_bytes                scratch of at least dgnn_weight_grad_workspace() bytes
- * The sum over rows has a fixed order: results repeat bit for bit.
+ * The sum over rows has a fixed order (fp32 within a workgroup, 64 bits over the workgroups, rounded once): results repeat
+ * bit for bit.
  */
 int dgnn_weight_grad(const void *x, const void *g, int64_t n, int32_t f_in, int32_t f_out, float *dw,
                      int32_t accumulate, dgnn_dtype dt, void *ws, size_t ws_bytes, void *stream);
@@ -510,7 +511,8 @@ typedef struct {
 /*
  * dgnn_weight_grad for `count` gradients over n rows each (one weight per timestep, or one item over the rows of several
  * timesteps).  Items that follow each other with the same dw are summed into it, in this order: one weight whose timesteps lie
- * in tensors of their own.  With z = the layer's output the gradient passes its ReLU on the way in: with x = A~ X and g = dL/dZ this is
+ * in tensors of their own.  Gradients of one call share the device: those of large items are sums of fewer and longer parts than a
+ * call of their own would form.  With z = the layer's output the gradient passes its ReLU on the way in: with x = A~ X and g = dL/dZ this is
  * the gradient of W for a layer evaluated as Z = sigma((A~ X) W), X^T A~^T G_P = (A~ X)^T G_P: no aggregation going back.
  * Workspace as dgnn_weight_grad.
  */
@@ -565,7 +567,11 @@ int dgnn_lstm_cell(const void *gates_x, const void *gates_h, const float *bias, 
  *   c [n][hidden]        cell state, updated IN PLACE;   h_next [n][hidden]   a buffer of its own
  * Supported: fp32 storage with hidden = 16 or 32, bf16 storage with hidden = 32 or 64, and f_y = hidden or
  * 2 * hidden (DGNN_ERR_SHAPE otherwise: use the two dense transforms and dgnn_lstm_cell).  fp32: same result as that
- * composition up to the order of the fp32 sums.  bf16: the pre-activations stay in fp32 here, where the composition
+ * composition up to the rounding and the order of the fp32 sums: a product is formed from parts of 8 bits, up to 2^-24 of it
+ * away, and numbers below 2^-110 take part with an absolute error of up to 2^-134.  Where a tile of 32 vertices (from a multiple
+ * of 32 on) has a number from 2^60 on, an infinity or a NaN among its operands, or a weight is such a number, all of its products are
+ * formed whole instead: the last bits of a vertex's results then depend on its neighbours in the tile, nothing else of them does.
+ * bf16: the pre-activations stay in fp32 here, where the composition
  * rounds the two products to bf16 before it adds them; c and h are rounded once, when they are stored.
  */
 int dgnn_lstm_step(const void *y, int32_t f_y, const void *h_prev, const void *w_x, const void *w_h,
@@ -623,7 +629,7 @@ int dgnn_lstm_series_backward(const void *y, int32_t f_y, const void *h0, const 
 
 /*
  * dw_x = sum_t y_t^T da_t, dw_h = sum_t h_{t-1}^T da_t, db = column sums of da (or added to them) in one pass over da; shapes as
- * dgnn_lstm_series_backward.  The sums have a fixed order.
+ * dgnn_lstm_series_backward.  The sums have a fixed order: fp32 within a workgroup, 64 bits over the workgroups, rounded once.
  */
 int dgnn_lstm_weight_grad_workspace(int32_t f_y, int32_t hidden, size_t *bytes);
 int dgnn_lstm_weight_grad(const void *y, int32_t f_y, const void *h0, const void *h, const void *da, int64_t n, int32_t T, int32_t hidden,

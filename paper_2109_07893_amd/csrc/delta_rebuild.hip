@@ -305,7 +305,8 @@ __device__ __forceinline__ void lds_bound(const int *a, int (&pos)[K], const int
 // What bounds it is the instructions beside these two streams, so the accesses go through buffer descriptors: no branch and no
 // 64-bit address per access, and what lies outside is 0 or dropped; the loads in flight can then be counted, so that a sub-tile waits
 // for its own and not for the last one's stores.  us per rebuild, this form and its ranges against a branch per access, a search per list and
-// 16384 ranges or ranges of 8192: R-MAT, 4.2 M entries 24.7 -> 18.8, 17 M 54.2 -> 41.2, 140 M 350 -> 333 (the merge alone 249: 4.5 TB/s);
+// 16384 ranges or ranges of 8192: R-MAT, 4.2 M entries 24.7 -> 18.8, 17 M 54.2 -> 41.2, 140 M 350 -> 333, 280 M 665 -> 657
+// (the merge alone 545: 4.1 TB/s of column indices);
 // with values and updates for nearly all 8.5 M entries 101 -> 77, for a tenth of 9 M 59 -> 48.
 // VALUES: every stored entry carries a value, which travels with its column index (same position); added
 // entries bring theirs.  UPDATES (with VALUES): a third list, sorted like the other two, names surviving entries

@@ -67,9 +67,12 @@ template <> struct Store<true> {
     }
 };
 
-// ---- fp32 products on the bf16 matrix cores.  An fp32 number is the sum of three bf16 numbers, each the rounded rest of the
-// ones before it (8 + 8 + 8 bits), and of the nine products of two such sums the six largest are formed, 2.6 times as fast as the fp32 matrix
-// instruction forms the one; what is left out is below 2^-25 of the product, less than the rounding of one of the sums' additions.
+// ---- fp32 products on the bf16 matrix cores (the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019).  An fp32 number is the sum of three bf16 numbers, each the rounded rest
+// of the ones before it (8 + 8 + 8 bits), and of the nine products of two such sums the six largest are formed, 2.6 times as fast as the fp32 matrix
+// instruction forms the one.  The second part is at most 2^-8 of a number in [1, 2), the third 2^-17, so what is left out is up to 2^-24 of the
+// product (1.7 x 2^-25 met with random numbers), no more than rounding the product would take.  That holds for numbers from 2^-110 on: the matrix
+// cores keep denormal numbers, but bf16 has none below 2^-133, so smaller ones enter with an absolute error of up to 2^-134.
 // From kSplitBelow on a wavefront's step takes the fp32 instruction: there a smaller product could pass fp32 ahead of the largest, with the
 // other sign, and the sum would be no number where the product is infinite.  Below, the at most 128 products of a sum, 2^120 each, stay
 // in fp32 whatever their order.
