@@ -231,11 +231,14 @@ class GcnStack:
                     with self.stage("weight_grad"):
                         B.weight_grad(blk.x[t + j], self.h[j], dw_t[t + j][0], self.ws_wgrad)
             else:                                  # the frames of X are tensors of their own, added up from the last one on
+                B._need(dw[0], torch.float32, "dw")
+                if dw[0].shape != (f, f):
+                    raise ValueError("shape mismatch in weight_grad")
                 a, h, down = self.wgrad, self.h, range(k - 1, -1, -1)
                 a.words[:k, a.X] = self.x.addresses([blk.x[t + j] for j in down])
                 a.words[:k, a.G] = pointers([h[j] for j in down])
                 a.words[:k, a.Z] = 0
-                a.words[:k, a.DW] = dw[0].data_ptr()
+                a.words[:k, a.DW] = B._ptr(dw[0])
                 with self.stage("weight_grad"):
                     B.weight_grad_batch(k, a.at(), n, f, f, accumulate, dt, self.ws_wgrad, stream)
             if layer == 0 and not self.want_dx:

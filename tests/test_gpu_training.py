@@ -289,6 +289,19 @@ def test_weight_gradients_of_every_timestep_over_all_of_the_device(n, f, dtype, 
         assert torch.equal(tr.dw_t[t][0], want), t
 
 
+@pytest.mark.parametrize("wrong", ["type", "shape", "strides"])
+def test_gradient_of_the_first_layer_goes_into_fp32_of_its_shape_only(wrong):
+    wl = replace(WORKLOADS["c2"].scaled(1003, T=3), layers=1, f=64, dtype="bf16", window=0, name="first-layer")
+    blk = make_block(wl, DEV, gen_device="cpu")
+    tr = make_trainer(wl, blk)
+    assert tr.stack.p0 is None
+    tr.forward()
+    tr.dw[0] = {"type": torch.empty((64, 64), dtype=torch.float64, device=DEV), "shape": torch.empty((64, 32), device=DEV),
+                "strides": torch.empty((64, 128), device=DEV)[:, ::2]}[wrong]
+    with pytest.raises((ValueError, TypeError, AssertionError)):
+        tr.backward(torch.stack([gradient(wl, t) for t in range(1, wl.T + 1)]).to(DEV))
+
+
 def test_gradient_descent_on_the_weights_reduces_a_loss():
     """End to end: the weight gradients drive plain gradient descent on L = 1/2 |Y - Y*|^2, where Y* comes from a
     hidden weight pair; the loss layer (Y - Y*) is the caller's, everything below it is the library's."""
