@@ -301,7 +301,8 @@ __global__ __launch_bounds__(WAVES * kWave) void lstm_series_kernel(const void *
     typedef Weights<FY, HID, BF16> W;
     constexpr int P = S::kPiece;
     // The widest step is the faster with an address and a mask per piece, all others behind buffer descriptors (bf16, 200 K vertices, 6 steps,
-    // 128 + 64 columns with c kept 285 / 309 us, without 252 / 255; 64 + 64 198.9 / 196.3)
+    // 128 + 64 columns with c kept 285 / 309 us, without 252 / 255; 64 + 64 198.9 / 196.3; these without c kept: one step of 2^20 174 / 157, six of
+    // 20 K 48 / 49.5, eight of 1000 57 / 60)
     constexpr bool BY_ADDRESS = BF16 && FY == 128;
     constexpr bool DIRECT = kDirectY<FY, HID, BF16, KEEP_C>;
     // the tile buffer: [Y | h], or h alone where Y's operands come straight from memory; in fp32, where W's parts take 80 KB, the lanes
